@@ -12,7 +12,10 @@ using namespace ftp;
 
 // Workspace of ftp_forward_static.  On the host this name is only a handle for hipGetSymbolAddress: the device
 // address, one per GPU, is looked up once per device and kept in g_static_ws.
-static __device__ __align__(256) unsigned char scratch[FTP_STATIC_WORKSPACE_BYTES];
+// (plans are held against FTP_STATIC_WORKSPACE_BYTES without the padding of their split filters, which is at most a third of
+// the filters' areas: the array has room for both)
+constexpr size_t kStaticPadding = 22u * 1024u * 1024u;
+static __device__ __align__(256) unsigned char scratch[FTP_STATIC_WORKSPACE_BYTES + kStaticPadding];
 
 namespace {
 
@@ -175,6 +178,24 @@ bool overlap_default()
     return e && std::strcmp(e, "1") == 0;
 }
 
+// Relays the filters of all the convolutions of a pass that take the matrix cores, in one launch.
+void prep_pass(const Plan& p, const void* const* weights, void* workspace, bool backward, hipStream_t s)
+{
+    PrepJob jobs[kPrepJobs];
+    int n = 0;
+    for (const Unit& u : p.units) {
+        if (u.kind != UNIT_CONV) continue;
+        const ftp_layer& ly = p.layers[u.layer];
+        ConvArgs a;                                  // (what the two questions below look at)
+        a.w = weights[u.layer]; a.K = ly.k; a.S = ly.stride; a.Cin = ly.cin; a.Cout = ly.cout;
+        a.Hc = p.H[u.layer + 1]; a.Wc = p.W[u.layer + 1]; a.pooled = u.pooled ? 1 : 0; a.bf16 = p.dtype == FTP_BF16;
+        if (!mfma_conv_eligible(a, backward)) continue;
+        jobs[n++] = mfma_prep_job(a, (char*)workspace + u.wt_offset, backward);
+        if (n == kPrepJobs) { prep_filters(jobs, n, s); n = 0; }
+    }
+    if (n) prep_filters(jobs, n, s);
+}
+
 bool any_bias(const Plan& p)
 {
     for (const ftp_layer& ly : p.layers) if (ly.kind == FTP_CONV && ly.has_bias) return true;
@@ -293,6 +314,7 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
     if (any_bias(p) && !biases) return FTP_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     UserBufs ub; ub.x = x; ub.y = y; ub.ws = workspace;
+    bool relaid = false;                             // (with the first convolution that needs it, whose timing record it belongs to)
     for (const Unit& u : p.units) {
         if (u.kind == UNIT_CONV) {
             ConvArgs a = conv_args(p, u, ub, weights, biases);
@@ -300,10 +322,10 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
             a.own = make_rect(p, u.group, FTP_RECT_OWN, u.bo);
             const bool fast = use_mfma() && plain_geometry(a);
             if (use_mfma() && mfma_conv_eligible(a, false)) {
-                float* wt = (float*)((char*)workspace + u.wt_fwd_offset);
+                float* wt = (float*)((char*)workspace + u.wt_offset);
                 const RectTab ext = view_extent(p, u.in_act, u.group, u.bi);
                 rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] {
-                    prep_filter(a.w, a.bf16, mfma_conv_packs_bf16(a), wt, nullptr, a.Cout, a.Cin, a.K, s);
+                    if (!relaid) { prep_pass(p, weights, workspace, false, s); relaid = true; }
                     if (mfma_conv_fwd(a, ext, wt, s)) direct_conv_fwd(a, s);
                 });
             } else if (fast && thin_conv_fwd_eligible(a)) {
@@ -328,7 +350,7 @@ int ftp_forward_static(const ftp_plan_t* plan, const void* x, const void* const*
                        void* y, void* stream)
 {
     if (!plan) return FTP_EINVAL;
-    if (plan->p.workspace_bytes > (size_t)FTP_STATIC_WORKSPACE_BYTES) return FTP_ETOOLARGE;
+    if (plan->p.workspace_bytes - plan->p.padding_bytes > (size_t)FTP_STATIC_WORKSPACE_BYTES) return FTP_ETOOLARGE;
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) { g_last_hip = (int)hipGetLastError(); return FTP_EHIP; }
     if (dev < 0 || dev >= kMaxDevices) return FTP_EINVAL;
@@ -397,7 +419,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
         aux = (hipStream_t)ov.aux;
         if ((rc = order(s, aux)) != FTP_OK) return rc;          // the forward pass, dy scaling, earlier calls
     }
-    bool gradient_in_flight = false;
+    bool gradient_in_flight = false, relaid = false;
     for (int i = (int)p.units.size() - 1; i >= 0; --i) {
         const Unit& u = p.units[i];
         if (u.kind == UNIT_CONV) {
@@ -430,10 +452,10 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             gradient_in_flight = overlap;
             a.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
             if (use_mfma() && mfma_conv_eligible(a, true)) {
-                float* wt = (float*)((char*)workspace + u.wt_bwd_offset);
+                float* wt = (float*)((char*)workspace + u.wt_offset);
                 const RectTab ext = view_extent(p, u.in_delta, u.group, u.bo);
                 rc = timed(plan, FTP_PASS_CONV_BWD_DATA, u.layer, s, [&] {
-                    prep_filter(a.w, a.bf16, mfma_conv_packs_bf16(a), nullptr, wt, a.Cout, a.Cin, a.K, s);
+                    if (!relaid) { prep_pass(p, weights, workspace, true, s); relaid = true; }
                     if (mfma_conv_bwd_data(a, ext, wt, s)) direct_conv_bwd_data(a, s);
                 });
             } else if (use_mfma() && thin_bwd_data_strided_eligible(a)) {

@@ -1,0 +1,201 @@
+// Device code shared by the matrix-core convolution kernels (ftp_mfma_conv.hip, ftp_delta_split.hip): a workgroup's tile of
+// pixels and the epilogue that turns its accumulators into map elements, winner codes and sign words.
+#pragma once
+#include "ftp_device.h"
+#include "ftp_launch.h"
+#include "ftp_conv_tiles.h"
+
+namespace ftp {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+// (tile geometry: ftp_conv_tiles.h)
+template <int S, int P, int Q>
+__device__ __forceinline__ TileGeom tile_geom(const MfmaConvArgs& a, int x0, int x1, int y0, int y1, int bx)
+{
+    return conv_tile_geom(a.tiles_x, a.TC, a.cap, a.flat, a.batch, x0, x1, y0, y1, bx, S, P, Q);
+}
+template <int S, int P>
+__device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) { return conv_tile_pix(g, wq, x1, S, P); }
+
+// Epilogue shared by the convolution kernels: bias, leaky ReLU, the fused 2x2 max-pool, the decision codes and
+// the stores.  A lane holds, per 32x32 tile, 16 channels (8*(i/4) + 4*hi + i%4) of one pixel.  `bias_lds` is LDS
+// no wavefront reads any more once all of them have arrived here (BM floats are used).
+// Every map store is a buffer store: the lane's 32-bit byte offset carries the pixel (and the lane half's 4 channels),
+// the channel travels as a scalar offset, and a lane that has nothing to store uses an offset beyond the buffer's
+// records, which the hardware drops - no address arithmetic in 64 bits, no branch and no scalar reload per element.
+__device__ __forceinline__ void store_elem(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, float v, const float*)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, vo, so, 0);
+}
+__device__ __forceinline__ void store_elem(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, float v, const bf16_t*)
+{
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)bf16_bits(v), r, vo, so, 0);
+}
+
+// ... of a value that already is what the map holds (a bfloat widened to fp32: its upper half is stored)
+__device__ __forceinline__ void store_rounded(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, float v, const float*)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, vo, so, 0);
+}
+__device__ __forceinline__ void store_rounded(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, float v, const bf16_t*)
+{
+    __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(__float_as_uint(v) >> 16), r, vo, so, 0);
+}
+
+template <typename T, int K, int S, int WAVES_M, int MT, bool POOL_OUT, bool DELTA_IN, int NT>
+__device__ __forceinline__ void conv_epilogue(const MfmaConvArgs& a, const TileGeom& g, v16f (&acc)[MT][NT], float* bias_lds,
+                                              int m0, int x0, int x1, int y0, int stack, int ti, int tj)
+{
+    constexpr int BM = 32 * MT * WAVES_M;
+    constexpr int P = K / 2;                           // S: patch positions per tile pixel and dimension (pool or stride)
+    constexpr unsigned ES = sizeof(T);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_m = wave % WAVES_M, wave_n = wave / WAVES_M;
+    const int hi = lane >> 5, l32 = lane & 31;
+    const View& ov = DELTA_IN ? a.dout : a.out;
+    // the tile's images start at image n_a of the stack; offsets from there fit 32 bits (checked by the launcher)
+    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((T*)ov.p + (long long)stack * ov.ss + (long long)g.n_a * ov.ns),
+                                                                            (short)0, (int)0x7FFFFFFF, 0x00020000);
+    const unsigned ocs = ES * (unsigned)ov.cs;         // bytes between channels
+    // The bias goes through LDS: a global load between the stores below would make every store wait for all
+    // earlier ones (loads and stores share one counter).
+    if (!DELTA_IN) {
+        __syncthreads();                               // every wavefront has left the multiply loop
+        if (tid < BM) bias_lds[tid] = (a.bias && m0 + tid < a.Mtot) ? ld((const T*)a.bias + m0 + tid) : 0.0f;
+        __syncthreads();
+    }
+    if (DELTA_IN) {
+        // Deltas are stored as dLoss/dZ: where the boundary written to carries an activation, its derivative is
+        // applied now.  A lane's 16 channels of a 32-channel block share one sign word; all words are loaded
+        // before the first store, so that no load has to wait for stores.
+        unsigned vo[NT];
+        uint32_t sw[NT][MT];
+        float in_slope = a.in_slope;
+        asm volatile("" : "+v"(in_slope));             // (kept in a register: not re-read from the argument block per element)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int q = (wave_n * NT + t) * 32 + l32;
+            const TilePix tp = tile_pix<S, P>(g, q, x1);
+            const int pn = tp.valid ? tp.n : 0, py = tp.valid ? y0 + tp.y : y0, pxx = tp.valid ? g.ox0 + tp.xl : x0;
+            vo[t] = tp.valid ? ES * (unsigned)((pn - g.n_a) * (int)ov.ns + (py - ov.y0[ti]) * ov.pitch + (pxx - ov.x0[tj])) + 4u * hi * ocs : 0x80000000u;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int mb = m0 + (wave_m * MT + mt) * 32;            // first channel of the block
+                sw[t][mt] = (a.scale_out && mb < a.Mtot) ? *at<uint32_t>(a.isign, stack, ti, tj, pn, mb >> 5, py, pxx) : 0xFFFFFFFFu;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int mb = m0 + (wave_m * MT + mt) * 32;
+                const uint32_t w = sw[t][mt] >> (4 * hi);
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    // (the channel count is a multiple of 4: a group of 4 channels exists as a whole or not at all)
+                    const unsigned vg = mb + 8 * g4 + 4 * hi < a.Mtot ? vo[t] : 0x80000000u;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int i = 4 * g4 + e;
+                        float v = acc[mt][t][i];
+                        if (a.scale_out) v = scaled_delta<T>(v, (w >> (8 * g4 + e)) & 1u, in_slope);
+                        store_elem(orsrc, vg, (unsigned)(mb + 8 * g4 + e) * ocs, v, (const T*)nullptr);
+                    }
+                }
+            }
+        return;
+    }
+    // While another workgroup's wavefront keeps the matrix cores of this SIMD busy, every vector-ALU instruction issued
+    // here waits for a gap between its instructions, so the loop below is written for few of them: the bias is added in a
+    // pass of its own that layers without bias skip, the sign bits are collected with constant masks and brought into
+    // place once per word, scalar offsets carry the channel.
+    float slope = a.slope;
+    asm volatile("" : "+v"(slope));
+    if (a.bias) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const float4 b4 = *(const float4*)(bias_lds + (wave_m * MT + mt) * 32 + 8 * g4 + 4 * hi);
+                const float bb[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[mt][t][4 * g4 + e] += bb[e];
+            }
+    }
+    const __amdgpu_buffer_rsrc_t mrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        POOL_OUT ? (void*)((uint8_t*)a.mask.p + (long long)stack * a.mask.ss + (long long)g.n_a * a.mask.ns) : (void*)ov.p, (short)0, (int)0x7FFFFFFF, 0x00020000);
+    const unsigned mcs = (unsigned)a.mask.cs;
+    // which of the lane's 4 groups of 4 channels exist, as a mask over its 16 sign bits (before they are shifted by 4 * hi)
+    uint32_t gmask[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int mb = m0 + (wave_m * MT + mt) * 32;
+        gmask[mt] = 0;
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4)
+            if (mb + 8 * g4 + 4 * hi < a.Mtot) gmask[mt] |= 0xFu << (8 * g4);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const int q = (wave_n * NT + t) * 32 + l32;
+        const TilePix tp = tile_pix<S, P>(g, POOL_OUT ? (q >> 2) : q, x1);
+        const int pn = tp.n, py = y0 + tp.y, pxx = g.ox0 + tp.xl;
+        bool pvalid = tp.valid;
+        if (POOL_OUT) pvalid = pvalid && (lane & 3) == 0;       // the window's first lane stores
+        const bool powned = pvalid && py >= a.own.y0[ti] && py <= a.own.y1[ti] && pxx >= a.own.x0[tj] && pxx <= a.own.x1[tj];
+        const unsigned vo = pvalid ? ES * (unsigned)((pn - g.n_a) * (int)ov.ns + (py - ov.y0[ti]) * ov.pitch + (pxx - ov.x0[tj])) + 4u * hi * ocs : 0x80000000u;
+        // (code bytes exist only behind a pool, and only for owned pixels)
+        const unsigned mvo = (POOL_OUT && powned) ? (unsigned)((pn - g.n_a) * (int)a.mask.ns + (py - a.mask.y0[ti]) * a.mask.pitch + (pxx - a.mask.x0[tj])) + 4u * hi * mcs
+                                                  : 0x80000000u;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int mb = m0 + (wave_m * MT + mt) * 32;
+            uint32_t signs = 0;                                 // this lane's 16 channels of the block's sign word, bits 8 * g4 + e
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+                const bool gok = (gmask[mt] >> (8 * g4)) & 1u;
+                const unsigned vg = gok ? vo : 0x80000000u, mvg = gok ? mvo : 0x80000000u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int i = 4 * g4 + e;
+                    // compared and recorded as the map will hold it (rounded to the storage type)
+                    float v;
+                    bool pos;
+                    int bi = 0;
+                    if constexpr (sizeof(T) == 4 && !POOL_OUT) {
+                        // (slopes are >= 0, so the activation is positive exactly where the convolution's result is)
+                        const float z = acc[mt][t][i];
+                        pos = z > 0.0f;
+                        v = pos ? z : slope * z;
+                    } else {
+                        v = stored(leaky(acc[mt][t][i], slope), (const T*)nullptr);
+                        if (POOL_OUT) {
+                            // the 4 pixels of a window sit in 4 adjacent lanes, in window order; the first lane decides
+                            const float o1 = quad_xor<1>(v), o2 = quad_xor<2>(v), o3 = quad_xor<3>(v);
+                            if (o1 > v) { v = o1; bi = 1; }
+                            if (o2 > v) { v = o2; bi = 2; }
+                            if (o3 > v) { v = o3; bi = 3; }
+                        }
+                        pos = v > 0.0f;
+                    }
+                    const unsigned so = (unsigned)(mb + 8 * g4 + e);
+                    store_rounded(orsrc, vg, so * ocs, v, (const T*)nullptr);
+                    if (POOL_OUT) __builtin_amdgcn_raw_buffer_store_b8((uint8_t)((bi << 1) | (pos ? 1 : 0)), mrsrc, mvg, so * mcs, 0);
+                    signs |= (pos ? 1u : 0u) << (8 * g4 + e);
+                }
+            }
+            signs = (pvalid ? signs & gmask[mt] : 0u) << (4 * hi);
+            // the other half of the block's channels sits 32 lanes away (same pixel)
+            signs |= (uint32_t)__shfl_xor((int)signs, 32, 64);
+            if (powned && hi == 0 && mb < a.Mtot)
+                *at<uint32_t>(a.osign, stack, ti, tj, pn, mb >> 5, py, pxx) = signs;
+        }
+    }
+}
+
+}  // namespace ftp

@@ -20,6 +20,12 @@ FTP_HD constexpr int conv_dl_max_positions(int K, int BN, bool strided_fwd, bool
                   : strided_fwd ? 768 : K >= 5 ? (BN == 256 ? 768 : 512) : K == 1 ? 256 : (BN == 256 || quad ? 512 : 256);
 }
 
+// The fp32 delta kernel on the bfloat matrix cores (ftp_delta_split.hip): reduction channels per stage, the same for every workgroup
+// shape, so that the summation order, and with it every bit of the result, does not depend on which shape the launch
+// heuristics pick (they look at the batch size); and patch positions in LDS (6 bytes a position and channel: 48 KB, two to
+// three workgroups a CU; 72 KB for the large patches).
+FTP_HD constexpr int split_stage_channels(int K) { return K == 1 ? 32 : 16; }
+FTP_HD constexpr int split_max_positions(int K, int BN) { return K >= 5 ? (BN == 256 ? 768 : 512) : K == 1 ? 256 : 512; }
 
 // Geometry of one tile.  A rectangle is cut into column blocks of TC columns and runs of whole rows (c0 = 0), or, where
 // the launch says so (a rectangle of one column block whose rows fill a tile badly), into runs of `cap` consecutive pixels
@@ -37,8 +43,9 @@ struct TileGeom {
     bool empty;
 };
 
-// Q: positions of a patch row a lane loads at once (0: one; 4: fp32 quads; 8: packed bfloats, whose rows start up to one
-// position early, on the dword grid of the map): patch rows are padded to whole units.
+// Q: positions of a patch row a lane loads at once (0: one; 4: fp32 quads; 2: fp32 quads through pool winners, whose rows
+// start up to one position early, at a window's left pixel; 8: packed bfloats, whose rows start up to one position early, on
+// the dword grid of the map): patch rows are padded to whole units.
 FTP_HD inline TileGeom conv_tile_geom(int tiles_x, int TC, int cap, int flat, int batch, int x0, int x1, int y0, int y1, int bx, int S, int P, int Q)
 {
     TileGeom g;
@@ -64,6 +71,7 @@ FTP_HD inline TileGeom conv_tile_geom(int tiles_x, int TC, int cap, int flat, in
     const int n_l = (g.R0 + g.nrows - 1) / g.rh;
     g.PW = g.TC * S + 2 * P;
     if (Q == 4) g.PW = (g.PW + 3) & ~3;
+    if (Q == 2) g.PW = (g.PW + 1 + 3) & ~3;
     if (Q == 8) g.PW = (g.PW + 1 + 7) & ~7;
     const int first_rows = g.rh - g.y_a < g.nrows ? g.rh - g.y_a : g.nrows;
     g.first_cnt = S * first_rows + 2 * P;
@@ -91,7 +99,7 @@ FTP_HD inline TilePix conv_tile_pix(const TileGeom& g, int wq, int x1, int S, in
 struct TileChoice { int TC, tiles_x, tiles_r, cap, cs, max_img, flat; };
 
 // Tile capacity (pixels or pool windows), column blocking and the worst-case patch size over all stacks.
-// npl: positions of a patch row the kernel loads per lane (0, 4 or 8): rows are padded as tile_geom pads them.
+// npl: positions of a patch row the kernel loads per lane (0, 2, 4 or 8): rows are padded as tile_geom pads them.
 // gather: every further patch position is expensive (the patch is collected element by element - through pool winners,
 // between inserted zeros - or the kernel is bound by the latency of its patch loads).
 inline TileChoice choose_tile(const int* rws, const int* rhs, int N, int M, int batch, int cap0, int S, int P, int max_pos, int npl, bool gather)
@@ -130,7 +138,7 @@ inline TileChoice choose_tile(const int* rws, const int* rhs, int N, int M, int 
                     tiles_all += (double)tiles * ((rw + tc - 1) / tc);
                     int nimg = (rows + rh - 2) / rh + 1; if (nimg > batch) nimg = batch;
                     if (nimg > c.max_img) c.max_img = nimg;
-                    const int pw = npl == 8 ? (tc * S + 2 * P + 1 + 7) & ~7 : npl == 4 ? (tc * S + 2 * P + 3) & ~3 : tc * S + 2 * P;
+                    const int pw = npl == 8 ? (tc * S + 2 * P + 1 + 7) & ~7 : npl == 4 ? (tc * S + 2 * P + 3) & ~3 : npl == 2 ? (tc * S + 2 * P + 1 + 3) & ~3 : tc * S + 2 * P;
                     const int npos = (S * rows + 2 * P * nimg) * pw;
                     if (npos > c.cs) c.cs = npos;
                     if (npos > max_pos && rows > 1) fits = false;

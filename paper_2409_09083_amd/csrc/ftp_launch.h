@@ -89,11 +89,31 @@ struct MfmaConvArgs {
 };
 
 bool mfma_conv_eligible(const ConvArgs& a, bool backward);
-// packed16: relay the filter for the bfloat matrix-core path (what mfma_conv_packs_bf16 says for the layer)
+// 16-bit storage: the layer multiplies on the bfloat matrix cores (stride-1 1x1 / 3x3)
 bool mfma_conv_packs_bf16(const ConvArgs& a);
-void prep_filter(const void* w, int bf16, int packed16, float* wt_fwd, float* wt_bwd, int Cout, int Cin, int K, hipStream_t s);
-int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, const float* wt, hipStream_t s);       // non-zero: does not fit
-int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, const float* wt, hipStream_t s);
+
+// Filter relayout (ftp_prep.hip): one job per convolution of a pass, all in one launch.
+enum PrepKind : int {
+    PREP_PLAIN = 0,                                 // fp32 [tap][reduction channel][output channel]
+    PREP_PACK16 = 1,                                // bfloat [tap][8 channels][output channel][8]
+    PREP_SPLIT = 2                                  // fp32 as three planes of bfloats [8 channels][tap][plane][output channel][8]
+};
+constexpr int kPrepJobs = 48;                       // jobs of one launch (kernel arguments: 48 bytes a job)
+struct PrepJob {
+    const void* w;                                  // filter, OIHW
+    void* wt;
+    int Cout, Cin, KK, kind;
+    int rot;                                        // 1: output channel = ci, reduction channel = co, taps rotated by 180 degrees (delta pass)
+    int bf16;                                       // storage type of w
+    int first;                                      // first block of the job (filled in by prep_filters)
+};
+PrepJob mfma_prep_job(const ConvArgs& c, void* wt, bool backward);
+void prep_filters(PrepJob* jobs, int n, hipStream_t s);
+// wt: the filter as mfma_prep_job's job left it.
+int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);       // non-zero: does not fit
+int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
+// ... of fp32 maps, on the bfloat matrix cores (ftp_delta_split.hip)
+int split_conv_bwd_data(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s);
 // delta through a 3x3 stride-2 convolution by parity classes (ftp_delta_s2.hip); non-zero: does not fit
 int delta_s2_mfma(const ConvArgs& c, const RectTab& inrect, const float* wt, hipStream_t s);
 

@@ -263,13 +263,17 @@ int build_plan(const ftp_layer* layers, int n_layers, int batch, int in_c, int i
     const size_t pp0 = alloc(pp_bytes), pp1 = alloc(pp_bytes);
     for (int b = 1; b <= L; ++b)
         if (delta[b].kind == BUF_WS && delta[b].per_stack) delta[b].offset = delta[b].offset ? pp1 : pp0;
-    // relaid filters for the matrix-core kernels (fp32, two orders per convolution: forward and rotated)
+    // relaid filters for the matrix-core kernels, one area per convolution: every pass writes the form it multiplies with.
+    // fp32 maps keep three planes of bfloats (6 bytes a weight, reduction channels in groups of 8), which fit the 8 bytes a
+    // weight reserved here except where a group is mostly padding (9, 10, 11 or 17 reduction channels): those areas are larger.
     for (Unit& u : p.units) {
         if (u.kind != UNIT_CONV) continue;
         const ftp_layer& ly = p.layers[u.layer];
-        const size_t bytes = (size_t)ly.cout * ly.cin * ly.k * ly.k * sizeof(float);
-        u.wt_fwd_offset = alloc(bytes);
-        u.wt_bwd_offset = alloc(bytes);
+        const size_t area = 2 * align256((size_t)ly.cout * ly.cin * ly.k * ly.k * sizeof(float));
+        const size_t planes = align256(split_filter_bytes(ly.cout, ly.cin, ly.k));
+        const size_t more = dtype == FTP_F32 && planes > area ? planes - area : 0;
+        u.wt_offset = alloc(area + more);
+        p.padding_bytes += more;
     }
     {
         size_t scratch = 0;

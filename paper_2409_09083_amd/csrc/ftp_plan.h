@@ -55,7 +55,7 @@ struct Unit {
     float in_slope = 1.0f;                    // leaky slope of the convolution whose output is boundary bi
     size_t param_offset = 0;                  // first filter element in the parameter vector
     size_t bias_offset = 0;
-    size_t wt_fwd_offset = 0, wt_bwd_offset = 0;   // relaid filter copies in the workspace (bytes)
+    size_t wt_offset = 0;                          // relaid filter in the workspace (bytes; each pass writes its own form)
     int wgrad_shares = 1, wgrad_shares_thin = 1;   // shares of the two matrix-core filter-gradient kernels (the scratch is sized for them)
     int wgrad_shares16 = 1;                        // ... and of the bfloat 3x3 kernel
 };
@@ -78,6 +78,7 @@ struct Plan {
     std::vector<float> act_slope;
     BufRef dy_scaled;                         // whole map at boundary L: the caller's dy times the derivative (if any)
     size_t workspace_bytes = 0, n_params = 0;
+    size_t padding_bytes = 0;                 // part of workspace_bytes: padding of split filters (at most a third of the filters' areas)
     size_t wgrad_scratch_offset = 0;          // batch shares of one layer's partial gradients (bytes)
     size_t split[4] = {0, 0, 0, 0};
     double useful_macs = 0, executed_macs = 0, halo_bytes[2] = {0, 0};
@@ -88,6 +89,13 @@ struct Plan {
 #else
 #define FTP_HD
 #endif
+
+// Bytes of a filter in three planes of bfloats, as the delta pass of fp32 maps reads it (reduction channels padded to groups of
+// 8); 0 where that pass does not take the matrix cores (mfma_conv_eligible).
+inline size_t split_filter_bytes(int cout, int cin, int k)
+{
+    return cin >= 16 && cin % 4 == 0 && cout >= 8 ? (size_t)((cout + 7) / 8 * 8) * cin * k * k * 6 : 0;
+}
 
 // How the matrix-core filter-gradient kernel cuts one stack's owned rectangle (rw x rh, batch images) into chunks
 // of at most 64 pixels (rows padded to an even length) and 192 patch positions: column blocks of TC, row blocks

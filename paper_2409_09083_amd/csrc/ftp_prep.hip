@@ -1,0 +1,101 @@
+// Filter relayout for the matrix-core convolution kernels.  A pass relays the filters of all its convolutions in one launch
+// (a launch per layer took 2 to 4 us each in front of kernels of 10 to 20 us at batch 1): job j of the list owns the blocks
+// from its `first` on; a thread handles 8 reduction channels of one tap and one output channel (PREP_PLAIN: one weight).
+#include "ftp_device.h"
+#include "ftp_launch.h"
+#include "ftp_split.h"
+
+namespace ftp {
+
+struct PrepArgs { PrepJob job[kPrepJobs]; int n; };
+
+__global__ void __launch_bounds__(256)
+k_prep_filters(PrepArgs a)
+{
+    int j = 0;
+    while (j + 1 < a.n && (int)blockIdx.x >= a.job[j + 1].first) ++j;
+    const PrepJob& p = a.job[j];
+    const int Mtot = p.rot ? p.Cin : p.Cout, C = p.rot ? p.Cout : p.Cin, C8 = (C + 7) >> 3, KK = p.KK;
+    // (32 bits count the threads of any filter that fits the memory)
+    const unsigned i = (blockIdx.x - (unsigned)p.first) * 256u + threadIdx.x;
+    if (p.kind == PREP_PLAIN) {
+        // [tap][reduction channel][output channel], fp32; read in the order of the source
+        if (i >= (unsigned)C * (unsigned)Mtot * (unsigned)KK) return;
+        const unsigned e = i / (unsigned)KK, co = e / (unsigned)p.Cin;
+        const int t = (int)(i - e * (unsigned)KK), ci = (int)(e - co * (unsigned)p.Cin);
+        const float v = p.bf16 ? ld((const bf16_t*)p.w + i) : ((const float*)p.w)[i];
+        const int c = p.rot ? (int)co : ci, m = p.rot ? ci : (int)co;
+        ((float*)p.wt)[((long long)(p.rot ? KK - 1 - t : t) * C + c) * Mtot + m] = v;
+        return;
+    }
+    const int taps = p.kind == PREP_PACK16 && KK == 9 ? 10 : KK;
+    if (i >= (unsigned)C8 * (unsigned)taps * (unsigned)Mtot) return;
+    // (taps fastest: the 72 weights of 8 channels x 9 taps are consecutive in the source of the forward order)
+    const unsigned it = i / (unsigned)taps, uq = it / (unsigned)Mtot;
+    const int t = (int)(i - it * (unsigned)taps), m = (int)(it - uq * (unsigned)Mtot), q = (int)uq;
+    auto index = [&](int c) -> long long {
+        const int co = p.rot ? c : m, ci = p.rot ? m : c;
+        return ((long long)co * p.Cin + ci) * KK + (p.rot ? KK - 1 - t : t);
+    };
+    if (p.kind == PREP_SPLIT) {
+        // [8 channels][tap][plane][output channel][8 bfloats]; missing reduction channels are zero.  A weight that is not
+        // finite keeps its upper plane only; one that would round to infinity is truncated instead, so the three planes
+        // always add up to the weight.
+        const float* const w = (const float*)p.w;
+        uint32_t o[3][4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            o[0][d] = o[1][d] = o[2][d] = 0u;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = 8 * q + 2 * d + e;
+                const float v = c < C ? w[index(c)] : 0.0f;
+                uint32_t h, md, lo;
+                split3(v, 0.0f, h, md, lo);
+                if (!(__builtin_fabsf(v) < __builtin_inff())) { md = 0u; lo = 0u; }
+                else if (!(__builtin_fabsf(__uint_as_float(h << 16)) < __builtin_inff())) {
+                    h = __float_as_uint(v) >> 16;
+                    uint32_t z;
+                    split3(v - __uint_as_float(h << 16), 0.0f, md, lo, z);
+                }
+                o[0][d] |= (h & 0xFFFFu) << (16 * e); o[1][d] |= (md & 0xFFFFu) << (16 * e); o[2][d] |= (lo & 0xFFFFu) << (16 * e);
+            }
+        }
+        uint4* const dst = (uint4*)p.wt + ((long long)(q * KK + t) * 3) * Mtot + m;
+#pragma unroll
+        for (int s = 0; s < 3; ++s) dst[(long long)s * Mtot] = make_uint4(o[s][0], o[s][1], o[s][2], o[s][3]);
+    } else {
+        // [tap][8 channels][output channel][8 bfloats], taps padded to an even count with zeros (one instruction multiplies 8
+        // channels of two taps, or 16 channels of one), reduction channels padded to whole groups
+        const bf16_t* const w = (const bf16_t*)p.w;
+        uint32_t o[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            o[d] = 0u;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int c = 8 * q + 2 * d + e;
+                if (t < KK && c < C) o[d] |= (uint32_t)w[index(c)] << (16 * e);
+            }
+        }
+        ((uint4*)p.wt)[((long long)t * C8 + q) * Mtot + m] = make_uint4(o[0], o[1], o[2], o[3]);
+    }
+}
+
+// n <= kPrepJobs
+void prep_filters(PrepJob* jobs, int n, hipStream_t s)
+{
+    PrepArgs a;
+    a.n = n;
+    long long blocks = 0;
+    for (int j = 0; j < n; ++j) {
+        PrepJob& p = jobs[j];
+        const long long C = p.rot ? p.Cout : p.Cin, Mtot = p.rot ? p.Cin : p.Cout, taps = p.kind == PREP_PACK16 && p.KK == 9 ? 10 : p.KK;
+        p.first = (int)blocks;
+        blocks += ((p.kind == PREP_PLAIN ? C : (C + 7) / 8) * taps * Mtot + 255) / 256;
+        a.job[j] = p;
+    }
+    hipLaunchKernelGGL(k_prep_filters, dim3((unsigned)blocks), dim3(256), 0, s, a);
+}
+
+}  // namespace ftp
