@@ -113,7 +113,7 @@ ConvArgs conv_args(const Plan& p, const Unit& u, const UserBufs& ub, const void*
     a.slope = ly.leaky_slope;
     a.N = p.N; a.M = p.M; a.batch = p.batch;
     a.bf16 = p.dtype == FTP_BF16;
-    a.wgrad_shares = u.wgrad_shares; a.wgrad_shares_thin = u.wgrad_shares_thin; a.wgrad_shares16 = u.wgrad_shares16;
+    a.wgrad_shares = u.wgrad_shares; a.wgrad_shares_thin = u.wgrad_shares_thin; a.wgrad_shares16 = u.wgrad_shares16; a.wgrad_shares_split = u.wgrad_shares_split;
     a.in_ws = u.in_act.kind == BUF_WS ? 1 : 0; a.din_ws = u.in_delta.kind == BUF_WS ? 1 : 0;
     return a;
 }
@@ -440,6 +440,9 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 // (its wide loads round addresses down and may run a few bytes past a map: only inside the workspace, which has margins)
                 shares = a.wgrad_shares16;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { wgrad16(a, scratch, aux); });
+            } else if (use_mfma() && !a.has_bias && wgrad_split_eligible(a)) {
+                shares = a.wgrad_shares_split;
+                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { wgrad_split(a, scratch, aux); });
             } else if (use_mfma() && mfma_wgrad_eligible(a)) {
                 shares = a.wgrad_shares;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { mfma_wgrad(a, scratch, aux); });
@@ -566,7 +569,7 @@ int ftp_profile_read(ftp_plan_t* plan, ftp_kernel_time* out, int32_t capacity, i
                 t.bytes_per_launch = stacks * wel * 4.0 + 2.0 * wel * es;
             } else if (g.pass == FTP_PASS_WGRAD_SUM) {
                 const double wel = (double)ly.cout * ly.cin * ly.k * ly.k;
-                const double sh = g.kernel == nullptr ? 1.0 : (double)std::max(std::max(u->wgrad_shares, u->wgrad_shares_thin), u->wgrad_shares16);
+                const double sh = g.kernel == nullptr ? 1.0 : (double)std::max(std::max(u->wgrad_shares, u->wgrad_shares_thin), std::max(u->wgrad_shares16, u->wgrad_shares_split));
                 t.flops_per_launch = stacks * wel * (sh - 1.0);
                 t.bytes_per_launch = stacks * wel * 4.0 * (sh + 1.0);              // (upper bound: the largest share count of the layer)
             } else if (g.pass == FTP_PASS_SCALE_DY) {

@@ -43,7 +43,7 @@ struct ConvArgs {
     int N = 1, M = 1, batch = 1;
     int bf16 = 0;
     int wgrad_shares = 1, wgrad_shares_thin = 1;   // shares of the matrix-core filter-gradient kernels (from the plan, which sized the scratch)
-    int wgrad_shares16 = 1;
+    int wgrad_shares16 = 1, wgrad_shares_split = 1;
     int in_ws = 0, din_ws = 0;      // the activation at the input / the delta at the output lie inside the workspace (which has margins)
 };
 
@@ -137,6 +137,9 @@ bool mfma_wgrad_eligible(const ConvArgs& a);
 // bfloat 3x3 stride-1 filter gradient with packed staging (ftp_wgrad16.hip)
 bool wgrad16_eligible(const ConvArgs& a);
 void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s);
+// fp32 3x3 stride-1 filter gradient on the bfloat matrix cores (ftp_wgrad_split.hip)
+bool wgrad_split_eligible(const ConvArgs& c);
+void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
 // The three matrix-core filter-gradient kernels leave `shares` > 1 partial results per stack in the scratch area;
 // this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own).

@@ -320,6 +320,21 @@ int build_plan(const ftp_layer* layers, int n_layers, int batch, int in_c, int i
             const int shares = std::max(std::max(u.wgrad_shares, u.wgrad_shares_thin), u.wgrad_shares16);
             if (shares > 1) scratch = std::max(scratch, stacks * shares * (size_t)ly.cout * ly.cin * ly.k * ly.k * sizeof(float));
         }
+        // (as many shares as the scratch of the other kernels has room for)
+        for (Unit& u : p.units) {
+            if (u.kind != UNIT_CONV || dtype != FTP_F32) continue;
+            const ftp_layer& ly = p.layers[u.layer];
+            if (ly.k != 3 || ly.stride != 1) continue;
+            const GroupRects& gr = p.groups[u.group];
+            int chunks = 1;
+            const int rh = max_len(gr, FTP_RECT_OWN, u.layer + 1, 1, N);
+            for (int j = 0; j < M; ++j) {
+                const int rw = seg_len(gr.at(FTP_RECT_OWN, u.layer + 1, 0, j));
+                chunks = std::max(chunks, wsplit_chunks(rw, rh, batch, wsplit_tc(rw, rh, batch, u.pooled)).total);
+            }
+            const size_t one = stacks * (size_t)ly.cout * ly.cin * 9 * sizeof(float);
+            u.wgrad_shares_split = wsplit_shares(ly.cout, ly.cin, N * M, chunks, (int)std::max<size_t>(1, std::min<size_t>(scratch / one, 256)));
+        }
         p.wgrad_scratch_offset = alloc(scratch);
     }
     // (a margin at the end: wide loads of the 16-bit kernels may run a few bytes past the last map)

@@ -57,7 +57,7 @@ struct Unit {
     size_t bias_offset = 0;
     size_t wt_offset = 0;                          // relaid filter in the workspace (bytes; each pass writes its own form)
     int wgrad_shares = 1, wgrad_shares_thin = 1;   // shares of the two matrix-core filter-gradient kernels (the scratch is sized for them)
-    int wgrad_shares16 = 1;                        // ... and of the bfloat 3x3 kernel
+    int wgrad_shares16 = 1, wgrad_shares_split = 1;   // ... and of the 3x3 kernels for bfloat and for split fp32 maps
 };
 
 struct Plan {
@@ -197,6 +197,81 @@ inline int wgrad16_shares(int cout, int cin, int stacks, int chunks)
     const double unit_us = 1.6;                                                        // one chunk of one block
     const double share_us = (double)stacks * cout * cin * 9 * 8.0 / 3.0e6;
     const int smax = chunks / 2 < 64 ? (chunks / 2 < 1 ? 1 : chunks / 2) : 64;
+    int best = 1; double best_t = 0;
+    for (int s = 1; s <= smax; ++s) {
+        const double rounds = (double)(long long)((blocks * s + 511.0) / 512.0);
+        const double t = rounds * 2.0 * ((chunks + s - 1) / s) * unit_us + (s > 1 ? s * share_us : 0.0);
+        if (s == 1 || t < best_t) { best = s; best_t = t; }
+    }
+    return best;
+}
+
+// Chunks of the fp32 3x3 filter-gradient kernel on the bfloat matrix cores (ftp_wgrad_split.hip): rows of the owned rectangle at
+// a pitch of ZP positions - whole groups of 8, or, where that is less, the pitch PW of the patch rows (two columns more,
+// padded to quads), so that a group may run over a row's end -, images at a pitch IP of whole groups; up to 64 positions (a column block of TC pixels x RB rows of
+// one image, or TI whole small images) to a chunk, and their patch of X, at most 128 positions a channel.  LDS bytes of one
+// channel of one plane: 128 positions and 4 more that a shifted read may touch, an odd number of 8-byte units; 64 deltas and
+// 16 bytes, an odd number of 16-byte units (lanes read consecutive channels without bank conflicts).
+constexpr int kWsplitPos = 64, kWsplitPatch = 128, kWsplitXRow = 264, kWsplitZRow = 144;
+FTP_HD constexpr int wsplit_waves_ci(int cin) { return cin > 32 ? 2 : 1; }
+FTP_HD constexpr int wsplit_waves_co(int cout, int cin) { return cin > 32 || cout > 32 ? 2 : 1; }
+struct WsplitChunks { int TC, PW, ZP, IP, RB, TI, col_blocks, row_blocks, img_blocks, total; };
+FTP_HD inline WsplitChunks wsplit_chunks(int rw, int rh, int batch, int TC)
+{
+    WsplitChunks c;
+    c.TC = TC;
+    c.PW = (TC + 2 + 3) & ~3;
+    c.ZP = (TC + 7) & ~7; if (c.ZP > c.PW) c.ZP = c.PW;
+    c.col_blocks = (rw + TC - 1) / TC;
+    c.RB = (kWsplitPos - TC) / c.ZP + 1;
+    if (c.RB > kWsplitPatch / c.PW - 2) c.RB = kWsplitPatch / c.PW - 2;
+    if (c.RB > rh) c.RB = rh;
+    c.TI = 1;
+    c.IP = (rh * c.ZP + 7) & ~7;
+    if (c.RB == rh && c.col_blocks == 1) {
+        c.TI = (kWsplitPos - (rh - 1) * c.ZP - TC) / c.IP + 1;
+        const int by_patch = kWsplitPatch / ((rh + 2) * c.PW);
+        if (c.TI > by_patch) c.TI = by_patch;
+        if (c.TI > batch) c.TI = batch;
+        if (c.TI < 1) c.TI = 1;
+    }
+    c.row_blocks = (rh + c.RB - 1) / c.RB;
+    c.img_blocks = (batch + c.TI - 1) / c.TI;
+    c.total = c.img_blocks * c.row_blocks * c.col_blocks;
+    return c;
+}
+// Steps (16 positions of a (co, ci) block, 54 matrix instructions a wavefront) of a chunk of ni images x nr rows x nc columns.
+FTP_HD inline int wsplit_steps(const WsplitChunks& c, int ni, int nr, int nc) { return ((ni - 1) * c.IP + (nr - 1) * c.ZP + nc + 15) / 16; }
+// The column block of rectangles rw wide and up to rh high that takes least: steps, and per chunk loads, splits and barriers.
+// Blocks of 38 pixels are the widest whose three patch rows fit.  (Host; the kernel is told.)
+inline int wsplit_tc(int rw, int rh, int batch, bool pooled, double* steps_per_image = nullptr)
+{
+    int best = 0; double best_cost = 0;
+    const int cb0 = (rw + 37) / 38;
+    for (int cb = cb0; cb <= cb0 + 7 && cb <= rw; ++cb) {
+        int TC = (rw + cb - 1) / cb;
+        if (pooled) TC = (TC + 1) & ~1;                // (whole windows)
+        if (TC > 38) continue;
+        const WsplitChunks c = wsplit_chunks(rw, rh, batch, TC);
+        double steps = 0;
+        for (int r = 0; r < c.row_blocks; ++r) {
+            const int nr = rh - r * c.RB < c.RB ? rh - r * c.RB : c.RB;
+            for (int k = 0; k < c.col_blocks; ++k) steps += wsplit_steps(c, c.TI, nr, rw - k * TC < TC ? rw - k * TC : TC);
+        }
+        const double cost = (steps + 1.5 * c.row_blocks * c.col_blocks) / c.TI;
+        if (best == 0 || cost < best_cost) { best = TC; best_cost = cost; if (steps_per_image) *steps_per_image = steps / c.TI; }
+    }
+    return best;
+}
+// Shares of one stack's chunk list for that kernel, at most `room` (what the scratch area holds): see wgrad16_shares.
+inline int wsplit_shares(int cout, int cin, int stacks, int chunks, int room)
+{
+    const int bco = 32 * wsplit_waves_co(cout, cin), bci = 32 * wsplit_waves_ci(cin);
+    const double blocks = (double)((cout + bco - 1) / bco) * ((cin + bci - 1) / bci) * stacks;
+    const double unit_us = 2.2 * bco * bci / 4096.0 + 1.2;                             // one chunk of one block
+    const double share_us = (double)stacks * cout * cin * 9 * 8.0 / 3.0e6;
+    int smax = chunks < 256 ? chunks : 256;
+    if (smax > room) smax = room;
     int best = 1; double best_t = 0;
     for (int s = 1; s <= smax; ++s) {
         const double rounds = (double)(long long)((blocks * s + 511.0) / 512.0);

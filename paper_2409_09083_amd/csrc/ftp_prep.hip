@@ -1,6 +1,6 @@
 // Filter relayout for the matrix-core convolution kernels.  A pass relays the filters of all its convolutions in one launch
 // (a launch per layer took 2 to 4 us each in front of kernels of 10 to 20 us at batch 1): job j of the list owns the blocks
-// from its `first` on; a thread handles 8 reduction channels of one tap and one output channel (PREP_PLAIN: one weight).
+// from its `first` on; a thread handles two reduction channels of one tap and one output channel (PREP_PLAIN: one weight).
 #include "ftp_device.h"
 #include "ftp_launch.h"
 #include "ftp_split.h"
@@ -29,56 +29,46 @@ k_prep_filters(PrepArgs a)
         return;
     }
     const int taps = p.kind == PREP_PACK16 && KK == 9 ? 10 : KK;
-    if (i >= (unsigned)C8 * (unsigned)taps * (unsigned)Mtot) return;
-    // (taps fastest: the 72 weights of 8 channels x 9 taps are consecutive in the source of the forward order)
-    const unsigned it = i / (unsigned)taps, uq = it / (unsigned)Mtot;
-    const int t = (int)(i - it * (unsigned)taps), m = (int)(it - uq * (unsigned)Mtot), q = (int)uq;
+    if (i >= 4u * (unsigned)C8 * (unsigned)taps * (unsigned)Mtot) return;
+    // (the channel pair, then the tap fastest: the 72 weights of 8 channels x 9 taps are consecutive in the source of the
+    // forward order; 4 threads write 16 consecutive bytes)
+    const unsigned u = i >> 2, ut = u / (unsigned)taps, uq = ut / (unsigned)Mtot;
+    const int d = (int)(i & 3u), t = (int)(u - ut * (unsigned)taps), m = (int)(ut - uq * (unsigned)Mtot), q = (int)uq;
     auto index = [&](int c) -> long long {
         const int co = p.rot ? c : m, ci = p.rot ? m : c;
         return ((long long)co * p.Cin + ci) * KK + (p.rot ? KK - 1 - t : t);
     };
+    const int c0 = 8 * q + 2 * d;
     if (p.kind == PREP_SPLIT) {
         // [8 channels][tap][plane][output channel][8 bfloats]; missing reduction channels are zero.  A weight that is not
         // finite keeps its upper plane only; one that would round to infinity is truncated instead, so the three planes
         // always add up to the weight.
         const float* const w = (const float*)p.w;
-        uint32_t o[3][4];
+        uint32_t o[3] = {0u, 0u, 0u};
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            o[0][d] = o[1][d] = o[2][d] = 0u;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int c = 8 * q + 2 * d + e;
-                const float v = c < C ? w[index(c)] : 0.0f;
-                uint32_t h, md, lo;
-                split3(v, 0.0f, h, md, lo);
-                if (!(__builtin_fabsf(v) < __builtin_inff())) { md = 0u; lo = 0u; }
-                else if (!(__builtin_fabsf(__uint_as_float(h << 16)) < __builtin_inff())) {
-                    h = __float_as_uint(v) >> 16;
-                    uint32_t z;
-                    split3(v - __uint_as_float(h << 16), 0.0f, md, lo, z);
-                }
-                o[0][d] |= (h & 0xFFFFu) << (16 * e); o[1][d] |= (md & 0xFFFFu) << (16 * e); o[2][d] |= (lo & 0xFFFFu) << (16 * e);
+        for (int e = 0; e < 2; ++e) {
+            const float v = c0 + e < C ? w[index(c0 + e)] : 0.0f;
+            uint32_t h, md, lo;
+            split3(v, 0.0f, h, md, lo);
+            if (!(__builtin_fabsf(v) < __builtin_inff())) { md = 0u; lo = 0u; }
+            else if (!(__builtin_fabsf(__uint_as_float(h << 16)) < __builtin_inff())) {
+                h = __float_as_uint(v) >> 16;
+                uint32_t z;
+                split3(v - __uint_as_float(h << 16), 0.0f, md, lo, z);
             }
+            o[0] |= (h & 0xFFFFu) << (16 * e); o[1] |= (md & 0xFFFFu) << (16 * e); o[2] |= (lo & 0xFFFFu) << (16 * e);
         }
-        uint4* const dst = (uint4*)p.wt + ((long long)(q * KK + t) * 3) * Mtot + m;
+        uint32_t* const dst = (uint32_t*)p.wt + 4 * (((long long)(q * KK + t) * 3) * Mtot + m) + d;
 #pragma unroll
-        for (int s = 0; s < 3; ++s) dst[(long long)s * Mtot] = make_uint4(o[s][0], o[s][1], o[s][2], o[s][3]);
+        for (int s = 0; s < 3; ++s) dst[4 * (long long)s * Mtot] = o[s];
     } else {
         // [tap][8 channels][output channel][8 bfloats], taps padded to an even count with zeros (one instruction multiplies 8
         // channels of two taps, or 16 channels of one), reduction channels padded to whole groups
         const bf16_t* const w = (const bf16_t*)p.w;
-        uint32_t o[4];
+        uint32_t o = 0u;
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            o[d] = 0u;
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int c = 8 * q + 2 * d + e;
-                if (t < KK && c < C) o[d] |= (uint32_t)w[index(c)] << (16 * e);
-            }
-        }
-        ((uint4*)p.wt)[((long long)t * C8 + q) * Mtot + m] = make_uint4(o[0], o[1], o[2], o[3]);
+        for (int e = 0; e < 2; ++e) if (t < KK && c0 + e < C) o |= (uint32_t)w[index(c0 + e)] << (16 * e);
+        ((uint32_t*)p.wt)[4 * (((long long)t * C8 + q) * Mtot + m) + d] = o;
     }
 }
 
@@ -92,7 +82,7 @@ void prep_filters(PrepJob* jobs, int n, hipStream_t s)
         PrepJob& p = jobs[j];
         const long long C = p.rot ? p.Cout : p.Cin, Mtot = p.rot ? p.Cin : p.Cout, taps = p.kind == PREP_PACK16 && p.KK == 9 ? 10 : p.KK;
         p.first = (int)blocks;
-        blocks += ((p.kind == PREP_PLAIN ? C : (C + 7) / 8) * taps * Mtot + 255) / 256;
+        blocks += ((p.kind == PREP_PLAIN ? C : 4 * ((C + 7) / 8)) * taps * Mtot + 255) / 256;
         a.job[j] = p;
     }
     hipLaunchKernelGGL(k_prep_filters, dim3((unsigned)blocks), dim3(256), 0, s, a);
