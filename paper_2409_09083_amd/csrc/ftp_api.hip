@@ -433,19 +433,22 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             // are serial among themselves on `aux`, they share the scratch)
             if (overlap && gradient_in_flight && (rc = order(aux, s)) != FTP_OK) return rc;
             int shares = 1;
+            auto with_bias = [&](void (*gradient)(const ConvArgs&, float*, hipStream_t)) {
+                gradient(a, scratch, aux);
+                if (a.has_bias) bias_grad(a, aux);
+            };
             if (use_mfma() && thin_wgrad_eligible(a)) {
                 shares = a.wgrad_shares_thin;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { thin_wgrad(a, scratch, aux); });
-            } else if (use_mfma() && plain_geometry(a) && u.in_act.kind == BUF_WS && u.in_delta.kind == BUF_WS && wgrad16_eligible(a)) {
-                // (its wide loads round addresses down and may run a few bytes past a map: only inside the workspace, which has margins)
+                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(thin_wgrad); });
+            } else if (use_mfma() && plain_geometry(a) && u.in_delta.kind == BUF_WS && wgrad16_eligible(a)) {
                 shares = a.wgrad_shares16;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { wgrad16(a, scratch, aux); });
-            } else if (use_mfma() && !a.has_bias && wgrad_split_eligible(a)) {
+                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad16); });
+            } else if (use_mfma() && wgrad_split_eligible(a)) {
                 shares = a.wgrad_shares_split;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { wgrad_split(a, scratch, aux); });
+                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad_split); });
             } else if (use_mfma() && mfma_wgrad_eligible(a)) {
                 shares = a.wgrad_shares;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { mfma_wgrad(a, scratch, aux); });
+                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(mfma_wgrad); });
             } else {
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { direct_wgrad(a, aux); });
             }

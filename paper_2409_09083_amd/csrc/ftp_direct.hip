@@ -251,6 +251,35 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
     }
 }
 
+// Bias gradient of one output channel and stack: the sum of its deltas (behind a pool: every pooled delta reaches one pixel,
+// so the pooled map is summed over the windows the stack owns).  A launch of its own beside the filter-gradient kernels
+// that do not compute it.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_bias_grad(View din, RectTab own, float* __restrict__ partial, long long n_params, long long b_off, int pooled, int Hp, int Wp, int M, int batch)
+{
+    const int co = blockIdx.x, stack = blockIdx.y, ti = stack / M, tj = stack % M;
+    int x0 = own.x0[tj], x1 = own.x1[tj], y0 = own.y0[ti], y1 = own.y1[ti];
+    if (pooled) {
+        // (windows whose first pixel is owned; a pool fused with its convolution has whole windows in every rectangle)
+        x0 = (x0 + 1) >> 1; y0 = (y0 + 1) >> 1; x1 >>= 1; y1 >>= 1;
+        if (x1 >= Wp) x1 = Wp - 1;
+        if (y1 >= Hp) y1 = Hp - 1;
+    }
+    const int rw = x1 - x0 + 1, px = rw * (y1 - y0 + 1), items = px * batch;
+    float v = 0.0f;
+    for (int it = threadIdx.x; it < items; it += 256) {
+        const int n = it / px, r = it - n * px, y = r / rw;
+        v += ld(at<T>(din, stack, ti, tj, n, co, y0 + y, x0 + r - y * rw));
+    }
+    __shared__ float red[4];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) partial[(long long)stack * n_params + b_off + co] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 // ---- lone 2x2 max-pool ---------------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(64)
@@ -457,6 +486,14 @@ void wgrad_t(const ConvArgs& a, hipStream_t s)
 void direct_conv_fwd(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_conv_fwd_direct"; if (a.bf16) conv_fwd_t<bf16_t>(a, s); else conv_fwd_t<float>(a, s); }
 void direct_conv_bwd_data(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_conv_bwd_data_direct"; if (a.bf16) conv_bwd_data_t<bf16_t>(a, s); else conv_bwd_data_t<float>(a, s); }
 void direct_wgrad(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_wgrad_direct"; if (a.bf16) wgrad_t<bf16_t>(a, s); else wgrad_t<float>(a, s); }
+
+// a.rect = owned rectangle at the convolution output (before the pool)
+void bias_grad(const ConvArgs& a, hipStream_t s)
+{
+    dim3 grid(a.Cout, a.N * a.M), block(256);
+    if (a.bf16) hipLaunchKernelGGL(k_bias_grad<bf16_t>, grid, block, 0, s, a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch);
+    else        hipLaunchKernelGGL(k_bias_grad<float>, grid, block, 0, s, a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch);
+}
 
 void pool_fwd(const PoolArgs& a, hipStream_t s)
 {

@@ -133,6 +133,15 @@ struct MfmaWgradArgs {
     int M, batch;
 };
 
+// The matrix-core filter-gradient kernels multiply blocks of 32 or 64 output by 32 or 64 input channels; narrower layers pay for
+// whole blocks and are worth it once there is something to multiply: the direct kernel reaches 1.8e12 multiply-adds a second
+// (208 -> 16 channels, 17 images of 40 x 148: 1.67 ms), so below about 4e7 of them it is done before a matrix-core kernel and
+// its share sum have started (8 -> 16 channels at 32 x 32: 10 us).
+inline bool wgrad_wide_enough(const ConvArgs& c)
+{
+    if (c.Cout >= 32 && c.Cin >= 16) return true;
+    return c.Cin > 4 && (double)c.batch * c.Hc * c.Wc * c.Cout * c.Cin * c.K * c.K >= 4.0e7;
+}
 bool mfma_wgrad_eligible(const ConvArgs& a);
 // bfloat 3x3 stride-1 filter gradient with packed staging (ftp_wgrad16.hip)
 bool wgrad16_eligible(const ConvArgs& a);
@@ -160,6 +169,7 @@ void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
 void direct_conv_fwd(const ConvArgs& a, hipStream_t s);
 void direct_conv_bwd_data(const ConvArgs& a, hipStream_t s);
 void direct_wgrad(const ConvArgs& a, hipStream_t s);
+void bias_grad(const ConvArgs& a, hipStream_t s);   // (direct_wgrad computes it itself, the other filter-gradient kernels do not)
 void pool_fwd(const PoolArgs& a, hipStream_t s);
 void pool_bwd(const PoolArgs& a, hipStream_t s);
 void reduce_wgrad(const float* partial, float* wgrad, long long n_params, int stacks, hipStream_t s);

@@ -25,6 +25,7 @@
 // so larger filters are split over blockIdx.x, each part staging the same chunks.
 #include "ftp_device.h"
 #include "ftp_launch.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace ftp {
@@ -443,12 +444,18 @@ bool mfma_wgrad_eligible(const ConvArgs& c)
 {
     if (c.pooled && (c.S != 1 || c.K > 3)) return false;
     if (c.S == 2 && c.K > 3) return false;
-    // (the fp32 patch loads address one stack's images with 32-bit byte offsets; a chunk spans at most 64 images)
-    const bool direct = !c.bf16 || c.S == 2;           // (the patch goes straight into LDS)
-    if (direct && 4.0 * (64.0 * (double)c.in.ns + (double)c.Cin * (double)c.in.cs) >= 2.0e9) return false;
-    if (direct && 4.0 * (64.0 * (double)c.din.ns + (double)c.Cout * (double)c.din.cs) >= 2.0e9) return false;
-    if (!c.bf16 && c.pooled && 64.0 * (double)c.mask.ns + (double)c.Cout * (double)c.mask.cs >= 2.0e9) return false;
-    return !c.has_bias && c.Cout >= 32 && c.Cin >= 16;
+    // (the patch loads of the fp32 path address one chunk's images with 32-bit byte offsets)
+    if (!c.bf16 || c.S == 2) {
+        int ti = 1;
+        for (int i = 0; i < c.N; ++i)
+            for (int j = 0; j < c.M; ++j)
+                ti = std::max(ti, wgrad_chunks(c.rect.x1[j] - c.rect.x0[j] + 1, c.rect.y1[i] - c.rect.y0[i] + 1, c.batch, c.K / 2, c.S).TI);
+        if (ti > c.batch) ti = c.batch;
+        if (4.0 * ((double)ti * (double)c.in.ns + (double)c.Cin * (double)c.in.cs) >= 2.0e9) return false;
+        if (4.0 * ((double)ti * (double)c.din.ns + (double)c.Cout * (double)c.din.cs) >= 2.0e9) return false;
+        if (!c.bf16 && c.pooled && (double)ti * (double)c.mask.ns + (double)c.Cout * (double)c.mask.cs >= 2.0e9) return false;
+    }
+    return wgrad_wide_enough(c);
 }
 
 // c.rect = owned rectangle at the convolution output (before the pool), c.own = owned rectangle at the convolution

@@ -94,7 +94,7 @@ struct Plan {
 // 8); 0 where that pass does not take the matrix cores (mfma_conv_eligible).
 inline size_t split_filter_bytes(int cout, int cin, int k)
 {
-    return cin >= 16 && cin % 4 == 0 && cout >= 8 ? (size_t)((cout + 7) / 8 * 8) * cin * k * k * 6 : 0;
+    return cin >= 8 && cin % 4 == 0 && cout >= 8 ? (size_t)((cout + 7) / 8 * 8) * cin * k * k * 6 : 0;
 }
 
 // How the matrix-core filter-gradient kernel cuts one stack's owned rectangle (rw x rh, batch images) into chunks

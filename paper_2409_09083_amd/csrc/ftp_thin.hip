@@ -1200,7 +1200,7 @@ ThinStream stream_geom(const ConvArgs& c)
 // c.rect must hold the owned rectangles.
 bool thin_wgrad_eligible(const ConvArgs& c)
 {
-    if (c.has_bias || !(c.Cin * c.K * c.K <= 32 || (c.Cin <= 4 && c.Cin * c.K * c.K <= 160))) return false;
+    if (!(c.Cin * c.K * c.K <= 32 || (c.Cin <= 4 && c.Cin * c.K * c.K <= 160))) return false;
     if (c.pooled && (c.S != 1 || c.K > 3)) return false;
     if (c.pooled) {
         // owned rectangles of a pooled convolution consist of whole windows; anything else goes to the generic kernel

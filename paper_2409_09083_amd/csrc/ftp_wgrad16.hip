@@ -23,6 +23,7 @@
 // Two patch buffers alternate, so the loads of chunk i+1 are in flight while the matrix cores work on chunk i.
 #include "ftp_device.h"
 #include "ftp_launch.h"
+#include <algorithm>
 
 namespace ftp {
 
@@ -49,7 +50,9 @@ __device__ __forceinline__ uint32_t alignhalf(uint32_t hi, uint32_t lo) { return
 
 // HALF: 0 = deltas at the resolution of the owned rectangle; 1 = a 2x2 pool follows the convolution: the deltas sit
 // at pooled resolution and a pixel receives its window's delta only if it is the window's winner.
-template <int WAVES_CI, int HALF>
+// WS: the input map lies inside the workspace, which has margins; in a buffer of the caller's, units that reach beyond its
+// first or last element (a few of the first and last image) are collected element by element.
+template <int WAVES_CI, int HALF, bool WS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_mfma16(Wgrad16Args a)
 {
@@ -131,6 +134,12 @@ k_wgrad_mfma16(Wgrad16Args a)
     // so dword loads would take four times as many instructions).  A unit is loaded if its row lies in the map and it
     // overlaps the needed columns [xb - 1, xb + nc] cut to the map.  Its address is a multiple of 4 bytes, possibly
     // 4 bytes before the view (the buffer resource starts 4 bytes early).
+    // (element offset of the unit from the start of the caller's buffer: one stack stride, whole maps)
+    const long long in_total = (long long)batch * in_ns;
+    auto beyond = [&](const auto& c, int ci, int il, int y, int mx) {
+        const long long e = (long long)(c.n0 + il) * in_ns + (long long)(ci0 + ci) * in_cs + (long long)(y - in_y0) * in_pitch + (mx - in_x0);
+        return e < 0 || e + 8 > in_total;
+    };
     const bf16_t* const xstack = (const bf16_t*)a.in.p + (long long)stack * a.in.ss - 2;
     auto issue_x = [&](unsigned char* Xb, const Chunk& c) {
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(xstack + (long long)c.n0 * in_ns), (short)0, (int)kRecords16, 0x00020000);
@@ -144,7 +153,8 @@ k_wgrad_mfma16(Wgrad16Args a)
 #pragma unroll
             for (int k = 0; k < BCI / 4; ++k) {
                 const int ci = wave + 4 * k;
-                const unsigned v = ci0 + ci < Cin ? vo : kOob16;
+                unsigned v = ci0 + ci < Cin ? vo : kOob16;
+                if (!WS && beyond(c, ci, x_il, y, mx)) v = kOob16;
                 const unsigned so = 2u * (unsigned)((ci0 + ci) * in_cs);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, FTP_LDS_PTR(Xb + ci * XSB), 16, v, so, 0, 0);
             }
@@ -156,6 +166,17 @@ k_wgrad_mfma16(Wgrad16Args a)
     // them once its loads have landed: lane = patch row, a few zero stores per channel.
     auto fixup_x = [&](unsigned char* Xb, const Chunk& c) {
         const int na = c.xb - 1 > 0 ? c.xb - 1 : 0, nb = c.xb + c.nc < Wc ? c.xb + c.nc : Wc - 1;
+        if constexpr (!WS) {
+            const int y = c.yb - 1 + x_lr, mx = c.xb - 1 - xs + 8 * x_u;
+            if (lane < c.ni * (c.nr + 2) * G && y >= 0 && y < Hc && mx + 7 >= na && mx <= nb)
+                for (int k = 0; k < BCI / 4; ++k) {
+                    const int ci = wave + 4 * k;
+                    if (ci0 + ci >= Cin || !beyond(c, ci, x_il, y, mx)) continue;
+                    const bf16_t* const row = (const bf16_t*)a.in.p + (long long)(c.n0 + x_il) * in_ns + (long long)(ci0 + ci) * in_cs + (long long)(y - in_y0) * in_pitch - in_x0;
+                    for (int e = 0; e < 8; ++e)
+                        if (mx + e >= na && mx + e <= nb) *(bf16_t*)(Xb + ci * XSB + 16 * lane + 2 * e) = row[mx + e];
+                }
+        }
         const int e_first = na - (c.xb - 1) + xs, e_last = nb - (c.xb - 1) + xs;      // first / last needed position (e_first <= 2)
         int z = e_last + 1;
         const int zend = (e_last | 7) + 1;                         // positions [e_last + 1, zend) of the last unit are cleared
@@ -426,10 +447,14 @@ bool even_view(const View& v)
 // boundary (pairs of pixels travel as dwords), offsets inside one stack within 31 bits.
 bool wgrad16_eligible(const ConvArgs& c)
 {
-    if (!c.bf16 || c.K != 3 || c.S != 1 || c.has_bias || c.Cout < 32 || c.Cin < 16) return false;
+    if (!c.bf16 || c.K != 3 || c.S != 1 || !wgrad_wide_enough(c)) return false;
     if (c.pooled && ((c.Hc | c.Wc) & 1)) return false;
     if (!even_view(c.in) || ((uintptr_t)c.din.p & 3) || ((uintptr_t)c.mask.p & 3)) return false;
-    const double img = (double)kW16Groups;              // a chunk spans at most this many images
+    double img = 1.0;                                   // images a chunk spans
+    for (int i = 0; i < c.N; ++i)
+        for (int j = 0; j < c.M; ++j)
+            img = std::max(img, (double)wgrad16_chunks(c.rect.x1[j] - c.rect.x0[j] + 1, c.rect.y1[i] - c.rect.y0[i] + 1, c.batch, w16_patch_elems(w16_waves_ci(c.Cin)), 1).TI);
+    img = std::min(img + 1.0, (double)c.batch);          // (one more where the patch starts on the dword grid)
     if (2.0 * (img * (double)c.in.ns + (double)c.Cin * (double)c.in.cs) >= 2.0e9) return false;
     if (2.0 * (img * (double)c.din.ns + (double)c.Cout * (double)c.din.cs) >= 2.0e9) return false;
     if (c.pooled && img * (double)c.mask.ns + (double)c.Cout * (double)c.mask.cs >= 2.0e9) return false;
@@ -450,13 +475,15 @@ void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s)
     const int tiles = ((c.Cout + 63) / 64) * ((c.Cin + BCI - 1) / BCI);
     a.gx = tiles; a.stacks = c.N * c.M;
     dim3 grid(xcd_grid(a.splits * a.stacks, a.gx)), block(256);
-#define FTP_W16(WCI, HF) do { \
+#define FTP_W16(WCI, HF, WSP) do { \
         static thread_local bool granted = false; \
-        if (!granted) { (void)hipFuncSetAttribute((const void*)k_wgrad_mfma16<WCI, HF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); granted = true; } \
-        g_kernel_label = "k_wgrad_mfma16<" #WCI ", " #HF ">"; \
-        hipLaunchKernelGGL((k_wgrad_mfma16<WCI, HF>), grid, block, lds, s, a); } while (0)
-    if (waves_ci == 2) { if (c.pooled) FTP_W16(2, 1); else FTP_W16(2, 0); }
-    else               { if (c.pooled) FTP_W16(1, 1); else FTP_W16(1, 0); }
+        if (!granted) { (void)hipFuncSetAttribute((const void*)k_wgrad_mfma16<WCI, HF, WSP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); granted = true; } \
+        g_kernel_label = "k_wgrad_mfma16<" #WCI ", " #HF ", " #WSP ">"; \
+        hipLaunchKernelGGL((k_wgrad_mfma16<WCI, HF, WSP>), grid, block, lds, s, a); } while (0)
+#define FTP_W16P(WCI, WSP) do { if (c.pooled) FTP_W16(WCI, 1, WSP); else FTP_W16(WCI, 0, WSP); } while (0)
+    if (waves_ci == 2) { if (c.in_ws) FTP_W16P(2, true); else FTP_W16P(2, false); }
+    else               { if (c.in_ws) FTP_W16P(1, true); else FTP_W16P(1, false); }
+#undef FTP_W16P
 #undef FTP_W16
 }
 

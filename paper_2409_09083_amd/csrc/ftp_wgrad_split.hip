@@ -355,7 +355,7 @@ k_wgrad_split(WsplitArgs a)
 // fp32 maps, 3x3, stride 1, with or without the fused pool; offsets of a chunk's images within 31 bits.
 bool wgrad_split_eligible(const ConvArgs& c)
 {
-    if (c.bf16 || c.K != 3 || c.S != 1 || c.Cout < 32 || c.Cin < 16) return false;
+    if (c.bf16 || c.K != 3 || c.S != 1 || !wgrad_wide_enough(c)) return false;
     if (c.pooled) {
         if ((c.Hc | c.Wc) & 1) return false;
         // (owned rectangles of a pooled convolution consist of whole windows)
