@@ -8,9 +8,6 @@
 namespace ftp {
 
 FTP_HD constexpr bool conv_dl_quads(size_t elem, bool pool_in, bool up_in) { return elem == 4 && !pool_in && !up_in; }
-// 16-bit maps on the bfloat matrix-core path (stride-1 1x1 / 3x3), patch not gathered through pool winners: the patch may
-// stay packed in LDS, two bytes a position, loaded 8 positions (16 bytes) a lane
-FTP_HD constexpr bool conv_dl_packable(size_t elem, int K, int stride, bool pool_in) { return elem == 2 && K <= 3 && stride == 1 && !pool_in; }
 // (a multiple of 256; quads pad every patch row to a multiple of 4 positions, which costs the narrow rectangles of deep
 // layers up to a fifth more positions: their 128-pixel tiles get the room of the 256-pixel ones)
 // (packed bfloats: twice the positions in the same bytes, in blocks of 512)
@@ -26,6 +23,11 @@ FTP_HD constexpr int conv_dl_max_positions(int K, int BN, bool strided_fwd, bool
 // three workgroups a CU; 72 KB for the large patches).
 FTP_HD constexpr int split_stage_channels(int K) { return K == 1 ? 32 : 16; }
 FTP_HD constexpr int split_max_positions(int K, int BN) { return K >= 5 ? (BN == 256 ? 768 : 512) : K == 1 ? 256 : 512; }
+
+// The 16-bit kernel (ftp_conv_bf16.hip): patch positions in LDS and groups of 8 reduction channels per stage, one unit of 8
+// positions x 8 channels a thread (32 KB).
+FTP_HD constexpr int conv_bf_positions(int K, int BN) { return K == 3 ? (BN == 512 ? 1024 : 512) : BN == 512 ? 512 : 256; }
+FTP_HD constexpr int conv_bf_octets(int K, int BN) { return 2048 / conv_bf_positions(K, BN); }
 
 // Geometry of one tile.  A rectangle is cut into column blocks of TC columns and runs of whole rows (c0 = 0), or, where
 // the launch says so (a rectangle of one column block whose rows fill a tile badly), into runs of `cap` consecutive pixels

@@ -10,10 +10,8 @@
 // and the filter slice of a few channels x K*K taps sit in LDS; v_mfma_f32_32x32x2_f32 reads both from there.
 // MFMA lane layout (64 lanes): A[m = lane%32][k = lane/32], B[k = lane/32][n = lane%32],
 // D[m = 8*(i/4) + 4*(lane/32) + i%4][n = lane%32] for accumulator register i of 16.
-// With 16-bit (bfloat) maps and filters the stride-1 1x1 / 3x3 layers multiply with v_mfma_f32_32x32x16_bf16
-// instead (A[m][k = 8*(lane/32) + j], B[k = 8*(lane/32) + j][n], j < 8, same D): products of two bfloats are exact in
-// fp32 and the sums are accumulated in fp32, so this is the same arithmetic at sixteen times the rate (the older
-// 32x32x8 form runs at half of that on this chip).
+// 16-bit maps: forward and deltas of the 5x5 / 7x7 and of the strided layers (the elements widen to fp32); the stride-1 1x1 /
+// 3x3 ones multiply bfloats (ftp_conv_bf16.hip).  fp32: the forward pass; fp32 deltas multiply bfloats (ftp_delta_split.hip).
 #include "ftp_device.h"
 #include "ftp_launch.h"
 #include "ftp_conv_tiles.h"
@@ -43,69 +41,48 @@ constexpr unsigned kBufRecords = 0x7FFFFFFFu;
 // bit of the result, does not depend on which shape the launch heuristics pick (they look at the batch size).
 // (5x5 and 7x7 filters take 2 channels per stage so that a slice of all taps still fits; a strided forward pass
 // reads a patch four times the size of its tile.)
-// (the bfloat matrix-core path takes 8 channels of a 3x3 filter per stage: one instruction multiplies 8 of them)
-__host__ __device__ constexpr int conv_dl_stage_channels(int K, bool strided_fwd, bool bf_mfma) { return K >= 5 ? 2 : (K == 1 && !strided_fwd) ? 16 : bf_mfma ? 8 : 4; }
-// POOL_IN (delta back-propagation through a fused pool): the patch lives at the convolution output, the delta at
-// pooled resolution; a patch position receives its window's delta only if it is the window's winner for that
-// channel.  The winner codes of the stage after next are loaded into registers one stage ahead, and a lane whose
-// position lost simply loads from an out-of-range offset (= 0).
+__host__ __device__ constexpr int conv_dl_stage_channels(int K, bool strided_fwd) { return K >= 5 ? 2 : (K == 1 && !strided_fwd) ? 16 : 4; }
 // STRIDE = 2, forward: output pixel (y, x) reads the patch at (2y, 2x), as the first pixel of a pool window does.
 // STRIDE = 2, delta back-propagation: the adjoint of a strided convolution is the stride-1 one applied to the
 // deltas with zeros inserted between them; a patch position at even coordinates loads delta (y/2, x/2), every
 // other one loads from an out-of-range offset (three quarters of the matrix-core work multiply zeros).
-// Wavefronts per SIMD the register allocation aims at: two as a rule (the fp32 tiles have 128 accumulator registers; the
-// small tiles of the bfloat path then come out at about 160 registers, three wavefronts per SIMD); four for the pooled
-// forward kernels of the bfloat path (32 accumulator registers; their epilogue is what needs the registers), which wait for
-// loads more than they multiply and are as fast as the number of workgroups a CU holds (LDS holds four): config 5,
-// forward of the three pooled layers 0.45 / 0.28 / 0.22 -> 0.44 / 0.26 / 0.21 ms; the same target made the unpooled and the
-// delta kernels of the deep layers slower (more workgroups competing for the L2) and is not used there.
-__host__ __device__ constexpr int conv_dl_waves(size_t elem, int K, int stride, int MT, int BN, int WAVES_M, bool pool_out)
+// Wavefronts per SIMD the register allocation aims at: two as a rule (the fp32 tiles have 128 accumulator registers).
+__host__ __device__ constexpr int conv_dl_waves(size_t elem, int K, int stride, int MT, int BN, int WAVES_M)
 {
     // (fp32 3x3, 256 pixels, at most 64 accumulator registers: these came out at 131-134 registers, one too many for a
     // fourth workgroup on the CU, which LDS would hold: config 4, forward of the 32 -> 64 layer 2.34 -> 2.22 ms)
-    if (elem == 4 && K == 3 && stride == 1 && BN == 256 && MT * (BN / 32 / (4 / WAVES_M)) <= 4) return 4;
-    return (elem == 2 && K <= 3 && stride == 1 && pool_out && BN == 128 && MT * (BN / 32 / (4 / WAVES_M)) <= 2) ? 4 : 2;
+    return elem == 4 && K == 3 && stride == 1 && BN == 256 && MT * (BN / 32 / (4 / WAVES_M)) <= 4 ? 4 : 2;
 }
 
-template <typename T, int K, int WAVES_M, int MT, int BN, bool POOL_OUT, bool DELTA_IN, bool POOL_IN, int STRIDE, bool WIDE>
-__global__ void __launch_bounds__(256, conv_dl_waves(sizeof(T), K, STRIDE, MT, BN, WAVES_M, POOL_OUT))
+template <typename T, int K, int WAVES_M, int MT, int BN, bool POOL_OUT, bool DELTA_IN, int STRIDE, bool WIDE>
+__global__ void __launch_bounds__(256, conv_dl_waves(sizeof(T), K, STRIDE, MT, BN, WAVES_M))
 k_conv_mfma_dl(MfmaConvArgs a)
 {
-    // WIDE: the patch travels 16 bytes a lane (fp32: quads of positions; bfloat matrix-core path: packed, 8 positions)
-    static_assert(!WIDE || conv_dl_packable(sizeof(T), K, STRIDE, POOL_IN) || conv_dl_quads(sizeof(T), POOL_IN, STRIDE == 2 && DELTA_IN),
-                  "wide patch loads: fp32 patches that are not gathered element by element, and the bfloat matrix-core path");
-    static_assert(STRIDE == 1 || !(POOL_OUT || POOL_IN), "strided convolutions with a fused pool take the direct kernels");
-    constexpr bool STRIDED_FWD = STRIDE == 2 && !DELTA_IN, UP_IN = STRIDE == 2 && DELTA_IN, HALF_IN = POOL_IN || UP_IN;
+    // WIDE: the patch travels 16 bytes a lane, a quad of positions
+    static_assert(!WIDE || conv_dl_quads(sizeof(T), false, STRIDE == 2 && DELTA_IN), "wide patch loads: fp32 patches that are not gathered element by element");
+    static_assert(sizeof(T) == 4 || K >= 5 || STRIDE == 2, "16-bit 1x1 / 3x3 layers of stride 1 take ftp_conv_bf16.hip");
+    static_assert(STRIDE == 1 || !POOL_OUT, "strided convolutions with a fused pool take the direct kernels");
+    constexpr bool STRIDED_FWD = STRIDE == 2 && !DELTA_IN, UP_IN = STRIDE == 2 && DELTA_IN;
     constexpr unsigned ES = sizeof(T);                 // bytes per map element
     constexpr int WAVES_N = 4 / WAVES_M;
     constexpr int NT = BN / 32 / WAVES_N;
     constexpr int BM = 32 * MT * WAVES_M;
-    constexpr bool BF = sizeof(T) == 2 && K <= 3 && STRIDE == 1;
-    constexpr int kCK = conv_dl_stage_channels(K, STRIDED_FWD, BF);
+    constexpr int kCK = conv_dl_stage_channels(K, STRIDED_FWD);
     constexpr int KK = K * K, P = K / 2;
     constexpr int S = (POOL_OUT || STRIDED_FWD) ? 2 : 1;
-    constexpr bool XH = WIDE && sizeof(T) == 2;        // the patch stays packed: [channel][position] bfloats
-    constexpr bool XQ = WIDE && sizeof(T) == 4;        // fp32 quads
-    constexpr int XMAX = conv_dl_max_positions(K, BN, STRIDED_FWD, XQ, XH);
+    constexpr int XMAX = conv_dl_max_positions(K, BN, STRIDED_FWD, WIDE);
     constexpr int MAXPOS = XMAX / 256;
-    // fp32 patches (not those gathered element by element through pool winners or between inserted zeros) travel 16
+    // fp32 patches (not those gathered element by element between inserted zeros) travel 16
     // bytes a lane: a quad of consecutive positions of one patch row (rows are padded to whole quads), 64 quads = 256
     // positions to an instruction, NQB such blocks per channel; the wavefronts take (block, channel) pairs in turn.
-    // Packed bfloat patches travel the same way, 8 positions (16 bytes) a lane, 512 positions to an instruction; their rows
-    // begin on the dword grid of the map (up to one position before the first column the tile needs).
-    constexpr bool XW = XQ || XH;                      // wide loads
-    constexpr int NPL = XH ? 8 : 4;                    // positions per lane
-    constexpr int NQB = XMAX / (64 * NPL), NXI = (NQB * kCK + 3) / 4;
+    constexpr int NQB = XMAX / 256, NXI = (NQB * kCK + 3) / 4;
     constexpr bool ONEBLK = 4 % NQB == 0;              // a wavefront always meets the same block
     constexpr int NXB = ONEBLK ? 1 : NXI;
-    // bfloat matrix-core path: the filter slice is ROWS rows of [BM][8 bfloats]; a row is (tap, the stage's 8
-    // channels) for 3x3 (9 taps + 1 row of zeros) and (channels 8r .. 8r+7) for 1x1; step s multiplies rows 2s, 2s+1
-    constexpr int ROWS = K == 3 ? 10 : kCK / 8;
-    constexpr int WF = BF ? ROWS * BM * 4 : KK * kCK * BM;   // dwords of one filter slice (fp32: [tap][channel][BM])
-    constexpr int WPIECES = WF / 64;                   // 64-dword pieces of the slice, dealt round-robin to the 4 wavefronts
+    constexpr int WF = KK * kCK * BM;                  // floats of one filter slice, [tap][channel][BM]
+    constexpr int WPIECES = WF / 64;                   // 64-float pieces of the slice, dealt round-robin to the 4 wavefronts
     constexpr int WINSTR = (WPIECES + 3) / 4;
     static_assert(WF % 64 == 0, "the filter slice is loaded in 64-float pieces");
-    constexpr int XDW = XH ? kCK * XMAX / 2 : kCK * XMAX;      // dwords of one stage's patch
+    constexpr int XDW = kCK * XMAX;                    // dwords of one stage's patch
     __shared__ __attribute__((aligned(16))) float bufA[WF + XDW];
     __shared__ __attribute__((aligned(16))) float bufB[WF + XDW];
 
@@ -126,39 +103,35 @@ k_conv_mfma_dl(MfmaConvArgs a)
     }
     const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
-    const TileGeom g = tile_geom<S, P, XH ? 8 : XQ ? 4 : 0>(a, x0, x1, y0, y1, vtile);
+    const TileGeom g = tile_geom<S, P, WIDE ? 4 : 0>(a, x0, x1, y0, y1, vtile);
     if (g.empty) return;
     const int m0 = (vgroup % a.mblocks) * BM;
     const int PW = g.PW, CS = a.cs;                    // CS: whole 64-position blocks cover every patch
 
-    // packed patches: a row starts `sh` (0 or 1) positions before the tile's first patch column, where the map's dword grid falls
-    const int sh = XH ? ((g.ox0 * S - P - (DELTA_IN ? a.din : a.in).x0[tj]) & 1) : 0;
     int baseB[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int q = (wave_n * NT + t) * 32 + l32;
         const TilePix tp = tile_pix<S, P>(g, POOL_OUT ? (q >> 2) : q, x1);
         const int pos = POOL_OUT ? (q & 3) : 0;
-        baseB[t] = (tp.valid ? (tp.prow + (pos >> 1)) * PW + tp.xl * S + (pos & 1) + sh : 0) + (BF ? 0 : hi * CS);
+        baseB[t] = (tp.valid ? (tp.prow + (pos >> 1)) * PW + tp.xl * S + (pos & 1) : 0) + hi * CS;
     }
-    const int baseA = (BF ? 0 : hi * BM) + wave_m * (32 * MT) + l32;
+    const int baseA = hi * BM + wave_m * (32 * MT) + l32;
 
     // ---- byte offset of each lane's patch positions from the workgroup's base (channel 0); padding -> out of range
     const int npos = g.npos;
     const View& sv = DELTA_IN ? a.din : a.in;
     const T* src = (const T*)sv.p + (long long)stack * sv.ss + (long long)g.n_a * sv.ns;
-    unsigned xoff[XW ? NXB : MAXPOS];
-    int moff[MAXPOS];               // POOL_IN: element offset in the code map (channel 0), this position's place in its window in the top bits
+    unsigned xoff[WIDE ? NXB : MAXPOS];
     unsigned xfix[NXB];             // wide loads: elements of the lane's unit that lie beside the map (zero padding): cleared once the unit has landed
-    const uint8_t* __restrict__ msk = (const uint8_t*)a.mask.p + (long long)stack * a.mask.ss + (long long)g.n_a * a.mask.ns;
-    if constexpr (XW) {
-        // The buffer starts one unit in front of the images' first element, so that a unit that begins beside the map's
+    if constexpr (WIDE) {
+        // The buffer starts one quad in front of the images' first element, so that a quad that begins beside the map's
         // left border still has a non-negative offset (the maps lie inside the workspace, which has margins).
-        src -= NPL;
+        src -= 4;
 #pragma unroll
         for (int ub = 0; ub < NXB; ++ub) {
             const int blk = ONEBLK ? wave % NQB : (wave + 4 * ub) % NQB;
-            const int s = NPL * (blk * 64 + lane);
+            const int s = 4 * (blk * 64 + lane);
             xoff[ub] = kOobOffset; xfix[ub] = 0;
             if (s < npos) {
                 const int pr = s / PW, c = s - pr * PW;
@@ -167,22 +140,22 @@ k_conv_mfma_dl(MfmaConvArgs a)
                     const int t = pr - g.first_cnt;
                     k = 1 + t / g.per_cnt; lr = t - (k - 1) * g.per_cnt; ybase = 0;
                 }
-                const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P - sh + c;
+                const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P + c;
                 // rows no valid output pixel of this stack reads may lie outside the view; columns beside the needed ones
                 // just bring along what lies there (never multiplied into a valid pixel)
-                if (g.n_a + k < a.batch && gy >= 0 && gy < a.Hc && gy >= a.iy0[ti] && gy <= a.iy1[ti] && gx + NPL - 1 >= 0 && gx < a.Wc) {
-                    xoff[ub] = ES * (unsigned)(NPL + k * (int)sv.ns + (gy - sv.y0[ti]) * sv.pitch + (gx - sv.x0[tj]));
+                if (g.n_a + k < a.batch && gy >= 0 && gy < a.Hc && gy >= a.iy0[ti] && gy <= a.iy1[ti] && gx + 3 >= 0 && gx < a.Wc) {
+                    xoff[ub] = ES * (unsigned)(4 + k * (int)sv.ns + (gy - sv.y0[ti]) * sv.pitch + (gx - sv.x0[tj]));
 #pragma unroll
-                    for (int e = 0; e < NPL; ++e)
+                    for (int e = 0; e < 4; ++e)
                         if (gx + e < 0 || gx + e >= a.Wc) xfix[ub] |= 1u << e;
                 }
             }
         }
     }
 #pragma unroll
-    for (int j = 0; j < (XW ? 0 : MAXPOS); ++j) {
+    for (int j = 0; j < (WIDE ? 0 : MAXPOS); ++j) {
         const int s = tid + j * 256;
-        xoff[j] = kOobOffset; moff[j] = 0;
+        xoff[j] = kOobOffset;
         if (s < npos) {
             const int pr = s / PW, c = s - pr * PW;
             int k = 0, lr = pr, ybase = g.y_a * S;
@@ -192,33 +165,17 @@ k_conv_mfma_dl(MfmaConvArgs a)
             }
             const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P + c;
             if (g.n_a + k < a.batch && gy >= 0 && gy < a.Hc && gx >= 0 && gx < a.Wc) {
-                const int sy = HALF_IN ? (gy >> 1) : gy, sx = HALF_IN ? (gx >> 1) : gx;
+                const int sy = UP_IN ? (gy >> 1) : gy, sx = UP_IN ? (gx >> 1) : gx;
                 // positions no valid output pixel of this stack reads may lie outside the view
-                if (sy >= a.iy0[ti] && sy <= a.iy1[ti] && sx >= a.ix0[tj] && sx <= a.ix1[tj] && !(UP_IN && ((gy | gx) & 1))) {
+                if (sy >= a.iy0[ti] && sy <= a.iy1[ti] && sx >= a.ix0[tj] && sx <= a.ix1[tj] && !(UP_IN && ((gy | gx) & 1)))
                     xoff[j] = ES * (unsigned)(k * (int)sv.ns + (sy - sv.y0[ti]) * sv.pitch + (sx - sv.x0[tj]));
-                    if (POOL_IN) moff[j] = (k * (int)a.mask.ns + (sy - a.mask.y0[ti]) * a.mask.pitch + (sx - a.mask.x0[tj]))
-                                           | ((((gy & 1) << 1) | (gx & 1)) << 29);
-                }
             }
         }
     }
-    // winner codes of one stage, per position and channel
-    uint8_t codes[MAXPOS][kCK];
-    auto load_codes = [&](int c0) {
-        if (!POOL_IN) return;
-#pragma unroll
-        for (int j = 0; j < MAXPOS; ++j)
-#pragma unroll
-            for (int k = 0; k < kCK; ++k) {
-                const int ci = c0 + k < a.C ? c0 + k : a.C - 1;
-                codes[j][k] = msk[(moff[j] & 0x1FFFFFFF) + (long long)ci * a.mask.cs];
-            }
-    };
     // filter: a load instruction covers 64 consecutive floats of the slice; with BM >= 64 that is (part of) one
     // row, with BM = 32 two rows (two consecutive reduction channels)
-    // (bfloat path: one 16-byte load per lane = the 8 bfloats of one output channel; 64 channels to an instruction)
-    // (fp32 slices whose 1 KB pieces hold rows of one tap only: 16 bytes per lane, lane -> (row of the piece, 4 channels))
-    constexpr bool W16 = !BF && kCK % (256 / BM) == 0 && WF % 256 == 0;
+    // (slices whose 1 KB pieces hold rows of one tap only: 16 bytes per lane, lane -> (row of the piece, 4 channels))
+    constexpr bool W16 = kCK % (256 / BM) == 0 && WF % 256 == 0;
     unsigned woff;
     int wrow = 0;
     if constexpr (W16) {
@@ -243,25 +200,6 @@ k_conv_mfma_dl(MfmaConvArgs a)
     auto issue = [&](float* buf, int c0) {
         float* Wl = buf;
         float* Xl = buf + WF;
-        if constexpr (BF) {
-            // rows x parts of 64 output channels, dealt round-robin to the 4 wavefronts
-            constexpr int PARTS = (BM + 63) / 64, NLOAD = ROWS * PARTS;
-            const int C8 = (a.C + 7) >> 3;
-#pragma unroll
-            for (int u = 0; u < (NLOAD + 3) / 4; ++u) {
-                const int idx = wave + 4 * u;
-                if (idx < NLOAD) {
-                    const int r = idx / PARTS, part = idx - r * PARTS;
-                    const int tap = K == 3 ? r : 0, oct = (c0 >> 3) + (K == 3 ? 0 : r);
-                    const int col = part * 64 + lane;
-                    if (col < BM) {
-                        const unsigned so = 16u * (unsigned)((tap * C8 + oct) * a.Mtot + m0);
-                        const unsigned vo = (oct < C8 && m0 + col < a.Mtot) ? 16u * (unsigned)col : kOobOffset;
-                        __builtin_amdgcn_raw_ptr_buffer_load_lds(wrsrc, FTP_LDS_PTR(Wl + (r * BM + part * 64) * 4), 16, vo, so, 0, 0);
-                    }
-                }
-            }
-        }
         if constexpr (W16) {
             // a load instruction covers 256 consecutive floats of the slice: 16 bytes per lane, RPP rows of one tap
             constexpr int RPP = 256 / BM, WP4 = WF / 256;
@@ -279,7 +217,7 @@ k_conv_mfma_dl(MfmaConvArgs a)
         for (int u = 0; u < WINSTR; ++u) {
             const int idx = wave + 4 * u;                              // 64-dword piece of the slice
             if (idx >= WPIECES) break;
-            if constexpr (BF || W16) continue;
+            if constexpr (W16) continue;
             const int row = BM >= 64 ? idx / (BM / 64 > 0 ? BM / 64 : 1) : 2 * idx;
             const int tap = row / kCK, k = row - tap * kCK;
             const unsigned so = 4u * (unsigned)((tap * a.C + c0 + k) * a.Mtot + m0);
@@ -288,26 +226,25 @@ k_conv_mfma_dl(MfmaConvArgs a)
             else          vo = c0 + k + (lane >> 5) < a.C ? woff : kOobOffset;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(wrsrc, FTP_LDS_PTR(Wl + idx * 64), 4, vo, so, 0, 0);
         }
-        if constexpr (XW) {
+        if constexpr (WIDE) {
 #pragma unroll
             for (int u = 0; u < NXI; ++u) {
                 const int id = wave + 4 * u;
                 const int blk = id % NQB, k = id / NQB;
-                if (id < NQB * kCK && blk * (64 * NPL) < npos) {
+                if (id < NQB * kCK && blk * 256 < npos) {
                     const unsigned vo = c0 + k < a.C ? xoff[ONEBLK ? 0 : u] : kOobOffset;
                     const unsigned so = ES * (unsigned)((c0 + k) * (int)sv.cs);
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, FTP_LDS_PTR((char*)Xl + (int)ES * (k * CS + blk * (64 * NPL))), 16, vo, so, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, FTP_LDS_PTR((char*)Xl + (int)ES * (k * CS + blk * 256)), 16, vo, so, 0, 0);
                 }
             }
         }
 #pragma unroll
-        for (int j = 0; j < (XW ? 0 : MAXPOS); ++j) {
+        for (int j = 0; j < (WIDE ? 0 : MAXPOS); ++j) {
             const int blk = wave + 4 * j;
             if (blk * 64 < npos) {
 #pragma unroll
                 for (int k = 0; k < kCK; ++k) {
-                    unsigned vo = c0 + k < a.C ? xoff[j] : kOobOffset;
-                    if (POOL_IN && ((codes[j][k] >> 1) & 3) != ((unsigned)moff[j] >> 29)) vo = kOobOffset;
+                    const unsigned vo = c0 + k < a.C ? xoff[j] : kOobOffset;
                     const unsigned so = ES * (unsigned)((c0 + k) * (int)sv.cs);
                     // (the element size has to be a literal)
                     if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, FTP_LDS_PTR(Xl + k * CS + blk * 64), 4, vo, so, 0, 0);
@@ -322,47 +259,6 @@ k_conv_mfma_dl(MfmaConvArgs a)
     auto multiply = [&](const float* buf) {
         const float* Wl = buf;
         const float* Xl = buf + WF;
-        if constexpr (BF) {
-            // one step = rows 2s and 2s+1 of the slice: lanes 0-31 feed row 2s, lanes 32-63 row 2s+1 (8 reduction
-            // elements each); the 8 patch values of a lane are zero-extended bfloats and are packed two to a dword
-            constexpr int NSTEP16 = ROWS / 2;
-            uint4 av[2][MT], bv[2][NT];
-            auto load_step = [&](int s2, int b) {
-                const int r = 2 * s2 + hi;
-                int boff;
-                if (K == 3) { const int tap = r < KK ? r : 0; boff = (tap / 3) * PW + (tap - (tap / 3) * 3); }
-                else        boff = 8 * r * CS;
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) av[b][mt] = *(const uint4*)(Wl + ((r * BM + baseA + 32 * mt) << 2));
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    uint32_t x[8];
-                    if constexpr (XH) {
-                        const bf16_t* xp = (const bf16_t*)Xl + baseB[t] + boff;
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) x[k] = xp[k * CS];
-                    } else {
-                        const float* xp = Xl + baseB[t] + boff;
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) x[k] = __float_as_uint(xp[k * CS]);
-                    }
-                    bv[b][t] = make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16), x[6] | (x[7] << 16));
-                }
-            };
-            load_step(0, 0);
-#pragma unroll
-            for (int j = 0; j < NSTEP16; ++j) {
-                if (j + 1 < NSTEP16) load_step(j + 1, (j + 1) & 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int t = 0; t < NT; ++t)
-                        acc[mt][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, av[j & 1][mt]),
-                                                                            __builtin_bit_cast(v8bf, bv[j & 1][t]), acc[mt][t], 0, 0, 0);
-            }
-            return;
-        }
         constexpr int NSTEP = KK * (kCK / 2);
         float av[2][MT], bv[2][NT];
         auto load_step = [&](int j, int b) {
@@ -388,7 +284,7 @@ k_conv_mfma_dl(MfmaConvArgs a)
 
     // wide loads: once this wavefront's units of a stage have landed, the elements beside the map become the zero padding
     auto fixup = [&](float* buf) {
-        if constexpr (XW) {
+        if constexpr (WIDE) {
             T* Xl = (T*)(buf + WF);                    // (elements as the maps hold them)
 #pragma unroll
             for (int u = 0; u < NXI; ++u) {
@@ -396,29 +292,27 @@ k_conv_mfma_dl(MfmaConvArgs a)
                 const int blk = id % NQB, k = id / NQB;
                 const unsigned f = xfix[ONEBLK ? 0 : u];
                 if (id < NQB * kCK && f) {
-                    T* q = Xl + k * CS + blk * (64 * NPL) + NPL * lane;
+                    T* q = Xl + k * CS + blk * 256 + 4 * lane;
 #pragma unroll
-                    for (int e = 0; e < NPL; ++e)
+                    for (int e = 0; e < 4; ++e)
                         if ((f >> e) & 1u) q[e] = (T)0;
                 }
             }
         }
     };
     const int nst = (a.C + kCK - 1) / kCK;
-    load_codes(0);
-    issue(bufA, 0);                                     // (waits for the codes it selects by)
-    load_codes(kCK);
+    issue(bufA, 0);
     for (int st = 0; st < nst; st += 2) {
         __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0): this wavefront's share of the stage has landed
         fixup(bufA);
         __syncthreads();                               // ... and everybody's; the other buffer is free again
-        if (st + 1 < nst) { issue(bufB, (st + 1) * kCK); load_codes((st + 2) * kCK); }
+        if (st + 1 < nst) issue(bufB, (st + 1) * kCK);
         multiply(bufA);
         if (st + 1 < nst) {
             __builtin_amdgcn_s_waitcnt(0x0F70);
             fixup(bufB);
             __syncthreads();
-            if (st + 2 < nst) { issue(bufA, (st + 2) * kCK); load_codes((st + 3) * kCK); }
+            if (st + 2 < nst) issue(bufA, (st + 2) * kCK);
             multiply(bufB);
         }
     }
@@ -441,27 +335,23 @@ struct DlShape { int BM, BN, per_cu; };
 // The largest workgroup whose filter slice (all taps of a stage) still fits LDS next to the patch.
 constexpr int conv_dl_max_bm(int K) { return K >= 7 ? 64 : 128; }
 
-template <typename T, int K, bool POOL_OUT, bool DELTA_IN, bool POOL_IN, int STRIDE>
+template <typename T, int K, bool POOL_OUT, bool DELTA_IN, int STRIDE>
 void launch_dl(const MfmaConvArgs& a, DlShape sh, bool wide, dim3 grid, hipStream_t s)
 {
     static char label[12][104];                  // (every write of an entry stores the same text: entries depend on the template and the shape only)
     const int v = ((sh.BM == 128 ? 0 : sh.BM == 64 ? 1 : 2) * 2 + (sh.BN == 256 ? 0 : 1)) * 2 + (wide ? 1 : 0);
-    std::snprintf(label[v], sizeof(label[v]), "k_conv_mfma_dl<%s, %d, %d, %d, %d, %s, %s, %s, %d, %s>", sizeof(T) == 4 ? "float" : "unsigned short",
+    std::snprintf(label[v], sizeof(label[v]), "k_conv_mfma_dl<%s, %d, %d, %d, %d, %s, %s, %d, %s>", sizeof(T) == 4 ? "float" : "unsigned short",
                   K, sh.BM == 128 ? 2 : 1, sh.BM == 32 ? 1 : 2, sh.BN, POOL_OUT ? "true" : "false", DELTA_IN ? "true" : "false",
-                  POOL_IN ? "true" : "false", STRIDE, wide ? "true" : "false");
+                  STRIDE, wide ? "true" : "false");
     g_kernel_label = label[v];
     constexpr bool STRIDED_FWD = STRIDE == 2 && !DELTA_IN;
-    // (which forms exist: the delta maps always lie inside the workspace, so an fp32 delta pass that can load wide always does)
-    constexpr bool QUADABLE = conv_dl_quads(sizeof(T), POOL_IN, STRIDE == 2 && DELTA_IN);
-    constexpr bool WIDEABLE = QUADABLE || conv_dl_packable(sizeof(T), K, STRIDE, POOL_IN);
-    constexpr bool NARROWABLE = !(QUADABLE && DELTA_IN);
+    constexpr bool QUADABLE = conv_dl_quads(sizeof(T), false, STRIDE == 2 && DELTA_IN);
 #define FTP_DL(WM, MT, BN) do { \
-        if (wide) { if constexpr (WIDEABLE) hipLaunchKernelGGL((k_conv_mfma_dl<T, K, WM, MT, BN, POOL_OUT, DELTA_IN, POOL_IN, STRIDE, true>), grid, dim3(256), 0, s, a); } \
-        else { if constexpr (NARROWABLE) hipLaunchKernelGGL((k_conv_mfma_dl<T, K, WM, MT, BN, POOL_OUT, DELTA_IN, POOL_IN, STRIDE, false>), grid, dim3(256), 0, s, a); } } while (0)
+        if (wide) { if constexpr (QUADABLE) hipLaunchKernelGGL((k_conv_mfma_dl<T, K, WM, MT, BN, POOL_OUT, DELTA_IN, STRIDE, true>), grid, dim3(256), 0, s, a); } \
+        else hipLaunchKernelGGL((k_conv_mfma_dl<T, K, WM, MT, BN, POOL_OUT, DELTA_IN, STRIDE, false>), grid, dim3(256), 0, s, a); } while (0)
     if (sh.BN == 256) {
         if constexpr (!STRIDED_FWD) {
-            // (the 3x3 bfloat path never takes 128 channels x 256 pixels: its 8-channel stages would not fit 64 KB of LDS)
-            if (sh.BM == 128) { if constexpr (conv_dl_max_bm(K) >= 128 && !(sizeof(T) == 2 && K == 3 && STRIDE == 1)) FTP_DL(2, 2, 256); }
+            if (sh.BM == 128) { if constexpr (conv_dl_max_bm(K) >= 128) FTP_DL(2, 2, 256); }
             else if (sh.BM == 64) FTP_DL(1, 2, 256); else FTP_DL(1, 1, 256);
         }
     } else {
@@ -487,15 +377,8 @@ DlShape choose_dl_shape(const MfmaConvArgs& a, const ConvArgs& c, int npl, bool 
     // whole input patch, and with many blocks in flight the filter no longer stays in the L2 cache
     int BM = a.Mtot >= 128 ? 128 : a.Mtot > 32 ? 64 : 32;
     if (BM > conv_dl_max_bm(K)) BM = conv_dl_max_bm(K);
-    // The bfloat path finishes a stage's multiply long before the next stage's loads arrive; what hides that is more
-    // workgroups per CU, so its 3x3 layers take 64-channel workgroups (half the accumulator registers): config 5
-    // forward of the 64 -> 128 layer 0.89 -> 0.41 ms.  (32 channels re-read the patch too often; 1x1 layers lose.)
-    if (c.bf16 && K == 3 && !STRIDED_FWD && c.S == 1 && BM > 64) BM = 64;
-    // (the cost model below is for kernels bound by the matrix cores; the bfloat 3x3 path is bound by latency and
-    // does best with the most workgroups per CU: 64 channels x 128 pixels; config 5: 14.6 -> 14.4 ms per step)
-    const bool small_wg = c.bf16 && K == 3 && !STRIDED_FWD && c.S == 1 && BM == 64;
     auto consider = [&](int bm, int BN) -> long long {
-        const int max_pos = conv_dl_max_positions(K, BN, STRIDED_FWD, npl == 4, npl == 8);
+        const int max_pos = conv_dl_max_positions(K, BN, STRIDED_FWD, npl == 4);
         const TileChoice tc = choose_tile(rws, rhs, c.N, c.M, c.batch, POOL_OUT ? BN / 4 : BN, S, K / 2, max_pos, npl, gather);
         if (tc.cs > max_pos) return -1;
         // tiles that exist: every stack has its own count, the grid is sized for the largest
@@ -517,21 +400,7 @@ DlShape choose_dl_shape(const MfmaConvArgs& a, const ConvArgs& c, int npl, bool 
         return wgs;
     };
     long long widest_wgs = 0;
-    int bn_first = (STRIDED_FWD || small_wg) ? 128 : 256;
-    if (small_wg && POOL_OUT) {
-        // ... unless 128-pixel tiles (32 pool windows) fit the rows of the rectangles badly: a row of 19 windows leaves
-        // 13 of 32 slots empty, while three such rows fill 57 of 64 (config 5, the 32 -> 64 layer: 0.68 -> 0.58 ms)
-        long long units = 0, slots = 0;
-        const TileChoice t128 = choose_tile(rws, rhs, c.N, c.M, c.batch, 32, S, K / 2, conv_dl_max_positions(K, 128, STRIDED_FWD, npl == 4, npl == 8), npl, gather);
-        for (int i = 0; i < c.N; ++i)
-            for (int j = 0; j < c.M; ++j) {
-                const int rw = a.rect.x1[j] - a.rect.x0[j] + 1, rh = a.rect.y1[i] - a.rect.y0[i] + 1;
-                units += (long long)c.batch * rh * rw;
-                slots += tile_slots(t128, rw, rh, c.batch) * t128.cap;
-            }
-        if (slots > 0 && (double)units < 0.7 * (double)slots) bn_first = 256;
-    }
-    for (int BN = bn_first; BN >= (bn_first == 256 && small_wg ? 256 : 128); BN /= 2) {
+    for (int BN = STRIDED_FWD ? 128 : 256; BN >= 128; BN /= 2) {
         const long long w = consider(BM, BN);
         if (w > widest_wgs) widest_wgs = w;
     }
@@ -545,31 +414,19 @@ DlShape choose_dl_shape(const MfmaConvArgs& a, const ConvArgs& c, int npl, bool 
 
 // Returns non-zero if the layer's geometry does not fit the kernel (offsets beyond 32 bits, a row of some stack
 // wider than the patch buffer); the caller then uses a direct kernel.
-template <typename T, int K, bool POOL_OUT, bool DELTA_IN, bool POOL_IN, int STRIDE>
+template <typename T, int K, bool POOL_OUT, bool DELTA_IN, int STRIDE>
 int launch_t(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
 {
     constexpr bool STRIDED_FWD = STRIDE == 2 && !DELTA_IN;
     TileChoice td;
     // fp32 patches are loaded 16 bytes a lane, a few bytes beyond the ends of map rows: only inside the workspace (the
     // caller's input, which a wide first layer reads, is loaded element by element)
-    constexpr bool quadable = conv_dl_quads(sizeof(T), POOL_IN && DELTA_IN, STRIDE == 2 && DELTA_IN);
-    const bool quad = quadable && (DELTA_IN ? c.din_ws : c.in_ws);
-    if (quadable && DELTA_IN && !quad) return 1;
-    // 16-bit maps on the bfloat matrix-core path: the patch stays packed in LDS and travels 16 bytes a lane where every row
-    // of the view starts on a 4-byte boundary (even strides) inside the workspace; otherwise element by element
-    bool pack = false;
-    if constexpr (conv_dl_packable(sizeof(T), K, STRIDE, POOL_IN && DELTA_IN)) {
-        const View& iv = DELTA_IN ? a.din : a.in;
-        pack = (DELTA_IN ? c.din_ws : c.in_ws) && ((uintptr_t)iv.p & 3) == 0 && !(iv.pitch & 1) && !(iv.cs & 1) && !(iv.ns & 1) && !(iv.ss & 1);
-    }
-    const int npl = quad ? 4 : pack ? 8 : 0;
-    // (16-bit maps through a fused pool: the kernel waits for its patch more than it multiplies, and runs of pixels, which
-    // touch more patch rows, were measured slower: config 5 forward of the pooled layers 0.45 / 0.28 / 0.22 -> 0.50 / 0.33 / 0.24 ms)
-    const bool costly_patch = ((POOL_IN || STRIDE == 2) && DELTA_IN) || (sizeof(T) == 2 && POOL_OUT && !DELTA_IN);
+    constexpr bool quadable = conv_dl_quads(sizeof(T), false, STRIDE == 2 && DELTA_IN);
+    const bool quad = quadable && c.in_ws;
+    const int npl = quad ? 4 : 0;
+    const bool costly_patch = STRIDE == 2 && DELTA_IN;
     const DlShape sh = choose_dl_shape<K, POOL_OUT, STRIDED_FWD>(a, c, npl, costly_patch, &td);
     if (!sh.BM) return 1;
-    // (the kernel keeps code-map offsets in 29 bits)
-    if (POOL_IN && DELTA_IN && (double)td.max_img * (double)a.mask.ns >= 5.0e8) return 1;
     if (!offsets_fit_32bit(a, DELTA_IN ? a.din : a.in, td.max_img, K)) return 1;
     // (the epilogue's buffer stores: the images a tile spans plus all output channels, maps and code bytes alike)
     {
@@ -577,23 +434,24 @@ int launch_t(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
         if (4.0 * ((double)td.max_img * (double)ov.ns + ((double)a.Mtot + 8.0) * (double)ov.cs) >= 2.0e9) return 1;
         if (POOL_OUT && !DELTA_IN && (double)td.max_img * (double)a.mask.ns + ((double)a.Mtot + 8.0) * (double)a.mask.cs >= 2.0e9) return 1;
     }
-    a.TC = td.TC; a.tiles_x = td.tiles_x; a.tiles_r = td.tiles_r; a.cap = td.cap; a.flat = td.flat; a.cs = pack ? (td.cs + 511) & ~511 : quad ? (td.cs + 255) & ~255 : (td.cs + 63) & ~63;
+    a.TC = td.TC; a.tiles_x = td.tiles_x; a.tiles_r = td.tiles_r; a.cap = td.cap; a.flat = td.flat; a.cs = quad ? (td.cs + 255) & ~255 : (td.cs + 63) & ~63;
     a.mblocks = (a.Mtot + sh.BM - 1) / sh.BM; a.stacks = c.N * c.M;
     // XCD order pays where several channel blocks compete for the L2 and the groups spread evenly over the 8 XCDs;
     // with one channel block the plain order (neighbouring tiles on different XCDs) balances better
     const int groups = a.mblocks * a.stacks, ntiles = a.tiles_x * a.tiles_r;
     a.xcd_groups = (a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0) ? 1 : 0;
     const unsigned nwg = a.xcd_groups ? xcd_grid(groups, ntiles) : (unsigned)(groups * ntiles);
-    launch_dl<T, K, POOL_OUT && !DELTA_IN, DELTA_IN, POOL_IN && DELTA_IN, STRIDE>(a, sh, quad || pack, dim3(nwg), s);
+    launch_dl<T, K, POOL_OUT, DELTA_IN, STRIDE>(a, sh, quad, dim3(nwg), s);
     return 0;
 }
 
-template <int K, bool POOL_OUT, bool DELTA_IN, bool POOL_IN, int STRIDE = 1>
+template <int K, bool POOL_OUT, bool DELTA_IN, int STRIDE = 1>
 int launch_m(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
 {
-    // (fp32 deltas take ftp_delta_split.hip)
-    if constexpr (!DELTA_IN) { if (!c.bf16) return launch_t<float, K, POOL_OUT, DELTA_IN, POOL_IN, STRIDE>(a, c, s); }
-    return launch_t<bf16_t, K, POOL_OUT, DELTA_IN, POOL_IN, STRIDE>(a, c, s);
+    // (fp32 deltas take ftp_delta_split.hip, 16-bit 1x1 / 3x3 layers of stride 1 ftp_conv_bf16.hip)
+    if constexpr (!DELTA_IN) { if (!c.bf16) return launch_t<float, K, POOL_OUT, DELTA_IN, STRIDE>(a, c, s); }
+    if constexpr (K >= 5 || STRIDE == 2) return launch_t<bf16_t, K, POOL_OUT, DELTA_IN, STRIDE>(a, c, s);
+    return 1;
 }
 
 void fill_common(MfmaConvArgs& a, const ConvArgs& c, const RectTab& inrect)
@@ -638,11 +496,12 @@ int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream
     a.wt = wt; a.bias = c.bias;
     a.C = c.Cin; a.Mtot = c.Cout;
     a.Hc = c.Hi; a.Wc = c.Wi;                           // the patch is cut from the input map
-    if (c.S == 2) return c.K == 3 ? launch_m<3, false, false, false, 2>(a, c, s) : launch_m<1, false, false, false, 2>(a, c, s);
-    if (c.K == 7) return launch_m<7, false, false, false>(a, c, s);
-    if (c.K == 5) return launch_m<5, false, false, false>(a, c, s);
-    if (c.K == 3) return c.pooled ? launch_m<3, true, false, false>(a, c, s) : launch_m<3, false, false, false>(a, c, s);
-    return c.pooled ? launch_m<1, true, false, false>(a, c, s) : launch_m<1, false, false, false>(a, c, s);
+    if (mfma_conv_packs_bf16(c)) return conv_bf16_fwd(a, c, s);
+    if (c.S == 2) return c.K == 3 ? launch_m<3, false, false, 2>(a, c, s) : launch_m<1, false, false, 2>(a, c, s);
+    if (c.K == 7) return launch_m<7, false, false>(a, c, s);
+    if (c.K == 5) return launch_m<5, false, false>(a, c, s);
+    if (c.K == 3) return c.pooled ? launch_m<3, true, false>(a, c, s) : launch_m<3, false, false>(a, c, s);
+    return c.pooled ? launch_m<1, true, false>(a, c, s) : launch_m<1, false, false>(a, c, s);
 }
 
 // Backward data: c.rect = backward rectangle at the unit's input boundary; inrect = extent of the delta view
@@ -658,6 +517,7 @@ int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipS
     // the patch is cut from the deltas as the stride-1 convolution sees them: at the convolution output (stride 1,
     // also through a pool), or with zeros inserted between them (stride 2: twice the extent)
     a.Hc = c.S == 2 ? 2 * c.Hc : c.Hc; a.Wc = c.S == 2 ? 2 * c.Wc : c.Wc;
+    if (mfma_conv_packs_bf16(c)) return conv_bf16_bwd_data(a, c, s);
     if (!c.bf16) {
         if (c.S == 2) {                                 // (the filter was relaid for the kernel that declined)
             PrepJob p = mfma_prep_job(c, wt, true);
@@ -666,11 +526,9 @@ int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipS
         }
         return split_conv_bwd_data(a, c, s);
     }
-    if (c.S == 2) return c.K == 3 ? launch_m<3, false, true, false, 2>(a, c, s) : launch_m<1, false, true, false, 2>(a, c, s);
-    if (c.K == 7) return launch_m<7, false, true, false>(a, c, s);
-    if (c.K == 5) return launch_m<5, false, true, false>(a, c, s);
-    if (c.K == 3) return c.pooled ? launch_m<3, false, true, true>(a, c, s) : launch_m<3, false, true, false>(a, c, s);
-    return c.pooled ? launch_m<1, false, true, true>(a, c, s) : launch_m<1, false, true, false>(a, c, s);
+    if (c.S == 2) return c.K == 3 ? launch_m<3, false, true, 2>(a, c, s) : launch_m<1, false, true, 2>(a, c, s);
+    if (c.K == 7) return launch_m<7, false, true>(a, c, s);
+    return launch_m<5, false, true>(a, c, s);
 }
 
 }  // namespace ftp
