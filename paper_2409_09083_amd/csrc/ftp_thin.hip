@@ -481,107 +481,149 @@ k_conv_bwd_data_thin4(View din, View mask, View dout, View isign, int scale_out,
 // Input pixel (2j + a, 2i + b) receives W[ky][kx] dZ[qy][qx] from the taps with ky = a + P, kx = b + P (mod 2), at
 // qy = j + (a + P - ky) / 2, qx likewise: the four pixels of a cell (j, i) together use every tap exactly once and
 // read the deltas of the cells [j + QLO, j + QHI] x [i + QLO, i + QHI] (4 x 4 for a 7x7 filter).
-// Workgroup = 16 x 32 cells (32 x 64 pixels) of one (stack, image), two neighbouring cells per thread.  Per 8 output channels the
-// delta patch (tile + that halo; zero outside the stack's delta rectangle) and the filter slice [co][tap][ci padded
-// to 4] (fp32) are staged in LDS; a thread reads its NQ x NQ deltas and one 16-byte filter vector per tap for
-// K * K * CI multiply-adds per output channel.
+// That is a product on the matrix cores: 16 rows (4 pixels of a cell x 4 input channels) times 16 cells, the reduction runs
+// over output channels and the cells of the neighbourhood, v_mfma_f32_16x16x4_f32 taking one row of it (3x3: the whole 2 x 2)
+// of one output channel.  Weights a pixel has no tap for are zeros: 7x7 with 3 channels uses 147 of 256 products, which
+// still is less time than 49 taps x 3 multiply-adds a cell and output channel on the vector ALU (one LDS read per weight):
+// 7x7 stem, 3 -> 64 channels, 32 images of 607^2, 3 x 3 tiles: 2.09 -> 1.16 ms (84 TFLOP/s issued, 48 useful); maps of a few tiles,
+// where 8 stages in a row were all there was to time, 0.23 -> 0.05 ms (11 images of 211 x 148).
+// Workgroup = 4 wavefronts of 16 x R cells, 2 x 2 of them: 32 x 2R cells of one (stack, image).  A wavefront reads each row
+// of deltas from LDS once for the NQ rows of cells it contributes to.  Per 8 output channels the delta patch (tile + that
+// halo; zero outside the stack's delta rectangle) and the weights, as the lanes need them, go through registers to LDS; the
+// next 8 travel meanwhile.  R = 8 re-reads a fifth of the deltas; R = 2 where that leaves CUs without a workgroup.
+// MFMA lane layout: A[m = lane%16][k = lane/16], B[k = lane/16][n = lane%16], D[m = 4*(lane/16) + i][n = lane%16], i < 4:
+// a lane ends up with the 4 channels of pixel (lane/32, lane/16 % 2) of cell lane % 16.
 template <int K> struct StridedTaps {
     static constexpr int P = K / 2;
     static constexpr int QLO = -((K - 1 - P) / 2), QHI = (1 + P) / 2, NQ = QHI - QLO + 1;
 };
-constexpr int kThinS2PerThread = 2;                   // cells per thread along a row: they share 3 of 4 delta columns and every weight read (1: 2.87 ms on the 7x7 stem, 2: 2.09, 4: 2.27)
-constexpr int kThinS2Coc = 8, kThinS2Cells = 16;      // (8 channels a stage, 18 KB of LDS: five workgroups a CU; 16 channels, four workgroups: 3.37 instead of 2.85 ms on the 7x7 stem)
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int kThinS2Coc = 8;                         // output channels of a stage
 
-template <typename T, int K, int CI>
-__global__ void __launch_bounds__(256, 5)
+template <typename T, int K, int R>
+__global__ void __launch_bounds__(256, 4)
 k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in_slope, RectTab rt, RectTab ext,
-                        const T* __restrict__ w, int Cin, int Cout, int M, int batch, int tiles_x)
+                        const T* __restrict__ w, int Cin, int Cout, int M, int batch, int tiles_x, int tiles)
 {
     typedef StridedTaps<K> G;
     constexpr int P = G::P, QLO = G::QLO, NQ = G::NQ, KK = K * K;
-    constexpr int COC = kThinS2Coc, TC = kThinS2Cells, NCX = kThinS2PerThread;
-    constexpr int TCX = NCX * TC, PDY = TC + NQ - 1, PDX = TCX + NQ - 1, PDP = PDX + 1;     // tile, patch extent, padded pitch
-    __shared__ __attribute__((aligned(16))) float dzl[COC * PDY * PDP];
-    __shared__ __attribute__((aligned(16))) float wl[COC * KK * 4];
-    const int tid = threadIdx.x;
-    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
+    constexpr bool SQ = K == 3;                        // the neighbourhood (2 x 2) is one step
+    constexpr int ND = SQ ? 1 : NQ;                    // steps of an output channel
+    constexpr int COC = kThinS2Coc, TY = 2 * R, TX = 32;
+    constexpr int PDY = TY + NQ - 1, PDX = TX + NQ - 1, PDP = PDX + 1;     // patch extent, padded pitch
+    constexpr int POS = PDY * PDX, PPT = (POS + 255) / 256;                // patch positions, and those of a thread
+    constexpr int APT = (COC * ND + 3) / 4;            // weights of a thread
+    __shared__ float dzl[COC * PDY * PDP];
+    __shared__ float wl[4 * APT * 64];                 // [output channel][step][lane]
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile = blockIdx.x % tiles, img = blockIdx.x / tiles;
+    const int stack = img / batch, n = img - stack * batch;
     const int ti = stack / M, tj = stack % M;
-    const int bx = blockIdx.x % tiles_x, by = blockIdx.x / tiles_x;
-    const int J0 = (rt.y0[ti] >> 1) + by * TC, I0 = (rt.x0[tj] >> 1) + bx * TCX;     // first cell of the tile
+    const int bx = tile % tiles_x, by = tile / tiles_x;
+    const int J0 = (rt.y0[ti] >> 1) + by * TY, I0 = (rt.x0[tj] >> 1) + bx * TX;     // first cell of the tile
     if (2 * J0 > rt.y1[ti] || 2 * I0 > rt.x1[tj]) return;
-    const int cy = tid / TC, cx = NCX * (tid % TC);     // this thread's cells: (cy, cx) .. (cy, cx + NCX - 1)
-    float acc[NCX][2][2][CI];
-#pragma unroll
-    for (int u = 0; u < NCX; ++u)
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int c = 0; c < CI; ++c) acc[u][a][b][c] = 0.0f;
+    const int jy = (wave >> 1) * R, ix0 = (wave & 1) * 16;     // this wavefront's cells: rows jy .. jy + R - 1, columns ix0 .. ix0 + 15
 
+    // ---- this thread's patch positions (the same for every channel) and weights
+    const T* const src = (const T*)din.p + (long long)stack * din.ss + (long long)n * din.ns;
+    unsigned poff[PPT]; int pslot[PPT];                // byte offset in a channel's map, place in LDS (-1: none)
+    unsigned pin = 0;                                  // bit p: inside the delta rectangle (else zero)
+#pragma unroll
+    for (int p = 0; p < PPT; ++p) {
+        const int e = tid + 256 * p, py = e / PDX, px = e - py * PDX;
+        const int qy = J0 + QLO + py, qx = I0 + QLO + px;
+        const bool ok = e < POS && qy >= ext.y0[ti] && qy <= ext.y1[ti] && qx >= ext.x0[tj] && qx <= ext.x1[tj];
+        poff[p] = ok ? (unsigned)sizeof(T) * (unsigned)((qy - din.y0[ti]) * din.pitch + (qx - din.x0[tj])) : 0u;
+        pin |= ok ? 1u << p : 0u;
+        pslot[p] = e < POS ? py * PDP + px : -1;
+    }
+    // row m = 4 * (2a + b) + ci of the weights, column k: neighbour (dy, k), or (k / 2, k % 2) of the 2 x 2
+    unsigned aoff[APT]; int aco[APT];                  // byte offset from the stage's first weight, channel of the stage (beyond all: zero)
+#pragma unroll
+    for (int p = 0; p < APT; ++p) {
+        const int f = wave + 4 * p, co = f / ND, st = f - co * ND;
+        const int a = l16 >> 3, b = (l16 >> 2) & 1, ci = l16 & 3;
+        const int dy = SQ ? kq >> 1 : st, dx = SQ ? kq & 1 : kq;
+        const int ky = a + P - 2 * (dy + QLO), kx = b + P - 2 * (dx + QLO);
+        const bool ok = co < COC && ci < Cin && dx < NQ && ky >= 0 && ky < K && kx >= 0 && kx < K;
+        aoff[p] = (unsigned)sizeof(T) * (unsigned)((co * Cin + ci) * KK + ky * K + kx);
+        aco[p] = ok ? co : 0x40000000;
+    }
+    T xr[COC][PPT], ar[APT];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int c = 0; c < COC; ++c) {
+            const char* const sc = (const char*)(src + (long long)(c0 + c < Cout ? c0 + c : Cout - 1) * din.cs);
+#pragma unroll
+            for (int p = 0; p < PPT; ++p) xr[c][p] = *(const T*)(sc + poff[p]);
+        }
+        const char* const wc = (const char*)(w + (size_t)c0 * Cin * KK);
+#pragma unroll
+        for (int p = 0; p < APT; ++p) {
+            ar[p] = (T)0;
+            if (c0 + aco[p] < Cout) ar[p] = *(const T*)(wc + aoff[p]);
+        }
+    };
+
+    v4f acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    // (columns beyond the neighbourhood have zero weights; they read the last one)
+    const int lb = SQ ? (jy + (kq >> 1)) * PDP + ix0 + l16 + (kq & 1) : jy * PDP + ix0 + l16 + (kq < NQ ? kq : NQ - 1);
+    fetch(0);
     for (int c0 = 0; c0 < Cout; c0 += COC) {
-        __syncthreads();                               // the previous slice has been consumed
-        // delta patch: rows QLO .. of the tile's cells, COC channels; lanes run along a patch row
-        for (int e = tid; e < COC * PDY * PDX; e += 256) {
-            const int c = e / (PDY * PDX), r = e - c * (PDY * PDX);
-            const int py = r / PDX, px = r - py * PDX;
-            const int qy = J0 + QLO + py, qx = I0 + QLO + px;
-            float v = 0.0f;
-            if (c0 + c < Cout && qy >= ext.y0[ti] && qy <= ext.y1[ti] && qx >= ext.x0[tj] && qx <= ext.x1[tj])
-                v = ld(at<T>(din, stack, ti, tj, n, c0 + c, qy, qx));
-            dzl[(c * PDY + py) * PDP + px] = v;
-        }
-        // filter slice as fp32, [co][tap][ci (4)]
-        for (int e = tid; e < COC * KK * 4; e += 256) {
-            const int c = e / (KK * 4), r = e - c * (KK * 4);
-            const int t = r >> 2, ci = r & 3;
-            wl[e] = (c0 + c < Cout && ci < Cin) ? ld(w + ((size_t)(c0 + c) * Cin + ci) * KK + t) : 0.0f;
-        }
+        __syncthreads();                               // the previous stage has been consumed
+#pragma unroll
+        for (int c = 0; c < COC; ++c)
+#pragma unroll
+            for (int p = 0; p < PPT; ++p)
+                if (pslot[p] >= 0) dzl[c * (PDY * PDP) + pslot[p]] = (pin >> p) & 1u ? ld(&xr[c][p]) : 0.0f;
+#pragma unroll
+        for (int p = 0; p < APT; ++p) wl[(wave + 4 * p) * 64 + lane] = ld(&ar[p]);
         __syncthreads();
+        if (c0 + COC < Cout) fetch(c0 + COC);
+#pragma unroll 1
         for (int c = 0; c < COC; ++c) {
             if (c0 + c >= Cout) break;
-            // neighbouring cells share all but one column of their deltas, and every weight
-            float dv[NQ][NQ + NCX - 1];
+            float av[ND];
 #pragma unroll
-            for (int y = 0; y < NQ; ++y)
+            for (int st = 0; st < ND; ++st) av[st] = wl[(c * ND + st) * 64 + lane];
+            const float* const rows = dzl + c * (PDY * PDP) + lb;
 #pragma unroll
-                for (int x = 0; x < NQ + NCX - 1; ++x) dv[y][x] = dzl[(c * PDY + cy + y) * PDP + cx + x];
-            const float4* wc = (const float4*)(wl + c * KK * 4);
+            for (int r = 0; r < R + ND - 1; ++r) {
+                const float bv = rows[r * PDP];
 #pragma unroll
-            for (int ky = 0; ky < K; ++ky)
-#pragma unroll
-                for (int kx = 0; kx < K; ++kx) {
-                    const int a = (ky + P) & 1, b = (kx + P) & 1;
-                    const int dy = (a + P - ky) / 2 - QLO, dx = (b + P - kx) / 2 - QLO;     // compile-time after unrolling
-                    const float4 wv = wc[ky * K + kx];
-#pragma unroll
-                    for (int u = 0; u < NCX; ++u) {
-                        const float d = dv[dy][dx + u];
-                        acc[u][a][b][0] = fmaf(wv.x, d, acc[u][a][b][0]);
-                        if (CI > 1) acc[u][a][b][1] = fmaf(wv.y, d, acc[u][a][b][1]);
-                        if (CI > 2) acc[u][a][b][2] = fmaf(wv.z, d, acc[u][a][b][2]);
-                        if (CI > 3) acc[u][a][b][3] = fmaf(wv.w, d, acc[u][a][b][3]);
-                    }
-                }
+                for (int st = 0; st < ND; ++st)
+                    if (r - st >= 0 && r - st < R) acc[r - st] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv, acc[r - st], 0, 0, 0);
+            }
         }
     }
+    const int pa = kq >> 1, pb = kq & 1;
 #pragma unroll
-    for (int u = 0; u < NCX; ++u)
+    for (int r = 0; r < R; ++r) {
+        const int iy = 2 * (J0 + jy + r) + pa, ix = 2 * (I0 + ix0 + l16) + pb;
+        if (iy < rt.y0[ti] || iy > rt.y1[ti] || ix < rt.x0[tj] || ix > rt.x1[tj]) continue;
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int iy = 2 * (J0 + cy) + a, ix = 2 * (I0 + cx + u) + b;
-                if (iy < rt.y0[ti] || iy > rt.y1[ti] || ix < rt.x0[tj] || ix > rt.x1[tj]) continue;
-#pragma unroll
-                for (int c = 0; c < CI; ++c)
-                    if (c < Cin) {
-                        float v = acc[u][a][b][c];
-                        if (scale_out) v = scaled_delta<T>(v, sign_bit(isign, stack, ti, tj, n, c, iy, ix), in_slope);
-                        st(at<T>(dout, stack, ti, tj, n, c, iy, ix), v);
-                    }
+        for (int c = 0; c < 4; ++c) {
+            if (c >= Cin) break;
+            float v = acc[r][c];
+            // a delta that is infinite or NaN has met the zero weights of pixels it does not reach: once more, over the taps alone
+            if (!(__builtin_fabsf(v) < __builtin_inff())) {
+                v = 0.0f;
+                for (int co = 0; co < Cout; ++co)
+                    for (int ky = (pa + P) & 1; ky < K; ky += 2)
+                        for (int kx = (pb + P) & 1; kx < K; kx += 2) {
+                            const int qy = (iy + P - ky) >> 1, qx = (ix + P - kx) >> 1;
+                            const bool in = qy >= ext.y0[ti] && qy <= ext.y1[ti] && qx >= ext.x0[tj] && qx <= ext.x1[tj];
+                            const float d = in ? ld(at<T>(din, stack, ti, tj, n, co, qy, qx)) : 0.0f;
+                            v = fmaf(ld(w + ((size_t)co * Cin + c) * KK + ky * K + kx), d, v);
+                        }
             }
+            if (scale_out) v = scaled_delta<T>(v, sign_bit(isign, stack, ti, tj, n, c, iy, ix), in_slope);
+            st(at<T>(dout, stack, ti, tj, n, c, iy, ix), v);
+        }
+    }
 }
 
 bool thin_bwd_data_strided_eligible(const ConvArgs& a) { return a.S == 2 && a.Cin <= 4 && !a.pooled && a.K >= 3; }
@@ -592,16 +634,18 @@ void thin_conv_bwd_data_strided(const ConvArgs& a, const RectTab& ext, hipStream
     int mw = 0, mh = 0;                                // cells per dimension of the largest rectangle
     for (int t = 0; t < a.M; ++t) mw = std::max(mw, (a.rect.x1[t] >> 1) - (a.rect.x0[t] >> 1) + 1);
     for (int t = 0; t < a.N; ++t) mh = std::max(mh, (a.rect.y1[t] >> 1) - (a.rect.y0[t] >> 1) + 1);
-    const int tcx = kThinS2PerThread * kThinS2Cells;
-    const int tiles_x = (mw + tcx - 1) / tcx, tiles_y = (mh + kThinS2Cells - 1) / kThinS2Cells;
-    dim3 grid(tiles_x * tiles_y, 1, a.N * a.M * a.batch), block(256);
+    // (R = 8: at least a workgroup a CU)
+    const int tiles_x = (mw + 31) / 32, images = a.N * a.M * a.batch;
+    const bool tall = (long long)tiles_x * ((mh + 15) / 16) * images >= 256;
+    const int ty = tall ? 16 : 4, tiles = tiles_x * ((mh + ty - 1) / ty);
+    dim3 grid((unsigned)(tiles * images)), block(256);
     g_kernel_label = "k_conv_bwd_data_thin_s2";
-#define FTP_S2(T, KK, CI) hipLaunchKernelGGL((k_conv_bwd_data_thin_s2<T, KK, CI>), grid, block, 0, s, a.din, a.dout, a.isign, a.scale_out, a.in_slope, a.rect, ext, (const T*)a.w, a.Cin, a.Cout, a.M, a.batch, tiles_x)
-#define FTP_S2C(T, KK) do { if (a.Cin <= 3) FTP_S2(T, KK, 3); else FTP_S2(T, KK, 4); } while (0)
-#define FTP_S2K(T) do { if (a.K == 7) FTP_S2C(T, 7); else if (a.K == 5) FTP_S2C(T, 5); else FTP_S2C(T, 3); } while (0)
+#define FTP_S2(T, KK, R) hipLaunchKernelGGL((k_conv_bwd_data_thin_s2<T, KK, R>), grid, block, 0, s, a.din, a.dout, a.isign, a.scale_out, a.in_slope, a.rect, ext, (const T*)a.w, a.Cin, a.Cout, a.M, a.batch, tiles_x, tiles)
+#define FTP_S2R(T, KK) do { if (tall) FTP_S2(T, KK, 8); else FTP_S2(T, KK, 2); } while (0)
+#define FTP_S2K(T) do { if (a.K == 7) FTP_S2R(T, 7); else if (a.K == 5) FTP_S2R(T, 5); else FTP_S2R(T, 3); } while (0)
     if (a.bf16) FTP_S2K(bf16_t); else FTP_S2K(float);
 #undef FTP_S2K
-#undef FTP_S2C
+#undef FTP_S2R
 #undef FTP_S2
 }
 
