@@ -482,7 +482,7 @@ bool mfma_conv_packs_bf16(const ConvArgs& a) { return a.bf16 && a.K <= 3 && a.S 
 PrepJob mfma_prep_job(const ConvArgs& c, void* wt, bool backward)
 {
     PrepJob p;
-    p.w = c.w; p.wt = wt; p.Cout = c.Cout; p.Cin = c.Cin; p.KK = c.K * c.K; p.rot = backward ? 1 : 0; p.bf16 = c.bf16; p.first = 0;
+    p.w = c.w; p.wt = wt; p.Cout = c.Cout; p.Cin = c.Cin; p.KK = c.K * c.K; p.rot = backward ? 1 : 0; p.bf16 = c.bf16;
     p.kind = mfma_conv_packs_bf16(c) ? PREP_PACK16 : (c.bf16 || !backward || c.S == 2) ? PREP_PLAIN : PREP_SPLIT;
     return p;
 }

@@ -7,17 +7,20 @@
 
 namespace ftp {
 
-struct PrepArgs { PrepJob job[kPrepJobs]; int n; };
+// (first[]: apart from the jobs, so that the search touches few lines of the argument block; a launch of one job, a single
+// layer's, searches nothing)
+template <int CAP> struct PrepArgs { int n, first[CAP]; PrepJob job[CAP]; };
 
+template <int CAP>
 __global__ void __launch_bounds__(256)
-k_prep_filters(PrepArgs a)
+k_prep_filters(PrepArgs<CAP> a)
 {
     int j = 0;
-    while (j + 1 < a.n && (int)blockIdx.x >= a.job[j + 1].first) ++j;
+    if (CAP > 1) while (j + 1 < a.n && (int)blockIdx.x >= a.first[j + 1]) ++j;
     const PrepJob& p = a.job[j];
     const int Mtot = p.rot ? p.Cin : p.Cout, C = p.rot ? p.Cout : p.Cin, C8 = (C + 7) >> 3, KK = p.KK;
     // (32 bits count the threads of any filter that fits the memory)
-    const unsigned i = (blockIdx.x - (unsigned)p.first) * 256u + threadIdx.x;
+    const unsigned i = (blockIdx.x - (unsigned)a.first[j]) * 256u + threadIdx.x;
     if (p.kind == PREP_PLAIN) {
         // [tap][reduction channel][output channel], fp32; read in the order of the source
         if (i >= (unsigned)C * (unsigned)Mtot * (unsigned)KK) return;
@@ -72,20 +75,32 @@ k_prep_filters(PrepArgs a)
     }
 }
 
-// n <= kPrepJobs
-void prep_filters(PrepJob* jobs, int n, hipStream_t s)
+namespace {
+
+template <int CAP>
+void launch_prep(const PrepJob* jobs, int n, hipStream_t s)
 {
-    PrepArgs a;
+    PrepArgs<CAP> a;
     a.n = n;
     long long blocks = 0;
     for (int j = 0; j < n; ++j) {
-        PrepJob& p = jobs[j];
+        const PrepJob& p = jobs[j];
         const long long C = p.rot ? p.Cout : p.Cin, Mtot = p.rot ? p.Cin : p.Cout, taps = p.kind == PREP_PACK16 && p.KK == 9 ? 10 : p.KK;
-        p.first = (int)blocks;
+        a.first[j] = (int)blocks;
         blocks += ((p.kind == PREP_PLAIN ? C : 4 * ((C + 7) / 8)) * taps * Mtot + 255) / 256;
         a.job[j] = p;
     }
-    hipLaunchKernelGGL(k_prep_filters, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_prep_filters<CAP>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+}
+
+}  // namespace
+
+// n <= kPrepJobs
+void prep_filters(const PrepJob* jobs, int n, hipStream_t s)
+{
+    if (n == 1) launch_prep<1>(jobs, n, s);
+    else if (n <= 8) launch_prep<8>(jobs, n, s);
+    else launch_prep<kPrepJobs>(jobs, n, s);
 }
 
 }  // namespace ftp

@@ -11,6 +11,9 @@ _NETS = {
     "pooled": ((conv(32, 64), pool(64)), 48, 64),
     "plain": ((conv(40, 48), conv(48, 24)), 30, 46),
     "narrow": ((conv(16, 24), conv(24, 12), conv(12, 8)), 66, 70),
+    # odd strides between channels and between images: rows of 16-bit maps that start between dwords
+    "oddchannels": ((conv(3, 9), conv(9, 16)), 33, 45),
+    "oddpool": ((conv(3, 8), conv(8, 9), pool(9)), 66, 70),
     "oddwidth": ((conv(16, 40), conv(40, 32)), 33, 45),
     "other": ((conv(24, 20, 5), conv(20, 12, 1), conv(12, 16, 3, stride=2)), 62, 58),
 }
