@@ -105,10 +105,9 @@ struct PrepJob {
     int Cout, Cin, KK, kind;
     int rot;                                        // 1: output channel = ci, reduction channel = co, taps rotated by 180 degrees (delta pass)
     int bf16;                                       // storage type of w
-    int first;                                      // first block of the job (filled in by prep_filters)
 };
 PrepJob mfma_prep_job(const ConvArgs& c, void* wt, bool backward);
-void prep_filters(PrepJob* jobs, int n, hipStream_t s);
+void prep_filters(const PrepJob* jobs, int n, hipStream_t s);
 // wt: the filter as mfma_prep_job's job left it.
 int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);       // non-zero: does not fit
 int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
@@ -168,6 +167,7 @@ bool thin_bwd_data_eligible(const ConvArgs& a);
 void thin_conv_bwd_data(const ConvArgs& a, hipStream_t s);
 bool thin_wgrad_eligible(const ConvArgs& c);
 void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
+bool thin16_wgrad(const ConvArgs& a, const MfmaWgradArgs& m, hipStream_t s);      // (ftp_wgrad_thin16.hip) false: does not apply
 
 void direct_conv_fwd(const ConvArgs& a, hipStream_t s);
 void direct_conv_bwd_data(const ConvArgs& a, hipStream_t s);
