@@ -1262,6 +1262,7 @@ void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
     a.partial = c.partial; a.scratch = scratch; a.n_params = c.n_params; a.w_off = c.w_off;
     a.Cin = c.Cin; a.Cout = c.Cout; a.Hc = c.Hi; a.Wc = c.Wi; a.slope = c.slope; a.M = c.M; a.batch = c.batch;
     a.splits = c.wgrad_shares_thin;
+    if (thin16_wgrad(c, a, s)) return;
     const int nb = (c.Cin * c.K * c.K + 31) / 32;      // 1 (up to 3x3), 2 or 4 (5x5), 4 to 7 (7x7: 5 for 3 channels)
     dim3 grid((c.Cout + 31) / 32, a.splits, c.N * c.M), block(256);
     const ThinStream ts = c.Cin <= 4 ? stream_geom(c) : ThinStream{0, 0, 0, 1, 1, 1, 0, false};
