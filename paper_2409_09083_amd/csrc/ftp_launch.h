@@ -167,6 +167,7 @@ bool thin_bwd_data_eligible(const ConvArgs& a);
 void thin_conv_bwd_data(const ConvArgs& a, hipStream_t s);
 bool thin_wgrad_eligible(const ConvArgs& c);
 void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
+bool thin16_bwd_data(const ConvArgs& a, hipStream_t s);        // (ftp_delta_thin16.hip) false: does not apply
 bool thin16_wgrad(const ConvArgs& a, const MfmaWgradArgs& m, hipStream_t s);      // (ftp_wgrad_thin16.hip) false: does not apply
 
 void direct_conv_fwd(const ConvArgs& a, hipStream_t s);

@@ -653,6 +653,7 @@ bool thin_bwd_data_eligible(const ConvArgs& a) { return a.Cin <= 4; }
 
 void thin_conv_bwd_data(const ConvArgs& a, hipStream_t s)
 {
+    if (thin16_bwd_data(a, s)) return;
     int mw = 0, mh = 0;
     for (int t = 0; t < a.M; ++t) mw = mw > a.rect.x1[t] - a.rect.x0[t] + 1 ? mw : a.rect.x1[t] - a.rect.x0[t] + 1;
     for (int t = 0; t < a.N; ++t) mh = mh > a.rect.y1[t] - a.rect.y0[t] + 1 ? mh : a.rect.y1[t] - a.rect.y0[t] + 1;
