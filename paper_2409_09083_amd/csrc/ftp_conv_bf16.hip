@@ -27,11 +27,12 @@ namespace ftp {
 //   WS      the map lies inside the workspace (which has margins) and all its rows, channels and images start on a dword: 16
 //           bytes a lane (patch rows start on that grid)
 //   ODD     ... and some start between dwords: 20 bytes from the dword at or below the first element, shifted into place
-//   CALLER  a buffer of the caller's: nothing outside it is read.  Where all strides are even and rows have 8 elements, 16
-//           bytes a lane, the unit moved inside its row and its elements shifted back; else element by element
+//   CALLER  a buffer of the caller's: nothing outside it is read.  All strides are even and rows have 8 elements: 16 bytes a
+//           lane, the unit moved inside its row and its elements shifted back
+//   NARROW  ... else: element by element
 //   POOL    delta back-propagation through a fused pool: a position of the convolution's output receives its window's delta
 //           if it is the window's winner for that channel.  Patch rows start at an even column: a unit is 4 windows
-enum ConvBfIn { BF_WS = 0, BF_ODD = 1, BF_CALLER = 2, BF_POOL = 3 };
+enum ConvBfIn { BF_WS = 0, BF_ODD = 1, BF_CALLER = 2, BF_POOL = 3, BF_NARROW = 4 };
 
 constexpr unsigned kOobB = 0x80000000u;               // beyond the records of every buffer resource below: reads as zero
 constexpr unsigned kRecordsB = 0x7FFFFFFFu;
@@ -84,7 +85,7 @@ k_conv_bf16(MfmaConvArgs a)
     }
 
     // ---- where this thread's unit of the patch comes from ---------------------------------------------------------
-    constexpr int FRONT = IN == BF_CALLER ? 0 : 8;     // (the buffers start 8 elements early: offsets stay non-negative)
+    constexpr int FRONT = IN == BF_CALLER || IN == BF_NARROW ? 0 : 8;     // (the buffers start 8 elements early: offsets stay non-negative)
     const bf16_t* const src = (const bf16_t*)sv.p + (long long)stack * sv.ss + (long long)g.n_a * sv.ns - FRONT;
     const uint8_t* const msk = (const uint8_t*)a.mask.p + (long long)stack * a.mask.ss + (long long)g.n_a * a.mask.ns - FRONT;
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, (int)kRecordsB, 0x00020000);
@@ -113,10 +114,9 @@ k_conv_bf16(MfmaConvArgs a)
             }
         }
     }
-    // CALLER (uniform): 16-byte loads; dwords the unit was moved by to lie inside its row
-    const bool wide = IN == BF_CALLER && !((sv.pitch | (int)sv.cs | (int)sv.ns | (int)sv.ss) & 1) && !((uintptr_t)sv.p & 3) && a.Wc >= 8;
+    // CALLER: dwords the unit was moved by to lie inside its row
     int moved = 0;
-    if (wide && xin != 0u) {
+    if (IN == BF_CALLER && xin != 0u) {
         const int gx = (int)(__builtin_ctz(xin));          // first element inside the map, and how many lie beyond
         const int behind = __builtin_clz(xin) - 24;
         moved = gx > 0 ? -(gx >> 1) : behind >> 1;         // (the unit starts at an even column and the map is even: whole dwords)
@@ -129,24 +129,34 @@ k_conv_bf16(MfmaConvArgs a)
     v4u xr[8];                                         // 8 elements of each of 8 channels
     uint32_t x5[IN == BF_ODD || IN == BF_POOL ? 8 : 1];  // ODD: the fifth dword; POOL: codes, high dword
     auto issue_x = [&](int c0) {
+        if constexpr (IN == BF_NARROW) {
+            // the loads of G channels in flight together (64 of them fit the registers of the smallest wavefront tile only; one
+            // channel at a time before: 288 -> 16 channels, 1x1, 4 images of 31^2, 33.8 -> 33.4 us)
+            constexpr int G = MT * NT <= 2 ? 8 : MT * NT <= 4 ? 2 : 1;
+#pragma unroll
+            for (int kg = 0; kg < 8; kg += G) {
+                uint32_t t[G][8];
+#pragma unroll
+                for (int k = 0; k < G; ++k) {
+                    const bool ok = c0 + 8 * u_oct + kg + k < a.C;
+                    const unsigned so = 2u * (unsigned)((c0 + kg + k) * (int)sv.cs);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) t[k][e] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xrsrc, ok && ((xin >> e) & 1u) ? xoff + 2u * e : kOobB, so, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < G; ++k)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) xr[kg + k][e] = t[k][2 * e] | (t[k][2 * e + 1] << 16);
+            }
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const bool ok = xin != 0u && c0 + 8 * u_oct + k < a.C;
             const unsigned so = 2u * (unsigned)((c0 + k) * (int)sv.cs);
-            if constexpr (IN == BF_WS) {
+            if constexpr (IN == BF_WS || IN == BF_CALLER) {
                 xr[k] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, ok ? xoff : kOobB, so, 0);
-            } else if constexpr (IN == BF_CALLER) {
-                if (wide) {
-                    xr[k] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, ok ? xoff : kOobB, so, 0);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t lo = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xrsrc, ok && ((xin >> (2 * e)) & 1u) ? xoff + 4u * e : kOobB, so, 0);
-                        const uint32_t up = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xrsrc, ok && ((xin >> (2 * e + 1)) & 1u) ? xoff + 4u * e + 2u : kOobB, so, 0);
-                        xr[k][e] = lo | (up << 16);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);     // (a channel at a time: 64 loads in flight would not fit the registers)
-                }
             } else {
                 // the dword at or below the first element: an odd element's half goes with the scalar part
                 const unsigned odd = so & 2u, vo = (xoff + odd) & ~3u, sa = so - odd;
@@ -403,7 +413,7 @@ int launch_bf_in(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
 // (the layers mfma_conv_packs_bf16 names; a.wt = the filter as PREP_PACK16 leaves it)
 int conv_bf16_fwd(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
 {
-#define FTP_F(K, PO) (!c.in_ws ? launch_bf_in<K, PO, false, BF_CALLER>(a, c, s) : even_view(a.in) ? launch_bf_in<K, PO, false, BF_WS>(a, c, s) : launch_bf_in<K, PO, false, BF_ODD>(a, c, s))
+#define FTP_F(K, PO) (!c.in_ws ? (even_view(a.in) && a.Wc >= 8 ? launch_bf_in<K, PO, false, BF_CALLER>(a, c, s) : launch_bf_in<K, PO, false, BF_NARROW>(a, c, s)) : even_view(a.in) ? launch_bf_in<K, PO, false, BF_WS>(a, c, s) : launch_bf_in<K, PO, false, BF_ODD>(a, c, s))
     if (c.K == 3) return c.pooled ? FTP_F(3, true) : FTP_F(3, false);
     return c.pooled ? FTP_F(1, true) : FTP_F(1, false);
 #undef FTP_F
