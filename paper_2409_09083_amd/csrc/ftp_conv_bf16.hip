@@ -29,7 +29,8 @@ namespace ftp {
 //   ODD     ... and some start between dwords: 20 bytes from the dword at or below the first element, shifted into place
 //   CALLER  a buffer of the caller's: nothing outside it is read.  All strides are even and rows have 8 elements: 16 bytes a
 //           lane, the unit moved inside its row and its elements shifted back
-//   NARROW  ... else: element by element
+//   NARROW  ... else as ODD, from an address rounded down to a dword, where that stays inside the buffer (all but the units at its two
+//           ends); a wavefront with a unit at an end loads element by element (everywhere: 288 -> 16 channels, 1x1, 4 images of 31^2, 33 us, so 23)
 //   POOL    delta back-propagation through a fused pool: a position of the convolution's output receives its window's delta
 //           if it is the window's winner for that channel.  Patch rows start at an even column: a unit is 4 windows
 enum ConvBfIn { BF_WS = 0, BF_ODD = 1, BF_CALLER = 2, BF_POOL = 3, BF_NARROW = 4 };
@@ -85,8 +86,10 @@ k_conv_bf16(MfmaConvArgs a)
     }
 
     // ---- where this thread's unit of the patch comes from ---------------------------------------------------------
-    constexpr int FRONT = IN == BF_CALLER || IN == BF_NARROW ? 0 : 8;     // (the buffers start 8 elements early: offsets stay non-negative)
-    const bf16_t* const src = (const bf16_t*)sv.p + (long long)stack * sv.ss + (long long)g.n_a * sv.ns - FRONT;
+    constexpr int FRONT = IN == BF_CALLER ? 0 : 8;     // (the buffers start 8 elements early: offsets stay non-negative)
+    const bf16_t* const src0 = (const bf16_t*)sv.p + (long long)stack * sv.ss + (long long)g.n_a * sv.ns - FRONT;
+    const unsigned skew = IN == BF_NARROW ? (unsigned)((uintptr_t)src0 & 2u) : 0u;       // (NARROW: the buffer starts on a dword)
+    const bf16_t* const src = (const bf16_t*)((const char*)src0 - skew);
     const uint8_t* const msk = (const uint8_t*)a.mask.p + (long long)stack * a.mask.ss + (long long)g.n_a * a.mask.ns - FRONT;
     const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)src, (short)0, (int)kRecordsB, 0x00020000);
     const __amdgpu_buffer_rsrc_t mrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)msk, (short)0, (int)kRecordsB, 0x00020000);
@@ -123,16 +126,26 @@ k_conv_bf16(MfmaConvArgs a)
         xoff -= 4u * (unsigned)moved;
     }
 
+    // NARROW: bytes from `src` to the caller's buffer and to its end
+    if (IN == BF_NARROW) xoff += skew;
+    const int first = IN == BF_NARROW ? (int)((const char*)sv.p - (const char*)src < 0 ? 0 : (const char*)sv.p - (const char*)src) : 0;
+    const long long room = IN == BF_NARROW ? (const char*)((const bf16_t*)sv.p + (long long)a.batch * sv.ns) - (const char*)src : 0;
+    bool rounded = true;                               // NARROW (uniform): this stage's units were loaded from rounded addresses
+
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
     typedef uint32_t v3u __attribute__((ext_vector_type(3)));
     typedef uint32_t v2u __attribute__((ext_vector_type(2)));
     v4u xr[8];                                         // 8 elements of each of 8 channels
-    uint32_t x5[IN == BF_ODD || IN == BF_POOL ? 8 : 1];  // ODD: the fifth dword; POOL: codes, high dword
+    uint32_t x5[IN == BF_ODD || IN == BF_NARROW || IN == BF_POOL ? 8 : 1];  // ODD: the fifth dword; POOL: codes, high dword
     auto issue_x = [&](int c0) {
         if constexpr (IN == BF_NARROW) {
-            // the loads of G channels in flight together (64 of them fit the registers of the smallest wavefront tile only; one
-            // channel at a time before: 288 -> 16 channels, 1x1, 4 images of 31^2, 33.8 -> 33.4 us)
-            constexpr int G = MT * NT <= 2 ? 8 : MT * NT <= 4 ? 2 : 1;
+            // (units of channels beyond the last are not loaded)
+            const int last = a.C - 1 - c0 - 8 * u_oct < 7 ? a.C - 1 - c0 - 8 * u_oct : 7;
+            const bool inside = xin == 0u || last < 0 || ((int)(xoff & ~3u) >= first && (long long)(xoff + 2u * (unsigned)((c0 + last) * (int)sv.cs)) + 20 <= room);
+            rounded = __builtin_amdgcn_ballot_w64(!inside) == 0ull;
+        }
+        if (IN == BF_NARROW && !rounded) {
+            constexpr int G = MT * NT <= 2 ? 2 : 1;    // channels whose loads are in flight together (registers)
 #pragma unroll
             for (int kg = 0; kg < 8; kg += G) {
                 uint32_t t[G][8];
@@ -174,10 +187,10 @@ k_conv_bf16(MfmaConvArgs a)
     };
     // registers -> LDS, transposed
     auto store_x = [&](int c0) {
-        if constexpr (IN == BF_ODD) {
+        if constexpr (IN == BF_ODD || IN == BF_NARROW) {
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                const unsigned s = 8u * ((xoff + 2u * (unsigned)((c0 + k) * (int)sv.cs)) & 2u);
+                const unsigned s = IN == BF_NARROW && !rounded ? 0u : 8u * ((xoff + 2u * (unsigned)((c0 + k) * (int)sv.cs)) & 2u);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) xr[k][i] = __builtin_amdgcn_alignbit(i < 3 ? xr[k][i + 1] : x5[k], xr[k][i], s);
             }

@@ -14,6 +14,7 @@ _NETS = {
     # odd strides between channels and between images: rows of 16-bit maps that start between dwords
     "oddchannels": ((conv(3, 9), conv(9, 16)), 33, 45),
     "oddpool": ((conv(3, 8), conv(8, 9), pool(9)), 66, 70),
+    "oddcaller": ((conv(72, 16, 1), conv(16, 32)), 31, 31),
     "oddwidth": ((conv(16, 40), conv(40, 32)), 33, 45),
     "other": ((conv(24, 20, 5), conv(20, 12, 1), conv(12, 16, 3, stride=2)), 62, 58),
 }
