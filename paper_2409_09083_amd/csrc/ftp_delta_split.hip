@@ -10,9 +10,11 @@
 // matrix cores cut what is far below the largest addend towards minus infinity, and with one accumulator for all six that
 // left every sum with a bias of -3e-8 of its size, which a filter gradient over many pixels adds up (its error rose from
 // 6e-7 to 7e-6).  Measured over random sums of 576 products, relative to their size: fp32 instruction 4.3e-7, this 1.4e-7, no
-// bias in either.  Values above the largest bfloat, infinities and NaN make such a sum NaN or infinite: accumulators that
-// are not finite are computed again, element by element in plain fp32, so overflow, infinities and NaN come out as an fp32
-// sum gives them.  (Deltas whose size is below 2^-110 or so lose low bits: their lower planes fall under the smallest bfloat.)
+// bias in either.  Values above the largest bfloat, infinities and NaN make such a sum NaN or infinite: a workgroup that
+// meets a sum that is not finite starts its tile again with the fp32 instruction, so overflow, infinities and NaN come out as an
+// fp32 sum gives them, at about the time the fp32 instruction takes for any values (64 <- 128 channels, 8 images of 76^2, all
+// deltas NaN: a step of 0.67 ms with finite ones took 70 ms while single lanes summed such elements up, 44 of them here).
+// (Deltas whose size is below 2^-110 or so lose low bits: their lower planes fall under the smallest bfloat.)
 // The forward pass keeps the fp32 instruction: every other rounding of it moves a few activations across the kink of the leaky
 // ReLU or to another winner of their pool window, and with them single gradient entries by their own size.
 //
@@ -51,8 +53,12 @@ enum SplitIn { IN_WIDE = 0, IN_POOL = 1, IN_UP = 2 };
 constexpr unsigned kOobS = 0x80000000u;               // beyond the records of every buffer resource below: reads as zero
 constexpr unsigned kRecordsS = 0x7FFFFFFFu;
 
+// Wavefronts per SIMD the register allocation aims at: both accumulator sets of four pixel blocks are 128 registers; the smaller
+// workgroups whose patches leave LDS for a third one a CU stay within 168.
+constexpr int split_waves(int K, int WAVES_M, int BN) { return BN * WAVES_M <= 256 && (K == 1 || (K >= 5 && BN == 128)) ? 3 : 2; }
+
 template <int K, int WAVES_M, int BN, int IN>
-__global__ void __launch_bounds__(256, 2)              // (two wavefronts a SIMD: both accumulator sets are 128 registers)
+__global__ void __launch_bounds__(256, split_waves(K, WAVES_M, BN))
 k_delta_split(MfmaConvArgs a)
 {
     constexpr int WAVES_N = 4 / WAVES_M;
@@ -66,6 +72,7 @@ k_delta_split(MfmaConvArgs a)
     static_assert(UPO % 64 == 0, "a wavefront's units belong to one group of 8 channels");
     constexpr int PLANE = OCT * XMAX;                  // 16-byte units per plane
     extern __shared__ __attribute__((aligned(16))) uint4 Xl[];         // [plane][group of 8 channels][position]
+    __shared__ int redo;                               // a sum of this workgroup is not finite
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -181,6 +188,29 @@ k_delta_split(MfmaConvArgs a)
             }
         }
     };
+    // a unit's elements as the patch holds them: through the pool's winners, zeros beside the map
+    auto arrange = [&](int u) {
+        if constexpr (IN == IN_POOL) {
+            const uint32_t row2 = (xin[u] >> 3) & 2u;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint32_t d0 = xr[u][k][0], d1 = xr[u][k][1];
+                const uint32_t w0 = ((xr[u][k][2] >> 1) & 3u) ^ row2, w1 = ((xr[u][k][3] >> 1) & 3u) ^ row2;     // 0 / 1: the left / right pixel of this row won
+                xr[u][k][0] = w0 == 0u ? d0 : 0u; xr[u][k][1] = w0 == 1u ? d0 : 0u;
+                xr[u][k][2] = w1 == 0u ? d1 : 0u; xr[u][k][3] = w1 == 1u ? d1 : 0u;
+            }
+        }
+        if constexpr (IN != IN_UP) {
+            if (__builtin_amdgcn_ballot_w64((xin[u] & 15u) != 15u && xin[u] != 0u) != 0ull) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool in = (xin[u] >> e) & 1u;
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) xr[u][k][e] = in ? xr[u][k][e] : 0u;
+                }
+            }
+        }
+    };
     // registers -> three planes in LDS
     auto store_x = [&]() {
 #pragma unroll
@@ -188,26 +218,7 @@ k_delta_split(MfmaConvArgs a)
             const int unit = tid + 256 * u;
             if (NU > 1 && unit >= UNITS) continue;
             const int slot = (unit / UPO) * XMAX + 4 * (unit % UPO);
-            if constexpr (IN == IN_POOL) {
-                const uint32_t row2 = (xin[u] >> 3) & 2u;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const uint32_t d0 = xr[u][k][0], d1 = xr[u][k][1];
-                    const uint32_t w0 = ((xr[u][k][2] >> 1) & 3u) ^ row2, w1 = ((xr[u][k][3] >> 1) & 3u) ^ row2;     // 0 / 1: the left / right pixel of this row won
-                    xr[u][k][0] = w0 == 0u ? d0 : 0u; xr[u][k][1] = w0 == 1u ? d0 : 0u;
-                    xr[u][k][2] = w1 == 0u ? d1 : 0u; xr[u][k][3] = w1 == 1u ? d1 : 0u;
-                }
-            }
-            if constexpr (IN != IN_UP) {
-                if (__builtin_amdgcn_ballot_w64((xin[u] & 15u) != 15u && xin[u] != 0u) != 0ull) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const bool in = (xin[u] >> e) & 1u;
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) xr[u][k][e] = in ? xr[u][k][e] : 0u;
-                    }
-                }
-            }
+            arrange(u);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 uint32_t h[4], m[4], l[4];
@@ -264,11 +275,13 @@ k_delta_split(MfmaConvArgs a)
     static_assert(RING == 2 || NSTEP % RING == 0, "a stage ends where the ring of fragments does");
     const int nst = (a.C + CK - 1) / CK;
     uint4 av[RING][3];
+    if (tid == 0) redo = 0;
     issue_x(0);
 #pragma unroll
     for (int j = 0; j < AHEAD; ++j) load_a(av[j], 0, j);
     for (int st = 0; st < nst; ++st) {
         __syncthreads();                               // the previous stage has been read
+        if (st > 0 && redo) break;                     // (one wavefront has met a sum that is not finite: see below)
         store_x();
         __syncthreads();
         const int oct0 = st * OCT;
@@ -309,6 +322,11 @@ k_delta_split(MfmaConvArgs a)
                 for (int p = 0; p < 3; ++p) bv[0][p] = bv[1][p];
             }
         }
+        // (what is not finite here will not become so; one accumulator of each block tells where a whole map is not)
+        float z = 0.0f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) z = __builtin_fmaf(acc[0][t][0], 0.0f, z);
+        if (!(z == 0.0f)) redo = 1;
     }
 
 #pragma unroll
@@ -316,55 +334,63 @@ k_delta_split(MfmaConvArgs a)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[0][t][i] += low[t][i];
 
-    // ---- sums that are not finite: once more, in plain fp32 ---------------------------------------------------------
-    uint32_t bad = 0;                                  // accumulator tiles of this lane with such an element in a valid pixel
+    // ---- sums that are not finite: the tile once more, multiplied with the fp32 instruction --------------------------
+    {
+        bool bad = false;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        float z = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[0][t][i], 0.0f, z);
-        if (tile_pix<1, P>(g, (wave_n * NT + t) * 32 + l32, x1).valid && !(z == 0.0f)) bad |= 1u << t;
-    }
-    if (__builtin_amdgcn_ballot_w64(bad != 0u) != 0ull) {
-        const float* const base = src + FRONT;
-        const uint8_t* const mbase = msk + FRONT;
-        const uint16_t* const wt = (const uint16_t*)a.wt;
-#pragma unroll 1
         for (int t = 0; t < NT; ++t) {
-            if (__builtin_amdgcn_ballot_w64(((bad >> t) & 1u) != 0u) == 0ull) continue;
-            const TilePix tp = tile_pix<1, P>(g, (wave_n * NT + t) * 32 + l32, x1);
-            const int cy = y0 + tp.y, cx = g.ox0 + tp.xl;
-            const long long n = tp.n - g.n_a;
-            v16f v = acc[0][0];
+            float z = 0.0f;
 #pragma unroll
-            for (int k = 1; k < NT; ++k) if (k == t) v = acc[0][k];
-#pragma unroll 1
-            for (int i = 0; i < 16; ++i) {
-                const int m = mb + 8 * (i >> 2) + 4 * hi + (i & 3);
-                float sum = v[i];
-                if (tp.valid && m < a.Mtot && !(__builtin_fabsf(sum) < __builtin_inff())) {
-                    sum = 0.0f;
-                    for (int c = 0; c < a.C; ++c)
-                        for (int tap = 0; tap < KK; ++tap) {
-                            const int gy = cy + tap / K - P, gx = cx + tap % K - P;
-                            float x = 0.0f;                // (padding and inserted zeros are multiplied too)
-                            const bool in = gy >= 0 && gy < a.Hc && gx >= 0 && gx < a.Wc && !(IN == IN_UP && ((gy | gx) & 1));
-                            const int sy = IN >= IN_POOL ? gy >> 1 : gy, sx = IN >= IN_POOL ? gx >> 1 : gx;
-                            if (in) x = base[n * sv.ns + c * sv.cs + (sy - sv.y0[ti]) * sv.pitch + (sx - sv.x0[tj])];
-                            if (IN == IN_POOL && in) {
-                                const int code = mbase[n * a.mask.ns + c * a.mask.cs + (sy - a.mask.y0[ti]) * a.mask.pitch + (sx - a.mask.x0[tj])];
-                                if (((code >> 1) & 3) != (((gy & 1) << 1) | (gx & 1))) x = 0.0f;
-                            }
-                            const uint16_t* const wp = wt + (((long long)((c >> 3) * KK + tap) * 3) * a.Mtot + m) * 8 + (c & 7);
-                            const float wh = __uint_as_float((uint32_t)wp[0] << 16), wm = __uint_as_float((uint32_t)wp[8 * (long long)a.Mtot] << 16);
-                            const float wl = __uint_as_float((uint32_t)wp[16 * (long long)a.Mtot] << 16);
-                            sum = __builtin_fmaf(x, wh + (wm + wl), sum);
-                        }
-                }
-                v[i] = sum;
+            for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[0][t][i], 0.0f, z);
+            bad = bad || (tile_pix<1, P>(g, (wave_n * NT + t) * 32 + l32, x1).valid && !(z == 0.0f));
+        }
+        if (bad) redo = 1;
+        __syncthreads();
+    }
+    if (redo) {
+        // a stage's patch as fp32 [channel][position] in the same LDS; a lane half takes one group of 8 channels, a channel of
+        // each a step (A[m = lane%32][k = lane/32], B[k = lane/32][n = lane%32]).  The filter as the caller holds it
+        float* const Xf = (float*)Xl;
+        const float* const w = (const float*)a.w;
+        // (everything is computed again, from the lane's number on: nothing stays in a register through the loop above for it)
+        const int tr = 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+#pragma unroll
+        for (int u = 0; u < NU; ++u) asm volatile("" : "+v"(xin[u]), "+v"(xoff[u]), "+v"(moff[u]));
+        const int hr = (tr >> 5) & 1, m = m0 + (__builtin_amdgcn_readfirstlane(tr >> 6) % WAVES_M) * 32 + (tr & 31);
+        int at[NT];                                    // the pixel's first patch position, this lane half's 8 channels
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const TilePix tp = tile_pix<1, P>(g, (__builtin_amdgcn_readfirstlane(tr >> 6) / WAVES_M * NT + t) * 32 + (tr & 31), x1);
+            at[t] = (tp.valid ? tp.prow * PW + tp.xl + sh : 0) + 8 * hr * XMAX;
+        }
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[0][t][i] = 0.0f;
+        for (int st = 0; st < nst; ++st) {
+            issue_x(st * CK);
+            __syncthreads();                           // the previous stage has been read
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int unit = tr + 256 * u;
+                if (NU > 1 && unit >= UNITS) continue;
+                arrange(u);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) *(v4u*)(Xf + (8 * (unit / UPO) + k) * XMAX + 4 * (unit % UPO)) = xr[u][k];
             }
+            __syncthreads();
+#pragma unroll 1
+            for (int j = 0; j < NSTEP; ++j) {
+                const int s = j / KK, tap = j - s * KK, c = st * CK + 16 * s + 8 * hr;
+                float wv[8];
 #pragma unroll
-            for (int k = 0; k < NT; ++k) if (k == t) acc[0][k] = v;
+                for (int k = 0; k < 8; ++k) wv[k] = c + k < a.C && m < a.Mtot ? w[((long long)(c + k) * a.Mtot + m) * KK + KK - 1 - tap] : 0.0f;
+                const float* const xp = Xf + 16 * s * XMAX + (tap / K) * PW + tap % K;
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[k], xp[k * XMAX + at[t]], acc[0][t], 0, 0, 0);
+            }
         }
     }
     conv_epilogue<float, K, 1, WAVES_M, 1, false, true>(a, g, acc, (float*)Xl, m0, x0, x1, y0, stack, ti, tj);

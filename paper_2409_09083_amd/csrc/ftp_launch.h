@@ -72,6 +72,7 @@ struct MfmaConvArgs {
     RectTab own;                                    // forward: owned part of it (decision codes are written there)
     int ix0[kTabGrid], ix1[kTabGrid], iy0[kTabGrid], iy1[kTabGrid];   // extent of the input view per tile column / row
     const float* wt;                                // relaid filter [tap][reduction channel][output channel]
+    const void* w;                                  // ... as the caller holds it (OIHW)
     const void* bias;                               // element type of the maps
     int C, Mtot;                                    // reduction channels, output channels
     int Hc, Wc;                                     // map extent at the convolution

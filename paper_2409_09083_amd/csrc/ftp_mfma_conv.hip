@@ -493,7 +493,7 @@ int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream
 {
     MfmaConvArgs a;
     fill_common(a, c, inrect);
-    a.wt = wt; a.bias = c.bias;
+    a.wt = wt; a.w = c.w; a.bias = c.bias;
     a.C = c.Cin; a.Mtot = c.Cout;
     a.Hc = c.Hi; a.Wc = c.Wi;                           // the patch is cut from the input map
     if (mfma_conv_packs_bf16(c)) return conv_bf16_fwd(a, c, s);
@@ -512,7 +512,7 @@ int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipS
     if (c.S == 2 && (c.K == 3 || c.K == 1) && delta_s2_mfma(c, inrect, wt, s) == 0) return 0;
     MfmaConvArgs a;
     fill_common(a, c, inrect);
-    a.wt = wt; a.bias = nullptr;
+    a.wt = wt; a.w = c.w; a.bias = nullptr;
     a.C = c.Cout; a.Mtot = c.Cin;
     // the patch is cut from the deltas as the stride-1 convolution sees them: at the convolution output (stride 1,
     // also through a pool), or with zeros inserted between them (stride 2: twice the extent)
