@@ -14,6 +14,9 @@
 // which take turns: while one loads and splits, the other multiplies (216 matrix instructions, 6.9 k cycles a chunk).
 // One set of accumulators is all the registers hold, and the matrix cores cut small addends towards minus infinity
 // (ftp_delta_split.hip): the deltas of every other chunk are negated, and the accumulators with them, so that the cuts cancel.
+// Sums that are not finite - infinities and NaN in the maps, values above the largest bfloat, overflow - come out as an fp32 sum
+// gives them: a workgroup that meets one multiplies its share again with the fp32 instruction (pair of 3x3 layers, 8 images of
+// 76^2, all deltas NaN: a step of 0.67 ms with finite ones took 26 ms while single lanes summed such elements up, 1.0 here).
 // Measured (64 images, 608^2, 6 x 6 tiles, useful TFLOP/s, fp32 instruction -> this): 128 x 64 at 152^2 108 -> 168, 256 x 128 at
 // 76^2 107 -> 167, 512 x 256 at 38^2 103 -> 150, 64 x 32 behind a pool 88 -> 138.  What bounds it: the matrix cores, at 225
 // TFLOP/s on the positions they multiply (six products at 1.35 PFLOP/s), of which rows of 25, 13 or 6 pixels fill 75-81 %.
@@ -59,6 +62,7 @@ k_wgrad_split(WsplitArgs a)
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     unsigned char* const Xl = lds;
     unsigned char* const Zl = lds + 3 * XPLANE;
+    __shared__ int redo;                                   // a sum of this workgroup is not finite
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -179,6 +183,21 @@ k_wgrad_split(WsplitArgs a)
             }
         }
     };
+    // zeros beside the patch; a quad of deltas through the pool's winners
+    auto clear_x = [&](int k) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xr[k][e] = (xin >> e) & 1u ? xr[k][e] : 0u;
+    };
+    auto spread_z = [&](int k) -> v4u {
+        v4u v = zr[k];
+        if constexpr (POOL) {
+            const uint32_t row2 = (zin >> 3) & 2u;
+            const uint32_t w0 = ((zr[k][2] >> 1) & 3u) ^ row2, w1 = ((zr[k][3] >> 1) & 3u) ^ row2;      // 0 / 1: the left / right pixel of this row won
+            v[0] = w0 == 0u ? zr[k][0] : 0u; v[1] = w0 == 1u ? zr[k][0] : 0u;
+            v[2] = w1 == 0u ? zr[k][1] : 0u; v[3] = w1 == 1u ? zr[k][1] : 0u;
+        }
+        return v;
+    };
     auto store = [&](uint32_t sign) {
         auto put = [](unsigned char* at, int plane, const v4u& v) {
             uint32_t h[2], m[2], l[2];
@@ -191,20 +210,12 @@ k_wgrad_split(WsplitArgs a)
         const bool xmask = __builtin_amdgcn_ballot_w64(xin != 0u && xin != 15u) != 0ull;
 #pragma unroll
         for (int k = 0; k < NX; ++k) {
-            if (xmask)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) xr[k][e] = (xin >> e) & 1u ? xr[k][e] : 0u;
+            if (xmask) clear_x(k);
             put(Xl + (8 * k + xch) * XROW + 8 * xq, XPLANE, xr[k]);
         }
 #pragma unroll
         for (int k = 0; k < NZ; ++k) {
-            v4u v = zr[k];
-            if constexpr (POOL) {
-                const uint32_t row2 = (zin >> 3) & 2u;
-                const uint32_t w0 = ((zr[k][2] >> 1) & 3u) ^ row2, w1 = ((zr[k][3] >> 1) & 3u) ^ row2;      // 0 / 1: the left / right pixel of this row won
-                v[0] = w0 == 0u ? zr[k][0] : 0u; v[1] = w0 == 1u ? zr[k][0] : 0u;
-                v[2] = w1 == 0u ? zr[k][1] : 0u; v[3] = w1 == 1u ? zr[k][1] : 0u;
-            }
+            v4u v = spread_z(k);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = (zin >> e) & 1u ? v[e] ^ sign : 0u;
             put(Zl + (16 * k + zch) * ZROW + 8 * zq, ZPLANE, v);
@@ -262,16 +273,89 @@ k_wgrad_split(WsplitArgs a)
             for (int i = 0; i < 16; ++i) acc[t][i] = -acc[t][i];
     };
 
+    if (tid == 0) redo = 0;
     for (int id = id0; id < id1; ++id) {
         const Chunk c = chunk_at(id);
         load(c);
+        // (what is not finite after a chunk will not become so: one accumulator tells where a whole map is not)
+        if (id > id0 && !(__builtin_fabsf(acc[4][0]) < __builtin_inff())) redo = 1;
         __syncthreads();                                   // everybody has read the previous chunk (and the cleared LDS is visible)
+        if (id > id0 && redo) break;
         store((id - id0) & 1 ? 0x80000000u : 0u);
         __syncthreads();
         if (id > id0) negate();
         multiply(wsplit_steps(wc, c.ni, c.nr, c.nc));
     }
     if (id1 > id0 && ((id1 - id0 - 1) & 1)) negate();      // (an even number of chunks ends on a negated one)
+
+    // ---- sums that are not finite: this share once more, multiplied with the fp32 instruction -------------------------------
+    {
+        bool bad = false;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+            float z = 0.0f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[t][i], 0.0f, z);
+            bad = bad || !(z == 0.0f);
+        }
+        if (bad) redo = 1;                                 // (channels beyond the last are zeros: not finite only beside others that are not)
+        __syncthreads();
+    }
+    if (redo) {
+        // fp32 [channel][position] in the same LDS; two positions a step (A[m = lane%32][k = lane/32], B[k = lane/32][n = lane%32]).
+        // A position that holds no pixel of the chunk has a zero delta and must not meet an infinity: its X counts as zero too
+        constexpr int XP = kWsplitPatch + 5, ZPF = kWsplitPos + 1;     // floats of a channel (odd: lanes read consecutive channels)
+        static_assert(4 * (BCI * XP + BCO * ZPF) <= 3 * (XPLANE + ZPLANE), "fp32 maps fit the planes' area");
+        float* const Xf = (float*)lds;
+        float* const Zf = Xf + BCI * XP;
+        // (everything is computed again, from the lane's number on: nothing stays in a register through the loop above for it)
+        const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int q_il = TI > 1 ? ln / IP : 0, q_r = (ln - q_il * IP) / ZP, q_c = ln - q_il * IP - q_r * ZP;       // position `ln` of a chunk
+        const int q_off = q_il < TI && q_r < RB && q_c < TC ? (q_il * (rh + 2) + q_r) * PW + q_c : 0;              // its first patch position
+        const float* const xf = Xf + (wave_ci * 32 + (ln & 31)) * XP;
+        const float* const zf = Zf + (wave_co * 32 + (ln & 31)) * ZPF + (ln >> 5);
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[t][i] = 0.0f;
+#pragma unroll 1
+        for (int id = id0; id < id1; ++id) {
+            const Chunk c = chunk_at(id);
+            load(c);
+            __syncthreads();                               // everybody has read the previous chunk
+            const int fx = ln & 31, fz = ln & 15;
+#pragma unroll
+            for (int k = 0; k < NX; ++k) {
+                clear_x(k);
+                float* const at = Xf + (8 * k + 2 * wave + (ln >> 5)) * XP + 4 * fx;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) at[e] = __uint_as_float(xr[k][e]);
+            }
+#pragma unroll
+            for (int k = 0; k < NZ; ++k) {
+                const v4u v = spread_z(k);
+                float* const at = Zf + (16 * k + 4 * wave + (ln >> 4)) * ZPF + 4 * fz;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) at[e] = (zin >> e) & 1u ? __uint_as_float(v[e]) : 0.0f;
+            }
+            __syncthreads();
+            const unsigned long long pixels = __builtin_amdgcn_ballot_w64(q_il < c.ni && q_r < c.nr && q_c < c.nc);
+            const int nsteps = 8 * wsplit_steps(wc, c.ni, c.nr, c.nc);
+#pragma unroll 1
+            for (int i = 0; i < nsteps; ++i) {
+                if (WAVES_K > 1 && (i >> 3) % WAVES_K != wave_k) continue;
+                const int o0 = __builtin_amdgcn_readlane(q_off, 2 * i), o1 = __builtin_amdgcn_readlane(q_off, 2 * i + 1);
+                const bool pixel = (pixels >> (2 * i + (ln >> 5))) & 1ull;
+                const float z = zf[2 * i];
+                const float* const x = xf + (ln >> 5 ? o1 : o0);
+                float xv[9];
+#pragma unroll
+                for (int t = 0; t < 9; ++t) { xv[t] = x[t / 3 * PW + t % 3]; if (!pixel) xv[t] = 0.0f; }
+#pragma unroll
+                for (int t = 0; t < 9; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(z, xv[t], acc[t], 0, 0, 0);
+            }
+        }
+    }
 
     // ---- combine the wavefronts that share a block (fixed order), then store ------------------------------------------
     if constexpr (WAVES_K > 1) {
@@ -298,47 +382,6 @@ k_wgrad_split(WsplitArgs a)
     }
     if (wave_k != 0) return;
     const int ci = ci0 + ci_l;
-    // sums that are not finite: once more, in plain fp32 (overflow, infinities and NaN as an fp32 sum gives them)
-    uint32_t bad = 0;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-        float z = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[t][i], 0.0f, z);
-        if (ci < Cin && !(z == 0.0f)) bad |= 1u << t;
-    }
-    if (__builtin_amdgcn_ballot_w64(bad != 0u) != 0ull) {
-#pragma unroll 1
-        for (int t = 0; t < 9; ++t) {
-            if (__builtin_amdgcn_ballot_w64(((bad >> t) & 1u) != 0u) == 0ull) continue;
-            v16f v = acc[0];
-#pragma unroll
-            for (int k = 1; k < 9; ++k) if (k == t) v = acc[k];
-#pragma unroll 1
-            for (int i = 0; i < 16; ++i) {
-                const int co = co0 + wave_co * 32 + 8 * (i >> 2) + 4 * hi + (i & 3);
-                float sum = v[i];
-                if (ci < Cin && co < Cout && !(__builtin_fabsf(sum) < __builtin_inff())) {
-                    sum = 0.0f;
-                    for (int id = id0; id < id1; ++id) {
-                        const Chunk c = chunk_at(id);
-                        for (int n = c.n0; n < c.n0 + c.ni; ++n)
-                            for (int y = c.yb; y < c.yb + c.nr; ++y)
-                                for (int x = c.xb; x < c.xb + c.nc; ++x) {
-                                    const int sy = POOL ? y >> 1 : y, sx = POOL ? x >> 1 : x, gy = y + t / 3 - 1, gx = x + t % 3 - 1;
-                                    float dz = *at<float>(a.din, stack, ti, tj, n, co, sy, sx);
-                                    if (POOL && ((*at<uint8_t>(a.mask, stack, ti, tj, n, co, sy, sx) >> 1) & 3) != (((y & 1) << 1) | (x & 1))) dz = 0.0f;
-                                    const float xv = gy >= 0 && gy < Hc && gx >= 0 && gx < Wc ? *at<float>(a.in, stack, ti, tj, n, ci, gy, gx) : 0.0f;
-                                    sum = __builtin_fmaf(dz, xv, sum);
-                                }
-                    }
-                }
-                v[i] = sum;
-            }
-#pragma unroll
-            for (int k = 0; k < 9; ++k) if (k == t) acc[k] = v;
-        }
-    }
     const long long layer_params = (long long)Cout * Cin * 9;
     float* dst = a.splits > 1 ? a.scratch + ((long long)stack * a.splits + split) * layer_params
                               : a.partial + (long long)stack * a.n_params + a.w_off;
