@@ -514,7 +514,8 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
     constexpr int POS = PDY * PDX, PPT = (POS + 255) / 256;                // patch positions, and those of a thread
     constexpr int APT = (COC * ND + 3) / 4;            // weights of a thread
     __shared__ float dzl[COC * PDY * PDP];
-    __shared__ float wl[4 * APT * 64];                 // [output channel][step][lane]
+    __shared__ __attribute__((aligned(16))) float wl[4 * APT * 64];        // [output channel][step][lane]
+    __shared__ int redo;                               // a delta of this tile is not finite
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = blockIdx.x % tiles, img = blockIdx.x / tiles;
@@ -571,9 +572,7 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
     for (int r = 0; r < R; ++r) acc[r] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
     // (columns beyond the neighbourhood have zero weights; they read the last one)
     const int lb = SQ ? (jy + (kq >> 1)) * PDP + ix0 + l16 + (kq & 1) : jy * PDP + ix0 + l16 + (kq < NQ ? kq : NQ - 1);
-    fetch(0);
-    for (int c0 = 0; c0 < Cout; c0 += COC) {
-        __syncthreads();                               // the previous stage has been consumed
+    auto stage = [&]() {
 #pragma unroll
         for (int c = 0; c < COC; ++c)
 #pragma unroll
@@ -581,6 +580,13 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
                 if (pslot[p] >= 0) dzl[c * (PDY * PDP) + pslot[p]] = (pin >> p) & 1u ? ld(&xr[c][p]) : 0.0f;
 #pragma unroll
         for (int p = 0; p < APT; ++p) wl[(wave + 4 * p) * 64 + lane] = ld(&ar[p]);
+    };
+    if (tid == 0) redo = 0;
+    fetch(0);
+    for (int c0 = 0; c0 < Cout; c0 += COC) {
+        __syncthreads();                               // the previous stage has been consumed
+        if (c0 > 0 && redo) break;
+        stage();
         __syncthreads();
         if (c0 + COC < Cout) fetch(c0 + COC);
 #pragma unroll 1
@@ -598,8 +604,50 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
                     if (r - st >= 0 && r - st < R) acc[r - st] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv, acc[r - st], 0, 0, 0);
             }
         }
+        if (!(__builtin_fabsf(acc[0][0]) < __builtin_inff())) redo = 1;
     }
     const int pa = kq >> 1, pb = kq & 1;
+    // Deltas that are infinite or NaN have met the zero weights of pixels they do not reach: the tile once more on the vector ALU,
+    // over the taps alone (7x7 stem, 4 images of 303^2, all deltas NaN: a step of 0.28 ms with finite ones took 7.0 ms while single
+    // lanes did this from global memory, 0.47 ms here).
+    {
+        float z = 0.0f;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) z = fmaf(acc[r][c], 0.0f, z);
+        if (!(z == 0.0f)) redo = 1;
+        __syncthreads();
+    }
+    if (redo) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+        for (int c0 = 0; c0 < Cout; c0 += COC) {
+            fetch(c0);
+            __syncthreads();                           // the previous stage has been consumed
+            stage();
+            __syncthreads();
+#pragma unroll 1
+            for (int c = 0; c < COC; ++c) {
+                if (c0 + c >= Cout) break;
+#pragma unroll 1
+                for (int t = 0; t < NQ * NQ; ++t) {
+                    const int dy = t / NQ, dx = t - dy * NQ, ky = pa + P - 2 * (dy + QLO), kx = pb + P - 2 * (dx + QLO);
+                    const bool tap = ky >= 0 && ky < K && kx >= 0 && kx < K;
+                    // (the 4 channels' weights of this lane's pixel; channels beyond the last are not stored)
+                    const float4 wv = *(const float4*)(wl + (SQ ? c : c * ND + dy) * 64 + 16 * (SQ ? t : dx) + 4 * kq);
+                    const float* const rows = dzl + c * (PDY * PDP) + (jy + dy) * PDP + ix0 + l16 + dx;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const float d = tap ? rows[r * PDP] : 0.0f;
+                        acc[r][0] = fmaf(wv.x, d, acc[r][0]); acc[r][1] = fmaf(wv.y, d, acc[r][1]);
+                        acc[r][2] = fmaf(wv.z, d, acc[r][2]); acc[r][3] = fmaf(wv.w, d, acc[r][3]);
+                    }
+                }
+            }
+        }
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const int iy = 2 * (J0 + jy + r) + pa, ix = 2 * (I0 + ix0 + l16) + pb;
@@ -608,18 +656,6 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
         for (int c = 0; c < 4; ++c) {
             if (c >= Cin) break;
             float v = acc[r][c];
-            // a delta that is infinite or NaN has met the zero weights of pixels it does not reach: once more, over the taps alone
-            if (!(__builtin_fabsf(v) < __builtin_inff())) {
-                v = 0.0f;
-                for (int co = 0; co < Cout; ++co)
-                    for (int ky = (pa + P) & 1; ky < K; ky += 2)
-                        for (int kx = (pb + P) & 1; kx < K; kx += 2) {
-                            const int qy = (iy + P - ky) >> 1, qx = (ix + P - kx) >> 1;
-                            const bool in = qy >= ext.y0[ti] && qy <= ext.y1[ti] && qx >= ext.x0[tj] && qx <= ext.x1[tj];
-                            const float d = in ? ld(at<T>(din, stack, ti, tj, n, co, qy, qx)) : 0.0f;
-                            v = fmaf(ld(w + ((size_t)co * Cin + c) * KK + ky * K + kx), d, v);
-                        }
-            }
             if (scale_out) v = scaled_delta<T>(v, sign_bit(isign, stack, ti, tj, n, c, iy, ix), in_slope);
             st(at<T>(dout, stack, ti, tj, n, c, iy, ix), v);
         }

@@ -13,6 +13,7 @@ _NETS = {
     "gradient": ((conv(64, 128, slope=1.0),), 76, 8, (3, 3), "f32"),
     "gradient_pooled": ((conv(32, 64, slope=1.0), pool(64)), 152, 4, (4, 4), "f32"),
     "gradient_narrow": ((conv(16, 32, slope=1.0), conv(32, 32, slope=1.0)), 152, 4, (1, 1), "f32"),
+    "stem": ((conv(3, 64, 7, slope=1.0, stride=2),), 303, 4, (3, 3), "f32"),
     "delta5": ((conv(32, 64, 5, slope=1.0),), 76, 4, (3, 3), "f32"),
 }
 
@@ -94,3 +95,18 @@ def test_filter_gradients(cin, cout, batch, h, w, grid, pooled):
     assert torch.equal(got[torch.isinf(ref)], ref[torch.isinf(ref)])
     # (one fp32 rounding, 2^-24 of the sum of magnitudes, per product summed)
     assert bool(((got - ref).abs()[fin] <= (batch * h * w + 8) * 2.0 ** -24 * mag[fin]).all())
+
+
+@pytest.mark.parametrize("k", [3, 5, 7])
+@pytest.mark.parametrize("batch", [2, 64])
+def test_deltas_of_a_strided_stem(k, batch):
+    """Tiles of 4 and of 16 rows of cells: the image's delta is not finite exactly where a tap reaches such a delta."""
+    from tests.test_gpu_strided_stem import _run
+    x, wt, dy, got = _run(conv(3, 20, k, slope=1.0, stride=2), batch, 69, 70, (1, 1), "f32", 9, poison=True)
+    ref = torch.nn.grad.conv2d_input(x.shape, wt.double(), dy.double(), stride=2, padding=k // 2)
+    mag = torch.nn.grad.conv2d_input(x.shape, wt.double().abs(), dy.double().abs().nan_to_num(0.0, 0.0, 0.0), stride=2, padding=k // 2)
+    fin = torch.isfinite(ref)
+    assert torch.equal(torch.isfinite(got), fin) and not bool(fin.all())
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    # (one fp32 rounding, 2^-24 of the sum of magnitudes, per product summed)
+    assert bool(((got.double() - ref).abs()[fin] <= (k * k * 20 + 4) * 2.0 ** -24 * mag[fin] + 1e-30).all())
