@@ -13,6 +13,7 @@ _NETS = {
     "gradient": ((conv(64, 128, slope=1.0),), 76, 8, (3, 3), "f32"),
     "gradient_pooled": ((conv(32, 64, slope=1.0), pool(64)), 152, 4, (4, 4), "f32"),
     "gradient_narrow": ((conv(16, 32, slope=1.0), conv(32, 32, slope=1.0)), 152, 4, (1, 1), "f32"),
+    "first_layer_16": ((conv(3, 32, slope=1.0), pool(32)), 304, 4, (4, 4), "bf16"),
     "stem": ((conv(3, 64, 7, slope=1.0, stride=2),), 303, 4, (3, 3), "f32"),
     "delta5": ((conv(32, 64, 5, slope=1.0),), 76, 4, (3, 3), "f32"),
 }
