@@ -281,7 +281,7 @@ k_delta_split(MfmaConvArgs a)
     for (int j = 0; j < AHEAD; ++j) load_a(av[j], 0, j);
     for (int st = 0; st < nst; ++st) {
         __syncthreads();                               // the previous stage has been read
-        if (st > 0 && redo) break;                     // (one wavefront has met a sum that is not finite: see below)
+        if (st == 1 && redo) break;                    // (a sum that is not finite: see below)
         store_x();
         __syncthreads();
         const int oct0 = st * OCT;
@@ -322,11 +322,13 @@ k_delta_split(MfmaConvArgs a)
                 for (int p = 0; p < 3; ++p) bv[0][p] = bv[1][p];
             }
         }
-        // (what is not finite here will not become so; one accumulator of each block tells where a whole map is not)
-        float z = 0.0f;
+        // (what is not finite now will not become so: where a whole map is not, one accumulator of each block tells after the first stage)
+        if (st == 0) {
+            float z = 0.0f;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) z = __builtin_fmaf(acc[0][t][0], 0.0f, z);
-        if (!(z == 0.0f)) redo = 1;
+            for (int t = 0; t < NT; ++t) z = __builtin_fmaf(acc[0][t][0], 0.0f, z);
+            if (!(z == 0.0f)) redo = 1;
+        }
     }
 
 #pragma unroll
@@ -347,7 +349,7 @@ k_delta_split(MfmaConvArgs a)
         if (bad) redo = 1;
         __syncthreads();
     }
-    if (redo) {
+    if (__builtin_expect(redo, 0)) {
         // a stage's patch as fp32 [channel][position] in the same LDS; a lane half takes one group of 8 channels, a channel of
         // each a step (A[m = lane%32][k = lane/32], B[k = lane/32][n = lane%32]).  The filter as the caller holds it
         float* const Xf = (float*)Xl;

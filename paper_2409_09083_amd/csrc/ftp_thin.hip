@@ -585,7 +585,7 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
     fetch(0);
     for (int c0 = 0; c0 < Cout; c0 += COC) {
         __syncthreads();                               // the previous stage has been consumed
-        if (c0 > 0 && redo) break;
+        if (c0 == COC && redo) break;
         stage();
         __syncthreads();
         if (c0 + COC < Cout) fetch(c0 + COC);
@@ -604,12 +604,12 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
                     if (r - st >= 0 && r - st < R) acc[r - st] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[st], bv, acc[r - st], 0, 0, 0);
             }
         }
-        if (!(__builtin_fabsf(acc[0][0]) < __builtin_inff())) redo = 1;
+        if (c0 == 0 && !(__builtin_fabsf(acc[0][0]) < __builtin_inff())) redo = 1;        // (where a whole map is not finite, the first stage tells)
     }
     const int pa = kq >> 1, pb = kq & 1;
     // Deltas that are infinite or NaN have met the zero weights of pixels they do not reach: the tile once more on the vector ALU,
     // over the taps alone (7x7 stem, 4 images of 303^2, all deltas NaN: a step of 0.28 ms with finite ones took 7.0 ms while single
-    // lanes did this from global memory, 0.47 ms here).
+    // lanes did this from global memory, 0.43 ms here).
     {
         float z = 0.0f;
 #pragma unroll
@@ -619,7 +619,7 @@ k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in
         if (!(z == 0.0f)) redo = 1;
         __syncthreads();
     }
-    if (redo) {
+    if (__builtin_expect(redo, 0)) {
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 1

@@ -277,10 +277,10 @@ k_wgrad_split(WsplitArgs a)
     for (int id = id0; id < id1; ++id) {
         const Chunk c = chunk_at(id);
         load(c);
-        // (what is not finite after a chunk will not become so: one accumulator tells where a whole map is not)
-        if (id > id0 && !(__builtin_fabsf(acc[4][0]) < __builtin_inff())) redo = 1;
+        // (what is not finite now will not become so: where a whole map is not, one accumulator tells after the first chunk)
+        if (id == id0 + 1 && !(__builtin_fabsf(acc[4][0]) < __builtin_inff())) redo = 1;
         __syncthreads();                                   // everybody has read the previous chunk (and the cleared LDS is visible)
-        if (id > id0 && redo) break;
+        if (id == id0 + 1 && redo) break;
         store((id - id0) & 1 ? 0x80000000u : 0u);
         __syncthreads();
         if (id > id0) negate();
