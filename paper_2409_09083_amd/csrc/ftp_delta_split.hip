@@ -14,7 +14,8 @@
 // meets a sum that is not finite starts its tile again with the fp32 instruction, so overflow, infinities and NaN come out as an
 // fp32 sum gives them, at about the time the fp32 instruction takes for any values (64 <- 128 channels, 8 images of 76^2, all
 // deltas NaN: a step of 0.67 ms with finite ones took 70 ms while single lanes summed such elements up, 44 of them here).
-// (Deltas whose size is below 2^-110 or so lose low bits: their lower planes fall under the smallest bfloat.)
+// Deltas and filters are split at 2^24 times their size (ftp_split.h): sums above 2^80 go that way too, and no small number
+// loses a bit.
 // The forward pass keeps the fp32 instruction: every other rounding of it moves a few activations across the kink of the leaky
 // ReLU or to another winner of their pool window, and with them single gradient entries by their own size.
 //
@@ -223,7 +224,7 @@ k_delta_split(MfmaConvArgs a)
             for (int e = 0; e < 4; ++e) {
                 uint32_t h[4], m[4], l[4];
 #pragma unroll
-                for (int p = 0; p < 4; ++p) split3(__uint_as_float(xr[u][2 * p][e]), __uint_as_float(xr[u][2 * p + 1][e]), h[p], m[p], l[p]);
+                for (int p = 0; p < 4; ++p) split3(kSplitScale * __uint_as_float(xr[u][2 * p][e]), kSplitScale * __uint_as_float(xr[u][2 * p + 1][e]), h[p], m[p], l[p]);
                 Xl[slot + e] = make_uint4(h[0], h[1], h[2], h[3]);
                 Xl[PLANE + slot + e] = make_uint4(m[0], m[1], m[2], m[3]);
                 Xl[2 * PLANE + slot + e] = make_uint4(l[0], l[1], l[2], l[3]);
@@ -334,7 +335,7 @@ k_delta_split(MfmaConvArgs a)
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[0][t][i] += low[t][i];
+        for (int i = 0; i < 16; ++i) acc[0][t][i] = (acc[0][t][i] + low[t][i]) * kSplitUnscale;
 
     // ---- sums that are not finite: the tile once more, multiplied with the fp32 instruction --------------------------
     {

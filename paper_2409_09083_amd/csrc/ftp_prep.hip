@@ -43,22 +43,14 @@ k_prep_filters(PrepArgs<CAP> a)
     };
     const int c0 = 8 * q + 2 * d;
     if (p.kind == PREP_SPLIT) {
-        // [8 channels][tap][plane][output channel][8 bfloats]; missing reduction channels are zero.  A weight that is not
-        // finite keeps its upper plane only; one that would round to infinity is truncated instead, so the three planes
-        // always add up to the weight.
+        // [8 channels][tap][plane][output channel][8 bfloats]; missing reduction channels are zero.  Weights that are not
+        // finite, or would not be at kSplitScale, give planes that are not: the kernel then turns to the filter itself.
         const float* const w = (const float*)p.w;
         uint32_t o[3] = {0u, 0u, 0u};
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-            const float v = c0 + e < C ? w[index(c0 + e)] : 0.0f;
             uint32_t h, md, lo;
-            split3(v, 0.0f, h, md, lo);
-            if (!(__builtin_fabsf(v) < __builtin_inff())) { md = 0u; lo = 0u; }
-            else if (!(__builtin_fabsf(__uint_as_float(h << 16)) < __builtin_inff())) {
-                h = __float_as_uint(v) >> 16;
-                uint32_t z;
-                split3(v - __uint_as_float(h << 16), 0.0f, md, lo, z);
-            }
+            split3(c0 + e < C ? kSplitScale * w[index(c0 + e)] : 0.0f, 0.0f, h, md, lo);
             o[0] |= (h & 0xFFFFu) << (16 * e); o[1] |= (md & 0xFFFFu) << (16 * e); o[2] |= (lo & 0xFFFFu) << (16 * e);
         }
         uint32_t* const dst = (uint32_t*)p.wt + 4 * (((long long)(q * KK + t) * 3) * Mtot + m) + d;

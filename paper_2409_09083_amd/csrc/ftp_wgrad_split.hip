@@ -31,6 +31,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct WsplitArgs {
     View in, din, mask;
@@ -198,11 +199,11 @@ k_wgrad_split(WsplitArgs a)
         }
         return v;
     };
-    auto store = [&](uint32_t sign) {
-        auto put = [](unsigned char* at, int plane, const v4u& v) {
+    auto store = [&](float scale) {                        // (of the deltas: kSplitScale, negated or not)
+        auto put = [](unsigned char* at, int plane, const v4f& v) {
             uint32_t h[2], m[2], l[2];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) split3(__uint_as_float(v[2 * p]), __uint_as_float(v[2 * p + 1]), h[p], m[p], l[p]);
+            for (int p = 0; p < 2; ++p) split3(v[2 * p], v[2 * p + 1], h[p], m[p], l[p]);
             *(uint2*)at = make_uint2(h[0], h[1]);
             *(uint2*)(at + plane) = make_uint2(m[0], m[1]);
             *(uint2*)(at + 2 * plane) = make_uint2(l[0], l[1]);
@@ -211,13 +212,17 @@ k_wgrad_split(WsplitArgs a)
 #pragma unroll
         for (int k = 0; k < NX; ++k) {
             if (xmask) clear_x(k);
-            put(Xl + (8 * k + xch) * XROW + 8 * xq, XPLANE, xr[k]);
+            v4f v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = kSplitScale * __uint_as_float(xr[k][e]);
+            put(Xl + (8 * k + xch) * XROW + 8 * xq, XPLANE, v);
         }
 #pragma unroll
         for (int k = 0; k < NZ; ++k) {
-            v4u v = spread_z(k);
+            const v4u z = spread_z(k);
+            v4f v;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (zin >> e) & 1u ? v[e] ^ sign : 0u;
+            for (int e = 0; e < 4; ++e) v[e] = (zin >> e) & 1u ? scale * __uint_as_float(z[e]) : 0.0f;
             put(Zl + (16 * k + zch) * ZROW + 8 * zq, ZPLANE, v);
         }
     };
@@ -281,7 +286,7 @@ k_wgrad_split(WsplitArgs a)
         if (id == id0 + 1 && !(__builtin_fabsf(acc[4][0]) < __builtin_inff())) redo = 1;
         __syncthreads();                                   // everybody has read the previous chunk (and the cleared LDS is visible)
         if (id == id0 + 1 && redo) break;
-        store((id - id0) & 1 ? 0x80000000u : 0u);
+        store((id - id0) & 1 ? -kSplitScale : kSplitScale);
         __syncthreads();
         if (id > id0) negate();
         multiply(wsplit_steps(wc, c.ni, c.nr, c.nc));
@@ -295,7 +300,7 @@ k_wgrad_split(WsplitArgs a)
         for (int t = 0; t < 9; ++t) {
             float z = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[t][i], 0.0f, z);
+            for (int i = 0; i < 16; ++i) { acc[t][i] *= kSplitUnscale; z = __builtin_fmaf(acc[t][i], 0.0f, z); }
             bad = bad || !(z == 0.0f);
         }
         if (bad) redo = 1;                                 // (channels beyond the last are zeros: not finite only beside others that are not)
