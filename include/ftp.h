@@ -145,7 +145,9 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
  * and bit-identical y as ftp_forward, but the workspace is a fixed array of FTP_STATIC_WORKSPACE_BYTES that lives in
  * the library's device image (every GPU the library runs on holds its own copy until the process ends).  The call
  * allocates nothing, on the device or through any library.  Plans whose ftp_plan_sizes workspace_bytes exceed the
- * limit are rejected with FTP_ETOOLARGE before anything is launched.  x, weights, biases, y, stream as for
+ * limit are rejected with FTP_ETOOLARGE before anything is launched, unless they exceed it only by the relaid filters of
+ * convolutions with 9, 10, 11 or 17 output channels, which ftp_backward alone uses (6 bytes a weight, output channels
+ * rounded up to 16 or 24).  x, weights, biases, y, stream as for
  * ftp_forward, on the current device.  The array keeps the previous call's contents (the forward pass needs
  * nothing cleared) and is shared by every call on that GPU: calls that overlap on one GPU (two streams, two threads)
  * race and must be serialised by the caller; ftp_backward cannot follow (it needs the caller's own workspace).

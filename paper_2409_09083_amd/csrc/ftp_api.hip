@@ -12,10 +12,7 @@ using namespace ftp;
 
 // Workspace of ftp_forward_static.  On the host this name is only a handle for hipGetSymbolAddress: the device
 // address, one per GPU, is looked up once per device and kept in g_static_ws.
-// (plans are held against FTP_STATIC_WORKSPACE_BYTES without the padding of their split filters, which is at most a third of
-// the filters' areas: the array has room for both)
-constexpr size_t kStaticPadding = 22u * 1024u * 1024u;
-static __device__ __align__(256) unsigned char scratch[FTP_STATIC_WORKSPACE_BYTES + kStaticPadding];
+static __device__ __align__(256) unsigned char scratch[FTP_STATIC_WORKSPACE_BYTES];
 
 namespace {
 
@@ -190,7 +187,7 @@ void prep_pass(const Plan& p, const void* const* weights, void* workspace, bool 
         a.w = weights[u.layer]; a.K = ly.k; a.S = ly.stride; a.Cin = ly.cin; a.Cout = ly.cout;
         a.Hc = p.H[u.layer + 1]; a.Wc = p.W[u.layer + 1]; a.pooled = u.pooled ? 1 : 0; a.bf16 = p.dtype == FTP_BF16;
         if (!mfma_conv_eligible(a, backward)) continue;
-        jobs[n++] = mfma_prep_job(a, (char*)workspace + u.wt_offset, backward);
+        jobs[n++] = mfma_prep_job(a, (char*)workspace + (backward ? u.wt_bwd_offset : u.wt_offset), backward);
         if (n == kPrepJobs) { prep_filters(jobs, n, s); n = 0; }
     }
     if (n) prep_filters(jobs, n, s);
@@ -350,7 +347,7 @@ int ftp_forward_static(const ftp_plan_t* plan, const void* x, const void* const*
                        void* y, void* stream)
 {
     if (!plan) return FTP_EINVAL;
-    if (plan->p.workspace_bytes - plan->p.padding_bytes > (size_t)FTP_STATIC_WORKSPACE_BYTES) return FTP_ETOOLARGE;
+    if (plan->p.static_bytes > (size_t)FTP_STATIC_WORKSPACE_BYTES) return FTP_ETOOLARGE;      // (what the forward pass never touches does not count)
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) { g_last_hip = (int)hipGetLastError(); return FTP_EHIP; }
     if (dev < 0 || dev >= kMaxDevices) return FTP_EINVAL;
@@ -458,7 +455,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             gradient_in_flight = overlap;
             a.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
             if (use_mfma() && mfma_conv_eligible(a, true)) {
-                float* wt = (float*)((char*)workspace + u.wt_offset);
+                float* wt = (float*)((char*)workspace + u.wt_bwd_offset);
                 const RectTab ext = view_extent(p, u.in_delta, u.group, u.bo);
                 rc = timed(plan, FTP_PASS_CONV_BWD_DATA, u.layer, s, [&] {
                     if (!relaid) { prep_pass(p, weights, workspace, true, s); relaid = true; }

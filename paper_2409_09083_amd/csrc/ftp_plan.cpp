@@ -264,16 +264,13 @@ int build_plan(const ftp_layer* layers, int n_layers, int batch, int in_c, int i
     for (int b = 1; b <= L; ++b)
         if (delta[b].kind == BUF_WS && delta[b].per_stack) delta[b].offset = delta[b].offset ? pp1 : pp0;
     // relaid filters for the matrix-core kernels, one area per convolution: every pass writes the form it multiplies with.
-    // fp32 maps keep three planes of bfloats (6 bytes a weight, reduction channels in groups of 8), which fit the 8 bytes a
-    // weight reserved here except where a group is mostly padding (9, 10, 11 or 17 reduction channels): those areas are larger.
+    // The fp32 delta pass keeps three planes of bfloats (6 bytes a weight, reduction channels in groups of 8), which fit the 8
+    // bytes a weight reserved here except where a group is mostly padding (9, 10, 11 or 17 reduction channels): those lie
+    // behind everything else, where the forward pass never looks.
     for (Unit& u : p.units) {
         if (u.kind != UNIT_CONV) continue;
         const ftp_layer& ly = p.layers[u.layer];
-        const size_t area = 2 * align256((size_t)ly.cout * ly.cin * ly.k * ly.k * sizeof(float));
-        const size_t planes = align256(split_filter_bytes(ly.cout, ly.cin, ly.k));
-        const size_t more = dtype == FTP_F32 && planes > area ? planes - area : 0;
-        u.wt_offset = alloc(area + more);
-        p.padding_bytes += more;
+        u.wt_offset = u.wt_bwd_offset = alloc(2 * align256((size_t)ly.cout * ly.cin * ly.k * ly.k * sizeof(float)));
     }
     {
         size_t scratch = 0;
@@ -338,6 +335,13 @@ int build_plan(const ftp_layer* layers, int n_layers, int batch, int in_c, int i
         p.wgrad_scratch_offset = alloc(scratch);
     }
     // (a margin at the end: wide loads of the 16-bit kernels may run a few bytes past the last map)
+    p.static_bytes = std::max<size_t>(ws, 256) + 256;
+    for (Unit& u : p.units) {
+        if (u.kind != UNIT_CONV || dtype != FTP_F32) continue;
+        const ftp_layer& ly = p.layers[u.layer];
+        const size_t planes = split_filter_bytes(ly.cout, ly.cin, ly.k);
+        if (planes > 2 * align256((size_t)ly.cout * ly.cin * ly.k * ly.k * sizeof(float))) u.wt_bwd_offset = alloc(planes);
+    }
     p.workspace_bytes = std::max<size_t>(ws, 256) + 256;
 
     size_t poff = 0;

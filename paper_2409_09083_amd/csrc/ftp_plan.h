@@ -55,7 +55,8 @@ struct Unit {
     float in_slope = 1.0f;                    // leaky slope of the convolution whose output is boundary bi
     size_t param_offset = 0;                  // first filter element in the parameter vector
     size_t bias_offset = 0;
-    size_t wt_offset = 0;                          // relaid filter in the workspace (bytes; each pass writes its own form)
+    size_t wt_offset = 0, wt_bwd_offset = 0;       // relaid filter in the workspace (bytes; each pass writes its own form; the same area
+                                                   // unless the backward pass's form is larger than it)
     int wgrad_shares = 1, wgrad_shares_thin = 1;   // shares of the two matrix-core filter-gradient kernels (the scratch is sized for them)
     int wgrad_shares16 = 1, wgrad_shares_split = 1;   // ... and of the 3x3 kernels for bfloat and for split fp32 maps
 };
@@ -78,7 +79,7 @@ struct Plan {
     std::vector<float> act_slope;
     BufRef dy_scaled;                         // whole map at boundary L: the caller's dy times the derivative (if any)
     size_t workspace_bytes = 0, n_params = 0;
-    size_t padding_bytes = 0;                 // part of workspace_bytes: padding of split filters (at most a third of the filters' areas)
+    size_t static_bytes = 0;                  // workspace_bytes without the areas behind all others that only the backward pass uses
     size_t wgrad_scratch_offset = 0;          // batch shares of one layer's partial gradients (bytes)
     size_t split[4] = {0, 0, 0, 0};
     double useful_macs = 0, executed_macs = 0, halo_bytes[2] = {0, 0};

@@ -218,3 +218,26 @@ def test_per_stack_memory_report(F):
         assert r["filters_and_gradients"] == rows[(1, 1)]["filters_and_gradients"] == 3418976 * 8
         assert 0.7 * n * n <= r["maps_vs_unpartitioned"] <= n * n
     assert rows[(6, 6)]["total"] < rows[(3, 3)]["total"] < rows[(2, 2)]["total"] < rows[(1, 1)]["total"]
+
+
+def test_static_forward_takes_plans_that_exceed_its_workspace_by_backward_areas_only(F):
+    """The fixed workspace of ftp_forward_static has to hold what the forward pass uses: relaid filters of 9 output channels (padded
+    to 16), which lie behind it, do not count.  Without a device the call is refused for its size or fails for want of one."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the call would run")
+    B = F.binding
+    limit = B.FTP_STATIC_WORKSPACE_BYTES
+    extra = 3 * 2 * 64 * 16 * 9                       # three bfloats a weight
+    seen = set()
+    for w in range(14110, 14140):
+        plan = F.ftp_plan((conv(64, 9),), 1, 64, 100, w, 2, 2, [1])
+        size = F.ftp_plan_sizes(plan)["workspace_bytes"]
+        kind = "fits" if size <= limit else "fits without" if size <= limit + extra else "too large"
+        if kind not in seen:
+            with pytest.raises(B.FtpError) as err:
+                B.ftp_forward_static(plan, 256, [256], None, 256, 0)
+            assert (err.value.code == B.FTP_ETOOLARGE) == (kind == "too large"), (w, size, err.value.code)
+        seen.add(kind)
+        F.ftp_plan_destroy(plan)
+    assert seen == {"fits", "fits without", "too large"}
