@@ -41,8 +41,12 @@ constexpr unsigned kRecordsB = 0x7FFFFFFFu;
 // LDS unit of a patch position: swizzled within its block of 8
 __device__ __forceinline__ int bf_slot(int p) { return p ^ ((p >> 3) & 7); }
 
+// Wavefronts per SIMD the register allocation aims at.  (3x3 with four blocks of accumulators: three would mean 168 registers, which
+// spilled 9 to 77 of them: 256 -> 100 channels of 164 x 45 from a caller's buffer with odd strides, 4 images, 74 us against 51 with two)
+constexpr int bf_waves(int K, int blocks) { return blocks <= 2 || (blocks == 4 && K == 1) ? 3 : 2; }
+
 template <int K, int WAVES_M, int MT, int NT, bool POOL_OUT, bool DELTA_IN, int IN>
-__global__ void __launch_bounds__(256, NT * MT <= 4 ? 3 : 2)
+__global__ void __launch_bounds__(256, bf_waves(K, NT * MT))
 k_conv_bf16(MfmaConvArgs a)
 {
     constexpr int WAVES_N = 4 / WAVES_M, BN = 32 * NT * WAVES_N, BM = 32 * MT * WAVES_M;
