@@ -8,9 +8,10 @@
 // permutes for 64 elements) and written to LDS as [8 channels][position][8 bfloats]: an operand is one 16-byte read, where a
 // patch kept channel-major takes eight 16-bit reads and four packs.  Positions are swizzled within blocks of 8 so that the
 // writes (a lane writes 8 consecutive positions) spread over the banks.  The filter fragments go from L2 straight into
-// registers, the five steps of 8 channels ahead; the patch of the next stage is loaded during the last 8 channels of the
-// current one, behind the fragments of these (loads return in order).  A workgroup is four wavefronts of 64 x 128, 64 x 64 or
-// 32 x 128 channels x pixels; two workgroups share a CU: while one transposes or stores, the other multiplies.
+// registers, a group (3x3: the five steps of 8 channels; 1x1: two of 16 channels) or, in the smallest workgroups, a whole stage
+// ahead; the patch of the next stage travels behind the fragments of the current one (loads return in order).  A workgroup is
+// four wavefronts of 64 x 128, 64 x 64, 32 x 64 or 32 x 32 channels x pixels; two workgroups share a CU: while one transposes or
+// stores, the other multiplies.
 // The order of the sums (8 channels, then tap pairs) and the epilogue do not depend on the workgroup's shape.
 // What bounds it: the few wavefronts in flight (two or three workgroups a CU) against the loads' latency, and the epilogue.
 // Against the kernel it replaces (patch channel-major in LDS, filters through LDS): 32 images, 256 -> 512
@@ -43,7 +44,7 @@ __device__ __forceinline__ int bf_slot(int p) { return p ^ ((p >> 3) & 7); }
 
 // Wavefronts per SIMD the register allocation aims at.  (3x3 with four blocks of accumulators: three would mean 168 registers, which
 // spilled 9 to 77 of them: 256 -> 100 channels of 164 x 45 from a caller's buffer with odd strides, 4 images, 74 us against 51 with two)
-constexpr int bf_waves(int K, int blocks) { return blocks <= 2 || (blocks == 4 && K == 1) ? 3 : 2; }
+constexpr int bf_waves(int K, int blocks) { return blocks == 2 || (blocks == 4 && K == 1) ? 3 : 2; }
 
 template <int K, int WAVES_M, int MT, int NT, bool POOL_OUT, bool DELTA_IN, int IN>
 __global__ void __launch_bounds__(256, bf_waves(K, NT * MT))
@@ -56,7 +57,10 @@ k_conv_bf16(MfmaConvArgs a)
     static_assert(OCT * UPO == 256, "one unit a thread");
     constexpr int STEPS = K == 3 ? 5 : 1;              // matrix-core steps of one (3x3) or two (1x1) groups of 8 channels
     constexpr int GROUPS = K == 3 ? OCT : OCT / 2;     // such groups of a stage
-    constexpr int RING = K == 3 ? 5 : 2;              // steps of filter fragments in registers
+    // groups whose filter fragments are in registers (a group of the smallest workgroup takes a quarter of the time of a load from L2)
+    constexpr int DEEP = NT * MT == 1 ? 4 : K == 3 ? 1 : 2;
+    constexpr int TURN = DEEP == 2 ? 1 : DEEP;         // groups a turn of the multiply loop
+    static_assert(GROUPS % TURN == 0, "a stage begins with the ring's first group");
     __shared__ __attribute__((aligned(16))) uint4 Xl[OCT * XMAX];      // [8 channels][position (swizzled)]
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -293,10 +297,12 @@ k_conv_bf16(MfmaConvArgs a)
     constexpr int CK = 8 * OCT;
     const int nst = (a.C + CK - 1) / CK;
     const int groups = K == 3 ? C8 : (C8 + 1) / 2;     // of the whole reduction
-    uint4 av[RING][MT];
+    uint4 av[DEEP][STEPS][MT];
     issue_x(0);
 #pragma unroll
-    for (int s = 0; s < RING; ++s) load_a(av[s], K == 3 ? 0 : 2 * (s < groups ? s : groups - 1), K == 3 ? s : 0);
+    for (int r = 0; r < DEEP; ++r)
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) load_a(av[r][s], (K == 3 ? 1 : 2) * (r < groups ? r : groups - 1), s);
     for (int st = 0; st < nst; ++st) {
         __syncthreads();                               // the previous stage has been read
         store_x(st * CK);
@@ -306,13 +312,14 @@ k_conv_bf16(MfmaConvArgs a)
 #pragma unroll
         for (int t = 0; t < NT; ++t) bv[t] = read_b(t, 0, 0, PW);
         // one group (8 channels, 1x1: 16); a step's operands replace those of the step before as soon as they are used, its
-        // filter fragments those of the next group (1x1: RING groups on; behind the last one once more the same, unused)
-        auto group = [&](int gr, bool last) {
+        // filter fragments those of DEEP groups on (behind the last one once more the same, unused)
+        auto group = [&](int gr, int r, bool last) {
             int pw = PW;
             asm volatile("" : "+s"(pw));
+            const int next = g0 + gr + DEEP < groups ? g0 + gr + DEEP : groups - 1;
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
-                uint4 (&w)[MT] = av[K == 3 ? s : 0];
+                uint4 (&w)[MT] = av[r][s];                 // (TURN = 1: the ring is shifted)
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
 #pragma unroll
@@ -321,22 +328,26 @@ k_conv_bf16(MfmaConvArgs a)
                     if (s + 1 < STEPS) bv[t] = read_b(t, gr, s + 1, pw);
                     else if (!last) bv[t] = read_b(t, gr + 1, 0, pw);
                 }
-                if constexpr (K == 3) {
-                    load_a(w, last && st + 1 == nst ? g0 + gr : g0 + gr + 1, s);
-                } else {
+                if constexpr (DEEP == 2) {
 #pragma unroll
-                    for (int r = 0; r + 1 < RING; ++r)
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) av[r][mt] = av[r + 1][mt];
-                    const int next = g0 + gr + RING < groups ? g0 + gr + RING : groups - 1;
-                    load_a(av[RING - 1], 2 * next, 0);
+                    for (int mt = 0; mt < MT; ++mt) w[mt] = av[1][s][mt];
                 }
+                load_a(av[TURN == 1 ? DEEP - 1 : r][s], (K == 3 ? 1 : 2) * next, s);
             }
         };
+        int gr = 0;
 #pragma unroll 1
-        for (int gr = 0; gr + 1 < ng; ++gr) group(gr, false);
+        for (; gr + TURN < ng; gr += TURN) {
+#pragma unroll
+            for (int r = 0; r < TURN; ++r) group(gr + r, r, false);
+        }
+        // (loads return in order: the patch travels behind the fragments of the groups left)
         if (st + 1 < nst) issue_x((st + 1) * CK);
-        group(ng - 1, true);
+#pragma unroll
+        for (int r = 0; r < TURN; ++r) {
+            if (TURN == 1) group(ng - 1, 0, true);
+            else if (gr + r < ng) group(gr + r, r, gr + r + 1 == ng);
+        }
     }
     conv_epilogue<bf16_t, K, S, WAVES_M, MT, POOL_OUT, DELTA_IN>(a, g, acc, (float*)Xl, m0, x0, x1, y0, stack, ti, tj);
 }
@@ -352,12 +363,12 @@ struct BfShape { int WM, MT, NT; };                     // wavefronts along the 
 template <int K, bool POOL_OUT, bool DELTA_IN, int IN>
 void launch_bf(const MfmaConvArgs& a, BfShape sh, dim3 grid, hipStream_t s)
 {
-    static char label[5][104];                   // (every write of an entry stores the same text: entries depend on the template and the shape only)
-    const int v = sh.MT == 1 ? 4 : (sh.WM == 2 ? 0 : 2) + (sh.NT == 4 ? 0 : 1);
+    static char label[6][104];                   // (every write of an entry stores the same text: entries depend on the template and the shape only)
+    const int v = sh.MT == 1 ? 3 + sh.NT : (sh.WM == 2 ? 0 : 2) + (sh.NT == 4 ? 0 : 1);
     std::snprintf(label[v], sizeof(label[v]), "k_conv_bf16<%d, %d, %d, %d, %s, %s, %d>", K, sh.WM, sh.MT, sh.NT, POOL_OUT ? "true" : "false", DELTA_IN ? "true" : "false", IN);
     g_kernel_label = label[v];
 #define FTP_BF(WM, MT, NT) hipLaunchKernelGGL((k_conv_bf16<K, WM, MT, NT, POOL_OUT, DELTA_IN, IN>), grid, dim3(256), 0, s, a)
-    if (sh.MT == 1) FTP_BF(1, 1, 2);
+    if (sh.MT == 1) { if (sh.NT == 2) FTP_BF(1, 1, 2); else FTP_BF(1, 1, 1); }
     else if (sh.WM == 2) { if (sh.NT == 4) FTP_BF(2, 2, 4); else FTP_BF(2, 2, 2); }
     else { if (sh.NT == 4) FTP_BF(1, 2, 4); else FTP_BF(1, 2, 2); }
 #undef FTP_BF
@@ -384,6 +395,7 @@ BfShape choose_bf_shape(const MfmaConvArgs& a, const ConvArgs& c, TileChoice* tc
     int rws[kTabGrid], rhs[kTabGrid];                   // widths / heights of the stacks' rectangles per tile column / row
     for (int j = 0; j < c.M; ++j) rws[j] = a.rect.x1[j] - a.rect.x0[j] + 1;
     for (int i = 0; i < c.N; ++i) rhs[i] = a.rect.y1[i] - a.rect.y0[i] + 1;
+    long long best_wgs = 0;
     auto consider = [&](BfShape sh) {
         const int bm = 32 * sh.MT * sh.WM, BN = 32 * sh.NT * (4 / sh.WM), max_pos = conv_bf_positions(K, BN);
         const TileChoice tc = choose_tile(rws, rhs, c.N, c.M, c.batch, POOL_OUT ? BN / 4 : BN, POOL_OUT ? 2 : 1, K / 2, max_pos, 8, IN == BF_POOL);
@@ -398,13 +410,17 @@ BfShape choose_bf_shape(const MfmaConvArgs& a, const ConvArgs& c, TileChoice* tc
         const double mul = (double)sh.MT * sh.NT * 32.0 * (K == 3 ? 5.0 * ((a.C + 7) / 8) : (a.C + 15) / 16.0);
         const double work = mul * (sh.MT == 2 && sh.NT == 4 ? 1.0 : 1.4) + 1200.0 * nst + 14000.0 * (sh.MT * sh.NT) / 8.0 + 4000.0;
         const double cost = rounds * work;
-        if (best.WM == 0 || cost < best_cost) { best = sh; best_cost = cost; *tc_out = tc; }
+        if (best.WM == 0 || cost < best_cost) { best = sh; best_cost = cost; best_wgs = wgs; *tc_out = tc; }
     };
     if (a.Mtot > 32) {
         if (a.Mtot > 64) { consider({2, 2, 4}); consider({2, 2, 2}); }
         consider({1, 2, 4}); consider({1, 2, 2});
     }
     if (a.Mtot <= 32 || c.batch * c.N * c.M < 64) consider({1, 1, 2});
+    // A launch that does not fill the CUs is bound by one workgroup's chain: half the pixels a workgroup,
+    // with a ring of filter fragments as deep as a stage (us, before: 32 x 256): 3x3, 128 -> 128 at 26^2 25.5 -> 20.3, 256 -> 256 at 19^2
+    // 38 -> 31; 1x1, 256 -> 256 at 13^2 22 -> 18.
+    if (best_wgs < 512) consider({1, 1, 1});
     return best;
 }
 
