@@ -434,16 +434,17 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 gradient(a, scratch, aux);
                 if (a.has_bias) bias_grad(a, aux);
             };
-            if (use_mfma() && thin_wgrad_eligible(a)) {
+            const bool cores = use_mfma() && wgrad_bias_pays(a);
+            if (cores && thin_wgrad_eligible(a)) {
                 shares = a.wgrad_shares_thin;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(thin_wgrad); });
-            } else if (use_mfma() && plain_geometry(a) && u.in_delta.kind == BUF_WS && wgrad16_eligible(a)) {
+            } else if (cores && plain_geometry(a) && u.in_delta.kind == BUF_WS && wgrad16_eligible(a)) {
                 shares = a.wgrad_shares16;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad16); });
-            } else if (use_mfma() && wgrad_split_eligible(a)) {
+            } else if (cores && wgrad_split_eligible(a)) {
                 shares = a.wgrad_shares_split;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad_split); });
-            } else if (use_mfma() && mfma_wgrad_eligible(a)) {
+            } else if (cores && mfma_wgrad_eligible(a)) {
                 shares = a.wgrad_shares;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(mfma_wgrad); });
             } else {

@@ -26,3 +26,32 @@ _NETS = {
 def test_gradients(oracle, net, dtype, bias, grid):
     layers, h, w = _NETS[net]
     P.check_case(oracle, Config("routes_" + net, 3, layers[0].cin, h, w, layers, grid, (len(layers),), dtype), has_bias=bias)
+
+
+def _kernels(layers, batch, h, w, grid, dtype, passes, has_bias=False):
+    """Kernels that the first layer's launches of these passes ran (a step on random values)."""
+    import torch
+    from paper_2409_09083_amd import binding as B
+    from paper_2409_09083_amd.harness import Session
+    s = Session([P._BiasLayer(ly) for ly in layers] if has_bias else layers, batch, layers[0].cin, h, w, grid, (len(layers),), dtype=dtype)
+    s.x.uniform_(0, 1)
+    s.dy.normal_()
+    s.weights = [torch.randn((ly.cout, ly.cin, ly.k, ly.k), device="cuda").to(s.x.dtype) / 20 for ly in layers]
+    s.biases = [torch.zeros(ly.cout, device="cuda").to(s.x.dtype) for ly in layers] if has_bias else None
+    B.ftp_profile(s.plan, 1)
+    s.step()
+    torch.cuda.synchronize()
+    names = {r["kernel"].split("<")[0] for r in B.ftp_profile_read(s.plan) if r["pass"] in passes and r["layer"] == 0}
+    s.close()
+    return names
+
+
+@pytest.mark.parametrize("layer,small,large", [
+    (conv(16, 32), (1, 52, (2, 2)), (8, 52, (1, 1))), (conv(64, 64), (1, 13, (1, 1)), (1, 26, (2, 2))), (conv(32, 32, 1), (8, 13, (1, 1)), (16, 104, (1, 1))),
+    (conv(3, 16), (1, 52, (2, 2)), (8, 52, (1, 1))), (conv(16, 32, 5), (1, 13, (1, 1)), (8, 52, (1, 1)))])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_small_gradients_with_a_bias_stay_one_launch(layer, small, large, dtype):
+    """(sizes at which either kernel is clearly the faster one)"""
+    wgrad = lambda size: _kernels((layer,), size[0], size[1], size[1], size[2], dtype, ("wgrad", "wgrad_sum"), has_bias=True)
+    assert wgrad(small) == {"k_wgrad_direct"}
+    assert "k_wgrad_direct" not in wgrad(large)
