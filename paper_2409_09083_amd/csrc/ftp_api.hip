@@ -185,7 +185,7 @@ void prep_pass(const Plan& p, const void* const* weights, void* workspace, bool 
         const ftp_layer& ly = p.layers[u.layer];
         ConvArgs a;                                  // (what the two questions below look at)
         a.w = weights[u.layer]; a.K = ly.k; a.S = ly.stride; a.Cin = ly.cin; a.Cout = ly.cout;
-        a.Hc = p.H[u.layer + 1]; a.Wc = p.W[u.layer + 1]; a.pooled = u.pooled ? 1 : 0; a.bf16 = p.dtype == FTP_BF16;
+        a.Hc = p.H[u.layer + 1]; a.Wc = p.W[u.layer + 1]; a.batch = p.batch; a.pooled = u.pooled ? 1 : 0; a.bf16 = p.dtype == FTP_BF16;
         if (!mfma_conv_eligible(a, backward)) continue;
         jobs[n++] = mfma_prep_job(a, (char*)workspace + (backward ? u.wt_bwd_offset : u.wt_offset), backward);
         if (n == kPrepJobs) { prep_filters(jobs, n, s); n = 0; }

@@ -55,3 +55,14 @@ def test_small_gradients_with_a_bias_stay_one_launch(layer, small, large, dtype)
     wgrad = lambda size: _kernels((layer,), size[0], size[1], size[1], size[2], dtype, ("wgrad", "wgrad_sum"), has_bias=True)
     assert wgrad(small) == {"k_wgrad_direct"}
     assert "k_wgrad_direct" not in wgrad(large)
+
+
+@pytest.mark.parametrize("layer,size,dtype,direct", [
+    (conv(8, 16, 1), (16, 128, (2, 2)), "f32", True), (conv(8, 32, 1), (16, 128, (2, 2)), "f32", False), (conv(8, 8, 1), (16, 128, (2, 2)), "bf16", True),
+    (conv(8, 8), (16, 128, (2, 2)), "f32", False), (conv(8, 16), (1, 32, (1, 1)), "f32", False),
+    (conv(8, 8, 3, stride=2), (16, 128, (2, 2)), "f32", True), (conv(12, 16, 3, stride=2), (16, 128, (2, 2)), "f32", False), (conv(8, 12, 3, stride=2), (1, 128, (2, 2)), "f32", False),
+    (conv(8, 16, 1, stride=2), (1, 32, (1, 1)), "f32", True), (conv(8, 48, 1, stride=2), (1, 32, (1, 1)), "f32", False)])
+def test_narrow_deltas_take_the_faster_kernel(layer, size, dtype, direct):
+    batch, hw, grid = size
+    names = _kernels((layer,), batch, hw, hw, grid, dtype, ("conv_bwd_data",))
+    assert ("k_conv_bwd_data_direct" in names) == direct, names
