@@ -385,7 +385,7 @@ bool offsets_fit(const MfmaConvArgs& a, int max_img)
     return (K == 3 ? 20.0 : 2.0) * ((double)a.C + 8.0) * (double)a.Mtot < 2.0e9;
 }
 
-// The workgroup shape whose launch finishes first: (full rounds + the last round's depth per CU) x work of one workgroup.
+// The workgroup shape whose launch finishes first: the time of one workgroup, and what every further one of its CU adds.
 // Measured as {WM, MT, NT} on 32 images (ms): 64 -> 128 at 152^2 {2,2,4} 0.244, {2,2,2} 0.261, {1,2,4} 0.278; 256 -> 512 at 38^2 {2,2,4} 0.434, {2,2,2} 0.289,
 // {1,2,4} 0.469; 32 -> 64 with a pool {1,2,4} 0.393, {1,2,2} 0.443, {1,1,2} 0.419; 32 <- 64 through a pool {1,1,2} 0.322, {1,2,4} 0.406.
 template <int K, bool POOL_OUT, bool DELTA_IN, int IN>
@@ -404,22 +404,23 @@ BfShape choose_bf_shape(const MfmaConvArgs& a, const ConvArgs& c, TileChoice* tc
         for (int i = 0; i < c.N; ++i)
             for (int j = 0; j < c.M; ++j) wgs += tile_slots(tc, rws[j], rhs[i], c.batch);
         wgs *= (a.Mtot + bm - 1) / bm;
-        const double per_cu = 2.0, rounds = (double)(wgs / 512) * per_cu + (double)((wgs % 512 + 255) / 256);
-        // cycles: matrix instructions, collecting and transposing the patch, epilogue and set-up
+        // cycles of one workgroup: matrix instructions, collecting and transposing the patches, epilogue and set-up.  A lone one waits
+        // for every patch, those of a CU hide part of that from each other
         const int ck = 8 * conv_bf_octets(K, BN), nst = (a.C + ck - 1) / ck;
         const double mul = (double)sh.MT * sh.NT * 32.0 * (K == 3 ? 5.0 * ((a.C + 7) / 8) : (a.C + 15) / 16.0);
-        const double work = mul * (sh.MT == 2 && sh.NT == 4 ? 1.0 : 1.4) + 1200.0 * nst + 14000.0 * (sh.MT * sh.NT) / 8.0 + 4000.0;
-        const double cost = rounds * work;
+        const double fixed = mul * (sh.MT == 2 && sh.NT == 4 ? 1.0 : 1.4) + 14000.0 * (sh.MT * sh.NT) / 8.0 + 4000.0;
+        const double per_cu = std::max(1.0, (double)wgs / 256.0);
+        const double cost = fixed + 3000.0 * nst + (per_cu - 1.0) * (fixed + (K == 3 ? 1200.0 : 2400.0) * nst);
         if (best.WM == 0 || cost < best_cost) { best = sh; best_cost = cost; best_wgs = wgs; *tc_out = tc; }
     };
     if (a.Mtot > 32) {
         if (a.Mtot > 64) { consider({2, 2, 4}); consider({2, 2, 2}); }
         consider({1, 2, 4}); consider({1, 2, 2});
     }
-    if (a.Mtot <= 32 || c.batch * c.N * c.M < 64) consider({1, 1, 2});
-    // A launch that does not fill the CUs is bound by one workgroup's chain: half the pixels a workgroup,
-    // with a ring of filter fragments as deep as a stage (us, before: 32 x 256): 3x3, 128 -> 128 at 26^2 25.5 -> 20.3, 256 -> 256 at 19^2
-    // 38 -> 31; 1x1, 256 -> 256 at 13^2 22 -> 18.
+    // The smaller workgroups collect the patch once per 32 channels: worth it for narrow layers and where the others are few.  The
+    // smallest has half the pixels and a ring of filter fragments as deep as a stage (us, {2,2,2} or {1,2,2} / {1,1,2} / {1,1,1}, 3x3: 256 -> 128,
+    // 16 images of 44 x 33, 41 / 37 / 49; 128 -> 64, 8 of 78 x 64, 25 / 22 / 21; 64 -> 64, 4 of 152^2, 23 / 27 / 28; 128 -> 128, one of 26^2, 22 / 17 / 12).
+    if (a.Mtot <= 32 || best_wgs < 1024) consider({1, 1, 2});
     if (best_wgs < 512) consider({1, 1, 1});
     return best;
 }
