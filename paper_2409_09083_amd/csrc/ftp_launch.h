@@ -139,28 +139,34 @@ struct MfmaWgradArgs {
 // The matrix-core filter-gradient kernels multiply blocks of 32 or 64 output by 32 or 64 input channels; narrower layers pay for
 // whole blocks and are worth it once there is something to multiply: the direct kernel reaches 1.8e12 multiply-adds a second
 // (208 -> 16 channels, 17 images of 40 x 148: 1.67 ms), so below about 4e7 of them it is done before a matrix-core kernel and
-// its share sum have started (8 -> 16 channels at 32 x 32: 10 us).
+// its share sum have started (8 -> 16 channels at 32 x 32: 10 us).  With stride 2, whose deltas have zeros in between, blocks
+// filled to less than an eighth do not pay (48 -> 3 channels, 3x3, 16 images of 128 x 65: 35 us direct, 98).
 inline bool wgrad_wide_enough(const ConvArgs& c)
 {
     if (c.Cout >= 32 && c.Cin >= 16) return true;
-    return c.Cin > 4 && (double)c.batch * c.Hc * c.Wc * c.Cout * c.Cin * c.K * c.K >= 4.0e7;
+    if (c.Cin <= 4 || (double)c.batch * c.Hc * c.Wc * c.Cout * c.Cin * c.K * c.K < 4.0e7) return false;
+    const int bco = c.Cout > 32 ? (c.Cout + 63) & ~63 : 32, bci = c.Cin > 32 ? (c.Cin + 63) & ~63 : 32;
+    return c.S == 1 || 8.0 * c.Cout * c.Cin >= (double)bco * bci;
 }
 // Layers with a bias: the direct kernel sums it up in the same launch, the matrix-core kernels leave it to one more, and usually
-// another for their shares.  They are worth that (about 20 us; 10 for wide 1x1 layers; 60 for 1x1 layers of 5 to 32 input
-// channels, whose chunks are serial in a few workgroups) where the direct kernel takes longer: a workgroup of it walks a stack's
-// pixels, every pair of channels costs a start, and all of them together reach 1.7e12 multiply-adds a second (within a third
-// of it over 14 layers and 7 sizes; us, direct / matrix cores: 16 -> 32 channels 3x3, 52^2 18 / 26, 8 images 171 / 74; 64 -> 64, 13^2
-// 20 / 27, 26^2 in 4 tiles 54 / 28; 32 -> 32 1x1, 8 images of 13^2 9 / 47; 3 -> 16, 52^2 12 / 20).
+// another for their shares.  They are worth that (about 20 us; 10 for wide 1x1 layers) where the direct kernel takes longer: a
+// workgroup of it walks a stack's pixels, every pair of channels costs a start, and all of them together reach 1.7e12
+// multiply-adds a second, 1x1 0.6e12 (within a third of it over 14 layers and 7 sizes; us, direct / matrix cores: 16 -> 32
+// channels 3x3, 52^2 18 / 26, 8 images 171 / 74; 64 -> 64, 13^2 20 / 27, 26^2 in 4 tiles 54 / 28; 3 -> 16, 52^2 12 / 20).  The kernel for
+// 1x1 layers of up to 32 input channels starts at 36 us and walks the pixels as slowly as the direct one: it is for many pairs
+// (32 -> 32, 8 images of 13^2 9 / 47, of 52^2 59 / 65, 16 of 104^2 400 / 331; 24 -> 256, 150 x 44 90 / 40).
 inline bool wgrad_bias_pays(const ConvArgs& c)
 {
     if (!c.has_bias) return true;
     int rw = 0, rh = 0;                             // the largest owned rectangle
     for (int j = 0; j < c.M; ++j) rw = rw > c.rect.x1[j] - c.rect.x0[j] + 1 ? rw : c.rect.x1[j] - c.rect.x0[j] + 1;
     for (int i = 0; i < c.N; ++i) rh = rh > c.rect.y1[i] - c.rect.y0[i] + 1 ? rh : c.rect.y1[i] - c.rect.y0[i] + 1;
-    const double taps = c.K * c.K, pairs = (double)c.Cout * c.Cin;
-    const double walk = (double)rw * rh * c.batch * (1.7e-3 + 0.56e-3 * taps), start = pairs * c.N * c.M * (0.5e-3 + 0.25e-3 * taps);
-    const double rate = pairs * taps * c.batch * c.Hc * c.Wc / 1.7e6, least = c.K > 1 || c.Cin <= 4 ? 20.0 : c.Cin <= 32 ? 60.0 : 10.0;
-    return walk >= least || start >= least || rate >= least;
+    const double taps = c.K * c.K, pairs = (double)c.Cout * c.Cin, px = (double)rw * rh * c.batch;
+    const double walk = px * (1.2e-3 + 0.6e-3 * taps), start = pairs * c.N * c.M * (0.5e-3 + 0.25e-3 * taps);
+    const double rate = pairs * taps * c.batch * c.Hc * c.Wc / (c.K > 1 ? 1.7e6 : 0.62e6), work = rate > start ? rate : start;
+    if (c.K > 1) return walk >= 20.0 || work >= 20.0;
+    const double least = c.Cin <= 32 ? 29.0 + 1.7e-3 * px : 10.0;
+    return walk * walk + work * work >= least * least;
 }
 bool mfma_wgrad_eligible(const ConvArgs& a);
 // bfloat 3x3 stride-1 filter gradient with packed staging (ftp_wgrad16.hip)

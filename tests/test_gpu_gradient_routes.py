@@ -66,3 +66,9 @@ def test_narrow_deltas_take_the_faster_kernel(layer, size, dtype, direct):
     batch, hw, grid = size
     names = _kernels((layer,), batch, hw, hw, grid, dtype, ("conv_bwd_data",))
     assert ("k_conv_bwd_data_direct" in names) == direct, names
+
+
+@pytest.mark.parametrize("layer,size,direct", [(conv(48, 3, 3, stride=2), (16, 128, (4, 3)), True), (conv(48, 24, 3, stride=2), (16, 128, (4, 3)), False), (conv(208, 16), (4, 104, (1, 1)), False)])
+def test_narrow_gradients_take_the_faster_kernel(layer, size, direct):
+    batch, hw, grid = size
+    assert ("k_wgrad_direct" in _kernels((layer,), batch, hw, hw, grid, "f32", ("wgrad",))) == direct
