@@ -13,7 +13,8 @@
 // four wavefronts of 64 x 128, 64 x 64, 32 x 64 or 32 x 32 channels x pixels; two workgroups share a CU: while one transposes or
 // stores, the other multiplies.
 // The order of the sums (8 channels, then tap pairs) and the epilogue do not depend on the workgroup's shape.
-// What bounds it: the few wavefronts in flight (two or three workgroups a CU) against the loads' latency, and the epilogue.
+// What bounds it: re-fetched lines of HBM in the 1x1 deltas and the deltas through a pool (4.5 to 4.9 TB/s: rows of a map are cut
+// among stacks on different XCDs), else the few wavefronts in flight against the loads' latency, and the epilogue.
 // Against the kernel it replaces (patch channel-major in LDS, filters through LDS): 32 images, 256 -> 512
 // channels at 38^2 0.368 -> 0.289 ms; 64 -> 128 at 152^2 0.274 -> 0.244 ms; 32 -> 64 with a pool, the caller's input, 304^2: 0.487 -> 0.458 ms, delta through the pool 0.517 -> 0.322 ms; 64 <- 128 channels 0.241 -> 0.175 ms.
 // MFMA lane layout: A[m = lane%32][k = 8*(lane/32) + j], B[k = 8*(lane/32) + j][n = lane%32], j < 8,

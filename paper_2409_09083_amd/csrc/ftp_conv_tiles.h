@@ -10,11 +10,9 @@ namespace ftp {
 FTP_HD constexpr bool conv_dl_quads(size_t elem, bool pool_in, bool up_in) { return elem == 4 && !pool_in && !up_in; }
 // (a multiple of 256; quads pad every patch row to a multiple of 4 positions, which costs the narrow rectangles of deep
 // layers up to a fifth more positions: their 128-pixel tiles get the room of the 256-pixel ones)
-// (packed bfloats: twice the positions in the same bytes, in blocks of 512)
-FTP_HD constexpr int conv_dl_max_positions(int K, int BN, bool strided_fwd, bool quad, bool packed = false)          // patch positions in LDS
+FTP_HD constexpr int conv_dl_max_positions(int K, int BN, bool strided_fwd, bool quad)          // patch positions in LDS
 {
-    return packed ? (K == 3 && BN == 256 ? 1024 : 512)
-                  : strided_fwd ? 768 : K >= 5 ? (BN == 256 ? 768 : 512) : K == 1 ? 256 : (BN == 256 || quad ? 512 : 256);
+    return strided_fwd ? 768 : K >= 5 ? (BN == 256 ? 768 : 512) : K == 1 ? 256 : (BN == 256 || quad ? 512 : 256);
 }
 
 // The fp32 delta kernel on the bfloat matrix cores (ftp_delta_split.hip): reduction channels per stage, the same for every workgroup

@@ -3,8 +3,8 @@
 //
 // Why: v_mfma_f32_32x32x2_f32 multiplies 2 reduction elements in 64 cycles, v_mfma_f32_32x32x16_bf16 16 in 32 - sixteen times
 // the rate.  An fp32 number is the sum of three bfloats to its last bit (x = h + m + l: 8 significant bits each, nearest,
-// so |m| <= 2^-9 |x|, |l| <= 2^-18 |x|), a product of two bfloats is exact in fp32 and the matrix cores add in fp32, so
-//   x w = h h' + (h m' + m h') + (h l' + m m' + l h')   + terms below 2^-26 |x w|
+// so |m| <= 2^-8 |x|, |l| <= 2^-17 |x|), a product of two bfloats is exact in fp32 and the matrix cores add in fp32, so
+//   x w = h h' + (h m' + m h') + (h l' + m m' + l h')   + terms of at most 2^-24 |x w|
 // in six matrix instructions costs 3/8 of the fp32 instruction's time, at an error no larger than that of an fp32
 // product's own rounding.  The five small products have accumulators of their own, added to the main ones at the end: the
 // matrix cores cut what is far below the largest addend towards minus infinity, and with one accumulator for all six that
@@ -30,9 +30,10 @@
 // The patch of the next stage is loaded during the last step of the current one (any earlier and the filter loads, which
 // return in order, would wait for it).
 // Measured (64 images, 608^2, 6 x 6 tiles, useful TFLOP/s, fp32 instruction -> this): 64 <- 128 channels at 152^2 133 -> 223,
-// 256 <- 512 at 38^2 131 -> 219, through pools 86-109 -> 162-202; 1x1 layers 35-71 -> 38-74 (bound by their loads).  What
-// bounds it: the matrix cores (six products at 1.3 of the 1.25 PFLOP/s a large library product reaches), then the patch
-// collection through pool winners.
+// 256 <- 512 at 38^2 131 -> 219, through pools 86-109 -> 162-202; 1x1 layers 35-71 -> 38-74 (bound by loading and splitting
+// their patches; launches that do not fill the chip are 2 to 4 us longer than the fp32 instruction's).  What bounds the others:
+// the matrix cores (six products at 1.3 PFLOP/s, where a large library product reaches 1.25 to 1.35 with the sizes), then
+// the patch collection through pool winners.
 // MFMA lane layout: A[m = lane%32][k = 8*(lane/32) + j], B[k = 8*(lane/32) + j][n = lane%32], j < 8,
 // D[m = 8*(i/4) + 4*(lane/32) + i%4][n = lane%32] for accumulator register i of 16.
 #include "ftp_conv_epilogue.h"
@@ -48,7 +49,7 @@ namespace ftp {
 //           receives its window's delta if it is the window's winner for that channel.  Patch rows start at an even column, so
 //           a quad is two pixels of each of two windows
 //   UP      of a strided convolution, as the stride-1 one over deltas with zeros in between, element by element (layers the
-//           parity-class kernel declines: offsets beyond its 32 bits)
+//           parity-class kernel declines: 8 or 12 produced channels, offsets beyond its 32 bits)
 enum SplitIn { IN_WIDE = 0, IN_POOL = 1, IN_UP = 2 };
 
 constexpr unsigned kOobS = 0x80000000u;               // beyond the records of every buffer resource below: reads as zero

@@ -19,7 +19,10 @@
 // 76^2, all deltas NaN: a step of 0.67 ms with finite ones took 26 ms while single lanes summed such elements up, 1.0 here).
 // Measured (64 images, 608^2, 6 x 6 tiles, useful TFLOP/s, fp32 instruction -> this): 128 x 64 at 152^2 108 -> 168, 256 x 128 at
 // 76^2 107 -> 167, 512 x 256 at 38^2 103 -> 150, 64 x 32 behind a pool 88 -> 138.  What bounds it: the matrix cores, at 225
-// TFLOP/s on the positions they multiply (six products at 1.35 PFLOP/s), of which rows of 25, 13 or 6 pixels fill 75-81 %.
+// TFLOP/s on the positions they multiply (six products at 1.35 PFLOP/s), of which rows of 25, 13 or 6 pixels fill 75-81 %; the
+// 64 x 32 pooled layer, whose chunks hold two of 51 rows and load four, HBM: column blocks run fastest, so the rows of a chunk come
+// back only after a whole row of blocks, and a launch fetches 10.4 GB (the fp32 instruction's kernel 2.2; matrix cores 41 % busy,
+// 55 % in the others).
 #include "ftp_device.h"
 #include "ftp_launch.h"
 #include "ftp_split.h"

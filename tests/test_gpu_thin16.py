@@ -36,3 +36,30 @@ def test_non_finite_deltas_reach_only_the_pixels_with_a_tap():
     # (a 16-bit map's rounding, twice)
     assert float(((got - ref).abs() / (ref.abs() + 1))[fin].max()) < 2.0 ** -7
     s.close()
+
+
+@pytest.mark.parametrize("cin,cout", [(1, 5), (2, 33), (3, 32)])
+@pytest.mark.parametrize("batch,h,w,grid", [(2, 16, 32, (1, 1)), (3, 44, 100, (1, 1)), (4, 128, 192, (2, 1))])
+def test_filter_gradient_against_64_bits(cin, cout, batch, h, w, grid):
+    """The gradient is an fp32 sum of exact products: nothing of it is rounded to 16 bits."""
+    import torch
+    from paper_2409_09083_amd import binding as B
+    from paper_2409_09083_amd.harness import Session
+    g = torch.Generator().manual_seed(6)
+    s = Session((conv(cin, cout, slope=1.0), pool(cout)), batch, cin, h, w, grid, (2,), dtype="bf16")
+    x = torch.rand(s.in_shape, generator=g).bfloat16()
+    wt = (torch.randn((cout, cin, 3, 3), generator=g) / 5).bfloat16()
+    dy = torch.randn(s.out_shape, generator=g).bfloat16()
+    s.load(x=x.float().numpy(), weights=[wt.float().numpy(), None], dy=dy.float().numpy())
+    s.step()
+    torch.cuda.synchronize()
+    # (the winners as the forward pass decided them)
+    win = (torch.from_numpy(s.get_boundary(2, B.FTP_BUF_MASK)).long() >> 1) & 3
+    dz = torch.zeros((batch, cout, h, w), dtype=torch.float64)
+    for q in range(4):
+        dz[:, :, q >> 1::2, q & 1::2] = torch.where(win == q, dy.double(), 0.0)
+    ref = torch.nn.grad.conv2d_weight(x.double(), wt.shape, dz, padding=1)
+    err = float((s.wgrad.cpu().double().reshape(ref.shape) - ref).norm() / ref.norm())
+    # (one rounding of 2^-24 per 16 pixels summed at most, all of one sign; random ones leave 1e-7 or so)
+    assert err < 1e-6, err
+    s.close()

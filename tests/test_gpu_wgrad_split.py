@@ -31,10 +31,11 @@ def test_against_64_bits(cin, cout, batch, h, w, grid, pooled):
     # every sum has batch * h * w terms; a term is rounded into a partial sum once per 8 terms and product of planes
     dz = torch.nn.functional.interpolate(dy.abs(), scale_factor=2) if pooled else dy.abs()
     mag = torch.nn.grad.conv2d_weight(x.abs().double(), ws[0].shape, dz.double(), padding=1)
-    bound = (3 * 2.0 ** -26 + (6 * (batch * h * w // 8 + 8)) * 2.0 ** -24) * mag
+    bound = (6 * (batch * h * w // 8 + 8) + 1) * 2.0 ** -24 * mag
     err = (s.wgrad.cpu().double().reshape(ref.shape) - ref).abs()
     assert bool((err <= bound).all())
-    assert float(err.norm() / ref.norm()) < 2e-6
+    # (without one of the three smallest products random sums are off by 2.4e-6)
+    assert float(err.norm() / ref.norm()) < 1e-6
     s.close()
 
 
