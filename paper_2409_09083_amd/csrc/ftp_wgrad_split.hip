@@ -294,16 +294,16 @@ k_wgrad_split(WsplitArgs a)
         if (id > id0) negate();
         multiply(wsplit_steps(wc, c.ni, c.nr, c.nc));
     }
-    if (id1 > id0 && ((id1 - id0 - 1) & 1)) negate();      // (an even number of chunks ends on a negated one)
 
     // ---- sums that are not finite: this share once more, multiplied with the fp32 instruction -------------------------------
     {
+        const float unscale = id1 > id0 && ((id1 - id0 - 1) & 1) ? -kSplitUnscale : kSplitUnscale;      // (an even number of chunks ends on a negated one)
         bool bad = false;
 #pragma unroll
         for (int t = 0; t < 9; ++t) {
             float z = 0.0f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { acc[t][i] *= kSplitUnscale; z = __builtin_fmaf(acc[t][i], 0.0f, z); }
+            for (int i = 0; i < 16; ++i) { acc[t][i] *= unscale; z = __builtin_fmaf(acc[t][i], 0.0f, z); }
             bad = bad || !(z == 0.0f);
         }
         if (bad) redo = 1;                                 // (channels beyond the last are zeros: not finite only beside others that are not)
