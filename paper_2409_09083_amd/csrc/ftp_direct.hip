@@ -253,9 +253,11 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
 
 // Bias gradient of one output channel and stack: the sum of its deltas (behind a pool: every pooled delta reaches one pixel,
 // so the pooled map is summed over the windows the stack owns).  A launch of its own beside the filter-gradient kernels
-// that do not compute it.
-template <typename T>
-__global__ void __launch_bounds__(256)
+// that do not compute it.  A workgroup is a channel and stack: where that leaves each many deltas (above 8192), 16 wavefronts with
+// 8 loads of a thread in flight (16 channels, one stack, 16 images of 104^2: 200 us less than 4 wavefronts with one); below, the
+// counting of what is in flight costs more than it saves (three layers of 272 deltas a stack: 6 us of a step of 146).
+template <typename T, int kBiasThreads, int U>
+__global__ void __launch_bounds__(kBiasThreads)
 k_bias_grad(View din, RectTab own, float* __restrict__ partial, long long n_params, long long b_off, int pooled, int Hp, int Wp, int M, int batch)
 {
     const int co = blockIdx.x, stack = blockIdx.y, ti = stack / M, tj = stack % M;
@@ -266,18 +268,40 @@ k_bias_grad(View din, RectTab own, float* __restrict__ partial, long long n_para
         if (x1 >= Wp) x1 = Wp - 1;
         if (y1 >= Hp) y1 = Hp - 1;
     }
-    const int rw = x1 - x0 + 1, px = rw * (y1 - y0 + 1), items = px * batch;
-    float v = 0.0f;
-    for (int it = threadIdx.x; it < items; it += 256) {
-        const int n = it / px, r = it - n * px, y = r / rw;
-        v += ld(at<T>(din, stack, ti, tj, n, co, y0 + y, x0 + r - y * rw));
-    }
-    __shared__ float red[4];
+    const int rw = x1 - x0 + 1, px = rw * (y1 - y0 + 1);
+    float v[U];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    for (int u = 0; u < U; ++u) v[u] = 0.0f;
+    const T* const base = at<T>(din, stack, ti, tj, 0, co, y0, x0);
+    const int images = 0x20000000 / (px > 0 ? px : 1) < 1 ? 1 : 0x20000000 / (px > 0 ? px : 1);       // at a time (32-bit counts)
+    for (int n0 = 0; n0 < batch; n0 += images) {
+        const int items = px * (batch - n0 < images ? batch - n0 : images);
+        for (int it0 = threadIdx.x; it0 < items; it0 += U * kBiasThreads) {
+            float d[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {              // (beyond the last one: the last one again, not added)
+                const int it = it0 + u * kBiasThreads < items ? it0 + u * kBiasThreads : items - 1;
+                const int n = it / px, r = it - n * px, y = r / rw;
+                d[u] = ld(base + (long long)(n0 + n) * din.ns + (long long)y * din.pitch + (r - y * rw));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] += it0 + u * kBiasThreads < items ? d[u] : 0.0f;
+        }
+    }
+    float sum = v[0];
+#pragma unroll
+    for (int u = 1; u < U; ++u) sum += v[u];
+    __shared__ float red[kBiasThreads / 64];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
     __syncthreads();
-    if (threadIdx.x == 0) partial[(long long)stack * n_params + b_off + co] = (red[0] + red[1]) + (red[2] + red[3]);
+    if (threadIdx.x == 0) {
+        float s = 0.0f;
+#pragma unroll
+        for (int k = 0; k < kBiasThreads / 64; ++k) s += red[k];
+        partial[(long long)stack * n_params + b_off + co] = s;
+    }
 }
 
 // ---- lone 2x2 max-pool ---------------------------------------------------------------------------------
@@ -506,9 +530,15 @@ void direct_wgrad(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_wgrad_
 // a.rect = owned rectangle at the convolution output (before the pool)
 void bias_grad(const ConvArgs& a, hipStream_t s)
 {
-    dim3 grid(a.Cout, a.N * a.M), block(256);
-    if (a.bf16) hipLaunchKernelGGL(k_bias_grad<bf16_t>, grid, block, 0, s, a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch);
-    else        hipLaunchKernelGGL(k_bias_grad<float>, grid, block, 0, s, a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch);
+    int rw = 0, rh = 0;
+    for (int j = 0; j < a.M; ++j) rw = std::max(rw, a.rect.x1[j] - a.rect.x0[j] + 1);
+    for (int i = 0; i < a.N; ++i) rh = std::max(rh, a.rect.y1[i] - a.rect.y0[i] + 1);
+    const double deltas = (double)rw * rh * a.batch / (a.pooled ? 4 : 1);
+    const dim3 grid(a.Cout, a.N * a.M);
+#define FTP_BG(T, TH, U) hipLaunchKernelGGL((k_bias_grad<T, TH, U>), grid, dim3(TH), 0, s, a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch)
+    if (a.bf16) { if (deltas > 8192) FTP_BG(bf16_t, 1024, 8); else FTP_BG(bf16_t, 256, 1); }
+    else        { if (deltas > 8192) FTP_BG(float, 1024, 8); else FTP_BG(float, 256, 1); }
+#undef FTP_BG
 }
 
 void pool_fwd(const PoolArgs& a, hipStream_t s)

@@ -153,8 +153,8 @@ inline bool wgrad_wide_enough(const ConvArgs& c)
 // workgroup of it walks a stack's pixels, every pair of channels costs a start, and all of them together reach 1.7e12
 // multiply-adds a second, 1x1 0.6e12 (within a third of it over 14 layers and 7 sizes; us, direct / matrix cores: 16 -> 32
 // channels 3x3, 52^2 18 / 26, 8 images 171 / 74; 64 -> 64, 13^2 20 / 27, 26^2 in 4 tiles 54 / 28; 3 -> 16, 52^2 12 / 20).  The kernel for
-// 1x1 layers of up to 32 input channels starts at 36 us and walks the pixels as slowly as the direct one: it is for many pairs
-// (32 -> 32, 8 images of 13^2 9 / 47, of 52^2 59 / 65, 16 of 104^2 400 / 331; 24 -> 256, 150 x 44 90 / 40).
+// 1x1 layers of up to 32 input channels starts at 38 us and walks the pixels at a third of the direct one's time (32 -> 32, 8 images
+// of 13^2 9 / 47, of 52^2 58 / 45, 16 of 104^2 400 / 149; 24 -> 256, 150 x 44 90 / 40).
 inline bool wgrad_bias_pays(const ConvArgs& c)
 {
     if (!c.has_bias) return true;
@@ -165,7 +165,7 @@ inline bool wgrad_bias_pays(const ConvArgs& c)
     const double walk = px * (1.2e-3 + 0.6e-3 * taps), start = pairs * c.N * c.M * (0.5e-3 + 0.25e-3 * taps);
     const double rate = pairs * taps * c.batch * c.Hc * c.Wc / (c.K > 1 ? 1.7e6 : 0.62e6), work = rate > start ? rate : start;
     if (c.K > 1) return walk >= 20.0 || work >= 20.0;
-    const double least = c.Cin <= 32 ? 29.0 + 1.7e-3 * px : 10.0;
+    const double least = c.Cin <= 32 ? 31.0 + 0.65e-3 * px : 10.0;
     return walk * walk + work * work >= least * least;
 }
 bool mfma_wgrad_eligible(const ConvArgs& a);

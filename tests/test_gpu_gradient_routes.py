@@ -72,3 +72,25 @@ def test_narrow_deltas_take_the_faster_kernel(layer, size, dtype, direct):
 def test_narrow_gradients_take_the_faster_kernel(layer, size, direct):
     batch, hw, grid = size
     assert ("k_wgrad_direct" in _kernels((layer,), batch, hw, hw, grid, "f32", ("wgrad",))) == direct
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("layers,batch,h,w,grid", [((conv(16, 40, slope=1.0),), 5, 97, 131, (1, 1)), ((conv(16, 40, slope=1.0), pool(40)), 5, 98, 130, (1, 1)),
+                                                   ((conv(48, 64, 1, slope=1.0),), 3, 33, 45, (2, 3)), ((conv(64, 64, slope=1.0),), 1, 31, 29, (1, 1))])
+def test_bias_gradients_against_64_bits(layers, batch, h, w, grid, dtype):
+    """Sums of one workgroup a channel and stack: a few hundred deltas, and more than its threads take in one go."""
+    import torch
+    from paper_2409_09083_amd.harness import Session
+    s = Session([P._BiasLayer(layers[0])] + list(layers[1:]), batch, layers[0].cin, h, w, grid, (len(layers),), dtype=dtype)
+    g = torch.Generator(device="cuda").manual_seed(8)
+    s.x.uniform_(0, 1, generator=g)
+    s.dy.normal_(generator=g)
+    s.weights = [torch.randn(tuple((layers[0].cout, layers[0].cin, layers[0].k, layers[0].k)), device="cuda", generator=g).to(s.x.dtype) / 20] + [None] * (len(layers) - 1)
+    s.biases = [torch.zeros(layers[0].cout, device="cuda").to(s.x.dtype)] + [None] * (len(layers) - 1)
+    s.step()
+    torch.cuda.synchronize()
+    got = s.wgrad[-layers[0].cout:].double()
+    ref, mag = s.dy.double().sum((0, 2, 3)), s.dy.double().abs().sum((0, 2, 3))
+    # (fp32 sums: a rounding of 2^-24 of the magnitudes per addition of a thread, 64 at most here, of the tree and the last sum)
+    assert bool(((got - ref).abs() <= 100 * 2.0 ** -24 * mag).all())
+    s.close()
