@@ -475,7 +475,8 @@ bool mfma_conv_eligible(const ConvArgs& a, bool backward)
     // 32 x 32 54 -> 15 us), unless there is little to sum up: 1x1 fp32, 8 <- 16, 16 images of 128^2, 17 us direct against 21, 8 <- 24
     // 27 / 22; stride 2, whose inserted zeros are multiplied by all but ftp_delta_s2.hip, 3x3, 8 <- 8, 23 / 39, one image of 128^2
     // 18 / 17, 8 <- 16 114 / 95 (32 images of 200^2); 1x1, 8 <- 48, one image 22 / 18, 32 images 66 / 99.
-    if (backward && Mtot < 16) {
+    // (Through a pool the direct kernel compares winners too: never the faster one.)
+    if (backward && Mtot < 16 && !a.pooled) {
         const int terms = C * a.K * a.K;
         const bool few = (double)a.batch * a.Hc * a.Wc < 5.0e4;        // positions
         if (terms < (a.bf16 ? 12 : a.S == 1 ? 24 : few ? 40 : 144)) return false;
