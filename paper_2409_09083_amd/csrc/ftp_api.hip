@@ -317,7 +317,6 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
             ConvArgs a = conv_args(p, u, ub, weights, biases);
             a.rect = make_rect(p, u.group, FTP_RECT_FWD, u.bo);
             a.own = make_rect(p, u.group, FTP_RECT_OWN, u.bo);
-            const bool fast = use_mfma() && plain_geometry(a);
             if (use_mfma() && mfma_conv_eligible(a, false)) {
                 float* wt = (float*)((char*)workspace + u.wt_offset);
                 const RectTab ext = view_extent(p, u.in_act, u.group, u.bi);
@@ -325,10 +324,8 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
                     if (!relaid) { prep_pass(p, weights, workspace, false, s); relaid = true; }
                     if (mfma_conv_fwd(a, ext, wt, s)) direct_conv_fwd(a, s);
                 });
-            } else if (fast && thin_conv_fwd_eligible(a)) {
-                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { thin_conv_fwd(a, s); });
-            } else if (use_mfma() && thin_conv_fwd_gen_eligible(a)) {
-                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { thin_conv_fwd_gen(a, s); });
+            } else if (use_mfma() && stem_fwd_eligible(a)) {
+                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { stem_fwd(a, s); });
             } else {
                 rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { direct_conv_fwd(a, s); });
             }

@@ -180,11 +180,9 @@ void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
 // this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own).
 void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, hipStream_t s);
 
-bool thin_conv_fwd_eligible(const ConvArgs& a);
-void thin_conv_fwd(const ConvArgs& a, hipStream_t s);
-// ... with a 5x5 / 7x7 filter or stride 2 (no fused pool)
-bool thin_conv_fwd_gen_eligible(const ConvArgs& a);
-void thin_conv_fwd_gen(const ConvArgs& a, hipStream_t s);
+// forward pass of first layers on the fp32 matrix cores (ftp_stem_fwd.hip)
+bool stem_fwd_eligible(const ConvArgs& a);
+void stem_fwd(const ConvArgs& a, hipStream_t s);
 bool thin_bwd_data_strided_eligible(const ConvArgs& a);
 void thin_conv_bwd_data_strided(const ConvArgs& a, const RectTab& ext, hipStream_t s);   // ext: extent of the delta view per stack
 bool thin_bwd_data_eligible(const ConvArgs& a);

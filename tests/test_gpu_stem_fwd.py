@@ -1,0 +1,47 @@
+"""First layers (at most 4 input channels) against the oracle: tiles of one and several columns and rows, the last ones partly
+filled, runs of tiles that a workgroup takes one after the other, channel counts around blocks of 16 and 32, biases, every filter."""
+import pytest
+
+from ftp_synth.configs import Config, conv, pool
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+def _biased(ly):
+    object.__setattr__(ly, "has_bias", 1)
+    return ly
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cin,cout,batch,h,w,grid", [
+    (3, 8, 1, 6, 6, (1, 1)), (1, 17, 2, 34, 66, (1, 1)), (4, 33, 1, 70, 130, (2, 2)), (3, 64, 3, 36, 10, (3, 1)),
+    (3, 32, 64, 136, 32, (2, 2)), (2, 16, 64, 72, 48, (4, 4))])
+def test_pooled(oracle, dtype, cin, cout, batch, h, w, grid):
+    P.check_case(oracle, Config("stem", batch, cin, h, w, (conv(cin, cout), pool(cout)), grid, (2,), dtype))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("k,stride,cin,cout,batch,h,w,grid", [
+    (3, 1, 3, 8, 1, 5, 7, (1, 1)), (3, 1, 4, 40, 2, 33, 65, (2, 1)), (3, 1, 3, 16, 64, 76, 40, (4, 4)), (3, 2, 2, 20, 2, 35, 67, (1, 2)),
+    (5, 1, 3, 24, 1, 18, 34, (1, 1)), (5, 2, 4, 16, 1, 37, 41, (2, 2)), (7, 1, 1, 48, 1, 17, 33, (1, 1)), (7, 2, 3, 64, 2, 67, 131, (2, 1)),
+    (7, 2, 4, 72, 1, 65, 67, (1, 1)), (1, 2, 3, 36, 2, 31, 70, (1, 3))])
+def test_unpooled(oracle, dtype, k, stride, cin, cout, batch, h, w, grid):
+    P.check_case(oracle, Config("stem", batch, cin, h, w, (conv(cin, cout, k, stride=stride),), grid, (1,), dtype))
+
+
+@pytest.mark.parametrize("slope", [0.0, 1.0, 1.5])
+def test_slopes_and_bias(slope):
+    """Slopes outside (0, 1) and a bias take the general epilogue: values against 64 bits."""
+    import torch
+    from paper_2409_09083_amd.harness import Session
+    g = torch.Generator().manual_seed(3)
+    s = Session((_biased(conv(3, 20, slope=slope)), pool(20)), 2, 3, 38, 44, (1, 2), (2,))
+    x, w, b = torch.randn(s.in_shape, generator=g), torch.randn((20, 3, 3, 3), generator=g) / 5, torch.randn(20, generator=g)
+    s.load(x=x.numpy(), weights=[w.numpy(), None], biases=[b.numpy(), None])
+    s.forward()
+    z = torch.nn.functional.conv2d(x.double(), w.double(), b.double(), padding=1)
+    ref = torch.nn.functional.max_pool2d(torch.where(z > 0, z, z * slope), 2)
+    # (27 products and their sums, each rounded to 24 bits)
+    assert float((s.y.cpu().double() - ref).abs().max() / ref.abs().max()) < 28 * 2.0 ** -24
+    s.close()
