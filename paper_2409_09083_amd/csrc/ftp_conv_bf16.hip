@@ -13,10 +13,10 @@
 // four wavefronts of 64 x 128, 64 x 64, 32 x 64 or 32 x 32 channels x pixels; two workgroups share a CU: while one transposes or
 // stores, the other multiplies.
 // The order of the sums (8 channels, then tap pairs) and the epilogue do not depend on the workgroup's shape.
-// What bounds it: re-fetched lines of HBM in the 1x1 deltas and the deltas through a pool (4.5 to 4.9 TB/s: rows of a map are cut
-// among stacks on different XCDs), else the few wavefronts in flight against the loads' latency, and the epilogue.
+// What bounds it: the few wavefronts in flight against the loads' latency, and the epilogue (order_tiles keeps stacks that share lines on one
+// XCD: before, the deltas through a pool and of 1x1 layers fetched lines of HBM again, 4.5 to 4.9 TB/s).
 // Against the kernel it replaces (patch channel-major in LDS, filters through LDS): 32 images, 256 -> 512
-// channels at 38^2 0.368 -> 0.289 ms; 64 -> 128 at 152^2 0.274 -> 0.244 ms; 32 -> 64 with a pool, the caller's input, 304^2: 0.487 -> 0.458 ms, delta through the pool 0.517 -> 0.322 ms; 64 <- 128 channels 0.241 -> 0.175 ms.
+// channels at 38^2 0.368 -> 0.289 ms; 64 -> 128 at 152^2 0.274 -> 0.244 ms; 32 -> 64 with a pool, the caller's input, 304^2: 0.487 -> 0.458 ms (0.358 -> 0.261 by the row order), delta through the pool 0.517 -> 0.322 ms (0.279); 64 <- 128 channels 0.241 -> 0.175 ms.
 // MFMA lane layout: A[m = lane%32][k = 8*(lane/32) + j], B[k = 8*(lane/32) + j][n = lane%32], j < 8,
 // D[m = 8*(i/4) + 4*(lane/32) + i%4][n = lane%32] for accumulator register i of 16.
 #include "ftp_conv_epilogue.h"
@@ -69,12 +69,7 @@ k_conv_bf16(MfmaConvArgs a)
     const int wave_m = wave % WAVES_M, wave_n = wave / WAVES_M;
     const int hi = lane >> 5, l32 = lane & 31;
     int vgroup, vtile;
-    const int ntiles = a.tiles_x * a.tiles_r;
-    if (a.xcd_groups) {
-        if (!xcd_order(a.mblocks * a.stacks, ntiles, vgroup, vtile)) return;
-    } else {
-        vgroup = (int)blockIdx.x / ntiles; vtile = (int)blockIdx.x - vgroup * ntiles;
-    }
+    if (!tile_order(a, vgroup, vtile)) return;
     const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<S, P, 8>(a, x0, x1, y0, y1, vtile);
@@ -434,11 +429,7 @@ int launch_bf_in(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
     if (!sh.WM) return 1;
     a.TC = td.TC; a.tiles_x = td.tiles_x; a.tiles_r = td.tiles_r; a.cap = td.cap; a.flat = td.flat; a.cs = 0;
     a.mblocks = (a.Mtot + 32 * sh.MT * sh.WM - 1) / (32 * sh.MT * sh.WM); a.stacks = c.N * c.M;
-    // XCD order pays where several channel blocks compete for the L2 and the groups spread evenly over the 8 XCDs;
-    // with one channel block the plain order (neighbouring tiles on different XCDs) balances better
-    const int groups = a.mblocks * a.stacks, ntiles = a.tiles_x * a.tiles_r;
-    a.xcd_groups = (a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0) ? 1 : 0;
-    const unsigned nwg = a.xcd_groups ? xcd_grid(groups, ntiles) : (unsigned)(groups * ntiles);
+    const unsigned nwg = order_tiles(a, c, td, DELTA_IN);
     launch_bf<K, POOL_OUT, DELTA_IN, IN>(a, sh, dim3(nwg), s);
     return 0;
 }

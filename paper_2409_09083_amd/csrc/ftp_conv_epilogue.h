@@ -19,6 +19,16 @@ __device__ __forceinline__ TileGeom tile_geom(const MfmaConvArgs& a, int x0, int
 template <int S, int P>
 __device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) { return conv_tile_pix(g, wq, x1, S, P); }
 
+// The workgroup's stack and channel block (vgroup = stack * mblocks + channel block) and tile, in the order the launch chose.
+__device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int& vgroup, int& vtile)
+{
+    const int ntiles = a.tiles_x * a.tiles_r;
+    if (a.row_run) return row_order((int)blockIdx.x, a.stacks / a.M, a.M, a.mblocks, ntiles, a.row_run, vgroup, vtile);
+    if (a.xcd_groups) return xcd_order(a.mblocks * a.stacks, ntiles, vgroup, vtile);
+    vgroup = (int)blockIdx.x / ntiles; vtile = (int)blockIdx.x - vgroup * ntiles;
+    return true;
+}
+
 // Epilogue shared by the convolution kernels: bias, leaky ReLU, the fused 2x2 max-pool, the decision codes and
 // the stores.  A lane holds, per 32x32 tile, 16 channels (8*(i/4) + 4*hi + i%4) of one pixel.  `bias_lds` is LDS
 // no wavefront reads any more once all of them have arrived here (BM floats are used).

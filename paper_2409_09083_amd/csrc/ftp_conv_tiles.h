@@ -198,4 +198,54 @@ inline long long tile_slots(const TileChoice& tc, int rw, int rh, int batch)
     return ((rtot + trf - 1) / trf) * ((rw + tcw - 1) / tcw);
 }
 
+// Order of a launch's workgroups by rows of stacks.  Stacks cut the rows of a map into pieces of a few dozen elements: neighbours
+// share most cache lines, and tiles one below the other the rows of their filter halos.  In this order the tiles `vtile` of all
+// stacks of a grid row and all channel blocks are neighbours, `run` such tile rows one after the other form a unit, and a unit runs on
+// one XCD (workgroups go to the 8 XCDs round-robin by index), so that its L2 fetches the shared lines once.
+FTP_HD constexpr int row_order_units(int N, int ntiles, int run) { return N * ((ntiles + run - 1) / run); }
+FTP_HD inline unsigned row_order_grid(int N, int M, int mblocks, int ntiles, int run)
+{
+    return 8u * (unsigned)((row_order_units(N, ntiles, run) + 7) / 8) * (unsigned)(run * M * mblocks);
+}
+// Workgroup `block` -> channel block and stack (vgroup = stack * mblocks + channel block), tile.  False: padding.
+FTP_HD inline bool row_order(int block, int N, int M, int mblocks, int ntiles, int run, int& vgroup, int& vtile)
+{
+    const int row = M * mblocks, size = run * row, slot = block >> 3, round = slot / size, w = slot - round * size;
+    const int unit = (block & 7) + 8 * round, per = (ntiles + run - 1) / run, ti = unit / per, v = w / row;
+    vtile = (unit - ti * per) * run + v;
+    vgroup = ti * row + (w - v * row);
+    return ti < N && vtile < ntiles;
+}
+// Tile rows of a unit: as many as leave the XCDs evenly loaded (a tile row more or less weighs more than the lines shared between two of
+// them), 0 if they would not be (few tile rows): the plain order then.
+inline int choose_row_order(const TileChoice& tc, const int* rws, const int* rhs, int N, int M, int batch)
+{
+    const int ntiles = tc.tiles_x * tc.tiles_r;
+    int rows[kMaxGrid];                                // tile rows per grid row (of its widest stack)
+    long long all = 0;
+    int mw = 0;
+    for (int j = 0; j < M; ++j) mw = mw > rws[j] ? mw : rws[j];
+    for (int i = 0; i < N; ++i) { rows[i] = (int)tile_slots(tc, mw, rhs[i], batch); all += rows[i]; }
+    int best = 0;
+    double best_cost = 1.15 * (double)all / 8.0;
+    for (int per = 1; per <= 64; per *= 2) {           // units of a grid row
+        const int run = (ntiles + per - 1) / per;
+        long long load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        const int have = (ntiles + run - 1) / run;
+        for (int i = 0; i < N; ++i)
+            for (int u = 0; u < have; ++u) {
+                const int left = rows[i] - u * run;
+                load[(i * have + u) & 7] += left < 0 ? 0 : left < run ? left : run;
+            }
+        long long most = 0;
+        for (int x = 0; x < 8; ++x) most = most > load[x] ? most : load[x];
+        const double cost = (double)most * (1.0 + 0.05 / run);
+        if (cost < best_cost) { best_cost = cost; best = run; }
+        if (run == 1) break;
+    }
+    // (single tile rows: at most one of them more on one XCD than on another)
+    if (1.05 * (double)((all + 7) / 8) < best_cost) best = 1;
+    return best;
+}
+
 }  // namespace ftp

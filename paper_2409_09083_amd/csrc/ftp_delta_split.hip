@@ -83,12 +83,7 @@ k_delta_split(MfmaConvArgs a)
     // (tile, channel block, stack), tile fastest; in XCD order where the launch says so: the tiles of one stack and channel
     // block then run on one XCD, which meets one channel block's slice of the filter only
     int vgroup, vtile;
-    const int ntiles = a.tiles_x * a.tiles_r;
-    if (a.xcd_groups) {
-        if (!xcd_order(a.mblocks * a.stacks, ntiles, vgroup, vtile)) return;
-    } else {
-        vgroup = (int)blockIdx.x / ntiles; vtile = (int)blockIdx.x - vgroup * ntiles;
-    }
+    if (!tile_order(a, vgroup, vtile)) return;
     const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<1, P, IN == IN_POOL ? 2 : 4>(a, x0, x1, y0, y1, vtile);
@@ -479,11 +474,7 @@ int launch_in(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
     if (IN == IN_POOL && (double)td.max_img * (double)a.mask.ns + ((double)a.C + 32.0) * (double)a.mask.cs >= 2.0e9) return 1;
     a.TC = td.TC; a.tiles_x = td.tiles_x; a.tiles_r = td.tiles_r; a.cap = td.cap; a.flat = td.flat; a.cs = 0;
     a.mblocks = (a.Mtot + sh.BM - 1) / sh.BM; a.stacks = c.N * c.M;
-    // XCD order pays where several channel blocks compete for the L2 and the groups spread evenly over the 8 XCDs;
-    // with one channel block the plain order (neighbouring tiles on different XCDs) balances better
-    const int groups = a.mblocks * a.stacks, ntiles = a.tiles_x * a.tiles_r;
-    a.xcd_groups = (a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0) ? 1 : 0;
-    const unsigned nwg = a.xcd_groups ? xcd_grid(groups, ntiles) : (unsigned)(groups * ntiles);
+    const unsigned nwg = order_tiles(a, c, td, true);
     launch_split<K, IN>(a, sh, dim3(nwg), s);
     return 0;
 }

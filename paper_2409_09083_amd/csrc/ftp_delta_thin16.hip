@@ -28,7 +28,7 @@ __device__ __forceinline__ int dt16_unit(int row, int pos, int win) { return (ro
 
 __global__ void __launch_bounds__(256, 2)
 k_delta_thin16(View din, View mask, View dout, View isign, int scale_out, float in_slope, RectTab rt, const bf16_t* __restrict__ w,
-               int Cin, int Cout, int Hc, int Wc, int M, int batch, int tiles_x, int tiles, int TX, int total)
+               int Cin, int Cout, int Hc, int Wc, int N, int M, int tiles_x, int tiles, int TX, int total)
 {
     typedef float v4f __attribute__((ext_vector_type(4)));
     typedef uint32_t v3u __attribute__((ext_vector_type(3), aligned(4)));
@@ -62,9 +62,10 @@ k_delta_thin16(View din, View mask, View dout, View isign, int scale_out, float 
         for (;; t += (int)gridDim.x) {
             r.t = t < total ? t : total;
             if (r.t == total) { r.stack = r.n = r.ti = r.tj = r.J0 = r.I0 = 0; return r; }
-            const int img = t / tiles, tile = t - img * tiles, by = tile / tiles_x, bx = tile - by * tiles_x;
-            r.stack = img / batch; r.n = img - r.stack * batch;
-            r.ti = r.stack / M; r.tj = r.stack - r.ti * M;
+            // (image, grid row, tile row, grid column, tile column)
+            const int row = t / (M * tiles_x), i = t - row * (M * tiles_x), tiles_y = tiles / tiles_x, by = row % tiles_y, gr = row / tiles_y, bx = i % tiles_x;
+            r.tj = i / tiles_x; r.n = gr / N; r.ti = gr - r.n * N;
+            r.stack = r.ti * M + r.tj;
             r.J0 = (rt.y0[r.ti] >> 1) + by * kDT16Rows; r.I0 = (rt.x0[r.tj] >> 1) + bx * TX;
             if (2 * r.J0 <= rt.y1[r.ti] && 2 * r.I0 <= rt.x1[r.tj]) return r;
         }
@@ -128,7 +129,9 @@ k_delta_thin16(View din, View mask, View dout, View isign, int scale_out, float 
         }
     };
 
-    Tile cur = seek((int)blockIdx.x);
+    // (a round's tiles go to the XCDs in eighths: neighbours share the lines of a map's rows; the grid is a multiple of 8 or has one round)
+    const int first = gridDim.x & 7 ? (int)blockIdx.x : (int)((blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3));
+    Tile cur = seek(first);
     if (cur.t == total) return;
     load(cur, 0);
     const int groups = (TX + 15) >> 4;                 // of 16 cells
@@ -270,7 +273,7 @@ bool thin16_bwd_data(const ConvArgs& c, hipStream_t s)
     if (!granted) { (void)hipFuncSetAttribute((const void*)k_delta_thin16, hipFuncAttributeMaxDynamicSharedMemorySize, 16 * (2 * kDT16Oct + 2 * (kDT16MaxC / 16) * 256)); granted = true; }
     g_kernel_label = "k_delta_thin16";
     hipLaunchKernelGGL(k_delta_thin16, dim3((unsigned)std::min<long long>(total, 512)), dim3(256), lds, s, c.din, c.mask, c.dout, c.isign, c.scale_out, c.in_slope,
-                       c.rect, (const bf16_t*)c.w, c.Cin, c.Cout, c.Hc, c.Wc, c.M, c.batch, tiles_x, tiles, TX, (int)total);
+                       c.rect, (const bf16_t*)c.w, c.Cin, c.Cout, c.Hc, c.Wc, c.N, c.M, tiles_x, tiles, TX, (int)total);
     return true;
 }
 

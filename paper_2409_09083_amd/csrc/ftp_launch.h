@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include "ftp_device.h"
 #include "ftp_plan.h"
+#include "ftp_conv_tiles.h"
 
 namespace ftp {
 
@@ -77,7 +78,8 @@ struct MfmaConvArgs {
     int C, Mtot;                                    // reduction channels, output channels
     int Hc, Wc;                                     // map extent at the convolution
     int TC, tiles_x, tiles_r;                       // column block (when tiles_x > 1), column / row-run tile counts
-    int mblocks, stacks, xcd_groups;                // output-channel blocks; stacks; 1: workgroups in XCD order (the grid is 1-D, see xcd_order)
+    int mblocks, stacks;                            // output-channel blocks; stacks
+    int row_run, xcd_groups;                        // order of the workgroups (the grid is 1-D): > 0: row_order; else 1: xcd_order
     int cap;                                        // pixels (pool windows) per tile
     int flat;                                       // 1: tiles are runs of cap pixels of the rectangle's pixel list, not runs of whole rows
     int cs;                                         // LDS channel stride of the patch = largest patch of any stack
@@ -92,6 +94,8 @@ struct MfmaConvArgs {
 bool mfma_conv_eligible(const ConvArgs& a, bool backward);
 // 16-bit storage: the layer multiplies on the bfloat matrix cores (stride-1 1x1 / 3x3)
 bool mfma_conv_packs_bf16(const ConvArgs& a);
+
+unsigned order_tiles(MfmaConvArgs& a, const ConvArgs& c, const TileChoice& tc, bool delta);      // sets row_run, xcd_groups; returns the grid
 
 // Filter relayout (ftp_prep.hip): one job per convolution of a pass, all in one launch.
 enum PrepKind : int {
@@ -129,7 +133,7 @@ struct MfmaWgradArgs {
     long long n_params, w_off;
     int Cin, Cout, Hc, Wc;
     int splits;                                     // batch shares per stack
-    int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_order)
+    int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
     int PK;                                         // pixels staged per step
     int zs = 0, stage_words = 0;                    // streamed thin-layer kernel: dwords between the dZ rows of two channels; dwords of a stage
     float slope;
@@ -190,7 +194,7 @@ void thin_conv_bwd_data(const ConvArgs& a, hipStream_t s);
 bool thin_wgrad_eligible(const ConvArgs& c);
 void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
 bool thin16_bwd_data(const ConvArgs& a, hipStream_t s);        // (ftp_delta_thin16.hip) false: does not apply
-bool thin16_wgrad(const ConvArgs& a, const MfmaWgradArgs& m, hipStream_t s);      // (ftp_wgrad_thin16.hip) false: does not apply
+bool thin16_wgrad(const ConvArgs& a, MfmaWgradArgs& m, hipStream_t s);      // (ftp_wgrad_thin16.hip) false: does not apply
 
 void direct_conv_fwd(const ConvArgs& a, hipStream_t s);
 void direct_conv_bwd_data(const ConvArgs& a, hipStream_t s);

@@ -18,7 +18,6 @@
 #include "ftp_conv_epilogue.h"
 #include <algorithm>
 #include <cstdio>
-#include <cstdlib>
 #include <cstring>
 
 namespace ftp {
@@ -95,12 +94,7 @@ k_conv_mfma_dl(MfmaConvArgs a)
     // only ever meets one channel block's slice of the filter (with all blocks on every XCD the filters of the
     // 256 -> 512 layers do not stay in a 4 MB L2).
     int vgroup, vtile;
-    const int ntiles = a.tiles_x * a.tiles_r;
-    if (a.xcd_groups) {
-        if (!xcd_order(a.mblocks * a.stacks, ntiles, vgroup, vtile)) return;
-    } else {
-        vgroup = (int)blockIdx.x / ntiles; vtile = (int)blockIdx.x - vgroup * ntiles;
-    }
+    if (!tile_order(a, vgroup, vtile)) return;
     const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<S, P, WIDE ? 4 : 0>(a, x0, x1, y0, y1, vtile);
@@ -320,6 +314,32 @@ k_conv_mfma_dl(MfmaConvArgs a)
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------
+// Row order (ftp_conv_tiles.h) where lines fetched by several XCDs are what a launch waits for: 16-bit maps, and fp32 ones where a whole
+// map is read or written, rounds are many and a stack's rows are not much longer than a line (ms, before / row order; 16 bits, 32 images: 32 -> 64 with a pool, caller's map of 304^2 0.358 / 0.261, through the
+// pool 0.313 / 0.280, 1x1 256 <- 128 at 76^2 0.118 / 0.073, inside a stack 64 -> 128 at 152^2 0.241 / 0.225; fp32, 64 images: 32 -> 64 with a pool
+// 2.06 / 1.92, 1x1 512 <- 256 at 38^2 0.62 / 0.46; but 128 -> 128, 16 images of 76^2 in 765 workgroups, 0.245 / 0.304, inside stacks
+// 1x1 64 <- 128 0.408 / 0.434, and 3x3 64 <- 64, 32 images of 304^2 in 3 x 3 stacks, 0.319 / 0.343).
+unsigned order_tiles(MfmaConvArgs& a, const ConvArgs& c, const TileChoice& tc, bool delta)
+{
+    const int groups = a.mblocks * a.stacks, ntiles = a.tiles_x * a.tiles_r;
+    const long long wgs = (long long)groups * ntiles;
+    const bool whole = delta ? !(a.din.ss && a.dout.ss) : !(a.in.ss && a.out.ss);
+    a.row_run = 0; a.xcd_groups = 0;
+    int mw = 0;
+    for (int j = 0; j < c.M; ++j) mw = std::max(mw, a.rect.x1[j] - a.rect.x0[j] + 1);
+    if (c.bf16 ? wgs >= 512 : whole && wgs >= 2048 && mw <= 40) {
+        int rws[kTabGrid], rhs[kTabGrid];               // widths / heights of the stacks' rectangles per tile column / row
+        for (int j = 0; j < c.M; ++j) rws[j] = a.rect.x1[j] - a.rect.x0[j] + 1;
+        for (int i = 0; i < c.N; ++i) rhs[i] = a.rect.y1[i] - a.rect.y0[i] + 1;
+        a.row_run = choose_row_order(tc, rws, rhs, c.N, c.M, c.batch);
+        if (a.row_run) return row_order_grid(c.N, c.M, a.mblocks, ntiles, a.row_run);
+    }
+    // XCD order pays where several channel blocks compete for the L2 and the groups spread evenly over the 8 XCDs;
+    // with one channel block the plain order (neighbouring tiles on different XCDs) balances better
+    a.xcd_groups = (a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0) ? 1 : 0;
+    return a.xcd_groups ? xcd_grid(groups, ntiles) : (unsigned)(groups * ntiles);
+}
+
 namespace {
 
 // Largest byte offset a workgroup forms from its base pointer: the images a tile can span plus all channels.
@@ -436,11 +456,7 @@ int launch_t(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
     }
     a.TC = td.TC; a.tiles_x = td.tiles_x; a.tiles_r = td.tiles_r; a.cap = td.cap; a.flat = td.flat; a.cs = quad ? (td.cs + 255) & ~255 : (td.cs + 63) & ~63;
     a.mblocks = (a.Mtot + sh.BM - 1) / sh.BM; a.stacks = c.N * c.M;
-    // XCD order pays where several channel blocks compete for the L2 and the groups spread evenly over the 8 XCDs;
-    // with one channel block the plain order (neighbouring tiles on different XCDs) balances better
-    const int groups = a.mblocks * a.stacks, ntiles = a.tiles_x * a.tiles_r;
-    a.xcd_groups = (a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0) ? 1 : 0;
-    const unsigned nwg = a.xcd_groups ? xcd_grid(groups, ntiles) : (unsigned)(groups * ntiles);
+    const unsigned nwg = order_tiles(a, c, td, DELTA_IN);
     launch_dl<T, K, POOL_OUT, DELTA_IN, STRIDE>(a, sh, quad, dim3(nwg), s);
     return 0;
 }

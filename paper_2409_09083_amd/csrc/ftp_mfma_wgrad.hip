@@ -59,11 +59,9 @@ k_wgrad_mfma(MfmaWgradArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // uniform: keeps the loop control scalar
     const int wave_co = wave % WAVES_CO, wave_ci = (wave / WAVES_CO) % WAVES_CI, wave_k = wave / (WAVES_CO * WAVES_CI);
     const int hi = lane >> 5, l32 = lane & 31;
-    // (block, share, stack), block fastest, in XCD order: the blocks of one stack and share read the same maps
-    int vgroup, bx;
-    if (!xcd_order(a.splits * a.stacks, a.gx, vgroup, bx)) return;
-    const int split = vgroup % a.splits;
-    const int stack = vgroup / a.splits, ti = stack / a.M, tj = stack % a.M;
+    int split, stack, bx;
+    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
     const int tiles_ci = (a.Cin + BCI - 1) / BCI, tiles = tiles_ci * ((a.Cout + BCO - 1) / BCO);
@@ -483,7 +481,7 @@ void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
     const int tiles = ((c.Cout + BCO - 1) / BCO) * ((c.Cin + BCI - 1) / BCI);
     const int parts = c.K == 5 ? 3 : c.K == 7 ? 7 : 1;                 // filter rows 2 + 2 + 1, or one at a time
     a.gx = tiles * parts; a.stacks = c.N * c.M;
-    dim3 grid(xcd_grid(a.splits * a.stacks, a.gx)), block(256);
+    dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx)), block(256);
     // more than 64 KB of dynamic LDS has to be granted per kernel, once
 #define FTP_WG1(TT, TN, KK, WCO, WCI, HF, TR) do { \
         static thread_local bool granted = false; \

@@ -14,6 +14,7 @@
 // ends up with 4 consecutive channels of its pixel.
 // A workgroup takes a run of tiles one below the other and loads the next one's patch while it multiplies (3 -> 32 with a pool, 32
 // images of 608^2 with 16-bit storage: 0.399 -> 0.345 ms; three wavefronts a SIMD without register spills instead of four: 0.323).
+// Workgroups of a line of tiles across all stacks of a grid row run on one XCD, which writes whole cache lines then: 0.343 -> 0.306.
 // What bounds it: the matrix instructions (0.14 ms there) and the vector ALU work of the epilogue (about 27 instructions a window and
 // channel), which do not run beside each other: fp32 matrix instructions keep the SIMD's vector ALU busy; then the stores.
 // Launches that do not fill the chip: latency.  Vector ALU -> this: 3 -> 32 with a pool 0.407 -> 0.325 ms (16 bits, 32 images of
@@ -33,8 +34,9 @@ struct StemArgs {
     const void* w; const void* bias;
     int Cin, Cout, Hi, Wi;
     float slope;
-    int M, batch;
+    int N, M;
     int tw, th, tiles_x, tiles_y;                      // tiles, in output pixels
+    int strips, lines, xcd;                            // runs of tiles of a stack one below the other; such runs of all images and grid rows; 1: xcd_order
     int run;                                           // tiles one below the other that a workgroup takes
     int plain;                                         // no bias, slope in (0, 1]
 };
@@ -81,9 +83,16 @@ k_conv_fwd_stem(StemArgs a)
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int tid = threadIdx.x, lane = tid & 63, n16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int stack = blockIdx.z / a.batch, n = blockIdx.z - stack * a.batch;
-    const int ti = stack / a.M, tj = stack - ti * a.M;
-    const int strip = blockIdx.x / a.tiles_x, bx = blockIdx.x - strip * a.tiles_x;
+    // (image, grid row, strip, grid column, tile column): the workgroups of a strip of the map share the lines of its rows, on one XCD
+    const int row = a.M * a.tiles_x;
+    int line, w;
+    if (a.xcd) {
+        if (!xcd_order(a.lines, row, line, w)) return;
+    } else {
+        line = (int)blockIdx.x / row; w = (int)blockIdx.x - line * row;
+    }
+    const int gr = line / a.strips, strip = line - gr * a.strips, n = gr / a.N, ti = gr - n * a.N;
+    const int tj = w / a.tiles_x, bx = w - tj * a.tiles_x, stack = ti * a.M + tj;
     const int x1 = a.rt.x1[tj], y1 = a.rt.y1[ti];
     const int ox0 = a.rt.x0[tj] + bx * a.tw;
     int oy0 = a.rt.y0[ti] + strip * a.run * a.th;
@@ -363,7 +372,7 @@ void stem_fwd(const ConvArgs& c, hipStream_t st)
 {
     StemArgs s;
     s.in = c.in; s.out = c.out; s.mask = c.mask; s.osign = c.osign; s.rt = c.rect; s.own = c.own;
-    s.w = c.w; s.bias = c.bias; s.Cin = c.Cin; s.Cout = c.Cout; s.Hi = c.Hi; s.Wi = c.Wi; s.slope = c.slope; s.M = c.M; s.batch = c.batch;
+    s.w = c.w; s.bias = c.bias; s.Cin = c.Cin; s.Cout = c.Cout; s.Hi = c.Hi; s.Wi = c.Wi; s.slope = c.slope; s.N = c.N; s.M = c.M;
     s.plain = !c.bias && c.slope > 0.0f && c.slope <= 1.0f;
     int mw = 0, mh = 0;
     for (int t = 0; t < c.M; ++t) mw = std::max(mw, c.rect.x1[t] - c.rect.x0[t] + 1);
@@ -391,7 +400,11 @@ void stem_fwd(const ConvArgs& c, hipStream_t st)
         const long long per = (long long)s.tiles_x * c.N * c.M * c.batch;
         while (s.run < s.tiles_y && per * ((s.tiles_y + s.run) / (s.run + 1)) >= 1024) ++s.run;
     }
-    dim3 grid(s.tiles_x * ((s.tiles_y + s.run - 1) / s.run), 1, c.N * c.M * c.batch);
+    s.strips = (s.tiles_y + s.run - 1) / s.run;
+    s.lines = s.strips * c.N * c.batch;
+    s.xcd = s.lines >= 64 ? 1 : 0;                     // (few lines would load the XCDs unevenly)
+    const int row = c.M * s.tiles_x;
+    dim3 grid(s.xcd ? xcd_grid(s.lines, row) : (unsigned)(s.lines * row));
     g_kernel_label = "k_conv_fwd_stem";
     if (c.bf16) launch_stem<bf16_t>(c, s, grid, lds, st); else launch_stem<float>(c, s, grid, lds, st);
 }

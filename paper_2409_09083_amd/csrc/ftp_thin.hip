@@ -494,11 +494,12 @@ k_wgrad_mfma_thin(MfmaWgradArgs a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: row bookkeeping stays scalar
     const int hi = lane >> 5, l32 = lane & 31;
-    const int stack = blockIdx.z, ti = stack / a.M, tj = stack % a.M;
+    int split, stack, bx;
+    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
-    const int co0 = blockIdx.x * 32;
-    const int split = blockIdx.y;
+    const int co0 = bx * 32;
 
     const ThinChunks tc = thin_wgrad_chunks(rw, rh, a.batch, a.PK, POOL);
     const int TCp = tc.TCp, TR = tc.TR, TI = tc.TI, row_blocks = tc.row_blocks;
@@ -718,11 +719,12 @@ k_wgrad_thin_dl(MfmaWgradArgs a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, l32 = lane & 31;
-    const int stack = blockIdx.z, ti = stack / a.M, tj = stack % a.M;
+    int split, stack, bx;
+    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
-    const int co0 = blockIdx.x * 32;
-    const int split = blockIdx.y;
+    const int co0 = bx * 32;
 
     const ThinStreamChunks tc = thin_stream_chunks(rw, rh, a.batch, POOL, a.PK);      // (a.PK: widest column block)
     const int TCp = tc.TC, TR = tc.TR, TI = tc.TI, row_blocks = tc.row_blocks, col_blocks = tc.col_blocks;
@@ -1052,7 +1054,8 @@ void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
     a.splits = c.wgrad_shares_thin;
     if (thin16_wgrad(c, a, s)) return;
     const int nb = (c.Cin * c.K * c.K + 31) / 32;      // 1 (up to 3x3), 2 or 4 (5x5), 4 to 7 (7x7: 5 for 3 channels)
-    dim3 grid((c.Cout + 31) / 32, a.splits, c.N * c.M), block(256);
+    a.gx = (c.Cout + 31) / 32; a.stacks = c.N * c.M;
+    dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx)), block(256);
     const ThinStream ts = c.Cin <= 4 ? stream_geom(c) : ThinStream{0, 0, 0, 1, 1, 1, 0, false};
     const bool stream = ts.fits;
     const ThinGeom g = stream ? ThinGeom{ts.cb_max, ts.lds} : thin_geom(c);

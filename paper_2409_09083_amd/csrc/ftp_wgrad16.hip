@@ -38,7 +38,7 @@ struct Wgrad16Args {
     long long n_params, w_off;
     int Cin, Cout, Hc, Wc;                          // map extent at the convolution (stride 1: input = output)
     int splits, M, batch;
-    int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_order)
+    int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
 };
 
 #define FTP_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
@@ -73,11 +73,9 @@ k_wgrad_mfma16(Wgrad16Args a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_co = wave % WAVES_CO, wave_ci = (wave / WAVES_CO) % WAVES_CI, wave_k = wave / (WAVES_CO * WAVES_CI);
     const int hi = lane >> 5, l32 = lane & 31;
-    // (block, share, stack), block fastest, in XCD order: the blocks of one stack and share read the same maps
-    int vgroup, bx;
-    if (!xcd_order(a.splits * a.stacks, a.gx, vgroup, bx)) return;
-    const int split = vgroup % a.splits;
-    const int stack = vgroup / a.splits, ti = stack / a.M, tj = stack % a.M;
+    int split, stack, bx;
+    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
     const int tiles_ci = (a.Cin + BCI - 1) / BCI;
@@ -474,7 +472,7 @@ void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s)
     const size_t lds = (size_t)2 * BCI * w16_row_bytes(waves_ci) + (size_t)kW16Groups * 64 * 20 + (size_t)kW16Groups * 4;
     const int tiles = ((c.Cout + 63) / 64) * ((c.Cin + BCI - 1) / BCI);
     a.gx = tiles; a.stacks = c.N * c.M;
-    dim3 grid(xcd_grid(a.splits * a.stacks, a.gx)), block(256);
+    dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx)), block(256);
 #define FTP_W16(WCI, HF, WSP) do { \
         static thread_local bool granted = false; \
         if (!granted) { (void)hipFuncSetAttribute((const void*)k_wgrad_mfma16<WCI, HF, WSP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); granted = true; } \

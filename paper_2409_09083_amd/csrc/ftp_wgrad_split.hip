@@ -44,7 +44,7 @@ struct WsplitArgs {
     long long n_params, w_off;
     int Cin, Cout, Hc, Wc;                          // map extent at the convolution (stride 1: input = output)
     int splits, M, batch;
-    int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_order)
+    int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
     int tc[kTabGrid];                               // column block of a chunk, per tile column
 };
 
@@ -72,11 +72,9 @@ k_wgrad_split(WsplitArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wave_co = wave % WAVES_CO, wave_ci = (wave / WAVES_CO) % WAVES_CI, wave_k = wave / (WAVES_CO * WAVES_CI);
     const int hi = lane >> 5, l32 = lane & 31;
-    // (block, share, stack), block fastest, in XCD order: the blocks of one stack and share read the same maps
-    int vgroup, bx;
-    if (!xcd_order(a.splits * a.stacks, a.gx, vgroup, bx)) return;
-    const int split = vgroup % a.splits;
-    const int stack = vgroup / a.splits, ti = stack / a.M, tj = stack % a.M;
+    int split, stack, bx;
+    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
     const int tiles_ci = (a.Cin + BCI - 1) / BCI;
@@ -447,7 +445,7 @@ void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s)
     const int wci = wsplit_waves_ci(c.Cin), wco = wsplit_waves_co(c.Cout, c.Cin);
     const int lds = 3 * 32 * (wci * kWsplitXRow + wco * kWsplitZRow) + 64;
     a.gx = ((c.Cout + 32 * wco - 1) / (32 * wco)) * ((c.Cin + 32 * wci - 1) / (32 * wci)); a.stacks = c.N * c.M;
-    dim3 grid(xcd_grid(a.splits * a.stacks, a.gx)), block(256);
+    dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx)), block(256);
 #define FTP_WS1(WCO, WCI, PL, WSP) do { \
         static thread_local bool granted = false; \
         if (!granted) { (void)hipFuncSetAttribute((const void*)k_wgrad_split<WCO, WCI, PL, WSP>, hipFuncAttributeMaxDynamicSharedMemorySize, lds); granted = true; } \

@@ -37,10 +37,12 @@ k_wgrad_thin16(MfmaWgradArgs a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, l32 = lane & 31;
-    const int stack = blockIdx.z, ti = stack / a.M, tj = stack % a.M;
+    int split, stack, bx;
+    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
-    const int co0 = blockIdx.x * 32, split = blockIdx.y;
+    const int co0 = bx * 32;
     const int col_blocks = (rw + kT16Cols - 1) / kT16Cols, row_blocks = (rh + ROWS - 1) / ROWS;
     const int TC = ((rw + col_blocks - 1) / col_blocks + 31) & ~31, steps = TC >> 5;
     const int total = a.batch * row_blocks * col_blocks;
@@ -218,7 +220,7 @@ k_wgrad_thin16(MfmaWgradArgs a)
 // Chunks are 32, 64 or 96 columns x 8 rows of one image; what lies beside the rectangle is multiplied all the same, so
 // rectangles that fill less than two fifths of their blocks of 32 x 8 keep the kernel whose chunks span images (a quarter is where
 // the two would meet).  (16 rows and 8 wavefronts: no faster.)
-bool thin16_wgrad(const ConvArgs& c, const MfmaWgradArgs& a, hipStream_t s)
+bool thin16_wgrad(const ConvArgs& c, MfmaWgradArgs& a, hipStream_t s)
 {
     if (!c.bf16 || c.K != 3 || c.S != 1 || !c.pooled || c.Cin > 3 || !c.din_ws) return false;
     if (2 * (c.Cin * c.in.cs + 16ll * c.in.pitch) > 0x7FFFFFFFll) return false;          // (32-bit offsets of the patch rows)
@@ -230,7 +232,8 @@ bool thin16_wgrad(const ConvArgs& c, const MfmaWgradArgs& a, hipStream_t s)
             padded += (double)((rw + 31) & ~31) * ((rh + 7) & ~7);
         }
     if (useful < 0.4 * padded) return false;
-    const dim3 grid((c.Cout + 31) / 32, a.splits, c.N * c.M);
+    a.gx = (c.Cout + 31) / 32; a.stacks = c.N * c.M;
+    const dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx));
     g_kernel_label = "k_wgrad_thin16";
     hipLaunchKernelGGL(k_wgrad_thin16, grid, dim3(256), 0, s, a);
     return true;

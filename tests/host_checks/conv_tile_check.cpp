@@ -50,13 +50,36 @@ static bool check_one(const int* rws, const int* rhs, int N, int M, int batch, i
             }
             for (size_t k = 0; k < hits.size(); ++k)
                 if (hits[k] != 1) { std::printf("pixel %zu covered %d times: rw %d rh %d batch %d cap0 %d S %d P %d npl %d flat %d tiles_x %d\n", k, hits[k], rw, rh, batch, cap0, S, P, npl, tc.flat, tc.tiles_x); return false; }
+            const int run = choose_row_order(tc, rws, rhs, N, M, batch);
+            if (run < 0 || run > ntiles) { std::printf("row order: unit of %d of %d tile rows\n", run, ntiles); return false; }
             if (nonempty != tile_slots(tc, rw, rh, batch)) { std::printf("tile count %lld != %lld\n", nonempty, tile_slots(tc, rw, rh, batch)); return false; }
         }
     return true;
 }
 
+// Row order: the workgroups of a launch name every (stack, channel block, tile) exactly once, whatever the unit.
+static bool check_order(int N, int M, int mblocks, int ntiles, int run)
+{
+    std::vector<int> hits((size_t)N * M * mblocks * ntiles, 0);
+    const unsigned grid = row_order_grid(N, M, mblocks, ntiles, run);
+    for (unsigned b = 0; b < grid; ++b) {
+        int vgroup, vtile;
+        if (!row_order((int)b, N, M, mblocks, ntiles, run, vgroup, vtile)) continue;
+        if (vgroup < 0 || vgroup >= N * M * mblocks || vtile < 0) { std::printf("row order: group %d tile %d\n", vgroup, vtile); return false; }
+        ++hits[(size_t)vgroup * ntiles + vtile];
+    }
+    for (int h : hits) if (h != 1) { std::printf("row order: N %d M %d blocks %d tiles %d run %d: named %d times\n", N, M, mblocks, ntiles, run, h); return false; }
+    return true;
+}
+
 int main()
 {
+    for (int N = 1; N <= 9; N += 2)
+        for (int M = 1; M <= 4; M += 3)
+            for (int mblocks = 1; mblocks <= 4; mblocks += 3)
+                for (int ntiles = 1; ntiles <= 40; ntiles += 3)
+                    for (int run = 1; run <= ntiles; run += run < 4 ? 1 : 7)
+                        if (!check_order(N, M, mblocks, ntiles, run)) return 1;
     // (K, pixels per tile, pooled / strided forward, loading mode) as the kernel is instantiated
     struct Mode { int K, BN, S, npl; bool strided; };
     const Mode modes[] = {
