@@ -175,10 +175,10 @@ bool overlap_default()
     return e && std::strcmp(e, "1") == 0;
 }
 
-// Relays the filters of all the convolutions of a pass that take the matrix cores, in one launch.
-void prep_pass(const Plan& p, const void* const* weights, void* workspace, bool backward, hipStream_t s)
+// The filter relayout of all the convolutions of a pass that take the matrix cores: the jobs of one launch, left to the caller; those of
+// networks with more of them are launched here.
+int prep_jobs(const Plan& p, const void* const* weights, void* workspace, bool backward, PrepJob (&jobs)[kPrepJobs], hipStream_t s)
 {
-    PrepJob jobs[kPrepJobs];
     int n = 0;
     for (const Unit& u : p.units) {
         if (u.kind != UNIT_CONV) continue;
@@ -187,9 +187,17 @@ void prep_pass(const Plan& p, const void* const* weights, void* workspace, bool 
         a.w = weights[u.layer]; a.K = ly.k; a.S = ly.stride; a.Cin = ly.cin; a.Cout = ly.cout;
         a.Hc = p.H[u.layer + 1]; a.Wc = p.W[u.layer + 1]; a.batch = p.batch; a.pooled = u.pooled ? 1 : 0; a.bf16 = p.dtype == FTP_BF16;
         if (!mfma_conv_eligible(a, backward)) continue;
-        jobs[n++] = mfma_prep_job(a, (char*)workspace + (backward ? u.wt_bwd_offset : u.wt_offset), backward);
         if (n == kPrepJobs) { prep_filters(jobs, n, s); n = 0; }
+        jobs[n++] = mfma_prep_job(a, (char*)workspace + (backward ? u.wt_bwd_offset : u.wt_offset), backward);
     }
+    return n;
+}
+
+// ... in a launch of its own.
+void prep_pass(const Plan& p, const void* const* weights, void* workspace, bool backward, hipStream_t s)
+{
+    PrepJob jobs[kPrepJobs];
+    const int n = prep_jobs(p, weights, workspace, backward, jobs, s);
     if (n) prep_filters(jobs, n, s);
 }
 
@@ -311,7 +319,7 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
     if (any_bias(p) && !biases) return FTP_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     UserBufs ub; ub.x = x; ub.y = y; ub.ws = workspace;
-    bool relaid = false;                             // (with the first convolution that needs it, whose timing record it belongs to)
+    bool relaid = false;                             // (with the first matrix-core kernel, whose timing record it belongs to)
     for (const Unit& u : p.units) {
         if (u.kind == UNIT_CONV) {
             ConvArgs a = conv_args(p, u, ub, weights, biases);
@@ -325,7 +333,13 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
                     if (mfma_conv_fwd(a, ext, wt, s)) direct_conv_fwd(a, s);
                 });
             } else if (use_mfma() && stem_fwd_eligible(a)) {
-                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { stem_fwd(a, s); });
+                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] {
+                    PrepJob jobs[kPrepJobs];
+                    int n = relaid ? 0 : prep_jobs(p, weights, workspace, false, jobs, s);
+                    if (n > kPrepFew) { prep_filters(jobs, n, s); n = 0; }
+                    relaid = true;
+                    stem_fwd(a, jobs, n, s);
+                });
             } else {
                 rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { direct_conv_fwd(a, s); });
             }
@@ -373,12 +387,16 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
     hipStream_t s = (hipStream_t)stream;
     UserBufs ub; ub.x = x; ub.dy = dy; ub.dx = dx; ub.ws = workspace;
     const int L = p.n_layers;
+    bool relaid = false;                             // (with the scaling of dy, or the first delta that needs it)
     if (p.act_slope[L] >= 0.0f) {
         // deltas are kept as dLoss/dZ: fold the last activation's derivative into a copy of dy
         const uint32_t* sg = (const uint32_t*)((const char*)workspace + p.sign[L].offset);
         void* dst = (char*)workspace + p.dy_scaled.offset;
         rc = timed(plan, FTP_PASS_SCALE_DY, p.units.back().layer, s, [&] {
-            scale_dy(dy, sg, dst, p.batch, p.C[L], (long long)p.H[L] * p.W[L], p.act_slope[L], p.dtype == FTP_BF16, s);
+            PrepJob jobs[kPrepJobs];
+            const int n = use_mfma() ? prep_jobs(p, weights, workspace, true, jobs, s) : 0;
+            relaid = true;
+            scale_dy(dy, sg, dst, p.batch, p.C[L], (long long)p.H[L] * p.W[L], p.act_slope[L], p.dtype == FTP_BF16, jobs, n, s);
         });
         if (rc != FTP_OK) return rc;
     }
@@ -413,7 +431,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
         aux = (hipStream_t)ov.aux;
         if ((rc = order(s, aux)) != FTP_OK) return rc;          // the forward pass, dy scaling, earlier calls
     }
-    bool gradient_in_flight = false, relaid = false;
+    bool gradient_in_flight = false;
     for (int i = (int)p.units.size() - 1; i >= 0; --i) {
         const Unit& u = p.units[i];
         if (u.kind == UNIT_CONV) {
@@ -429,7 +447,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             int shares = 1;
             auto with_bias = [&](void (*gradient)(const ConvArgs&, float*, hipStream_t)) {
                 gradient(a, scratch, aux);
-                if (a.has_bias) bias_grad(a, aux);
+                if (a.has_bias && !(shares > 1 && bias_small(a))) bias_grad(a, aux);
             };
             const bool cores = use_mfma() && wgrad_bias_pays(a);
             if (cores && thin_wgrad_eligible(a)) {
@@ -448,7 +466,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { direct_wgrad(a, aux); });
             }
             if (rc == FTP_OK && shares > 1)
-                rc = timed(plan, FTP_PASS_WGRAD_SUM, u.layer, aux, [&] { wgrad_share_sum(a, scratch, shares, aux); });
+                rc = timed(plan, FTP_PASS_WGRAD_SUM, u.layer, aux, [&] { wgrad_share_sum(a, scratch, shares, a.has_bias && bias_small(a), aux); });
             if (rc != FTP_OK) return rc;
             gradient_in_flight = overlap;
             a.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);

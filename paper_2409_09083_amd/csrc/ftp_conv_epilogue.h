@@ -23,7 +23,7 @@ __device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) {
 __device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int& vgroup, int& vtile)
 {
     const int ntiles = a.tiles_x * a.tiles_r;
-    if (a.row_run) return row_order((int)blockIdx.x, a.stacks / a.M, a.M, a.mblocks, ntiles, a.row_run, vgroup, vtile);
+    if (__builtin_expect(a.row_run, 0)) return row_order((int)blockIdx.x, a.stacks / a.M, a.M, a.mblocks, ntiles, a.row_run, vgroup, vtile);
     if (a.xcd_groups) return xcd_order(a.mblocks * a.stacks, ntiles, vgroup, vtile);
     vgroup = (int)blockIdx.x / ntiles; vtile = (int)blockIdx.x - vgroup * ntiles;
     return true;

@@ -227,8 +227,9 @@ inline int choose_row_order(const TileChoice& tc, const int* rws, const int* rhs
     for (int j = 0; j < M; ++j) mw = mw > rws[j] ? mw : rws[j];
     for (int i = 0; i < N; ++i) { rows[i] = (int)tile_slots(tc, mw, rhs[i], batch); all += rows[i]; }
     int best = 0;
-    double best_cost = 1.15 * (double)all / 8.0;
-    for (int per = 1; per <= 64; per *= 2) {           // units of a grid row
+    // (16 bits, 204 -> 256 channels, 9 images of 53 x 249, 1040 workgroups: 12 % more on one XCD than on average, 0.158 -> 0.177 ms)
+    double best_cost = 1.04 * (double)all / 8.0;
+    for (int per : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32, 64}) {       // units of a grid row
         const int run = (ntiles + per - 1) / per;
         long long load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
         const int have = (ntiles + run - 1) / run;
@@ -239,12 +240,10 @@ inline int choose_row_order(const TileChoice& tc, const int* rws, const int* rhs
             }
         long long most = 0;
         for (int x = 0; x < 8; ++x) most = most > load[x] ? most : load[x];
-        const double cost = (double)most * (1.0 + 0.05 / run);
+        const double cost = (double)most * (1.0 + 0.02 / run);
         if (cost < best_cost) { best_cost = cost; best = run; }
         if (run == 1) break;
     }
-    // (single tile rows: at most one of them more on one XCD than on another)
-    if (1.05 * (double)((all + 7) / 8) < best_cost) best = 1;
     return best;
 }
 

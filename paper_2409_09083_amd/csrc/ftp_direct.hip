@@ -3,7 +3,9 @@
 // One workgroup serves one (stack, image); stacks only read the rectangles the plan entitles them to.
 #include "ftp_device.h"
 #include "ftp_launch.h"
+#include "ftp_prep.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace ftp {
 
@@ -256,17 +258,19 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
 // that do not compute it.  A workgroup is a channel and stack: where that leaves each many deltas (above 8192), 16 wavefronts with
 // 8 loads of a thread in flight (16 channels, one stack, 16 images of 104^2: 200 us less than 4 wavefronts with one); below, the
 // counting of what is in flight costs more than it saves (three layers of 272 deltas a stack: 6 us of a step of 146).
+struct BiasArgs { View din; RectTab own; float* partial; long long n_params, b_off; int pooled, Hp, Wp, M, batch; };
+
 template <typename T, int kBiasThreads, int U>
-__global__ void __launch_bounds__(kBiasThreads)
-k_bias_grad(View din, RectTab own, float* __restrict__ partial, long long n_params, long long b_off, int pooled, int Hp, int Wp, int M, int batch)
+__device__ __forceinline__ void bias_block(const BiasArgs& a, int co, int stack)
 {
-    const int co = blockIdx.x, stack = blockIdx.y, ti = stack / M, tj = stack % M;
-    int x0 = own.x0[tj], x1 = own.x1[tj], y0 = own.y0[ti], y1 = own.y1[ti];
-    if (pooled) {
+    const View& din = a.din;
+    const int ti = stack / a.M, tj = stack % a.M, batch = a.batch;
+    int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
+    if (a.pooled) {
         // (windows whose first pixel is owned; a pool fused with its convolution has whole windows in every rectangle)
         x0 = (x0 + 1) >> 1; y0 = (y0 + 1) >> 1; x1 >>= 1; y1 >>= 1;
-        if (x1 >= Wp) x1 = Wp - 1;
-        if (y1 >= Hp) y1 = Hp - 1;
+        if (x1 >= a.Wp) x1 = a.Wp - 1;
+        if (y1 >= a.Hp) y1 = a.Hp - 1;
     }
     const int rw = x1 - x0 + 1, px = rw * (y1 - y0 + 1);
     float v[U];
@@ -300,7 +304,48 @@ k_bias_grad(View din, RectTab own, float* __restrict__ partial, long long n_para
         float s = 0.0f;
 #pragma unroll
         for (int k = 0; k < kBiasThreads / 64; ++k) s += red[k];
-        partial[(long long)stack * n_params + b_off + co] = s;
+        a.partial[(long long)stack * a.n_params + a.b_off + co] = s;
+    }
+}
+
+template <typename T, int kBiasThreads, int U>
+__global__ void __launch_bounds__(kBiasThreads)
+k_bias_grad(BiasArgs a)
+{
+    bias_block<T, kBiasThreads, U>(a, blockIdx.x, blockIdx.y);
+}
+
+// Sum of the batch shares of one layer's partial gradient, in share order.  V = 4: four consecutive parameters per thread,
+// the shares' 16-byte loads four at a time in flight (layers whose parameter count is a multiple of 4); V = 1 otherwise.
+// The sum of a small layer's bias gradient (bias_block, BIAS: further blocks) travels along: a launch less a layer.
+template <typename T, int V, bool BIAS>
+__global__ void __launch_bounds__(256)
+k_wgrad_splitk_reduce(const float* __restrict__ scratch, float* __restrict__ partial, long long layer_params, long long n_params,
+                      long long w_off, int splits, int blocks, BiasArgs bias)
+{
+    if constexpr (BIAS) {
+        if ((int)blockIdx.x >= blocks) { bias_block<T, 256, 1>(bias, (int)blockIdx.x - blocks, blockIdx.y); return; }
+    }
+    const long long i = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * V;
+    const int stack = blockIdx.y;
+    if (i >= layer_params) return;
+    const float* src = scratch + (long long)stack * splits * layer_params + i;
+    float* dst = partial + (long long)stack * n_params + w_off + i;
+    if constexpr (V == 4) {
+        auto ld4 = [&](int sh) { return *(const float4*)(src + (long long)sh * layer_params); };
+        auto add = [](float4& v, const float4& b) { v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w; };
+        float4 v = ld4(0);
+        int sh = 1;
+        for (; sh + 3 < splits; sh += 4) {
+            const float4 b0 = ld4(sh), b1 = ld4(sh + 1), b2 = ld4(sh + 2), b3 = ld4(sh + 3);
+            add(v, b0); add(v, b1); add(v, b2); add(v, b3);
+        }
+        for (; sh < splits; ++sh) add(v, ld4(sh));
+        dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;     // (the layer's place in the parameter vector need not be 16-byte aligned)
+    } else {
+        float v = src[0];
+        for (int sh = 1; sh < splits; ++sh) v += src[(long long)sh * layer_params];
+        dst[0] = v;
     }
 }
 
@@ -527,18 +572,45 @@ void direct_conv_fwd(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_con
 void direct_conv_bwd_data(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_conv_bwd_data_direct"; if (a.bf16) conv_bwd_data_t<bf16_t>(a, s); else conv_bwd_data_t<float>(a, s); }
 void direct_wgrad(const ConvArgs& a, hipStream_t s) { g_kernel_label = "k_wgrad_direct"; if (a.bf16) wgrad_t<bf16_t>(a, s); else wgrad_t<float>(a, s); }
 
+namespace {
+
+BiasArgs bias_args(const ConvArgs& a) { return BiasArgs{a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch}; }
+
+}  // namespace
+
 // a.rect = owned rectangle at the convolution output (before the pool)
-void bias_grad(const ConvArgs& a, hipStream_t s)
+bool bias_small(const ConvArgs& a)
 {
     int rw = 0, rh = 0;
     for (int j = 0; j < a.M; ++j) rw = std::max(rw, a.rect.x1[j] - a.rect.x0[j] + 1);
     for (int i = 0; i < a.N; ++i) rh = std::max(rh, a.rect.y1[i] - a.rect.y0[i] + 1);
-    const double deltas = (double)rw * rh * a.batch / (a.pooled ? 4 : 1);
+    return (double)rw * rh * a.batch / (a.pooled ? 4 : 1) <= 8192;
+}
+
+void bias_grad(const ConvArgs& a, hipStream_t s)
+{
+    const bool small = bias_small(a);
     const dim3 grid(a.Cout, a.N * a.M);
-#define FTP_BG(T, TH, U) hipLaunchKernelGGL((k_bias_grad<T, TH, U>), grid, dim3(TH), 0, s, a.din, a.rect, a.partial, a.n_params, a.b_off, a.pooled, a.Hc >> 1, a.Wc >> 1, a.M, a.batch)
-    if (a.bf16) { if (deltas > 8192) FTP_BG(bf16_t, 1024, 8); else FTP_BG(bf16_t, 256, 1); }
-    else        { if (deltas > 8192) FTP_BG(float, 1024, 8); else FTP_BG(float, 256, 1); }
+#define FTP_BG(T, TH, U) hipLaunchKernelGGL((k_bias_grad<T, TH, U>), grid, dim3(TH), 0, s, bias_args(a))
+    if (a.bf16) { if (small) FTP_BG(bf16_t, 256, 1); else FTP_BG(bf16_t, 1024, 8); }
+    else        { if (small) FTP_BG(float, 256, 1); else FTP_BG(float, 1024, 8); }
 #undef FTP_BG
+}
+
+// Sums the `shares` partial results one of the filter-gradient kernels left in the scratch area into the layer's place
+// in the per-stack gradient vectors, in share order; with the bias gradient where `bias` says so.
+void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, bool bias, hipStream_t s)
+{
+    const long long lp = (long long)c.Cout * c.Cin * c.K * c.K;
+    g_kernel_label = "k_wgrad_splitk_reduce";
+    // (the share scratch is 256-byte aligned, so with a parameter count that is a multiple of 4 every share's slice is too)
+    const int V = lp % 4 == 0 && ((uintptr_t)scratch & 15) == 0 ? 4 : 1, blocks = (int)((lp / V + 255) / 256);
+    const dim3 grid((unsigned)(blocks + (bias ? c.Cout : 0)), c.N * c.M);
+#define FTP_SR(T, VV, B) hipLaunchKernelGGL((k_wgrad_splitk_reduce<T, VV, B>), grid, dim3(256), 0, s, scratch, c.partial, lp, c.n_params, c.w_off, shares, blocks, bias_args(c))
+    if (!bias)       { if (V == 4) FTP_SR(float, 4, false); else FTP_SR(float, 1, false); }
+    else if (c.bf16) { if (V == 4) FTP_SR(bf16_t, 4, true); else FTP_SR(bf16_t, 1, true); }
+    else             { if (V == 4) FTP_SR(float, 4, true); else FTP_SR(float, 1, true); }
+#undef FTP_SR
 }
 
 void pool_fwd(const PoolArgs& a, hipStream_t s)
@@ -566,46 +638,63 @@ void pool_bwd(const PoolArgs& a, hipStream_t s)
 #undef FTP_PB
 }
 
-// 4 consecutive elements of one (image, channel) plane per thread (HW is a multiple of 4: the rows of a plane and of
-// the sign words then stay 16-byte aligned), else one element per thread.
-template <typename T, int V>
+// A thread handles V consecutive pixels (16 bytes; one, where rows of a plane do not start on 16 bytes) of kScaleCh channels: their
+// loads are in flight together and share the pixels' sign words, which cost as much traffic as the deltas with a channel a thread (16
+// bits, 64 channels of 152^2, 32 images: 47 -> 39 us, at the rate of a copy).  The blocks behind the last one relay filters.
+constexpr int kScaleCh = 4;
+struct ScaleArgs { const void* dy; const uint32_t* sign; void* dst; int C, groups, per, blocks; long long HW; float slope; };
+
+template <typename T, int V, int CAP>
 __global__ void __launch_bounds__(256)
-k_scale_dy(const T* __restrict__ dy, const uint32_t* __restrict__ sign, T* __restrict__ dst, int C, long long HW, long long total, float slope)
+k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
 {
-    const long long e = ((long long)blockIdx.x * blockDim.x + threadIdx.x) * V;
-    if (e >= total) return;
-    const long long plane = e / HW, off = e - plane * HW;
-    const int c = (int)(plane % C), G = (C + 31) / 32;
-    const long long n = plane / C;
-    const uint32_t* sg = sign + (n * G + (c >> 5)) * HW + off;
-    if (V == 4 && sizeof(T) == 4) {
-        const float4 v = *(const float4*)(dy + e);
-        const uint4 w = *(const uint4*)sg;
-        float4 r;
-        r.x = scaled_delta<T>(v.x, (w.x >> (c & 31)) & 1u, slope);
-        r.y = scaled_delta<T>(v.y, (w.y >> (c & 31)) & 1u, slope);
-        r.z = scaled_delta<T>(v.z, (w.z >> (c & 31)) & 1u, slope);
-        r.w = scaled_delta<T>(v.w, (w.w >> (c & 31)) & 1u, slope);
-        *(float4*)(dst + e) = r;
-    } else {
+    if ((int)blockIdx.x >= a.blocks) { prep_block(prep, (int)blockIdx.x - a.blocks); return; }
+    const int image = (int)blockIdx.x / a.per;
+    const unsigned i = ((unsigned)blockIdx.x - (unsigned)(image * a.per)) * 256u + threadIdx.x, units = (unsigned)(a.HW / V);
+    const unsigned g = i / units;
+    if (g >= (unsigned)a.groups) return;
+    const int c0 = kScaleCh * (int)g;
+    const long long off = (long long)(i - g * units) * V, plane = (long long)image * a.C + c0;
+    const uint32_t* const sg = a.sign + ((long long)image * ((a.C + 31) >> 5) + (c0 >> 5)) * a.HW + off;
+    const T* const src = (const T*)a.dy + plane * a.HW + off;
+    T* const dst = (T*)a.dst + plane * a.HW + off;
+    struct alignas(V * sizeof(T)) Unit { T e[V]; };
+    Unit d[kScaleCh];
+    uint32_t w[V];
 #pragma unroll
-        for (int u = 0; u < V; ++u) st(dst + e + u, scaled_delta<T>(ld(dy + e + u), (sg[u] >> (c & 31)) & 1u, slope));
+    for (int u = 0; u < V; ++u) w[u] = sg[u] >> (c0 & 31);
+#pragma unroll
+    for (int k = 0; k < kScaleCh; ++k) if (c0 + k < a.C) d[k] = *(const Unit*)(src + k * a.HW);
+#pragma unroll
+    for (int k = 0; k < kScaleCh; ++k) {
+        if (c0 + k >= a.C) break;
+#pragma unroll
+        for (int u = 0; u < V; ++u) st(&d[k].e[u], scaled_delta<T>(ld(&d[k].e[u]), (w[u] >> k) & 1u, a.slope));
+        *(Unit*)(dst + k * a.HW) = d[k];
     }
 }
 
-void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C, long long HW, float slope, int bf16, hipStream_t s)
+void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C, long long HW, float slope, int bf16, const PrepJob* jobs, int n, hipStream_t s)
 {
     g_kernel_label = "k_scale_dy";
-    const long long total = (long long)batch * C * HW;
-    const int V = HW % 4 == 0 ? 4 : 1;
-    dim3 grid((unsigned)((total / V + 255) / 256)), block(256);
-    if (bf16) {
-        if (V == 4) hipLaunchKernelGGL((k_scale_dy<bf16_t, 4>), grid, block, 0, s, (const bf16_t*)dy, sign, (bf16_t*)dst, C, HW, total, slope);
-        else        hipLaunchKernelGGL((k_scale_dy<bf16_t, 1>), grid, block, 0, s, (const bf16_t*)dy, sign, (bf16_t*)dst, C, HW, total, slope);
-    } else {
-        if (V == 4) hipLaunchKernelGGL((k_scale_dy<float, 4>), grid, block, 0, s, (const float*)dy, sign, (float*)dst, C, HW, total, slope);
-        else        hipLaunchKernelGGL((k_scale_dy<float, 1>), grid, block, 0, s, (const float*)dy, sign, (float*)dst, C, HW, total, slope);
-    }
+    const int V = bf16 ? 8 : 4;
+    const bool wide = HW % V == 0 && (((uintptr_t)dy | (uintptr_t)dst | (uintptr_t)sign) & 15) == 0;
+    ScaleArgs a{dy, sign, dst, C, (C + kScaleCh - 1) / kScaleCh, 0, 0, HW, slope};
+    a.per = (int)(((long long)a.groups * (HW / (wide ? V : 1)) + 255) / 256);
+    a.blocks = a.per * batch;
+    auto launch = [&](auto cap) {
+        constexpr int CAP = decltype(cap)::value;
+        PrepArgs<CAP> p;
+        const dim3 grid((unsigned)(a.blocks + fill_prep(p, jobs, n)));
+        if (bf16) {
+            if (wide) hipLaunchKernelGGL((k_scale_dy<bf16_t, 8, CAP>), grid, dim3(256), 0, s, a, p);
+            else      hipLaunchKernelGGL((k_scale_dy<bf16_t, 1, CAP>), grid, dim3(256), 0, s, a, p);
+        } else {
+            if (wide) hipLaunchKernelGGL((k_scale_dy<float, 4, CAP>), grid, dim3(256), 0, s, a, p);
+            else      hipLaunchKernelGGL((k_scale_dy<float, 1, CAP>), grid, dim3(256), 0, s, a, p);
+        }
+    };
+    if (n <= kPrepFew) launch(std::integral_constant<int, kPrepFew>()); else launch(std::integral_constant<int, kPrepJobs>());
 }
 
 void sgd_update(const float* partial, long long n_params, int stacks, void* w, long long count, float lr, float* wgrad,

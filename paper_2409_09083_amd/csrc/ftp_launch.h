@@ -63,8 +63,11 @@ struct PoolArgs {
 void sgd_update(const float* partial, long long n_params, int stacks, void* w, long long count, float lr, float* wgrad,
                 int bf16, hipStream_t s);
 
-// dst = dy * (activation > 0 ? 1 : slope) over a whole map [batch][C][HW]; sign = packed signs of that boundary.
-void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C, long long HW, float slope, int bf16, hipStream_t s);
+struct PrepJob;
+
+// dst = dy * (activation > 0 ? 1 : slope) over a whole map [batch][C][HW]; sign = packed signs of that boundary.  The n <= kPrepJobs jobs of
+// filter relayout run in the same launch.
+void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C, long long HW, float slope, int bf16, const PrepJob* jobs, int n, hipStream_t s);
 
 // Kernel argument block of the matrix-core convolution (forward and delta back-propagation).
 struct MfmaConvArgs {
@@ -103,6 +106,7 @@ enum PrepKind : int {
     PREP_PACK16 = 1,                                // bfloat [tap][8 channels][output channel][8]
     PREP_SPLIT = 2                                  // fp32 as three planes of bfloats [8 channels][tap][plane][output channel][8]
 };
+constexpr int kPrepFew = 8;                         // jobs that travel with another kernel's arguments
 constexpr int kPrepJobs = 48;                       // jobs of one launch (kernel arguments: 48 bytes a job)
 struct PrepJob {
     const void* w;                                  // filter, OIHW
@@ -181,12 +185,12 @@ bool wgrad_split_eligible(const ConvArgs& c);
 void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
 // The three matrix-core filter-gradient kernels leave `shares` > 1 partial results per stack in the scratch area;
-// this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own).
-void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, hipStream_t s);
+// this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own), with `bias` the bias gradient too.
+void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, bool bias, hipStream_t s);
 
 // forward pass of first layers on the fp32 matrix cores (ftp_stem_fwd.hip)
 bool stem_fwd_eligible(const ConvArgs& a);
-void stem_fwd(const ConvArgs& a, hipStream_t s);
+void stem_fwd(const ConvArgs& a, const PrepJob* jobs, int n, hipStream_t s);      // n <= kPrepFew jobs of filter relayout in the same launch
 bool thin_bwd_data_strided_eligible(const ConvArgs& a);
 void thin_conv_bwd_data_strided(const ConvArgs& a, const RectTab& ext, hipStream_t s);   // ext: extent of the delta view per stack
 bool thin_bwd_data_eligible(const ConvArgs& a);
@@ -199,6 +203,7 @@ bool thin16_wgrad(const ConvArgs& a, MfmaWgradArgs& m, hipStream_t s);      // (
 void direct_conv_fwd(const ConvArgs& a, hipStream_t s);
 void direct_conv_bwd_data(const ConvArgs& a, hipStream_t s);
 void direct_wgrad(const ConvArgs& a, hipStream_t s);
+bool bias_small(const ConvArgs& a);                 // few deltas a stack: the sum can travel with that of the shares
 void bias_grad(const ConvArgs& a, hipStream_t s);   // (direct_wgrad computes it itself, the other filter-gradient kernels do not)
 void pool_fwd(const PoolArgs& a, hipStream_t s);
 void pool_bwd(const PoolArgs& a, hipStream_t s);

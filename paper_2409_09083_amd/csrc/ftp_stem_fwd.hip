@@ -7,8 +7,8 @@
 // this one replaces, at twice their rate: 4 products of 64 lanes take 4 wavefront instructions there, 16 cycles, and 8 here.
 //
 // A wavefront multiplies 32 channels x 64 pixels a turn, as 2 blocks of 16 channels x 4 sets of 16 pixels.  Behind a pool set p
-// holds position p of 16 windows, so that a lane has all four candidates of its windows in its own registers; without one the
-// sets are 64 consecutive pixels of the tile.  The tile's patch (all input channels, zero beside the map) and the filters of 32 channels
+// holds position p of 16 windows, so that a lane has all four candidates of its windows in its own registers; without one it holds
+// pixel p of 16 groups of 4 neighbours, which a lane stores together (16 bytes, fp32).  The tile's patch (all input channels, zero beside the map) and the filters of 32 channels
 // sit in LDS: a step of 4 k reads one dword a set and a block, at an offset per k that a lane looks up (K = 3: keeps).
 // Lane layout: A[m = lane%16][k = lane/16], B[k = lane/16][n = lane%16], D[m = 4*(lane/16) + i][n = lane%16], i < 4: a lane
 // ends up with 4 consecutive channels of its pixel.
@@ -18,9 +18,12 @@
 // What bounds it: the matrix instructions (0.14 ms there) and the vector ALU work of the epilogue (about 27 instructions a window and
 // channel), which do not run beside each other: fp32 matrix instructions keep the SIMD's vector ALU busy; then the stores.
 // Launches that do not fill the chip: latency.  Vector ALU -> this: 3 -> 32 with a pool 0.407 -> 0.325 ms (16 bits, 32 images of
-// 608^2), 0.85 -> 0.73 (fp32, 64 images); 3 -> 16, one image of 416^2: 20 -> 10 us; 7x7/2 3 -> 64, 32 images of 607^2: 1.55 -> 0.83 ms.
+// 608^2), 0.85 -> 0.73 (fp32, 64 images); 3 -> 16, one image of 416^2: 20 -> 10 us; 7x7/2 3 -> 64, 32 images of 607^2: 1.55 -> 0.83 ms; with 4
+// neighbours a lane, stored together, 0.77 (3 -> 16 without a pool, 23 images of 548 x 247, 16 bits: 118 us on the vector ALU, 142 with single
+// stores, 116).
 #include "ftp_device.h"
 #include "ftp_launch.h"
+#include "ftp_prep.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -36,6 +39,7 @@ struct StemArgs {
     float slope;
     int N, M;
     int tw, th, tiles_x, tiles_y;                      // tiles, in output pixels
+    int blocks;                                        // of the convolution; those behind relay filters
     int strips, lines, xcd;                            // runs of tiles of a stack one below the other; such runs of all images and grid rows; 1: xcd_order
     int run;                                           // tiles one below the other that a workgroup takes
     int plain;                                         // no bias, slope in (0, 1]
@@ -58,6 +62,18 @@ __device__ __forceinline__ void stem_store(__amdgpu_buffer_rsrc_t r, unsigned vo
     __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(__float_as_uint(v) >> 16), r, vo, so, 0);      // (already rounded)
 }
 
+// ... of 4 neighbours (already rounded), which start on a dword
+__device__ __forceinline__ void stem_store4(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, const float (&v)[4], const float*)
+{
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128((v4u){__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, r, vo, so, 0);
+}
+__device__ __forceinline__ void stem_store4(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, const float (&v)[4], const bf16_t*)
+{
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64((v2u){__builtin_amdgcn_perm(__float_as_uint(v[1]), __float_as_uint(v[0]), 0x07060302u), __builtin_amdgcn_perm(__float_as_uint(v[3]), __float_as_uint(v[2]), 0x07060302u)}, r, vo, so, 0);
+}
+
 __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
     typedef __bf16 v2b __attribute__((ext_vector_type(2)));
@@ -76,8 +92,9 @@ __device__ __forceinline__ float stem_load(__amdgpu_buffer_rsrc_t r, unsigned vo
 
 template <typename T, int K, int S, bool POOL, int CI>
 __global__ void __launch_bounds__(256, 3)
-k_conv_fwd_stem(StemArgs a)
+k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
 {
+    if ((int)blockIdx.x >= a.blocks) { prep_block(prep, (int)blockIdx.x - a.blocks); return; }       // filters of the layers behind
     constexpr int KK = K * K, P = K / 2, STEPS = stem_steps(K, CI), NP = POOL ? 2 : 1;
     constexpr unsigned ES = sizeof(T);
     extern __shared__ __attribute__((aligned(16))) float lds[];
@@ -174,7 +191,8 @@ k_conv_fwd_stem(StemArgs a)
 
     const int count = a.tw * a.th, turns = POOL ? (count + 15) >> 4 : (count + 63) >> 6;
     const float rtw = 1.0f / (float)a.tw;
-    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((T*)a.out.p + (long long)stack * a.out.ss + (long long)n * a.out.ns), (short)0, 0x7FFFFFFF, 0x00020000);
+    T* const obase = (T*)a.out.p + (long long)stack * a.out.ss + (long long)n * a.out.ns;
+    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc((void*)obase, (short)0, 0x7FFFFFFF, 0x00020000);
     const __amdgpu_buffer_rsrc_t mrsrc = __builtin_amdgcn_make_buffer_rsrc(POOL ? (void*)((uint8_t*)a.mask.p + (long long)stack * a.mask.ss + (long long)n * a.mask.ns) : (void*)a.out.p, (short)0, 0x7FFFFFFF, 0x00020000);
     const unsigned ocs = ES * (unsigned)a.out.cs, mcs = (unsigned)a.mask.cs;
     float slope = a.slope;
@@ -184,17 +202,12 @@ k_conv_fwd_stem(StemArgs a)
         constexpr int NB = decltype(blocks)::value;    // blocks of 16 channels
         // this lane's pixels (pool: one window): patch position, output coordinates
         constexpr int NO = POOL ? 1 : 4;
-        int base[NO], oy[NO], ox[NO];
-        bool valid[NO];
-#pragma unroll
-        for (int o = 0; o < NO; ++o) {
-            const int f = POOL ? 16 * r + n16 : 64 * r + 16 * o + n16;
-            int wy = (int)(((float)f + 0.5f) * rtw), wx = f - wy * a.tw;
-            oy[o] = oy0 + wy; ox[o] = ox0 + wx;
-            valid[o] = f < count && oy[o] <= y1 && ox[o] <= x1;
-            if (f >= count) { wy = 0; wx = 0; }
-            base[o] = S * NP * (wy * PP + wx);
-        }
+        const int f = POOL ? 16 * r + n16 : 64 * r + 4 * n16;
+        int wy = (int)(((float)f + 0.5f) * rtw), wx = f - wy * a.tw;
+        const int oy = oy0 + wy, ox = ox0 + wx;
+        const int there = f < count && oy <= y1 ? (x1 - ox + 1 < NO ? x1 - ox + 1 : NO) : 0;      // of them, from the first on
+        if (f >= count) { wy = 0; wx = 0; }
+        const int base = S * NP * (wy * PP + wx);
         v4f acc[NB][4];
 #pragma unroll
         for (int b = 0; b < NB; ++b)
@@ -205,7 +218,7 @@ k_conv_fwd_stem(StemArgs a)
 #pragma unroll
             for (int b = 0; b < NB; ++b) av[b] = wl[(b * STEPS + j) * 64 + lane];
 #pragma unroll
-            for (int p = 0; p < 4; ++p) bv[p] = POOL ? (xp + base[0] + o)[(p >> 1) * PP + (p & 1)] : xp[base[POOL ? 0 : p] + o];
+            for (int p = 0; p < 4; ++p) bv[p] = (xp + base + o)[POOL ? (p >> 1) * PP + (p & 1) : S * p];
             if (4 * STEPS != CI * KK && j == STEPS - 1) {
                 // the last k of the last step is none: its product is 0 * 0, whatever the map holds
                 static_assert(4 * STEPS - CI * KK <= 1, "one missing k");
@@ -226,14 +239,15 @@ k_conv_fwd_stem(StemArgs a)
             step(STEPS - 1, offs[4 * (STEPS - 1) + q]);
         }
         // ---- bias, leaky ReLU, pool, stores: this lane's channels are c0 + 16 b + 4 q + i ------------------------------------
-        unsigned vo[NO], mo = kOobStem;
-        bool owned[NO];
-#pragma unroll
-        for (int o = 0; o < NO; ++o) {
-            owned[o] = valid[o] && oy[o] >= a.own.y0[ti] && oy[o] <= a.own.y1[ti] && ox[o] >= a.own.x0[tj] && ox[o] <= a.own.x1[tj];
-            vo[o] = valid[o] ? ES * (unsigned)((oy[o] - a.out.y0[ti]) * a.out.pitch + (ox[o] - a.out.x0[tj])) + (unsigned)(4 * q) * ocs : kOobStem;
-        }
-        if (POOL && owned[0]) mo = (unsigned)((oy[0] - a.mask.y0[ti]) * a.mask.pitch + (ox[0] - a.mask.x0[tj])) + (unsigned)(4 * q) * mcs;
+        const unsigned at_out = ES * (unsigned)((oy - a.out.y0[ti]) * a.out.pitch + (ox - a.out.x0[tj])) + (unsigned)(4 * q) * ocs;
+        // whole groups of 4 go out at once where they start on a dword, others pixel by pixel
+        const bool whole = POOL ? there > 0 : there == NO && ((ES == 4) || (((unsigned)(uintptr_t)obase | ocs | at_out) & 3u) == 0u);
+        const unsigned vo = whole ? at_out : kOobStem, vp = there > 0 && !whole ? at_out : kOobStem;
+        const bool pieces = !POOL && __builtin_amdgcn_ballot_w64(there > 0 && !whole) != 0ull;
+        unsigned mo = kOobStem;
+        const bool row_owned = there > 0 && oy >= a.own.y0[ti] && oy <= a.own.y1[ti];
+        if (POOL && row_owned && ox >= a.own.x0[tj] && ox <= a.own.x1[tj])
+            mo = (unsigned)((oy - a.mask.y0[ti]) * a.mask.pitch + (ox - a.mask.x0[tj])) + (unsigned)(4 * q) * mcs;
         // PLAIN: all 16 NB channels exist, no bias, slope in (0, 1] (the activation is then the larger of z and slope * z)
         uint32_t signs[NO];
         auto finish = [&](auto plain) {
@@ -284,14 +298,18 @@ k_conv_fwd_stem(StemArgs a)
                         if (c[2] > best) { best = c[2]; code = 4; }
                         if (c[3] > best) { best = c[3]; code = 6; }
                         code += best > 0.0f ? 1u : 0u;
-                        stem_store(orsrc, exists ? vo[0] : kOobStem, co * ocs, best, (const T*)nullptr);
+                        stem_store(orsrc, exists ? vo : kOobStem, co * ocs, best, (const T*)nullptr);
                         __builtin_amdgcn_raw_buffer_store_b8((uint8_t)code, mrsrc, exists ? mo : kOobStem, co * mcs, 0);
                         // (collected from the top down, 4 bits a block)
                         signs[0] = __builtin_amdgcn_alignbit(exists ? code : 0u, signs[0], 1);
                     } else {
+                        stem_store4(orsrc, exists ? vo : kOobStem, co * ocs, c, (const T*)nullptr);
+                        if (pieces) {
+#pragma unroll
+                            for (int p = 0; p < 4; ++p) stem_store(orsrc, exists && p < there ? vp + ES * p : kOobStem, co * ocs, c[p], (const T*)nullptr);
+                        }
 #pragma unroll
                         for (int p = 0; p < 4; ++p) {
-                            stem_store(orsrc, exists ? vo[p] : kOobStem, co * ocs, c[p], (const T*)nullptr);
                             signs[p] = __builtin_amdgcn_alignbit(exists && c[p] > 0.0f ? 1u : 0u, signs[p], 1);
                         }
                     }
@@ -308,7 +326,16 @@ k_conv_fwd_stem(StemArgs a)
             signs[o] <<= 4 * q;
             signs[o] |= (uint32_t)__shfl_xor((int)signs[o], 16, 64);
             signs[o] |= (uint32_t)__shfl_xor((int)signs[o], 32, 64);
-            if (owned[o] && q == o) *at<uint32_t>(a.osign, stack, ti, tj, n, c0 >> 5, oy[o], ox[o]) = signs[o];
+        }
+        if (row_owned && q == 0) {
+            uint32_t* const sp = at<uint32_t>(a.osign, stack, ti, tj, n, c0 >> 5, oy, ox);
+            typedef uint32_t v4s __attribute__((ext_vector_type(4), aligned(4)));
+            if (!POOL && there == 4 && ox >= a.own.x0[tj] && ox + 3 <= a.own.x1[tj]) {
+                *(v4s*)sp = v4s{signs[0], signs[NO > 1 ? 1 : 0], signs[NO > 1 ? 2 : 0], signs[NO > 1 ? 3 : 0]};
+            } else {
+#pragma unroll
+                for (int o = 0; o < NO; ++o) if (o < there && ox + o >= a.own.x0[tj] && ox + o <= a.own.x1[tj]) sp[o] = signs[o];
+            }
         }
     };
     // (a run of several tiles: at most 32 channels, and a patch that a thread's U positions cover; the next tile's patch travels
@@ -336,23 +363,23 @@ k_conv_fwd_stem(StemArgs a)
 namespace {
 
 template <typename T, int K, int S, bool POOL, int CI>
-void launch_stem(const StemArgs& s, dim3 grid, size_t lds, hipStream_t st)
+void launch_stem(const StemArgs& s, const PrepArgs<kPrepFew>& p, dim3 grid, size_t lds, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_conv_fwd_stem<T, K, S, POOL, CI>), grid, dim3(256), lds, st, s);
+    hipLaunchKernelGGL((k_conv_fwd_stem<T, K, S, POOL, CI>), grid, dim3(256), lds, st, s, p);
 }
 template <typename T, int K, int S, bool POOL>
-void launch_stem(const StemArgs& s, dim3 grid, size_t lds, hipStream_t st)
+void launch_stem(const StemArgs& s, const PrepArgs<kPrepFew>& p, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (s.Cin <= 3) launch_stem<T, K, S, POOL, 3>(s, grid, lds, st); else launch_stem<T, K, S, POOL, 4>(s, grid, lds, st);
+    if (s.Cin <= 3) launch_stem<T, K, S, POOL, 3>(s, p, grid, lds, st); else launch_stem<T, K, S, POOL, 4>(s, p, grid, lds, st);
 }
 template <typename T>
-void launch_stem(const ConvArgs& c, const StemArgs& s, dim3 grid, size_t lds, hipStream_t st)
+void launch_stem(const ConvArgs& c, const StemArgs& s, const PrepArgs<kPrepFew>& p, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (c.K == 3 && c.S == 1) { if (c.pooled) launch_stem<T, 3, 1, true>(s, grid, lds, st); else launch_stem<T, 3, 1, false>(s, grid, lds, st); }
-    else if (c.K == 3) launch_stem<T, 3, 2, false>(s, grid, lds, st);
-    else if (c.K == 5) { if (c.S == 2) launch_stem<T, 5, 2, false>(s, grid, lds, st); else launch_stem<T, 5, 1, false>(s, grid, lds, st); }
-    else if (c.K == 7) { if (c.S == 2) launch_stem<T, 7, 2, false>(s, grid, lds, st); else launch_stem<T, 7, 1, false>(s, grid, lds, st); }
-    else launch_stem<T, 1, 2, false>(s, grid, lds, st);
+    if (c.K == 3 && c.S == 1) { if (c.pooled) launch_stem<T, 3, 1, true>(s, p, grid, lds, st); else launch_stem<T, 3, 1, false>(s, p, grid, lds, st); }
+    else if (c.K == 3) launch_stem<T, 3, 2, false>(s, p, grid, lds, st);
+    else if (c.K == 5) { if (c.S == 2) launch_stem<T, 5, 2, false>(s, p, grid, lds, st); else launch_stem<T, 5, 1, false>(s, p, grid, lds, st); }
+    else if (c.K == 7) { if (c.S == 2) launch_stem<T, 7, 2, false>(s, p, grid, lds, st); else launch_stem<T, 7, 1, false>(s, p, grid, lds, st); }
+    else launch_stem<T, 1, 2, false>(s, p, grid, lds, st);
 }
 
 }  // namespace
@@ -368,7 +395,7 @@ bool stem_fwd_eligible(const ConvArgs& c)
     return !c.pooled && (c.K == 5 || c.K == 7 || (c.S == 2 && (c.K == 1 || c.K == 3)));
 }
 
-void stem_fwd(const ConvArgs& c, hipStream_t st)
+void stem_fwd(const ConvArgs& c, const PrepJob* jobs, int n, hipStream_t st)
 {
     StemArgs s;
     s.in = c.in; s.out = c.out; s.mask = c.mask; s.osign = c.osign; s.rt = c.rect; s.own = c.own;
@@ -381,6 +408,7 @@ void stem_fwd(const ConvArgs& c, hipStream_t st)
     // pixels a turn: several turns where the launch fills the chip (the patch's halo weighs less), one where it does not.
     s.tiles_x = (mw + kStemTile - 1) / kStemTile;
     s.tw = (mw + s.tiles_x - 1) / s.tiles_x;
+    if (!c.pooled) s.tw = (s.tw + 3) & ~3;             // (groups of 4 pixels lie in one row)
     s.tiles_x = (mw + s.tw - 1) / s.tw;
     const int least = c.pooled ? 64 : 256;
     const int NP = c.pooled ? 2 : 1, CI = c.Cin <= 3 ? 3 : 4, steps = stem_steps(c.K, CI);
@@ -404,9 +432,11 @@ void stem_fwd(const ConvArgs& c, hipStream_t st)
     s.lines = s.strips * c.N * c.batch;
     s.xcd = s.lines >= 64 ? 1 : 0;                     // (few lines would load the XCDs unevenly)
     const int row = c.M * s.tiles_x;
-    dim3 grid(s.xcd ? xcd_grid(s.lines, row) : (unsigned)(s.lines * row));
+    s.blocks = s.xcd ? (int)xcd_grid(s.lines, row) : s.lines * row;
+    PrepArgs<kPrepFew> p;
+    const dim3 grid((unsigned)(s.blocks + fill_prep(p, jobs, n)));
     g_kernel_label = "k_conv_fwd_stem";
-    if (c.bf16) launch_stem<bf16_t>(c, s, grid, lds, st); else launch_stem<float>(c, s, grid, lds, st);
+    if (c.bf16) launch_stem<bf16_t>(c, s, p, grid, lds, st); else launch_stem<float>(c, s, p, grid, lds, st);
 }
 
 }  // namespace ftp

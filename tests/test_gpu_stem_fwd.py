@@ -45,3 +45,37 @@ def test_slopes_and_bias(slope):
     # (27 products and their sums, each rounded to 24 bits)
     assert float((s.y.cpu().double() - ref).abs().max() / ref.abs().max()) < 28 * 2.0 ** -24
     s.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("h,w,cout,grid,slope", [(13, 13, 12, (1, 1), 0.1), (16, 24, 37, (2, 2), 0.1), (9, 31, 4, (1, 3), 1.0), (32, 40, 64, (2, 1), 0.5)])
+def test_step_whose_launches_carry_the_filter_relayout(oracle, dtype, h, w, cout, grid, slope):
+    """The first layer's forward pass and the scaling of dy (single pixels and groups, channel counts around groups of 4) relay the
+    filters of the layers behind: forward, deltas and gradients of a network of two, and of one with more jobs than travel along."""
+    def net(n):
+        ls = [conv(3, 16)]
+        for i in range(n):
+            ls.append(conv(16 if i == 0 else cout, cout, slope=slope if i == n - 1 else 0.1))
+        return tuple(ls)
+    P.check_case(oracle, Config("carry", 2, 3, h, w, net(1), grid, (2,), dtype))
+    P.check_case(oracle, Config("carry9", 1, 3, h, w, net(10), (1, 1), (4, 11), dtype))
+
+
+@pytest.mark.parametrize("cin,cout", [(36, 72), (33, 65)])
+def test_bias_sums_travel_with_the_shares(cin, cout):
+    """A small layer with a bias whose gradient comes in shares, 4 and 1 parameters a thread: the gradient against 64 bits."""
+    import torch
+    from paper_2409_09083_amd.harness import Session
+    g = torch.Generator().manual_seed(4)
+    s = Session((_biased(conv(cin, cout, slope=1.0)),), 3, cin, 44, 40, (2, 1), (1,))
+    x, w, b = torch.randn(s.in_shape, generator=g), torch.randn((cout, cin, 3, 3), generator=g) / 18, torch.randn(cout, generator=g)
+    dy = torch.randn(tuple(s.dy.shape), generator=g)
+    s.load(x=x.numpy(), weights=[w.numpy()], biases=[b.numpy()], dy=dy.numpy())
+    s.step()
+    w64, b64 = w.double().requires_grad_(True), b.double().requires_grad_(True)
+    torch.nn.functional.conv2d(x.double(), w64, b64, padding=1).backward(dy.double())
+    got, n = s.wgrad.cpu().double(), w.numel()
+    # (5280 products of normal numbers: sums of about 73, every partial sum rounded to 24 bits)
+    for a, ref in ((got[:n], w64.grad.reshape(-1)), (got[n:], b64.grad)):
+        assert float((a - ref).abs().max() / ref.abs().max()) < 1e-5
+    s.close()
