@@ -445,10 +445,12 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             // are serial among themselves on `aux`, they share the scratch)
             if (overlap && gradient_in_flight && (rc = order(aux, s)) != FTP_OK) return rc;
             int shares = 1;
+            auto bias_alone = [&] { return a.has_bias && !(shares > 1 && bias_small(a)); };
             auto with_bias = [&](void (*gradient)(const ConvArgs&, float*, hipStream_t)) {
                 gradient(a, scratch, aux);
-                if (a.has_bias && !(shares > 1 && bias_small(a))) bias_grad(a, aux);
+                if (bias_alone()) bias_grad(a, aux);
             };
+            bool delta_done = false;
             const bool cores = use_mfma() && wgrad_bias_pays(a);
             if (cores && thin_wgrad_eligible(a)) {
                 shares = a.wgrad_shares_thin;
@@ -458,7 +460,14 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad16); });
             } else if (cores && wgrad_split_eligible(a)) {
                 shares = a.wgrad_shares_split;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad_split); });
+                // (one launch with the delta's, unless the two have streams or timing records of their own)
+                if (!overlap && !plan->prof.on && relaid && mfma_conv_eligible(a, true)) {
+                    ConvArgs d = a;
+                    d.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
+                    delta_done = back_split(a, scratch, d, view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
+                }
+                if (delta_done) { if (bias_alone()) bias_grad(a, s); rc = check_hip(); }
+                else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad_split); });
             } else if (cores && mfma_wgrad_eligible(a)) {
                 shares = a.wgrad_shares;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(mfma_wgrad); });
@@ -470,7 +479,8 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             if (rc != FTP_OK) return rc;
             gradient_in_flight = overlap;
             a.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
-            if (use_mfma() && mfma_conv_eligible(a, true)) {
+            if (delta_done) {
+            } else if (use_mfma() && mfma_conv_eligible(a, true)) {
                 float* wt = (float*)((char*)workspace + u.wt_bwd_offset);
                 const RectTab ext = view_extent(p, u.in_delta, u.group, u.bo);
                 rc = timed(plan, FTP_PASS_CONV_BWD_DATA, u.layer, s, [&] {

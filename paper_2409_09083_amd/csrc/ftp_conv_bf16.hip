@@ -69,7 +69,7 @@ k_conv_bf16(MfmaConvArgs a)
     const int wave_m = wave % WAVES_M, wave_n = wave / WAVES_M;
     const int hi = lane >> 5, l32 = lane & 31;
     int vgroup, vtile;
-    if (!tile_order(a, vgroup, vtile)) return;
+    if (!tile_order(a, (int)blockIdx.x, vgroup, vtile)) return;
     const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<S, P, 8>(a, x0, x1, y0, y1, vtile);

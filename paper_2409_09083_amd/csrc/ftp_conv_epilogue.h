@@ -20,12 +20,12 @@ template <int S, int P>
 __device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) { return conv_tile_pix(g, wq, x1, S, P); }
 
 // The workgroup's stack and channel block (vgroup = stack * mblocks + channel block) and tile, in the order the launch chose.
-__device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int& vgroup, int& vtile)
+__device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int index, int& vgroup, int& vtile)
 {
     const int ntiles = a.tiles_x * a.tiles_r;
-    if (__builtin_expect(a.row_run, 0)) return row_order((int)blockIdx.x, a.stacks / a.M, a.M, a.mblocks, ntiles, a.row_run, vgroup, vtile);
-    if (a.xcd_groups) return xcd_order(a.mblocks * a.stacks, ntiles, vgroup, vtile);
-    vgroup = (int)blockIdx.x / ntiles; vtile = (int)blockIdx.x - vgroup * ntiles;
+    if (__builtin_expect(a.row_run, 0)) return row_order(index, a.stacks / a.M, a.M, a.mblocks, ntiles, a.row_run, vgroup, vtile);
+    if (a.xcd_groups) return xcd_order(index, a.mblocks * a.stacks, ntiles, vgroup, vtile);
+    vgroup = index / ntiles; vtile = index - vgroup * ntiles;
     return true;
 }
 

@@ -119,6 +119,7 @@ PrepJob mfma_prep_job(const ConvArgs& c, void* wt, bool backward);
 void prep_filters(const PrepJob* jobs, int n, hipStream_t s);
 // wt: the filter as mfma_prep_job's job left it.
 int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);       // non-zero: does not fit
+void mfma_conv_bwd_args(MfmaConvArgs& a, const ConvArgs& c, const RectTab& inrect, float* wt);
 int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 // ... of 16-bit maps, the layers mfma_conv_packs_bf16 names (ftp_conv_bf16.hip)
 int conv_bf16_fwd(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s);
@@ -183,6 +184,8 @@ void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s);
 // fp32 3x3 stride-1 filter gradient on the bfloat matrix cores (ftp_wgrad_split.hip)
 bool wgrad_split_eligible(const ConvArgs& c);
 void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);
+// ... together with the unit's delta back-propagation (ftp_back_split.h); false: nothing was launched
+bool back_split(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
 // The three matrix-core filter-gradient kernels leave `shares` > 1 partial results per stack in the scratch area;
 // this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own), with `bias` the bias gradient too.

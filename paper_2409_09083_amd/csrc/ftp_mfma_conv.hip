@@ -94,7 +94,7 @@ k_conv_mfma_dl(MfmaConvArgs a)
     // only ever meets one channel block's slice of the filter (with all blocks on every XCD the filters of the
     // 256 -> 512 layers do not stay in a 4 MB L2).
     int vgroup, vtile;
-    if (!tile_order(a, vgroup, vtile)) return;
+    if (!tile_order(a, (int)blockIdx.x, vgroup, vtile)) return;
     const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<S, P, WIDE ? 4 : 0>(a, x0, x1, y0, y1, vtile);
@@ -528,6 +528,16 @@ int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream
     return c.pooled ? launch_m<1, true, false>(a, c, s) : launch_m<1, false, false>(a, c, s);
 }
 
+void mfma_conv_bwd_args(MfmaConvArgs& a, const ConvArgs& c, const RectTab& inrect, float* wt)
+{
+    fill_common(a, c, inrect);
+    a.wt = wt; a.w = c.w; a.bias = nullptr;
+    a.C = c.Cout; a.Mtot = c.Cin;
+    // the patch is cut from the deltas as the stride-1 convolution sees them: at the convolution output (stride 1,
+    // also through a pool), or with zeros inserted between them (stride 2: twice the extent)
+    a.Hc = c.S == 2 ? 2 * c.Hc : c.Hc; a.Wc = c.S == 2 ? 2 * c.Wc : c.Wc;
+}
+
 // Backward data: c.rect = backward rectangle at the unit's input boundary; inrect = extent of the delta view
 // (at the unit's output boundary, pooled coordinates if the unit has a pool).
 int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s)
@@ -535,12 +545,7 @@ int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipS
     // (stride 2: the kernel that splits the pixels into their four parity classes multiplies no inserted zeros)
     if (c.S == 2 && (c.K == 3 || c.K == 1) && delta_s2_mfma(c, inrect, wt, s) == 0) return 0;
     MfmaConvArgs a;
-    fill_common(a, c, inrect);
-    a.wt = wt; a.w = c.w; a.bias = nullptr;
-    a.C = c.Cout; a.Mtot = c.Cin;
-    // the patch is cut from the deltas as the stride-1 convolution sees them: at the convolution output (stride 1,
-    // also through a pool), or with zeros inserted between them (stride 2: twice the extent)
-    a.Hc = c.S == 2 ? 2 * c.Hc : c.Hc; a.Wc = c.S == 2 ? 2 * c.Wc : c.Wc;
+    mfma_conv_bwd_args(a, c, inrect, wt);
     if (mfma_conv_packs_bf16(c)) return conv_bf16_bwd_data(a, c, s);
     if (!c.bf16) {
         if (c.S == 2) {                                 // (the filter was relaid for the kernel that declined)

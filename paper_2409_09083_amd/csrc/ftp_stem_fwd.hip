@@ -104,7 +104,7 @@ k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
     const int row = a.M * a.tiles_x;
     int line, w;
     if (a.xcd) {
-        if (!xcd_order(a.lines, row, line, w)) return;
+        if (!xcd_order((int)blockIdx.x, a.lines, row, line, w)) return;
     } else {
         line = (int)blockIdx.x / row; w = (int)blockIdx.x - line * row;
     }

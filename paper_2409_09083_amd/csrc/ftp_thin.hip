@@ -117,7 +117,7 @@ k_conv_bwd_data_thin4(View din, View mask, View dout, View isign, int scale_out,
     const int tid = threadIdx.x;
     // 1-D grid in XCD order: the tiles of one (stack, image), whose patches overlap, run on one XCD and share its L2
     int image, tile;
-    if (!xcd_order(images, tiles, image, tile)) return;
+    if (!xcd_order((int)blockIdx.x, images, tiles, image, tile)) return;
     const int stack = image / batch, n = image % batch;
     const int ti = stack / M, tj = stack % M;
     const int TW = 4 * ntx, TH = nty, PP = (TW + 2 + 3) & ~3;
@@ -495,7 +495,7 @@ k_wgrad_mfma_thin(MfmaWgradArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: row bookkeeping stays scalar
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares((int)blockIdx.x, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
@@ -720,7 +720,7 @@ k_wgrad_thin_dl(MfmaWgradArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares(a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares((int)blockIdx.x, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;

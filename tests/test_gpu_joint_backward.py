@@ -1,0 +1,37 @@
+"""Filter gradient and delta back-propagation in one launch against launches of their own (timing records on): the same bits, over the
+workgroup shapes both have, with and without a pool, from the caller's map and from the workspace."""
+import pytest
+import torch
+
+from ftp_synth.configs import conv, pool
+from paper_2409_09083_amd import binding as B
+from paper_2409_09083_amd.harness import Session
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("layers,batch,h,w,grid", [
+    ((conv(8, 24), conv(24, 32), pool(32)), 2, 30, 44, (2, 2)),            # at most 32 channels on both sides
+    ((conv(16, 72), conv(72, 72, slope=1.0)), 1, 37, 29, (1, 3)),           # 32 rows of the delta, 64 of the gradient; odd maps
+    ((conv(40, 64), pool(64), conv(64, 36)), 3, 52, 40, (3, 2)),            # 64 rows, through a pool and not
+    ((conv(128, 64), pool(64), conv(64, 32)), 1, 26, 26, (1, 1)),           # a launch too small for wide blocks of channels
+    ((conv(136, 48), conv(48, 128), pool(128)), 16, 76, 60, (2, 2)),        # 128 rows and several rounds
+    ((conv(64, 64), conv(64, 200)), 9, 65, 90, (3, 3)),
+])
+def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid):
+    g = torch.Generator().manual_seed(11)
+    out = []
+    for apart in (False, True):
+        s = Session(layers, batch, layers[0].cin, h, w, grid, (len(layers),))
+        g.manual_seed(11)
+        x, dy = torch.randn(s.in_shape, generator=g), torch.randn(tuple(s.dy.shape), generator=g)
+        ws = [torch.randn((ly.cout, ly.cin, ly.k, ly.k), generator=g).numpy() / (3 * ly.cin ** 0.5) if ly.kind == 0 else None for ly in layers]
+        s.load(x=x.numpy(), weights=ws, dy=dy.numpy())
+        if apart:
+            B.ftp_profile(s.plan, 1)
+        s.step()
+        torch.cuda.synchronize()
+        out.append((s.dx.clone(), s.wgrad.clone()))
+        s.close()
+    assert bool(torch.isfinite(out[0][1]).all())
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
