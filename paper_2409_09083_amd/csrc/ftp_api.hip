@@ -450,27 +450,31 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 gradient(a, scratch, aux);
                 if (bias_alone()) bias_grad(a, aux);
             };
+            // one launch for the gradient and the delta, unless the two have streams or timing records of their own
+            const bool joint = !overlap && !plan->prof.on;
             bool delta_done = false;
+            auto delta_args = [&] { ConvArgs d = a; d.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi); return d; };
             const bool cores = use_mfma() && wgrad_bias_pays(a);
             if (cores && thin_wgrad_eligible(a)) {
                 shares = a.wgrad_shares_thin;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(thin_wgrad); });
+                if (joint && fast && thin_bwd_data_eligible(a) && !mfma_conv_eligible(a, true)) delta_done = back_thin(a, scratch, delta_args(), s);
+                if (delta_done) { if (bias_alone()) bias_grad(a, s); rc = check_hip(); }
+                else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(thin_wgrad); });
             } else if (cores && plain_geometry(a) && u.in_delta.kind == BUF_WS && wgrad16_eligible(a)) {
                 shares = a.wgrad_shares16;
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad16); });
             } else if (cores && wgrad_split_eligible(a)) {
                 shares = a.wgrad_shares_split;
-                // (one launch with the delta's, unless the two have streams or timing records of their own)
-                if (!overlap && !plan->prof.on && relaid && mfma_conv_eligible(a, true)) {
-                    ConvArgs d = a;
-                    d.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
-                    delta_done = back_split(a, scratch, d, view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
-                }
+                if (joint && relaid && mfma_conv_eligible(a, true))
+                    delta_done = back_split(a, scratch, delta_args(), view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
                 if (delta_done) { if (bias_alone()) bias_grad(a, s); rc = check_hip(); }
                 else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad_split); });
             } else if (cores && mfma_wgrad_eligible(a)) {
                 shares = a.wgrad_shares;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(mfma_wgrad); });
+                if (joint && relaid && mfma_conv_eligible(a, true))
+                    delta_done = back_1x1(a, scratch, delta_args(), view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
+                if (delta_done) { if (bias_alone()) bias_grad(a, s); rc = check_hip(); }
+                else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(mfma_wgrad); });
             } else {
                 rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { direct_wgrad(a, aux); });
             }

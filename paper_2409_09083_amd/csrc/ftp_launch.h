@@ -187,6 +187,7 @@ void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);
 // ... together with the unit's delta back-propagation (ftp_back_split.h); false: nothing was launched
 bool back_split(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
+bool back_1x1(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 // The three matrix-core filter-gradient kernels leave `shares` > 1 partial results per stack in the scratch area;
 // this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own), with `bias` the bias gradient too.
 void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, bool bias, hipStream_t s);
@@ -200,6 +201,7 @@ bool thin_bwd_data_eligible(const ConvArgs& a);
 void thin_conv_bwd_data(const ConvArgs& a, hipStream_t s);
 bool thin_wgrad_eligible(const ConvArgs& c);
 void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
+bool back_thin(const ConvArgs& w, float* scratch, const ConvArgs& c, hipStream_t s);        // both of a small 3x3 layer; false: nothing was launched
 bool thin16_bwd_data(const ConvArgs& a, hipStream_t s);        // (ftp_delta_thin16.hip) false: does not apply
 bool thin16_wgrad(const ConvArgs& a, MfmaWgradArgs& m, hipStream_t s);      // (ftp_wgrad_thin16.hip) false: does not apply
 

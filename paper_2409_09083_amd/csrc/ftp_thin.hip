@@ -105,19 +105,35 @@ k_conv_bwd_data_thin(View din, View mask, View dout, View isign, int scale_out, 
 // six workgroups share a CU and cover each other's staging (8 channels, three workgroups: config 4 1.16 instead of 0.90 ms).
 constexpr int kThin4Coc = 4, kThin4Patch = 1344;     // channels per stage, floats of one channel's patch
 
+constexpr int thin4_row(int CI) { return (9 * CI + 3) & ~3; }          // (filter rows on 16-byte boundaries: read four weights at a time)
+constexpr int thin4_words(int CI) { return kThin4Coc * (kThin4Patch + thin4_row(CI)); }       // LDS
+
+struct Thin4Args {
+    View din, mask, dout, isign;
+    RectTab rt;
+    const void* w;
+    int scale_out; float in_slope;
+    int Cin, Cout, Hc, Wc, M, batch;
+    int ntx, nty, tiles_x, tiles, images;
+};
+
+// Workgroup `index` of the launch, its first 256 threads.
 template <typename T, bool POOL, int CI>
-__global__ void __launch_bounds__(256, 6)              // (six wavefronts a SIMD: the kernel waits for LDS and memory, not for registers)
-k_conv_bwd_data_thin4(View din, View mask, View dout, View isign, int scale_out, float in_slope, RectTab rt,
-                      const T* __restrict__ w, int Cin, int Cout, int Hc, int Wc, int M, int batch,
-                      int ntx, int nty, int tiles_x, int tiles, int images)
+__device__ __forceinline__ void bwd_thin4_group(const Thin4Args& a, int index, float* lds)
 {
-    constexpr int COC = kThin4Coc, CH = kThin4Patch, WR = (9 * CI + 3) & ~3;        // (filter rows on 16-byte boundaries: read four weights at a time)
-    __shared__ __attribute__((aligned(16))) float dz[COC * CH];
-    __shared__ __attribute__((aligned(16))) float wl[COC * WR];
+    constexpr int COC = kThin4Coc, CH = kThin4Patch, WR = thin4_row(CI);
+    float* const dz = lds;
+    float* const wl = lds + COC * CH;
+    const View &din = a.din, &mask = a.mask, &dout = a.dout, &isign = a.isign;
+    const RectTab& rt = a.rt;
+    const T* const w = (const T*)a.w;
+    const int scale_out = a.scale_out, Cin = a.Cin, Cout = a.Cout, Hc = a.Hc, Wc = a.Wc, M = a.M, batch = a.batch;
+    const int ntx = a.ntx, nty = a.nty, tiles_x = a.tiles_x;
+    const float in_slope = a.in_slope;
     const int tid = threadIdx.x;
     // 1-D grid in XCD order: the tiles of one (stack, image), whose patches overlap, run on one XCD and share its L2
     int image, tile;
-    if (!xcd_order((int)blockIdx.x, images, tiles, image, tile)) return;
+    if (!xcd_order(index, a.images, a.tiles, image, tile)) return;
     const int stack = image / batch, n = image % batch;
     const int ti = stack / M, tj = stack % M;
     const int TW = 4 * ntx, TH = nty, PP = (TW + 2 + 3) & ~3;
@@ -226,6 +242,14 @@ k_conv_bwd_data_thin4(View din, View mask, View dout, View isign, int scale_out,
                 st(at<T>(dout, stack, ti, tj, n, j, iy, ix), v);
             }
         }
+}
+
+template <typename T, bool POOL, int CI>
+__global__ void __launch_bounds__(256, 6)              // (six wavefronts a SIMD: the kernel waits for LDS and memory, not for registers)
+k_conv_bwd_data_thin4(Thin4Args a)
+{
+    __shared__ __attribute__((aligned(16))) float lds[thin4_words(CI)];
+    bwd_thin4_group<T, POOL, CI>(a, (int)blockIdx.x, lds);
 }
 
 // ---- delta at the input of a stride-2 convolution with at most 4 input channels (the image side of a strided stem) ----
@@ -438,33 +462,50 @@ void thin_conv_bwd_data_strided(const ConvArgs& a, const RectTab& ext, hipStream
 
 bool thin_bwd_data_eligible(const ConvArgs& a) { return a.Cin <= 4; }
 
+namespace {
+
+// Fills the launch's arguments and returns its grid; 0: another kernel takes the layer.
+unsigned thin4_plan(Thin4Args& t, const ConvArgs& a)
+{
+    if (a.K != 3) return 0;
+    int mw = 0, mh = 0;
+    for (int i = 0; i < a.M; ++i) mw = std::max(mw, a.rect.x1[i] - a.rect.x0[i] + 1);
+    for (int i = 0; i < a.N; ++i) mh = std::max(mh, a.rect.y1[i] - a.rect.y0[i] + 1);
+    // tile = 4*ntx x nty pixels fitted to the largest rectangle
+    int tiles_x = (mw + 63) / 64;
+    const int ntx = ((mw + tiles_x - 1) / tiles_x + 3) / 4;
+    tiles_x = (mw + 4 * ntx - 1) / (4 * ntx);
+    int nty_max = 256 / ntx; if (nty_max > 64) nty_max = 64;
+    const int tiles_y = (mh + nty_max - 1) / nty_max;
+    const int nty = (mh + tiles_y - 1) / tiles_y;
+    const int PP = (4 * ntx + 2 + 3) & ~3;
+    if ((nty + 2) * PP > kThin4Patch) return 0;
+    t.din = a.din; t.mask = a.mask; t.dout = a.dout; t.isign = a.isign; t.rt = a.rect; t.w = a.w;
+    t.scale_out = a.scale_out; t.in_slope = a.in_slope;
+    t.Cin = a.Cin; t.Cout = a.Cout; t.Hc = a.Hc; t.Wc = a.Wc; t.M = a.M; t.batch = a.batch;
+    t.ntx = ntx; t.nty = nty; t.tiles_x = tiles_x; t.tiles = tiles_x * tiles_y; t.images = a.N * a.M * a.batch;
+    return xcd_grid(t.images, t.tiles);
+}
+
+}  // namespace
+
 void thin_conv_bwd_data(const ConvArgs& a, hipStream_t s)
 {
     if (thin16_bwd_data(a, s)) return;
     int mw = 0, mh = 0;
     for (int t = 0; t < a.M; ++t) mw = mw > a.rect.x1[t] - a.rect.x0[t] + 1 ? mw : a.rect.x1[t] - a.rect.x0[t] + 1;
     for (int t = 0; t < a.N; ++t) mh = mh > a.rect.y1[t] - a.rect.y0[t] + 1 ? mh : a.rect.y1[t] - a.rect.y0[t] + 1;
-    if (a.K == 3) {
-        // tile = 4*ntx x nty pixels fitted to the largest rectangle
-        int tiles_x = (mw + 63) / 64;
-        const int ntx = ((mw + tiles_x - 1) / tiles_x + 3) / 4;
-        tiles_x = (mw + 4 * ntx - 1) / (4 * ntx);
-        int nty_max = 256 / ntx; if (nty_max > 64) nty_max = 64;
-        const int tiles_y = (mh + nty_max - 1) / nty_max;
-        const int nty = (mh + tiles_y - 1) / tiles_y;
-        const int PP = (4 * ntx + 2 + 3) & ~3;
-        if ((nty + 2) * PP <= kThin4Patch) {
-            const int tiles = tiles_x * tiles_y, images = a.N * a.M * a.batch;
-            dim3 grid(xcd_grid(images, tiles)), block(256);
-            g_kernel_label = "k_conv_bwd_data_thin4";
-#define FTP_T4(T, PL, CI) hipLaunchKernelGGL((k_conv_bwd_data_thin4<T, PL, CI>), grid, block, 0, s, a.din, a.mask, a.dout, a.isign, a.scale_out, a.in_slope, a.rect, (const T*)a.w, a.Cin, a.Cout, a.Hc, a.Wc, a.M, a.batch, ntx, nty, tiles_x, tiles, images)
+    Thin4Args t;
+    const unsigned groups = thin4_plan(t, a);
+    if (groups) {
+        g_kernel_label = "k_conv_bwd_data_thin4";
+#define FTP_T4(T, PL, CI) hipLaunchKernelGGL((k_conv_bwd_data_thin4<T, PL, CI>), dim3(groups), dim3(256), 0, s, t)
 #define FTP_T4C(T, PL) do { if (a.Cin <= 3) FTP_T4(T, PL, 3); else FTP_T4(T, PL, 4); } while (0)
-            if (a.bf16) { if (a.pooled) FTP_T4C(bf16_t, true); else FTP_T4C(bf16_t, false); }
-            else        { if (a.pooled) FTP_T4C(float, true); else FTP_T4C(float, false); }
+        if (a.bf16) { if (a.pooled) FTP_T4C(bf16_t, true); else FTP_T4C(bf16_t, false); }
+        else        { if (a.pooled) FTP_T4C(float, true); else FTP_T4C(float, false); }
 #undef FTP_T4C
 #undef FTP_T4
-            return;
-        }
+        return;
     }
     const int tiles_x = (mw + 63) / 64, tiles_y = (mh + 3) / 4;
     dim3 grid(tiles_x * tiles_y, 1, a.N * a.M * a.batch), block(256);
@@ -709,18 +750,16 @@ k_wgrad_mfma_thin(MfmaWgradArgs a)
 // multiply; these split the pixel pairs of every row among themselves as in the kernel above.
 #define FTP_THIN_LDS(p) ((__attribute__((address_space(3))) void*)(p))
 template <typename T, int K, int S, int NB, bool POOL>
-__global__ void __launch_bounds__(320)
-k_wgrad_thin_dl(MfmaWgradArgs a)
+__device__ __forceinline__ void wgrad_thin_dl_group(const MfmaWgradArgs& a, int index, float* lds)
 {
     constexpr int KK = K * K, P = K / 2, ES = sizeof(T);
     constexpr int ZPASS = kThinZPass(POOL);
     constexpr unsigned OOB = 0x80000000u;              // beyond the records of the buffer resources below: reads as zero
-    extern __shared__ float lds[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares((int)blockIdx.x, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares(index, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
@@ -986,6 +1025,30 @@ k_wgrad_thin_dl(MfmaWgradArgs a)
         }
     }
 }
+
+template <typename T, int K, int S, int NB, bool POOL>
+__global__ void __launch_bounds__(320)
+k_wgrad_thin_dl(MfmaWgradArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float thin_lds[];
+    wgrad_thin_dl_group<T, K, S, NB, POOL>(a, (int)blockIdx.x, thin_lds);
+}
+
+// Small 3x3 first layers: filter gradient and delta at the image in one launch, as in ftp_back_split.h: the first `wgroups` workgroups
+// are those of k_wgrad_thin_dl, the others (their first four wavefronts) those of k_conv_bwd_data_thin4.
+// 3 -> 8, one image of 32^2: step of its net 57 -> 49 us; 3 -> 16 with a pool, one image of 416^2: 157 -> 151.
+struct BackThinArgs { MfmaWgradArgs w; Thin4Args d; int wgroups; };
+
+template <typename T, int NB, bool POOL, int CI>
+__global__ void __launch_bounds__(320)
+k_back_thin(BackThinArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float thin_lds[];
+    const int index = (int)blockIdx.x;
+    if (index < a.wgroups) { wgrad_thin_dl_group<T, 3, 1, NB, POOL>(a.w, index, thin_lds); return; }
+    if (threadIdx.x >= 256) return;                    // (a whole wavefront)
+    bwd_thin4_group<T, POOL, CI>(a.d, index - a.wgroups, thin_lds);
+}
 #undef FTP_THIN_LDS
 
 namespace {
@@ -1031,6 +1094,8 @@ ThinStream stream_geom(const ConvArgs& c)
 
 }  // namespace
 
+constexpr long long kBackThinMost = 4096;            // workgroups (about two of them a CU at a time: four rounds and more hide each other's ends)
+
 // c.rect must hold the owned rectangles.
 bool thin_wgrad_eligible(const ConvArgs& c)
 {
@@ -1045,16 +1110,50 @@ bool thin_wgrad_eligible(const ConvArgs& c)
     return thin_geom(c).lds <= 64 * 1024;
 }
 
-void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
+namespace {
+
+MfmaWgradArgs thin_args(const ConvArgs& c, float* scratch)
 {
     MfmaWgradArgs a;
     a.in = c.in; a.din = c.din; a.mask = c.mask; a.own = c.rect;
     a.partial = c.partial; a.scratch = scratch; a.n_params = c.n_params; a.w_off = c.w_off;
     a.Cin = c.Cin; a.Cout = c.Cout; a.Hc = c.Hi; a.Wc = c.Wi; a.slope = c.slope; a.M = c.M; a.batch = c.batch;
     a.splits = c.wgrad_shares_thin;
+    a.gx = (c.Cout + 31) / 32; a.stacks = c.N * c.M;
+    return a;
+}
+
+}  // namespace
+
+// w: as for thin_wgrad; c: as for thin_conv_bwd_data.  False: nothing was launched.
+bool back_thin(const ConvArgs& w, float* scratch, const ConvArgs& c, hipStream_t s)
+{
+    if (w.K != 3 || w.S != 1 || w.Cin > 4 || (w.bf16 && w.pooled)) return false;          // (16-bit pooled ones: kernels of their own)
+    const ThinStream ts = stream_geom(w);
+    BackThinArgs a;
+    const unsigned dgroups = thin4_plan(a.d, c);
+    if (!ts.fits || !dgroups) return false;
+    a.w = thin_args(w, scratch);
+    a.w.PK = ts.cb_max; a.w.zs = ts.zs; a.w.stage_words = ts.stage_words;
+    a.wgroups = (int)xcd_shares_grid(a.w.splits, a.w.stacks, a.w.gx);
+    // (launches that fill the chip several times over keep their own kernels: more workgroups of the delta share a CU there)
+    if ((a.wgroups & 7) || (long long)a.wgroups + dgroups > kBackThinMost) return false;
+    g_kernel_label = "k_back_thin";
+    const dim3 grid((unsigned)a.wgroups + dgroups);
+#define FTP_BT(T, NB, PL, CI) hipLaunchKernelGGL((k_back_thin<T, NB, PL, CI>), grid, dim3(320), std::max<size_t>(ts.lds, 4 * (size_t)thin4_words(CI)), s, a)
+#define FTP_BTC(T, PL) do { if (w.Cin <= 3) FTP_BT(T, 1, PL, 3); else FTP_BT(T, 2, PL, 4); } while (0)
+    if (w.bf16) FTP_BTC(bf16_t, false);
+    else        { if (w.pooled) FTP_BTC(float, true); else FTP_BTC(float, false); }
+#undef FTP_BTC
+#undef FTP_BT
+    return true;
+}
+
+void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
+{
+    MfmaWgradArgs a = thin_args(c, scratch);
     if (thin16_wgrad(c, a, s)) return;
     const int nb = (c.Cin * c.K * c.K + 31) / 32;      // 1 (up to 3x3), 2 or 4 (5x5), 4 to 7 (7x7: 5 for 3 channels)
-    a.gx = (c.Cout + 31) / 32; a.stacks = c.N * c.M;
     dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx)), block(256);
     const ThinStream ts = c.Cin <= 4 ? stream_geom(c) : ThinStream{0, 0, 0, 1, 1, 1, 0, false};
     const bool stream = ts.fits;

@@ -35,3 +35,22 @@ def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid):
         s.close()
     assert bool(torch.isfinite(out[0][1]).all())
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("layers,batch,h,w,grid", [
+    ((conv(3, 8), conv(8, 16)), 1, 31, 33, (2, 2)),                         # first layer without a pool, odd maps
+    ((conv(3, 40), pool(40), conv(40, 20, 1)), 2, 36, 52, (1, 2)),          # ... with one, two blocks of output channels
+    ((conv(4, 16, slope=1.0),), 3, 20, 70, (3, 1)),                         # 36 columns of the product, the image wider than a tile
+    ((conv(1, 24), pool(24)), 1, 64, 130, (2, 1)),
+])
+def test_first_layers(layers, batch, h, w, grid):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid)
+
+
+@pytest.mark.parametrize("layers,batch,h,w,grid", [
+    ((conv(24, 64, 1), conv(64, 160, 1)), 1, 27, 31, (1, 2)),               # 32 and 64 input channels, odd maps
+    ((conv(136, 72, 1), pool(72), conv(72, 32, 1)), 2, 26, 30, (1, 1)),     # 128 rows of the delta, through a pool
+    ((conv(48, 256, 1), pool(256), conv(256, 44, 1)), 1, 52, 40, (2, 2)),
+])
+def test_one_by_one_layers(layers, batch, h, w, grid):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid)
