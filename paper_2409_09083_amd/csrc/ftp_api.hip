@@ -462,7 +462,10 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(thin_wgrad); });
             } else if (cores && plain_geometry(a) && u.in_delta.kind == BUF_WS && wgrad16_eligible(a)) {
                 shares = a.wgrad_shares16;
-                rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad16); });
+                if (joint && relaid && mfma_conv_eligible(a, true))
+                    delta_done = back16(a, scratch, delta_args(), view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
+                if (delta_done) { if (bias_alone()) bias_grad(a, s); rc = check_hip(); }
+                else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(wgrad16); });
             } else if (cores && wgrad_split_eligible(a)) {
                 shares = a.wgrad_shares_split;
                 if (joint && relaid && mfma_conv_eligible(a, true))

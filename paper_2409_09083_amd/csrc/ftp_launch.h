@@ -181,6 +181,7 @@ bool mfma_wgrad_eligible(const ConvArgs& a);
 // bfloat 3x3 stride-1 filter gradient with packed staging (ftp_wgrad16.hip)
 bool wgrad16_eligible(const ConvArgs& a);
 void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s);
+bool back16(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);         // with the delta (ftp_back16.h)
 // fp32 3x3 stride-1 filter gradient on the bfloat matrix cores (ftp_wgrad_split.hip)
 bool wgrad_split_eligible(const ConvArgs& c);
 void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);

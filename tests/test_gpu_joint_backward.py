@@ -18,11 +18,11 @@ pytestmark = pytest.mark.gpu
     ((conv(136, 48), conv(48, 128), pool(128)), 16, 76, 60, (2, 2)),        # 128 rows and several rounds
     ((conv(64, 64), conv(64, 200)), 9, 65, 90, (3, 3)),
 ])
-def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid):
+def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, dtype="f32"):
     g = torch.Generator().manual_seed(11)
     out = []
     for apart in (False, True):
-        s = Session(layers, batch, layers[0].cin, h, w, grid, (len(layers),))
+        s = Session(layers, batch, layers[0].cin, h, w, grid, (len(layers),), dtype)
         g.manual_seed(11)
         x, dy = torch.randn(s.in_shape, generator=g), torch.randn(tuple(s.dy.shape), generator=g)
         ws = [torch.randn((ly.cout, ly.cin, ly.k, ly.k), generator=g).numpy() / (3 * ly.cin ** 0.5) if ly.kind == 0 else None for ly in layers]
@@ -54,3 +54,13 @@ def test_first_layers(layers, batch, h, w, grid):
 ])
 def test_one_by_one_layers(layers, batch, h, w, grid):
     test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid)
+
+
+@pytest.mark.parametrize("layers,batch,h,w,grid", [
+    ((conv(24, 32), pool(32), conv(32, 72)), 2, 36, 44, (2, 2)),            # 32 input channels, through a pool and not
+    ((conv(64, 64), conv(64, 40, slope=1.0)), 1, 37, 29, (1, 2)),           # small workgroups of the delta, odd deltas
+    ((conv(128, 96), pool(96), conv(96, 128)), 6, 52, 60, (3, 2)),
+    ((conv(256, 64), conv(64, 256)), 16, 76, 77, (2, 2)),                   # wide ones, several rounds
+])
+def test_16_bit_layers(layers, batch, h, w, grid):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, "bf16")
