@@ -475,7 +475,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             } else if (cores && mfma_wgrad_eligible(a)) {
                 shares = a.wgrad_shares;
                 if (joint && relaid && mfma_conv_eligible(a, true))
-                    delta_done = back_1x1(a, scratch, delta_args(), view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
+                    delta_done = (a.bf16 ? back16_1x1 : back_small)(a, scratch, delta_args(), view_extent(p, u.in_delta, u.group, u.bo), (float*)((char*)workspace + u.wt_bwd_offset), s);
                 if (delta_done) { if (bias_alone()) bias_grad(a, s); rc = check_hip(); }
                 else rc = timed(plan, FTP_PASS_WGRAD, u.layer, aux, [&] { with_bias(mfma_wgrad); });
             } else {

@@ -350,7 +350,7 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
 }
 
 struct BfShape { int WM, MT, NT; };                     // wavefronts along the channels, blocks of 32 channels / pixels of a wavefront
-// A 3x3 delta's launch together with the filter gradient (ftp_back16.h): fills the arguments, names the form of the patch, returns the grid.
+// A delta's launch together with the filter gradient (ftp_back16.h, ftp_back16_1x1.h): fills the arguments, names the form of the patch, returns the grid.
 unsigned bf_delta_plan(MfmaConvArgs& a, const ConvArgs& c, BfShape& sh, int& in);
 
 }  // namespace ftp

@@ -121,6 +121,7 @@ int conv_bf16_fwd(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
 unsigned bf_delta_plan(MfmaConvArgs& a, const ConvArgs& c, BfShape& sh, int& in)
 {
     in = c.pooled ? BF_POOL : even_view(a.din) ? BF_WS : BF_ODD;
+    if (c.K == 1) return in == BF_POOL ? plan_bf_in<1, false, true, BF_POOL>(a, c, sh) : in == BF_WS ? plan_bf_in<1, false, true, BF_WS>(a, c, sh) : plan_bf_in<1, false, true, BF_ODD>(a, c, sh);
     return in == BF_POOL ? plan_bf_in<3, false, true, BF_POOL>(a, c, sh) : in == BF_WS ? plan_bf_in<3, false, true, BF_WS>(a, c, sh) : plan_bf_in<3, false, true, BF_ODD>(a, c, sh);
 }
 

@@ -105,9 +105,10 @@ int launch_in(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s)
 
 }  // namespace
 
-// The 1x1 and 3x3 stride-1 layers, for a launch together with the filter gradient (ftp_back_split.h, ftp_back_1x1.hip).
+// The 1x1, 3x3 and 5x5 stride-1 layers, for a launch together with the filter gradient (ftp_back_split.h, ftp_back_small.hip).
 unsigned split_delta_plan(MfmaConvArgs& a, const ConvArgs& c, SplitShape& sh)
 {
+    if (c.K == 5) return plan_in<5, IN_WIDE>(a, c, sh);
     if (c.K == 1) return c.pooled ? plan_in<1, IN_POOL>(a, c, sh) : plan_in<1, IN_WIDE>(a, c, sh);
     return c.pooled ? plan_in<3, IN_POOL>(a, c, sh) : plan_in<3, IN_WIDE>(a, c, sh);
 }

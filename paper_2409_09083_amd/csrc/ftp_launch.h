@@ -188,7 +188,9 @@ void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);
 // ... together with the unit's delta back-propagation (ftp_back_split.h); false: nothing was launched
 bool back_split(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
-bool back_1x1(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
+// ... of small layers together with the delta; false: nothing was launched
+bool back_small(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);        // fp32 1x1, 5x5
+bool back16_1x1(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 // The three matrix-core filter-gradient kernels leave `shares` > 1 partial results per stack in the scratch area;
 // this sums them into the per-stack gradient vectors (a launch, and a timing record, of its own), with `bias` the bias gradient too.
 void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, bool bias, hipStream_t s);

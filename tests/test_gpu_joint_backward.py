@@ -64,3 +64,17 @@ def test_one_by_one_layers(layers, batch, h, w, grid):
 ])
 def test_16_bit_layers(layers, batch, h, w, grid):
     test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, "bf16")
+
+
+@pytest.mark.parametrize("layers,batch,h,w,grid", [
+    ((conv(24, 64, 1), conv(64, 160, 1)), 1, 27, 31, (1, 2)),               # odd deltas
+    ((conv(136, 72, 1), pool(72), conv(72, 32, 1)), 2, 26, 30, (1, 1)),     # through a pool
+    ((conv(256, 44, 1), conv(44, 200, 1)), 1, 52, 40, (2, 2)),
+])
+def test_16_bit_one_by_one_layers(layers, batch, h, w, grid):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, "bf16")
+
+
+@pytest.mark.parametrize("cin,cout,batch,h,w,grid", [(24, 40, 1, 27, 31, (1, 2)), (64, 32, 2, 30, 20, (2, 1)), (128, 96, 1, 26, 26, (1, 1))])
+def test_5x5_layers(cin, cout, batch, h, w, grid):
+    test_same_bits_as_launches_of_their_own((conv(cin, cout, 5), conv(cout, 36, 5)), batch, h, w, grid)
