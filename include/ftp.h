@@ -197,7 +197,8 @@ int ftp_set_overlap(ftp_plan_t* plan, int32_t enable);
 
 /* Per-kernel timing for benchmarks.  While enabled, every kernel launch of the three passes is
  * bracketed by two HIP events on the caller's stream (host objects, created on first use and
- * owned by the plan).  ftp_profile(plan, 1) clears earlier records and starts collecting,
+ * owned by the plan); a unit's filter gradient and delta, one launch otherwise, are then two with a record each
+ * (the same bits).  ftp_profile(plan, 1) clears earlier records and starts collecting,
  * ftp_profile(plan, 0) stops.  ftp_profile_read waits for the recorded events and returns one
  * record per (pass, layer): number of launches, their summed duration, and the algorithmic
  * work of one launch - the FLOPs and HBM bytes of the untiled layer (each map read or written
