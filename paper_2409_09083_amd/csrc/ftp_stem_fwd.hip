@@ -24,6 +24,7 @@
 #include "ftp_device.h"
 #include "ftp_launch.h"
 #include "ftp_prep.h"
+#include "ftp_stem_tiles.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -45,12 +46,6 @@ struct StemArgs {
     int plain;                                         // no bias, slope in (0, 1]
 };
 
-// A tile is at most 32 x 16 output pixels (pool: windows); the patch's rows have the pitch of the widest one, so that the positions of a
-// window lie at constant distances.
-constexpr int kStemTile = 32, kStemRows = 16;
-constexpr int stem_pitch(int K, int S, bool pool) { return ((kStemTile * (pool ? 2 : 1) - 1) * S + K) | 1; }
-constexpr int stem_units(int K, int S, bool pool) { return pool ? 5 : K == 3 && S == 1 ? 3 : 4; }
-constexpr int stem_steps(int K, int CI) { return (CI * K * K + 3) / 4; }
 constexpr unsigned kOobStem = 0x80000000u;            // beyond the records of every buffer resource below: nothing is stored
 
 __device__ __forceinline__ void stem_store(__amdgpu_buffer_rsrc_t r, unsigned vo, unsigned so, float v, const float*)
@@ -404,31 +399,8 @@ void stem_fwd(const ConvArgs& c, const PrepJob* jobs, int n, hipStream_t st)
     int mw = 0, mh = 0;
     for (int t = 0; t < c.M; ++t) mw = std::max(mw, c.rect.x1[t] - c.rect.x0[t] + 1);
     for (int t = 0; t < c.N; ++t) mh = std::max(mh, c.rect.y1[t] - c.rect.y0[t] + 1);
-    // Tiles cover the widest rectangle in equal blocks of at most 32 columns.  A workgroup's four wavefronts take 16 windows or 64
-    // pixels a turn: several turns where the launch fills the chip (the patch's halo weighs less), one where it does not.
-    s.tiles_x = (mw + kStemTile - 1) / kStemTile;
-    s.tw = (mw + s.tiles_x - 1) / s.tiles_x;
-    if (!c.pooled) s.tw = (s.tw + 3) & ~3;             // (groups of 4 pixels lie in one row)
-    s.tiles_x = (mw + s.tw - 1) / s.tw;
-    const int least = c.pooled ? 64 : 256;
-    const int NP = c.pooled ? 2 : 1, CI = c.Cin <= 3 ? 3 : 4, steps = stem_steps(c.K, CI);
-    size_t lds = 0;
-    for (int room = c.pooled ? 256 : 512; ; room /= 2) {
-        const int th_max = std::max(1, std::min(room / s.tw, kStemRows));
-        s.tiles_y = (mh + th_max - 1) / th_max;
-        s.th = (mh + s.tiles_y - 1) / s.tiles_y;
-        const int PH = (s.th * NP - 1) * c.S + c.K;
-        lds = 4 * (((size_t)CI * PH * stem_pitch(c.K, c.S, c.pooled) + 3) / 4 * 4 + 2 * steps * 64 + 32 + 4 * steps);
-        if (room <= least || (lds <= 64 * 1024 && (long long)s.tiles_x * s.tiles_y * c.N * c.M * c.batch >= 512)) break;
-    }
-    // runs of tiles while every CU still gets its four workgroups
-    s.run = 1;
-    const int PH = (s.th * NP - 1) * c.S + c.K, PW = (s.tw * NP - 1) * c.S + c.K;
-    if (c.Cout <= 32 && PH * PW <= 256 * stem_units(c.K, c.S, c.pooled)) {
-        const long long per = (long long)s.tiles_x * c.N * c.M * c.batch;
-        while (s.run < s.tiles_y && per * ((s.tiles_y + s.run) / (s.run + 1)) >= 1024) ++s.run;
-    }
-    s.strips = (s.tiles_y + s.run - 1) / s.run;
+    const StemTiles t = stem_tiles(c.K, c.S, c.pooled, c.Cin, c.Cout, mw, mh, c.N * c.M, c.batch);
+    s.tw = t.tw; s.th = t.th; s.tiles_x = t.tiles_x; s.tiles_y = t.tiles_y; s.run = t.run; s.strips = t.strips;
     s.lines = s.strips * c.N * c.batch;
     s.xcd = s.lines >= 64 ? 1 : 0;                     // (few lines would load the XCDs unevenly)
     const int row = c.M * s.tiles_x;
@@ -436,7 +408,7 @@ void stem_fwd(const ConvArgs& c, const PrepJob* jobs, int n, hipStream_t st)
     PrepArgs<kPrepFew> p;
     const dim3 grid((unsigned)(s.blocks + fill_prep(p, jobs, n)));
     g_kernel_label = "k_conv_fwd_stem";
-    if (c.bf16) launch_stem<bf16_t>(c, s, p, grid, lds, st); else launch_stem<float>(c, s, p, grid, lds, st);
+    if (c.bf16) launch_stem<bf16_t>(c, s, p, grid, t.lds, st); else launch_stem<float>(c, s, p, grid, t.lds, st);
 }
 
 }  // namespace ftp

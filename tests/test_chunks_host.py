@@ -23,3 +23,7 @@ def test_wgrad_chunks_fit_their_lds_limits():
 
 def test_conv_tiles_fit_their_lds_limits_and_cover_every_pixel_once():
     _build_and_run("conv_tile_check")
+
+
+def test_first_layer_tiles_fit_their_lds_limits():
+    _build_and_run("stem_tile_check")

@@ -25,7 +25,7 @@ def test_pooled(oracle, dtype, cin, cout, batch, h, w, grid):
 @pytest.mark.parametrize("k,stride,cin,cout,batch,h,w,grid", [
     (3, 1, 3, 8, 1, 5, 7, (1, 1)), (3, 1, 4, 40, 2, 33, 65, (2, 1)), (3, 1, 3, 16, 64, 76, 40, (4, 4)), (3, 2, 2, 20, 2, 35, 67, (1, 2)),
     (5, 1, 3, 24, 1, 18, 34, (1, 1)), (5, 2, 4, 16, 1, 37, 41, (2, 2)), (7, 1, 1, 48, 1, 17, 33, (1, 1)), (7, 2, 3, 64, 2, 67, 131, (2, 1)),
-    (7, 2, 4, 72, 1, 65, 67, (1, 1)), (1, 2, 3, 36, 2, 31, 70, (1, 3))])
+    (7, 2, 4, 72, 1, 65, 67, (1, 1)), (7, 2, 4, 16, 1, 32, 32, (1, 1)), (7, 2, 4, 20, 2, 64, 30, (2, 1)), (1, 2, 3, 36, 2, 31, 70, (1, 3))])
 def test_unpooled(oracle, dtype, k, stride, cin, cout, batch, h, w, grid):
     P.check_case(oracle, Config("stem", batch, cin, h, w, (conv(cin, cout, k, stride=stride),), grid, (1,), dtype))
 
