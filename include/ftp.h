@@ -159,7 +159,7 @@ int ftp_forward_static(const ftp_plan_t* plan, const void* x, const void* const*
 /* Back-propagation of all groups in reverse (Sec. 4.1 delta and filter gradients).
  *   dy        device, dLoss/dy, shape of y
  *   x         device, the input of the preceding ftp_forward on the same workspace
- *   dx        device, receives dLoss/dx, shape of x
+ *   dx        device, receives dLoss/dx, shape of x; may be x itself (in place) or share memory with it
  *   wgrad_partials device, fp32 [N*M][n_params]: one partial parameter gradient per stack, summed
  *             over the batch and over the output pixels the stack owns; overwritten, not accumulated */
 int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x,

@@ -431,6 +431,11 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
         aux = (hipStream_t)ov.aux;
         if ((rc = order(s, aux)) != FTP_OK) return rc;          // the forward pass, dy scaling, earlier calls
     }
+    // dx may share memory with x (in place), which the first unit's gradient reads, or with dy: that gradient then ends before the
+    // delta at the image starts.
+    auto map_bytes = [&](int l) { return (size_t)p.batch * p.C[l] * p.H[l] * p.W[l] * (p.dtype == FTP_BF16 ? 2 : 4); };
+    auto shared = [&](const void* a, size_t an, const void* b, size_t bn) { return (uintptr_t)a < (uintptr_t)b + bn && (uintptr_t)b < (uintptr_t)a + an; };
+    const bool in_place = shared(dx, map_bytes(0), x, map_bytes(0)) || shared(dx, map_bytes(0), dy, map_bytes(L));
     bool gradient_in_flight = false;
     for (int i = (int)p.units.size() - 1; i >= 0; --i) {
         const Unit& u = p.units[i];
@@ -450,8 +455,9 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 gradient(a, scratch, aux);
                 if (bias_alone()) bias_grad(a, aux);
             };
-            // one launch for the gradient and the delta, unless the two have streams or timing records of their own
-            const bool joint = !overlap && !plan->prof.on;
+            // one launch for the gradient and the delta, unless the two have streams or timing records of their own, or one after the other
+            const bool apart = in_place && u.out_delta.kind == BUF_DX;
+            const bool joint = !overlap && !plan->prof.on && !apart;
             bool delta_done = false;
             auto delta_args = [&] { ConvArgs d = a; d.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi); return d; };
             const bool cores = use_mfma() && wgrad_bias_pays(a);
@@ -485,6 +491,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
                 rc = timed(plan, FTP_PASS_WGRAD_SUM, u.layer, aux, [&] { wgrad_share_sum(a, scratch, shares, a.has_bias && bias_small(a), aux); });
             if (rc != FTP_OK) return rc;
             gradient_in_flight = overlap;
+            if (overlap && apart && (rc = order(aux, s)) != FTP_OK) return rc;
             a.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
             if (delta_done) {
             } else if (use_mfma() && mfma_conv_eligible(a, true)) {

@@ -78,3 +78,32 @@ def test_16_bit_one_by_one_layers(layers, batch, h, w, grid):
 @pytest.mark.parametrize("cin,cout,batch,h,w,grid", [(24, 40, 1, 27, 31, (1, 2)), (64, 32, 2, 30, 20, (2, 1)), (128, 96, 1, 26, 26, (1, 1))])
 def test_5x5_layers(cin, cout, batch, h, w, grid):
     test_same_bits_as_launches_of_their_own((conv(cin, cout, 5), conv(cout, 36, 5)), batch, h, w, grid)
+
+
+@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("layers,batch,h,w,grid,dtype", [
+    ((conv(3, 16), pool(16), conv(16, 32)), 1, 64, 96, (2, 2), "f32"),      # first layers of each joint kernel: at most 4 channels,
+    ((conv(24, 64), conv(64, 32)), 2, 37, 50, (2, 1), "f32"),               # 3x3,
+    ((conv(40, 72, 1), conv(72, 16)), 1, 53, 41, (1, 2), "f32"),            # 1x1,
+    ((conv(32, 40, 5),), 1, 30, 44, (1, 1), "f32"),                         # 5x5,
+    ((conv(64, 128), pool(128)), 4, 44, 60, (2, 2), "bf16"),                # 3x3 and 1x1 with 16-bit storage
+    ((conv(160, 68, 1),), 2, 26, 46, (1, 1), "bf16"),
+])
+def test_deltas_in_place_of_the_input(layers, batch, h, w, grid, dtype, overlap):
+    """dx = x, and dx that begins inside x: the gradient of the first layer reads x before dx is written."""
+    g = torch.Generator().manual_seed(5)
+    s = Session(layers, batch, layers[0].cin, h, w, grid, (len(layers),), dtype)
+    s.set_overlap(overlap)
+    x, dy = torch.randn(s.in_shape, generator=g), torch.randn(tuple(s.dy.shape), generator=g)
+    ws = [torch.randn((ly.cout, ly.cin, ly.k, ly.k), generator=g).numpy() / (3 * ly.cin ** 0.5) if ly.kind == 0 else None for ly in layers]
+    s.load(x=x.numpy(), weights=ws, dy=dy.numpy())
+    s.step()
+    dx, wgrad, n = s.dx.clone(), s.wgrad.clone(), s.x.numel()
+    both = torch.empty(2 * n, dtype=s.tdtype, device="cuda")
+    for at in (0, n // 3 & ~7):
+        s.x, s.dx = both[:n].view(s.in_shape), both[at:at + n].view(s.in_shape)
+        s.load(x=x.numpy())
+        s.step()
+        torch.cuda.synchronize()
+        assert torch.equal(s.dx, dx) and torch.equal(s.wgrad, wgrad)
+    s.close()
