@@ -638,9 +638,10 @@ void pool_bwd(const PoolArgs& a, hipStream_t s)
 #undef FTP_PB
 }
 
-// A thread handles V consecutive pixels (16 bytes; one, where rows of a plane do not start on 16 bytes) of kScaleCh channels: their
-// loads are in flight together and share the pixels' sign words, which cost as much traffic as the deltas with a channel a thread (16
-// bits, 64 channels of 152^2, 32 images: 47 -> 39 us, at the rate of a copy).  The blocks behind the last one relay filters.
+// A thread handles V consecutive pixels (16 bytes; 8, where planes of 16-bit maps are a multiple of 4 pixels but not of 8; else one) of
+// kScaleCh channels: their loads are in flight together and share the pixels' sign words, which cost as much traffic as the deltas with
+// a channel a thread (16 bits, 64 channels of 152^2, 32 images: 39 -> 35 us; 512 of 38^2 22, with one pixel a thread 30).
+// Units start on dwords, no more (dy may).  The blocks behind the last one relay filters.
 constexpr int kScaleCh = 4;
 struct ScaleArgs { const void* dy; const uint32_t* sign; void* dst; int C, groups, per, blocks; long long HW; float slope; };
 
@@ -658,7 +659,7 @@ k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
     const uint32_t* const sg = a.sign + ((long long)image * ((a.C + 31) >> 5) + (c0 >> 5)) * a.HW + off;
     const T* const src = (const T*)a.dy + plane * a.HW + off;
     T* const dst = (T*)a.dst + plane * a.HW + off;
-    struct alignas(V * sizeof(T)) Unit { T e[V]; };
+    struct __attribute__((packed, aligned(V == 1 ? sizeof(T) : 4))) Unit { T e[V]; };
     Unit d[kScaleCh];
     uint32_t w[V];
 #pragma unroll
@@ -676,23 +677,20 @@ k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
 
 void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C, long long HW, float slope, int bf16, const PrepJob* jobs, int n, hipStream_t s)
 {
-    g_kernel_label = "k_scale_dy";
-    const int V = bf16 ? 8 : 4;
-    const bool wide = HW % V == 0 && (((uintptr_t)dy | (uintptr_t)dst | (uintptr_t)sign) & 15) == 0;
+    // (every plane starts where the map does, as far as a unit goes)
+    const bool dwords = (((uintptr_t)dy | (uintptr_t)dst) & 3) == 0;
+    const int V = !dwords ? 1 : bf16 && HW % 8 == 0 ? 8 : HW % 4 == 0 ? 4 : 1;
     ScaleArgs a{dy, sign, dst, C, (C + kScaleCh - 1) / kScaleCh, 0, 0, HW, slope};
-    a.per = (int)(((long long)a.groups * (HW / (wide ? V : 1)) + 255) / 256);
+    a.per = (int)(((long long)a.groups * (HW / V) + 255) / 256);
     a.blocks = a.per * batch;
     auto launch = [&](auto cap) {
         constexpr int CAP = decltype(cap)::value;
         PrepArgs<CAP> p;
         const dim3 grid((unsigned)(a.blocks + fill_prep(p, jobs, n)));
-        if (bf16) {
-            if (wide) hipLaunchKernelGGL((k_scale_dy<bf16_t, 8, CAP>), grid, dim3(256), 0, s, a, p);
-            else      hipLaunchKernelGGL((k_scale_dy<bf16_t, 1, CAP>), grid, dim3(256), 0, s, a, p);
-        } else {
-            if (wide) hipLaunchKernelGGL((k_scale_dy<float, 4, CAP>), grid, dim3(256), 0, s, a, p);
-            else      hipLaunchKernelGGL((k_scale_dy<float, 1, CAP>), grid, dim3(256), 0, s, a, p);
-        }
+#define FTP_SD(T, VV) do { g_kernel_label = "k_scale_dy<" #T ", " #VV ">"; hipLaunchKernelGGL((k_scale_dy<T, VV, CAP>), grid, dim3(256), 0, s, a, p); } while (0)
+        if (bf16) { if (V == 8) FTP_SD(bf16_t, 8); else if (V == 4) FTP_SD(bf16_t, 4); else FTP_SD(bf16_t, 1); }
+        else      { if (V == 4) FTP_SD(float, 4); else FTP_SD(float, 1); }
+#undef FTP_SD
     };
     if (n <= kPrepFew) launch(std::integral_constant<int, kPrepFew>()); else launch(std::integral_constant<int, kPrepJobs>());
 }
