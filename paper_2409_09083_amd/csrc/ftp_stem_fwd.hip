@@ -41,7 +41,7 @@ struct StemArgs {
     int N, M;
     int tw, th, tiles_x, tiles_y;                      // tiles, in output pixels
     int blocks;                                        // of the convolution; those behind relay filters
-    int strips, lines, xcd;                            // runs of tiles of a stack one below the other; such runs of all images and grid rows; 1: xcd_order
+    int rows, lines, xcd;                              // grid rows of all images; runs of tiles of them; 1: xcd_order
     int run;                                           // tiles one below the other that a workgroup takes
     int plain;                                         // no bias, slope in (0, 1]
 };
@@ -95,7 +95,7 @@ k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
     extern __shared__ __attribute__((aligned(16))) float lds[];
     const int tid = threadIdx.x, lane = tid & 63, n16 = lane & 15, q = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (image, grid row, strip, grid column, tile column): the workgroups of a strip of the map share the lines of its rows, on one XCD
+    // (strip, image, grid row, grid column, tile column): the workgroups of a strip of the map share the lines of its rows, on one XCD
     const int row = a.M * a.tiles_x;
     int line, w;
     if (a.xcd) {
@@ -103,7 +103,9 @@ k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
     } else {
         line = (int)blockIdx.x / row; w = (int)blockIdx.x - line * row;
     }
-    const int gr = line / a.strips, strip = line - gr * a.strips, n = gr / a.N, ti = gr - n * a.N;
+    int strip, gr;
+    stem_line(line, a.rows, strip, gr);
+    const int n = gr / a.N, ti = gr - n * a.N;
     const int tj = w / a.tiles_x, bx = w - tj * a.tiles_x, stack = ti * a.M + tj;
     const int x1 = a.rt.x1[tj], y1 = a.rt.y1[ti];
     const int ox0 = a.rt.x0[tj] + bx * a.tw;
@@ -399,9 +401,9 @@ void stem_fwd(const ConvArgs& c, const PrepJob* jobs, int n, hipStream_t st)
     int mw = 0, mh = 0;
     for (int t = 0; t < c.M; ++t) mw = std::max(mw, c.rect.x1[t] - c.rect.x0[t] + 1);
     for (int t = 0; t < c.N; ++t) mh = std::max(mh, c.rect.y1[t] - c.rect.y0[t] + 1);
-    const StemTiles t = stem_tiles(c.K, c.S, c.pooled, c.Cin, c.Cout, mw, mh, c.N * c.M, c.batch);
-    s.tw = t.tw; s.th = t.th; s.tiles_x = t.tiles_x; s.tiles_y = t.tiles_y; s.run = t.run; s.strips = t.strips;
-    s.lines = s.strips * c.N * c.batch;
+    const StemTiles t = stem_tiles(c.K, c.S, c.pooled, c.bf16, c.Cin, c.Cout, mw, mh, c.N * c.M, c.batch);
+    s.tw = t.tw; s.th = t.th; s.tiles_x = t.tiles_x; s.tiles_y = t.tiles_y; s.run = t.run;
+    s.rows = c.N * c.batch; s.lines = t.strips * s.rows;
     s.xcd = s.lines >= 64 ? 1 : 0;                     // (few lines would load the XCDs unevenly)
     const int row = c.M * s.tiles_x;
     s.blocks = s.xcd ? (int)xcd_grid(s.lines, row) : s.lines * row;

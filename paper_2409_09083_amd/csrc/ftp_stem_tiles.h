@@ -18,12 +18,12 @@ constexpr size_t kStemLds = 64 * 1024;                 // most LDS of a workgrou
 
 struct StemTiles {
     int tw, th, tiles_x, tiles_y;                      // tile extent in output pixels, tiles of the largest rectangle
-    int run, strips;                                   // tiles one below the other that a workgroup takes; such runs
+    int run, strips;                                   // tiles one below the other that a workgroup takes; such runs of a stack
     size_t lds;
 };
 
 // mw, mh: largest rectangle of a stack; stacks * images rectangles in all.
-inline StemTiles stem_tiles(int K, int S, bool pool, int Cin, int Cout, int mw, int mh, int stacks, int batch)
+inline StemTiles stem_tiles(int K, int S, bool pool, bool bf16, int Cin, int Cout, int mw, int mh, int stacks, int batch)
 {
     StemTiles s;
     // Tiles cover the widest rectangle in equal blocks of at most 32 columns.  A workgroup's four wavefronts take 16 windows or 64
@@ -47,15 +47,23 @@ inline StemTiles stem_tiles(int K, int S, bool pool, int Cin, int Cout, int mw, 
         if (room <= least) { while (s.lds > kStemLds && most > 1) rows(--most); break; }
         if (s.lds <= kStemLds && (long long)s.tiles_x * s.tiles_y * stacks * batch >= 512) break;
     }
-    // runs of tiles while every CU still gets its four workgroups
+    // Runs of tiles while every CU still gets its four workgroups, all of the same length (3 -> 16, 16 images of 304^2 in 3 x 3 stacks, 7
+    // tiles: 6 + 1 of them, of which the even XCDs had the long ones, 73 us, 4 + 3 45); of at most 2 where fp32 stores are most of the work
+    // (3 -> 32, 32 images of 608^2 in 8 x 8 stacks, runs of 1 / 2 / 3 / 6: 596 / 596 / 639 / 700; 24 of 548 x 247 159 / 190 / 204 / 211).
     s.run = 1;
     const int PH = (s.th * NP - 1) * S + K, PW = (s.tw * NP - 1) * S + K;
     if (Cout <= 32 && PH * PW <= 256 * stem_units(K, S, pool)) {
         const long long per = (long long)s.tiles_x * stacks * batch;
-        while (s.run < s.tiles_y && per * ((s.tiles_y + s.run) / (s.run + 1)) >= 1024) ++s.run;
+        const int most = K == 3 && !pool && !bf16 && Cout > 16 ? std::min(2, s.tiles_y) : s.tiles_y;
+        while (s.run < most && per * ((s.tiles_y + s.run) / (s.run + 1)) >= 1024) ++s.run;
     }
     s.strips = (s.tiles_y + s.run - 1) / s.run;
+    s.run = (s.tiles_y + s.strips - 1) / s.strips;
     return s;
 }
+
+// Runs (strip of the stack, image, grid row) in the order they are numbered: the strips of an image's grid row lie `rows` runs apart, so
+// that short last ones do not all fall to the same XCDs (runs go to them round-robin).  rows: grid rows of all images.
+FTP_HD inline void stem_line(int line, int rows, int& strip, int& row) { strip = line / rows; row = line - strip * rows; }
 
 }  // namespace ftp
