@@ -332,7 +332,7 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
                     if (!relaid) { prep_pass(p, weights, workspace, false, s); relaid = true; }
                     if (mfma_conv_fwd(a, ext, wt, s)) direct_conv_fwd(a, s);
                 });
-            } else if (use_mfma() && stem_fwd_eligible(a)) {
+            } else if (use_mfma() && stem_fwd_eligible(a) && stem_fwd_pays(a)) {
                 rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] {
                     PrepJob jobs[kPrepJobs];
                     int n = relaid ? 0 : prep_jobs(p, weights, workspace, false, jobs, s);
@@ -340,6 +340,10 @@ int ftp_forward(const ftp_plan_t* plan, const void* x, const void* const* weight
                     relaid = true;
                     stem_fwd(a, jobs, n, s);
                 });
+            } else if (use_mfma() && plain_geometry(a) && thin_conv_fwd_eligible(a)) {
+                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { thin_conv_fwd(a, s); });
+            } else if (use_mfma() && thin_conv_fwd_gen_eligible(a)) {
+                rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { thin_conv_fwd_gen(a, s); });
             } else {
                 rc = timed(plan, FTP_PASS_CONV_FWD, u.layer, s, [&] { direct_conv_fwd(a, s); });
             }

@@ -197,7 +197,13 @@ void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, bool b
 
 // forward pass of first layers on the fp32 matrix cores (ftp_stem_fwd.hip)
 bool stem_fwd_eligible(const ConvArgs& a);
+bool stem_fwd_pays(const ConvArgs& a);              // (against the two kernels below)
 void stem_fwd(const ConvArgs& a, const PrepJob* jobs, int n, hipStream_t s);      // n <= kPrepFew jobs of filter relayout in the same launch
+// ... on the vector ALU: 3x3 at stride 1, with or without a pool; 5x5, 7x7 and stride 2 without one (ftp_thin.hip)
+bool thin_conv_fwd_eligible(const ConvArgs& a);
+void thin_conv_fwd(const ConvArgs& a, hipStream_t s);
+bool thin_conv_fwd_gen_eligible(const ConvArgs& a);
+void thin_conv_fwd_gen(const ConvArgs& a, hipStream_t s);
 bool thin_bwd_data_strided_eligible(const ConvArgs& a);
 void thin_conv_bwd_data_strided(const ConvArgs& a, const RectTab& ext, hipStream_t s);   // ext: extent of the delta view per stack
 bool thin_bwd_data_eligible(const ConvArgs& a);

@@ -392,6 +392,20 @@ bool stem_fwd_eligible(const ConvArgs& c)
     return !c.pooled && (c.K == 5 || c.K == 7 || (c.S == 2 && (c.K == 1 || c.K == 3)));
 }
 
+// Blocks of 16 output channels of which most are empty cost as much as full ones: from some pixels on (below, the vector ALU's kernels
+// take the channels one after the other, and few workgroups wait for that) layers with few real channels a block go to them (us, vector ALU / here:
+// 3x3, 16 images of 304^2 in 3 x 3 stacks, 3 -> 8 34 / 47, -> 12 41 / 46, -> 16 50 / 45, -> 20 58 / 66, -> 32 82 / 62; with a pool 29 / 36, 33 / 36, 39 / 35, 45 / 51,
+// 61 / 49; 8 images of 304^2, one stack, with a pool, 3 -> 8 18 / 17; 5x5 3 -> 4 59 / 72, -> 8 78 / 73; 3x3 of stride 2, 32 images of 608^2, 3 -> 8 117 / 136, -> 16 207 / 153).
+bool stem_fwd_pays(const ConvArgs& c)
+{
+    const int rest = c.Cout % 32, blocks = c.Cout / 32 * 2 + (rest == 0 ? 0 : rest <= 16 ? 1 : 2);
+    const double real = (double)c.Cout / blocks * (c.Cin <= 3 ? 3 : 4) / 3.0, pixels = (double)c.batch * c.Hc * c.Wc;
+    if (c.K == 3 && c.S == 1) return pixels < 1.5e5 || real >= (pixels < (c.pooled ? 1e6 : 3e5) ? 9 : 13);
+    if (c.K >= 5 && c.S == 1) return pixels < 8e4 || real >= 6;
+    if (c.K == 3) return pixels < 5e5 || real >= 9;
+    return true;
+}
+
 void stem_fwd(const ConvArgs& c, const PrepJob* jobs, int n, hipStream_t st)
 {
     StemArgs s;

@@ -18,6 +18,255 @@ __device__ __forceinline__ bool in_rect_thin(const RectTab& r, int ti, int tj, i
 }
 
 // dZ of one element from the delta and the owner's decision code (see ftp_direct.hip: delta_z).
+// ---- forward of a K = 3 convolution with at most 4 input channels (+ leaky ReLU, + fused 2x2 pool) ---------------
+// Workgroup = ntx x nty threads on one (stack, image); a thread produces one pool window (2 x 2 convolution outputs)
+// or, without a pool, two neighbouring pixels, for every output channel in turn.  The input patch of the tile
+// (all input channels, filter halo, zero outside the map) and the filter with its bias sit in LDS; a thread keeps
+// its own 4 x 4 (or 3 x 4) patch per input channel in registers and reads the 9 * CI weights of an output channel
+// as broadcast vectors.  A thread sees all channels of its pixel, so it writes the sign words itself.
+constexpr int kThinFwdPatch = 1280, kThinFwdCout = 64;     // floats of one channel's patch; channels whose weights fit LDS
+
+template <typename T, bool POOL, int CI>
+__global__ void __launch_bounds__(256)
+k_conv_fwd_thin(View in, View out, View mask, View osign, RectTab rt, RectTab own, const T* __restrict__ w,
+                const T* __restrict__ bias, int Cin, int Cout, int Hc, int Wc, float slope, int M, int batch,
+                int ntx, int nty, int tiles_x)
+{
+    constexpr int PH = POOL ? 4 : 3, PWD = 4, WR = 9 * CI;         // register patch rows / columns, weights per channel
+    constexpr int SY = POOL ? 2 : 1, SX = 2;                        // convolution pixels per thread
+    __shared__ __attribute__((aligned(16))) float xp[CI * kThinFwdPatch];
+    __shared__ __attribute__((aligned(16))) float wl[kThinFwdCout * (WR + 1)];
+    const int tid = threadIdx.x;
+    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
+    const int ti = stack / M, tj = stack % M;
+    // the rectangle is in output coordinates (pooled if POOL); tiles of ntx x nty threads
+    const int bx = blockIdx.x % tiles_x, by = blockIdx.x / tiles_x;
+    const int OX = POOL ? 1 : 2;                                    // output pixels per thread along x
+    const int ox0 = rt.x0[tj] + bx * ntx * OX, oy0 = rt.y0[ti] + by * nty;
+    if (ox0 > rt.x1[tj] || oy0 > rt.y1[ti]) return;
+    // convolution-resolution origin of the patch and its extent
+    const int cx0 = ox0 * (POOL ? 2 : 1) - 1, cy0 = oy0 * SY - 1;
+    const int PW = SX * ntx + 2, PHT = SY * nty + 2, PP = (PW + 1) & ~1;
+    for (int i = tid; i < CI * PHT * PW; i += 256) {
+        const int ci = i / (PHT * PW), rem = i - ci * (PHT * PW), r = rem / PW, q = rem - r * PW;
+        const int y = cy0 + r, x = cx0 + q;
+        // positions only pixels beyond the rectangle would read may lie outside the input view
+        const int ylim = (rt.y1[ti] + 1) * SY, xlim = (rt.x1[tj] + 1) * (POOL ? 2 : 1);
+        const bool okp = ci < Cin && y >= 0 && y < Hc && x >= 0 && x < Wc && y <= ylim && x <= xlim;
+        xp[ci * kThinFwdPatch + r * PP + q] = okp ? ld(at<T>(in, stack, ti, tj, n, ci, y, x)) : 0.0f;
+    }
+    for (int i = tid; i < Cout * (WR + 1); i += 256) {
+        const int co = i / (WR + 1), r = i - co * (WR + 1);
+        float v = 0.0f;
+        if (r < WR) { const int ci = r / 9, t = r - ci * 9; if (ci < Cin) v = ld(w + ((size_t)co * Cin + ci) * 9 + t); }
+        else if (bias) v = ld(bias + co);
+        wl[i] = v;
+    }
+    __syncthreads();
+    const int tx = tid % ntx, ty = tid / ntx;
+    if (ty >= nty) return;
+    const int oy = oy0 + ty, ox = ox0 + tx * OX;
+    float p[CI][PH][PWD];
+#pragma unroll
+    for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+        for (int r = 0; r < PH; ++r) {
+            const float* row = xp + ci * kThinFwdPatch + (SY * ty + r) * PP + SX * tx;
+            const float2 a = *(const float2*)row, b = *(const float2*)(row + 2);
+            p[ci][r][0] = a.x; p[ci][r][1] = a.y; p[ci][r][2] = b.x; p[ci][r][3] = b.y;
+        }
+    const bool v0 = oy <= rt.y1[ti] && ox <= rt.x1[tj];
+    const bool v1 = !POOL && oy <= rt.y1[ti] && ox + 1 <= rt.x1[tj];
+    const bool o0 = v0 && in_rect_thin(own, ti, tj, oy, ox), o1 = v1 && in_rect_thin(own, ti, tj, oy, ox + 1);
+    uint32_t s0 = 0, s1 = 0;
+    for (int co = 0; co < Cout; ++co) {
+        const float* wc = wl + co * (WR + 1);
+        float acc[SY][SX];
+#pragma unroll
+        for (int a = 0; a < SY; ++a)
+#pragma unroll
+            for (int b = 0; b < SX; ++b) acc[a][b] = 0.0f;
+#pragma unroll
+        for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+            for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) {
+                    const float wv = wc[ci * 9 + ky * 3 + kx];
+#pragma unroll
+                    for (int a = 0; a < SY; ++a)
+#pragma unroll
+                        for (int b = 0; b < SX; ++b) acc[a][b] = fmaf(wv, p[ci][a + ky][b + kx], acc[a][b]);
+                }
+        const float bv = wc[WR];
+        if (POOL) {
+            // candidates are compared as the map would hold them; the first maximum in window order wins
+            float best = stored(leaky(acc[0][0] + bv, slope), (const T*)nullptr);
+            int bi = 0;
+            const float c1 = stored(leaky(acc[0][1] + bv, slope), (const T*)nullptr);
+            const float c2 = stored(leaky(acc[SY - 1][0] + bv, slope), (const T*)nullptr);
+            const float c3 = stored(leaky(acc[SY - 1][1] + bv, slope), (const T*)nullptr);
+            if (c1 > best) { best = c1; bi = 1; }
+            if (c2 > best) { best = c2; bi = 2; }
+            if (c3 > best) { best = c3; bi = 3; }
+            if (v0) {
+                st(at<T>(out, stack, ti, tj, n, co, oy, ox), best);
+                if (o0) *at<uint8_t>(mask, stack, ti, tj, n, co, oy, ox) = (uint8_t)((bi << 1) | (best > 0.0f ? 1 : 0));
+            }
+            s0 |= (best > 0.0f ? 1u : 0u) << (co & 31);
+        } else {
+            const float a0 = stored(leaky(acc[0][0] + bv, slope), (const T*)nullptr);
+            const float a1 = stored(leaky(acc[0][1] + bv, slope), (const T*)nullptr);
+            if (v0) st(at<T>(out, stack, ti, tj, n, co, oy, ox), a0);
+            if (v1) st(at<T>(out, stack, ti, tj, n, co, oy, ox + 1), a1);
+            s0 |= (a0 > 0.0f ? 1u : 0u) << (co & 31);
+            s1 |= (a1 > 0.0f ? 1u : 0u) << (co & 31);
+        }
+        if ((co & 31) == 31 || co == Cout - 1) {
+            if (o0) *at<uint32_t>(osign, stack, ti, tj, n, co >> 5, oy, ox) = s0;
+            if (o1) *at<uint32_t>(osign, stack, ti, tj, n, co >> 5, oy, ox + 1) = s1;
+            s0 = s1 = 0;
+        }
+    }
+}
+
+bool thin_conv_fwd_eligible(const ConvArgs& a) { return a.K == 3 && a.Cin <= 4 && a.Cout <= kThinFwdCout; }
+
+void thin_conv_fwd(const ConvArgs& a, hipStream_t s)
+{
+    int mw = 0, mh = 0;
+    for (int t = 0; t < a.M; ++t) mw = mw > a.rect.x1[t] - a.rect.x0[t] + 1 ? mw : a.rect.x1[t] - a.rect.x0[t] + 1;
+    for (int t = 0; t < a.N; ++t) mh = mh > a.rect.y1[t] - a.rect.y0[t] + 1 ? mh : a.rect.y1[t] - a.rect.y0[t] + 1;
+    const int OX = a.pooled ? 1 : 2, SY = a.pooled ? 2 : 1;
+    // threads along x cover the widest rectangle without a ragged last tile; at most 32 of them
+    const int need_x = (mw + OX - 1) / OX;
+    int tiles_x = (need_x + 31) / 32;
+    const int ntx = (need_x + tiles_x - 1) / tiles_x;
+    tiles_x = (need_x + ntx - 1) / ntx;
+    int nty_max = 256 / ntx; if (nty_max > 32) nty_max = 32;
+    const int tiles_y = (mh + nty_max - 1) / nty_max;
+    const int nty = (mh + tiles_y - 1) / tiles_y;
+    const int PP = (2 * ntx + 2 + 1) & ~1;
+    if ((SY * nty + 2) * PP > kThinFwdPatch) { direct_conv_fwd(a, s); return; }
+    dim3 grid(tiles_x * tiles_y, 1, a.N * a.M * a.batch), block(256);
+    g_kernel_label = "k_conv_fwd_thin";
+#define FTP_TF(T, PL, CI) hipLaunchKernelGGL((k_conv_fwd_thin<T, PL, CI>), grid, block, 0, s, a.in, a.out, a.mask, a.osign, a.rect, a.own, (const T*)a.w, (const T*)a.bias, a.Cin, a.Cout, a.Hc, a.Wc, a.slope, a.M, a.batch, ntx, nty, tiles_x)
+#define FTP_TFC(T, PL) do { if (a.Cin <= 3) FTP_TF(T, PL, 3); else FTP_TF(T, PL, 4); } while (0)
+    if (a.bf16) { if (a.pooled) FTP_TFC(bf16_t, true); else FTP_TFC(bf16_t, false); }
+    else        { if (a.pooled) FTP_TFC(float, true); else FTP_TFC(float, false); }
+#undef FTP_TFC
+#undef FTP_TF
+}
+
+// ---- forward of the other thin first layers: 5x5 / 7x7 filters, stride 2 (no fused pool) ------------------------------
+// Workgroup = 16 x 16 output pixels of one (stack, image), one pixel per thread.  The input patch of the tile (all
+// input channels, zero outside the map) is staged in LDS once; a thread copies its own K x K x CI patch into registers
+// and then walks the output channels, 16 at a time: their filters (+ bias) are staged in LDS as rows of whole float4s
+// and read as broadcast vectors, K * K * CI multiply-adds per channel.  A thread sees all channels of its pixel, so
+// it writes the sign words itself.
+constexpr int kThinGenTile = 16, kThinGenCoc = 16;
+
+template <typename T, int K, int S, int CI>
+__global__ void __launch_bounds__(256)
+k_conv_fwd_thin_gen(View in, View out, View osign, RectTab rt, RectTab own, const T* __restrict__ w,
+                    const T* __restrict__ bias, int Cin, int Cout, int Hi, int Wi, float slope, int M, int batch, int tiles_x)
+{
+    constexpr int P = K / 2, KK = K * K, TS = kThinGenTile, COC = kThinGenCoc;
+    constexpr int PD = S * (TS - 1) + K, PP = PD | 1;               // patch extent, odd pitch
+    constexpr int WR = CI * KK, WRP = (WR + 1 + 3) & ~3;            // weights of a channel (+ bias), padded to float4s
+    __shared__ __attribute__((aligned(16))) float xp[CI * PD * PP];
+    __shared__ __attribute__((aligned(16))) float wl[COC * WRP];
+    const int tid = threadIdx.x;
+    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
+    const int ti = stack / M, tj = stack % M;
+    const int bx = blockIdx.x % tiles_x, by = blockIdx.x / tiles_x;
+    const int ox0 = rt.x0[tj] + bx * TS, oy0 = rt.y0[ti] + by * TS;
+    if (ox0 > rt.x1[tj] || oy0 > rt.y1[ti]) return;
+    const int ix0 = S * ox0 - P, iy0 = S * oy0 - P;
+    // positions only pixels beyond the rectangle would read may lie outside the input view
+    const int ylim = S * rt.y1[ti] + P, xlim = S * rt.x1[tj] + P;
+    for (int i = tid; i < CI * PD * PD; i += 256) {
+        const int ci = i / (PD * PD), rem = i - ci * (PD * PD), r = rem / PD, q = rem - r * PD;
+        const int y = iy0 + r, x = ix0 + q;
+        const bool okp = ci < Cin && y >= 0 && y < Hi && x >= 0 && x < Wi && y <= ylim && x <= xlim;
+        xp[(ci * PD + r) * PP + q] = okp ? ld(at<T>(in, stack, ti, tj, n, ci, y, x)) : 0.0f;
+    }
+    __syncthreads();
+    const int tx = tid % TS, ty = tid / TS;
+    const int oy = oy0 + ty, ox = ox0 + tx;
+    float p[WR];
+#pragma unroll
+    for (int ci = 0; ci < CI; ++ci)
+#pragma unroll
+        for (int ky = 0; ky < K; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < K; ++kx) p[ci * KK + ky * K + kx] = xp[(ci * PD + S * ty + ky) * PP + S * tx + kx];
+    const bool v0 = oy <= rt.y1[ti] && ox <= rt.x1[tj];
+    const bool o0 = v0 && in_rect_thin(own, ti, tj, oy, ox);
+    uint32_t s0 = 0;
+    for (int c0 = 0; c0 < Cout; c0 += COC) {
+        __syncthreads();                               // the previous block's filters have been consumed
+        for (int i = tid; i < COC * WRP; i += 256) {
+            const int c = i / WRP, r = i - c * WRP;
+            float v = 0.0f;
+            if (c0 + c < Cout) {
+                if (r < WR) { const int ci = r / KK, t = r - ci * KK; if (ci < Cin) v = ld(w + ((size_t)(c0 + c) * Cin + ci) * KK + t); }
+                else if (r == WR && bias) v = ld(bias + c0 + c);
+            }
+            wl[i] = v;
+        }
+        __syncthreads();
+        for (int c = 0; c < COC; ++c) {
+            const int co = c0 + c;
+            if (co >= Cout) break;
+            const float4* w4 = (const float4*)(wl + c * WRP);
+            float acc = 0.0f;
+#pragma unroll
+            for (int q = 0; q < WRP / 4; ++q) {
+                const float4 wv = w4[q];
+                if (4 * q + 0 < WR) acc = fmaf(wv.x, p[4 * q + 0 < WR ? 4 * q + 0 : 0], acc);
+                if (4 * q + 1 < WR) acc = fmaf(wv.y, p[4 * q + 1 < WR ? 4 * q + 1 : 0], acc);
+                if (4 * q + 2 < WR) acc = fmaf(wv.z, p[4 * q + 2 < WR ? 4 * q + 2 : 0], acc);
+                if (4 * q + 3 < WR) acc = fmaf(wv.w, p[4 * q + 3 < WR ? 4 * q + 3 : 0], acc);
+            }
+            const float bv = wl[c * WRP + WR];
+            const float a0 = stored(leaky(acc + bv, slope), (const T*)nullptr);
+            if (v0) st(at<T>(out, stack, ti, tj, n, co, oy, ox), a0);
+            s0 |= (a0 > 0.0f ? 1u : 0u) << (co & 31);
+            if ((co & 31) == 31 || co == Cout - 1) {
+                if (o0) *at<uint32_t>(osign, stack, ti, tj, n, co >> 5, oy, ox) = s0;
+                s0 = 0;
+            }
+        }
+    }
+}
+
+bool thin_conv_fwd_gen_eligible(const ConvArgs& a)
+{
+    return a.Cin <= 4 && !a.pooled && (a.K == 5 || a.K == 7 || (a.S == 2 && (a.K == 1 || a.K == 3))) && (a.S == 1 || a.S == 2);
+}
+
+void thin_conv_fwd_gen(const ConvArgs& a, hipStream_t s)
+{
+    int mw = 0, mh = 0;
+    for (int t = 0; t < a.M; ++t) mw = std::max(mw, a.rect.x1[t] - a.rect.x0[t] + 1);
+    for (int t = 0; t < a.N; ++t) mh = std::max(mh, a.rect.y1[t] - a.rect.y0[t] + 1);
+    const int tiles_x = (mw + kThinGenTile - 1) / kThinGenTile, tiles_y = (mh + kThinGenTile - 1) / kThinGenTile;
+    dim3 grid(tiles_x * tiles_y, 1, a.N * a.M * a.batch), block(256);
+    g_kernel_label = "k_conv_fwd_thin_gen";
+#define FTP_TG(T, KK, SS, CI) hipLaunchKernelGGL((k_conv_fwd_thin_gen<T, KK, SS, CI>), grid, block, 0, s, a.in, a.out, a.osign, a.rect, a.own, (const T*)a.w, (const T*)a.bias, a.Cin, a.Cout, a.Hi, a.Wi, a.slope, a.M, a.batch, tiles_x)
+#define FTP_TGC(T, KK, SS) do { if (a.Cin <= 3) FTP_TG(T, KK, SS, 3); else FTP_TG(T, KK, SS, 4); } while (0)
+#define FTP_TGK(T) do { \
+        if (a.K == 7)      { if (a.S == 2) FTP_TGC(T, 7, 2); else FTP_TGC(T, 7, 1); } \
+        else if (a.K == 5) { if (a.S == 2) FTP_TGC(T, 5, 2); else FTP_TGC(T, 5, 1); } \
+        else if (a.K == 3) FTP_TGC(T, 3, 2); \
+        else               FTP_TGC(T, 1, 2); } while (0)
+    if (a.bf16) FTP_TGK(bf16_t); else FTP_TGK(float);
+#undef FTP_TGK
+#undef FTP_TGC
+#undef FTP_TG
+}
+
 // ---- delta at the input of a convolution with at most CIT input channels ------------------------------------
 // Workgroup = 64 x 4 pixels of one (stack, image): wide tiles keep the reads of the (pooled) delta rows long.
 // LDS = dZ patch of COC channels with the filter halo.

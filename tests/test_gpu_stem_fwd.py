@@ -79,3 +79,55 @@ def test_bias_sums_travel_with_the_shares(cin, cout):
     for a, ref in ((got[:n], w64.grad.reshape(-1)), (got[n:], b64.grad)):
         assert float((a - ref).abs().max() / ref.abs().max()) < 1e-5
     s.close()
+
+
+def _one_layer(k, stride, cin, cout, batch, h, w, grid, dtype, pooled, x, weights):
+    """y, signs, decision codes (all of image 0) and the kernel of a first layer's forward pass over copies of one image."""
+    import torch
+    from paper_2409_09083_amd import binding as B
+    from paper_2409_09083_amd.harness import Session
+    s = Session((conv(cin, cout, k, stride=stride),) + ((pool(cout),) if pooled else ()), batch, cin, h, w, grid, (2 if pooled else 1,), dtype)
+    s.x.copy_(x.expand(s.in_shape))
+    s.weights = [weights] + [None] * pooled
+    B.ftp_profile(s.plan, 1)
+    s.forward()
+    torch.cuda.synchronize()
+    names = {r["kernel"].split("<")[0] for r in B.ftp_profile_read(s.plan)}
+    last = 2 if pooled else 1
+    out = [s.y[0].clone(), s._buffer(last, B.FTP_BUF_SIGN)[0][0].clone()]
+    if pooled:
+        out.append(s._buffer(last, B.FTP_BUF_MASK)[0][0].clone())
+    s.close()
+    return out, names
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("k,stride,cin,cout,batch,h,w,grid,pooled", [
+    (3, 1, 3, 8, 10, 128, 130, (2, 2), True), (3, 1, 4, 9, 70, 124, 128, (1, 1), True), (3, 1, 3, 20, 20, 129, 131, (1, 3), False), (3, 1, 2, 37, 20, 127, 128, (1, 1), False),
+    (5, 1, 3, 4, 5, 131, 130, (2, 1), False), (7, 1, 1, 4, 5, 128, 133, (1, 1), False), (3, 2, 3, 8, 124, 129, 130, (1, 2), False)])
+def test_few_channels_of_large_launches_take_the_vector_alu(dtype, k, stride, cin, cout, batch, h, w, grid, pooled):
+    """The two kernels add in the same order: an image alone and among many has the same bits."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((1, cin, h, w), device="cuda", generator=g)
+    weights = (torch.randn((cout, cin, k, k), device="cuda", generator=g) / (k * cin ** 0.5)).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    alone, small = _one_layer(k, stride, cin, cout, 1, h, w, grid, dtype, pooled, x, weights)
+    many, large = _one_layer(k, stride, cin, cout, batch, h, w, grid, dtype, pooled, x, weights)
+    assert small == {"k_conv_fwd_stem"} and large == {"k_conv_fwd_thin" if k == 3 and stride == 1 else "k_conv_fwd_thin_gen"}
+    for a, b in zip(alone, many):
+        assert torch.equal(a, b)
+
+
+def test_maps_beyond_the_matrix_kernel_offsets():
+    """A map of more than 2 GB over all channels: the vector ALU's kernel, checked at two corners against 64 bits."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(9)
+    n = 2304
+    x, w = torch.randn((1, 3, n, n), device="cuda", generator=g), torch.randn((64, 3, 3, 3), device="cuda", generator=g) / 5
+    (y, _), names = _one_layer(3, 1, 3, 64, 1, n, n, (1, 1), "f32", False, x, w)
+    assert names == {"k_conv_fwd_thin"}
+    z = lambda part: torch.nn.functional.conv2d(part.cpu().double(), w.cpu().double(), padding=1)
+    for got, ref in ((y[:, :40, :40], z(x[:, :, :41, :41])[0, :, :40, :40]), (y[:, -40:, -40:], z(x[:, :, -41:, -41:])[0, :, 1:, 1:])):
+        ref = torch.where(ref > 0, ref, ref * 0.1)
+        # (27 products and their sums, each rounded to 24 bits)
+        assert float((got.cpu().double() - ref).abs().max() / ref.abs().max()) < 28 * 2.0 ** -24
