@@ -48,13 +48,14 @@ inline StemTiles stem_tiles(int K, int S, bool pool, bool bf16, int Cin, int Cou
         if (s.lds <= kStemLds && (long long)s.tiles_x * s.tiles_y * stacks * batch >= 512) break;
     }
     // Runs of tiles while every CU still gets its four workgroups, all of the same length (3 -> 16, 16 images of 304^2 in 3 x 3 stacks, 7
-    // tiles: 6 + 1 of them, of which the even XCDs had the long ones, 73 us, 4 + 3 45); of at most 2 where fp32 stores are most of the work
-    // (3 -> 32, 32 images of 608^2 in 8 x 8 stacks, runs of 1 / 2 / 3 / 6: 596 / 596 / 639 / 700; 24 of 548 x 247 159 / 190 / 204 / 211).
+    // tiles: 6 + 1 of them, of which the even XCDs had the long ones, 73 us, 4 + 3 45); of at most 2 (fp32) or 3 where stores are most of the
+    // work (3 -> 32, 32 images of 608^2 in 8 x 8 stacks, runs of 1 / 2 / 3 / 6: 596 / 596 / 639 / 700, 16 bits 448 / 426 / 415 / 423; 24 of
+    // 548 x 247 159 / 190 / 204 / 211, 129 / 121 / 121 / 129; 16 of 304^2 68 / 62 / 63 / 73, 72 / 69 / 70 / 81).
     s.run = 1;
     const int PH = (s.th * NP - 1) * S + K, PW = (s.tw * NP - 1) * S + K;
     if (Cout <= 32 && PH * PW <= 256 * stem_units(K, S, pool)) {
         const long long per = (long long)s.tiles_x * stacks * batch;
-        const int most = K == 3 && !pool && !bf16 && Cout > 16 ? std::min(2, s.tiles_y) : s.tiles_y;
+        const int most = K == 3 && !pool && Cout > 16 ? std::min(bf16 ? 3 : 2, s.tiles_y) : s.tiles_y;
         while (s.run < most && per * ((s.tiles_y + s.run) / (s.run + 1)) >= 1024) ++s.run;
     }
     s.strips = (s.tiles_y + s.run - 1) / s.run;
