@@ -19,12 +19,13 @@ __device__ __forceinline__ TileGeom tile_geom(const MfmaConvArgs& a, int x0, int
 template <int S, int P>
 __device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) { return conv_tile_pix(g, wq, x1, S, P); }
 
-// The workgroup's stack and channel block (vgroup = stack * mblocks + channel block) and tile, in the order the launch chose.
+// The workgroup's stack and channel block (vgroup = stack * mblocks + channel block) and tile, in the order the launch chose (one word of
+// the arguments says it: a wait more for them in front of every workgroup was 0.1 to 0.3 us of launches of 10 to 20).
 __device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int index, int& vgroup, int& vtile)
 {
-    const int ntiles = a.tiles_x * a.tiles_r;
-    if (__builtin_expect(a.row_run, 0)) return row_order(index, a.stacks / a.M, a.M, a.mblocks, ntiles, a.row_run, vgroup, vtile);
-    if (a.xcd_groups) return xcd_order(index, a.mblocks * a.stacks, ntiles, vgroup, vtile);
+    const int ntiles = a.tiles_x * a.tiles_r, order = a.order;
+    if (order > 0) return row_order(index, a.stacks / a.M, a.M, a.mblocks, ntiles, order, vgroup, vtile);
+    if (order < 0) return xcd_order(index, a.mblocks * a.stacks, ntiles, vgroup, vtile);
     vgroup = index / ntiles; vtile = index - vgroup * ntiles;
     return true;
 }

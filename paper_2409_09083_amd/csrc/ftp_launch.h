@@ -82,7 +82,7 @@ struct MfmaConvArgs {
     int Hc, Wc;                                     // map extent at the convolution
     int TC, tiles_x, tiles_r;                       // column block (when tiles_x > 1), column / row-run tile counts
     int mblocks, stacks;                            // output-channel blocks; stacks
-    int row_run, xcd_groups;                        // order of the workgroups (the grid is 1-D): > 0: row_order; else 1: xcd_order
+    int order;                                      // of the workgroups (the grid is 1-D): > 0: row_order with units of so many tile rows; 0: as they lie; < 0: xcd_order
     int cap;                                        // pixels (pool windows) per tile
     int flat;                                       // 1: tiles are runs of cap pixels of the rectangle's pixel list, not runs of whole rows
     int cs;                                         // LDS channel stride of the patch = largest patch of any stack
@@ -98,7 +98,7 @@ bool mfma_conv_eligible(const ConvArgs& a, bool backward);
 // 16-bit storage: the layer multiplies on the bfloat matrix cores (stride-1 1x1 / 3x3)
 bool mfma_conv_packs_bf16(const ConvArgs& a);
 
-unsigned order_tiles(MfmaConvArgs& a, const ConvArgs& c, const TileChoice& tc, bool delta);      // sets row_run, xcd_groups; returns the grid
+unsigned order_tiles(MfmaConvArgs& a, const ConvArgs& c, const TileChoice& tc, bool delta);      // sets a.order; returns the grid
 
 // Filter relayout (ftp_prep.hip): one job per convolution of a pass, all in one launch.
 enum PrepKind : int {

@@ -324,20 +324,21 @@ unsigned order_tiles(MfmaConvArgs& a, const ConvArgs& c, const TileChoice& tc, b
     const int groups = a.mblocks * a.stacks, ntiles = a.tiles_x * a.tiles_r;
     const long long wgs = (long long)groups * ntiles;
     const bool whole = delta ? !(a.din.ss && a.dout.ss) : !(a.in.ss && a.out.ss);
-    a.row_run = 0; a.xcd_groups = 0;
+    a.order = 0;
     int mw = 0;
     for (int j = 0; j < c.M; ++j) mw = std::max(mw, a.rect.x1[j] - a.rect.x0[j] + 1);
     if (c.bf16 ? wgs >= 512 : whole && wgs >= 2048 && mw <= 40) {
         int rws[kTabGrid], rhs[kTabGrid];               // widths / heights of the stacks' rectangles per tile column / row
         for (int j = 0; j < c.M; ++j) rws[j] = a.rect.x1[j] - a.rect.x0[j] + 1;
         for (int i = 0; i < c.N; ++i) rhs[i] = a.rect.y1[i] - a.rect.y0[i] + 1;
-        a.row_run = choose_row_order(tc, rws, rhs, c.N, c.M, c.batch);
-        if (a.row_run) return row_order_grid(c.N, c.M, a.mblocks, ntiles, a.row_run);
+        a.order = choose_row_order(tc, rws, rhs, c.N, c.M, c.batch);
+        if (a.order) return row_order_grid(c.N, c.M, a.mblocks, ntiles, a.order);
     }
     // XCD order pays where several channel blocks compete for the L2 and the groups spread evenly over the 8 XCDs;
     // with one channel block the plain order (neighbouring tiles on different XCDs) balances better
-    a.xcd_groups = (a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0) ? 1 : 0;
-    return a.xcd_groups ? xcd_grid(groups, ntiles) : (unsigned)(groups * ntiles);
+    if (!(a.mblocks >= 2 && 8 % a.mblocks == 0 && groups % 8 == 0)) return (unsigned)(groups * ntiles);
+    a.order = -1;
+    return xcd_grid(groups, ntiles);
 }
 
 namespace {
