@@ -8,16 +8,18 @@
 
 namespace ftp {
 
+// (the area that the gradient's workgroups have)
+struct Back16Lds { static __device__ __forceinline__ uint4* at() { extern __shared__ __attribute__((aligned(16))) unsigned char lds16[]; return (uint4*)lds16; } };
+
 struct Back16Args { Wgrad16Args w; MfmaConvArgs d; int wgroups; };
 
 template <int WAVES_CI, int WM, int MT, int NT, int IN, bool WS>
 __global__ void __launch_bounds__(256, 2)
 k_back16(Back16Args a)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char lds16[];
     const int index = (int)blockIdx.x;
     if (index < a.wgroups) wgrad16_group<WAVES_CI, IN == BF_POOL ? 1 : 0, WS>(a.w, index);
-    else conv_bf16_group<3, WM, MT, NT, false, true, IN>(a.d, index - a.wgroups, (uint4*)lds16);
+    else conv_bf16_group<3, WM, MT, NT, false, true, IN, Back16Lds>(a.d, index - a.wgroups);
 }
 
 // False: no such kernel.

@@ -7,16 +7,17 @@
 
 namespace ftp {
 
+struct Back16OneLds { static __device__ __forceinline__ uint4* at() { extern __shared__ __attribute__((aligned(16))) uint4 one_lds[]; return one_lds; } };
+
 struct Back16OneArgs { MfmaWgradArgs w; MfmaConvArgs d; int wgroups; };
 
 template <int WAVES_CI, int WM, int MT, int NT, int IN>
 __global__ void __launch_bounds__(256, 2)
 k_back16_1x1(Back16OneArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) uint4 one_lds[];
     const int index = (int)blockIdx.x;
     if (index < a.wgroups) wgrad_mfma_group<bf16_t, 1, 2, WAVES_CI, IN == BF_POOL ? 1 : 0, 1>(a.w, index);
-    else conv_bf16_group<1, WM, MT, NT, false, true, IN>(a.d, index - a.wgroups, one_lds);
+    else conv_bf16_group<1, WM, MT, NT, false, true, IN, Back16OneLds>(a.d, index - a.wgroups);
 }
 
 // Both areas lie below 64 KB.

@@ -5,12 +5,13 @@
 
 namespace ftp {
 
+struct ConvLds { static __device__ __forceinline__ uint4* at() { __shared__ __attribute__((aligned(16))) uint4 x[kBfLds]; return x; } };
+
 template <int K, int WAVES_M, int MT, int NT, bool POOL_OUT, bool DELTA_IN, int IN>
 __global__ void __launch_bounds__(256, bf_waves(K, NT * MT))
 k_conv_bf16(MfmaConvArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint4 Xl[kBfLds];
-    conv_bf16_group<K, WAVES_M, MT, NT, POOL_OUT, DELTA_IN, IN>(a, (int)blockIdx.x, Xl);
+    conv_bf16_group<K, WAVES_M, MT, NT, POOL_OUT, DELTA_IN, IN, ConvLds>(a, (int)blockIdx.x);
 }
 
 // ---- host side ------------------------------------------------------------------------------------------------
