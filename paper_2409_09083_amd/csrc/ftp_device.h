@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <cstdint>
+#include "ftp_order.h"
 
 namespace ftp {
 
@@ -39,44 +40,6 @@ __device__ __forceinline__ T* at(const View& v, int stack, int ti, int tj, int n
 {
     return (T*)v.p + (long long)stack * v.ss + (long long)n * v.ns + (long long)c * v.cs +
            (long long)(y - v.y0[ti]) * v.pitch + (x - v.x0[tj]);
-}
-
-// The dispatcher hands the workgroups of a launch to the 8 XCDs round-robin by linear index, and every XCD has an L2 of
-// its own.  Kernels in which a group of `gx` workgroups reads the same maps launch a 1-D grid of
-// 8 * gx * ceil(groups / 8) workgroups and number them so that a group's workgroups run on one XCD, one after the
-// other, while consecutive groups go to different XCDs (so uneven groups still spread over the chip):
-// XCD x = index % 8 (index: the workgroup's) works through the groups x, x + 8, x + 16, ...  Returns false for the padding (group >= groups).
-__device__ __forceinline__ bool xcd_order(int index, int groups, int gx, int& group, int& block)
-{
-    const int xcd = index & 7, slot = index >> 3;
-    const int round = slot / gx;
-    block = slot - round * gx;
-    group = xcd + 8 * round;
-    return group < groups;
-}
-inline unsigned xcd_grid(int groups, int gx) { return (unsigned)(8 * gx * ((groups + 7) / 8)); }
-
-// Filter gradients: a workgroup is one block of one stack's gradient and one share of its pixels.  The blocks of a stack and share read
-// the same maps, neighbouring stacks share the cache lines of whole ones.  With 8 shares and more the list runs (share, stack, block),
-// block fastest, and XCD x takes its x-th eighth: neighbours run side by side on one XCD, and each takes about a share of all stacks (fp32
-// 32 -> 64 with a pool, 64 images of 304^2, 6 x 6 stacks, 14 shares: 1.60 -> 1.39 ms).  With fewer shares an eighth would be a few stacks, whose sizes
-// differ (1x1 shares, 512 -> 256 at 38^2 in stacks of 6 or 7 rows: 1.52 -> 1.69 ms): stacks and shares go round-robin then.
-__device__ __forceinline__ bool xcd_shares(int index, int shares, int stacks, int gx, int& share, int& stack, int& block)
-{
-    if (shares < 8) {
-        int g;
-        const bool ok = xcd_order(index, shares * stacks, gx, g, block);
-        stack = g / shares; share = g - stack * shares;
-        return ok;
-    }
-    const int total = shares * stacks * gx, per = (total + 7) >> 3, slot = index >> 3;
-    const int i = (index & 7) * per + slot, r = i / gx;
-    block = i - r * gx; share = r / stacks; stack = r - share * stacks;
-    return slot < per && i < total;
-}
-inline unsigned xcd_shares_grid(int shares, int stacks, int gx)
-{
-    return shares < 8 ? xcd_grid(shares * stacks, gx) : 8u * (unsigned)(((long long)shares * stacks * gx + 7) / 8);
 }
 
 // Value of lane (lane ^ X) for X = 1, 2, 3: an exchange inside a quad of lanes, done by the vector ALU's data-parallel

@@ -48,6 +48,20 @@ struct ConvArgs {
     int in_ws = 0, din_ws = 0;      // the activation at the input / the delta at the output lie inside the workspace (which has margins)
 };
 
+// Largest rectangle a stack works on.
+inline int largest_width(const ConvArgs& c)
+{
+    int w = 0;
+    for (int j = 0; j < c.M; ++j) { const int v = c.rect.x1[j] - c.rect.x0[j] + 1; if (v > w) w = v; }
+    return w;
+}
+inline int largest_height(const ConvArgs& c)
+{
+    int h = 0;
+    for (int i = 0; i < c.N; ++i) { const int v = c.rect.y1[i] - c.rect.y0[i] + 1; if (v > h) h = v; }
+    return h;
+}
+
 struct PoolArgs {
     View in, out, mask, din, dout;
     View isign;                     // sign map at the input boundary (backward: see ConvArgs)
@@ -139,6 +153,7 @@ struct MfmaWgradArgs {
     int Cin, Cout, Hc, Wc;
     int splits;                                     // batch shares per stack
     int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
+    bool eighths;                                   // order of the workgroups
     int PK;                                         // pixels staged per step
     int zs = 0, stage_words = 0;                    // streamed thin-layer kernel: dwords between the dZ rows of two channels; dwords of a stage
     float slope;

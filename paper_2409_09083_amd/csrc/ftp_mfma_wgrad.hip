@@ -54,7 +54,7 @@ unsigned wgrad_mfma_plan(MfmaWgradArgs& a, const ConvArgs& c, float* scratch, si
     const int tiles = ((c.Cout + BCO - 1) / BCO) * ((c.Cin + BCI - 1) / BCI);
     const int parts = c.K == 5 ? 3 : c.K == 7 ? 7 : 1;                 // filter rows 2 + 2 + 1, or one at a time
     a.gx = tiles * parts; a.stacks = c.N * c.M;
-    return xcd_shares_grid(a.splits, a.stacks, a.gx);
+    return shares_order(a, wgrad_chunks(largest_width(c), largest_height(c), c.batch, c.K / 2, c.S).total);
 }
 
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)

@@ -785,7 +785,7 @@ k_wgrad_mfma_thin(MfmaWgradArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // uniform: row bookkeeping stays scalar
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares((int)blockIdx.x, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares((int)blockIdx.x, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
@@ -1008,7 +1008,7 @@ __device__ __forceinline__ void wgrad_thin_dl_group(const MfmaWgradArgs& a, int 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares(index, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares(index, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
@@ -1384,7 +1384,7 @@ bool back_thin(const ConvArgs& w, float* scratch, const ConvArgs& c, hipStream_t
     if (!ts.fits || !dgroups) return false;
     a.w = thin_args(w, scratch);
     a.w.PK = ts.cb_max; a.w.zs = ts.zs; a.w.stage_words = ts.stage_words;
-    a.wgroups = (int)xcd_shares_grid(a.w.splits, a.w.stacks, a.w.gx);
+    a.wgroups = (int)shares_order(a.w, ts.max_chunks);
     // (launches that fill the chip several times over keep their own kernels: more workgroups of the delta share a CU there)
     if ((a.wgroups & 7) || (long long)a.wgroups + dgroups > kBackThinMost) return false;
     g_kernel_label = "k_back_thin";
@@ -1403,11 +1403,11 @@ void thin_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
     MfmaWgradArgs a = thin_args(c, scratch);
     if (thin16_wgrad(c, a, s)) return;
     const int nb = (c.Cin * c.K * c.K + 31) / 32;      // 1 (up to 3x3), 2 or 4 (5x5), 4 to 7 (7x7: 5 for 3 channels)
-    dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx)), block(256);
     const ThinStream ts = c.Cin <= 4 ? stream_geom(c) : ThinStream{0, 0, 0, 1, 1, 1, 0, false};
     const bool stream = ts.fits;
     const ThinGeom g = stream ? ThinGeom{ts.cb_max, ts.lds} : thin_geom(c);
     a.PK = g.PK; a.zs = ts.zs; a.stage_words = ts.stage_words;
+    const dim3 grid(shares_order(a, stream ? ts.max_chunks : thin_wgrad_chunks(largest_width(c), largest_height(c), c.batch, g.PK, c.pooled != 0).total)), block(256);
     // more than 64 KB of dynamic LDS has to be granted per kernel, once
 #define FTP_TW(T, TN, KK, SS, NB, PL) do { \
         if (stream) { \

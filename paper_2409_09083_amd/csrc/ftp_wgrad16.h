@@ -39,6 +39,7 @@ struct Wgrad16Args {
     int Cin, Cout, Hc, Wc;                          // map extent at the convolution (stride 1: input = output)
     int splits, M, batch;
     int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
+    bool eighths;                                   // order of the workgroups
 };
 
 #define FTP_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
@@ -74,7 +75,7 @@ __device__ __forceinline__ void wgrad16_group(const Wgrad16Args& a, int index)
     const int wave_co = wave % WAVES_CO, wave_ci = (wave / WAVES_CO) % WAVES_CI, wave_k = wave / (WAVES_CO * WAVES_CI);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares(index, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares(index, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;

@@ -51,7 +51,7 @@ unsigned wgrad16_plan(Wgrad16Args& a, const ConvArgs& c, float* scratch, size_t&
     lds = (size_t)2 * BCI * w16_row_bytes(waves_ci) + (size_t)kW16Groups * 64 * 20 + (size_t)kW16Groups * 4;
     const int tiles = ((c.Cout + 63) / 64) * ((c.Cin + BCI - 1) / BCI);
     a.gx = tiles; a.stacks = c.N * c.M;
-    return xcd_shares_grid(a.splits, a.stacks, a.gx);
+    return shares_order(a, wgrad16_chunks(largest_width(c), largest_height(c), c.batch, w16_patch_elems(waves_ci), 1).total);
 }
 
 void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s)

@@ -53,7 +53,9 @@ unsigned wsplit_plan(WsplitArgs& a, const ConvArgs& c, float* scratch, int& wco,
     for (int j = 0; j < kTabGrid; ++j) a.tc[j] = j < c.M ? wsplit_tc(c.rect.x1[j] - c.rect.x0[j] + 1, mh, c.batch, c.pooled != 0) : 1;
     wci = wsplit_waves_ci(c.Cin); wco = wsplit_waves_co(c.Cout, c.Cin);
     a.gx = ((c.Cout + 32 * wco - 1) / (32 * wco)) * ((c.Cin + 32 * wci - 1) / (32 * wci)); a.stacks = c.N * c.M;
-    return xcd_shares_grid(a.splits, a.stacks, a.gx);
+    int chunks = 1;
+    for (int j = 0; j < c.M; ++j) chunks = std::max(chunks, wsplit_chunks(c.rect.x1[j] - c.rect.x0[j] + 1, mh, c.batch, a.tc[j]).total);
+    return shares_order(a, chunks);
 }
 
 void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s)

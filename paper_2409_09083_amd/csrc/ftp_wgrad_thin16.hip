@@ -38,7 +38,7 @@ k_wgrad_thin16(MfmaWgradArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares((int)blockIdx.x, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares((int)blockIdx.x, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;
@@ -233,7 +233,8 @@ bool thin16_wgrad(const ConvArgs& c, MfmaWgradArgs& a, hipStream_t s)
         }
     if (useful < 0.4 * padded) return false;
     a.gx = (c.Cout + 31) / 32; a.stacks = c.N * c.M;
-    const dim3 grid(xcd_shares_grid(a.splits, a.stacks, a.gx));
+    const int mw = largest_width(c), mh = largest_height(c);
+    const dim3 grid(shares_order(a, c.batch * ((mh + 7) / 8) * ((mw + kT16Cols - 1) / kT16Cols)));
     g_kernel_label = "k_wgrad_thin16";
     hipLaunchKernelGGL(k_wgrad_thin16, grid, dim3(256), 0, s, a);
     return true;

@@ -27,3 +27,7 @@ def test_conv_tiles_fit_their_lds_limits_and_cover_every_pixel_once():
 
 def test_first_layer_tiles_fit_their_lds_limits():
     _build_and_run("stem_tile_check")
+
+
+def test_orders_of_workgroups_name_each_once_and_load_the_xcds_evenly():
+    _build_and_run("order_check")
