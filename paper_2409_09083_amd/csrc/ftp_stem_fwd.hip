@@ -396,10 +396,17 @@ bool stem_fwd_eligible(const ConvArgs& c)
 // take the channels one after the other, and few workgroups wait for that) layers with few real channels a block go to them (us, vector ALU / here:
 // 3x3, 16 images of 304^2 in 3 x 3 stacks, 3 -> 8 34 / 47, -> 12 41 / 46, -> 16 50 / 45, -> 20 58 / 66, -> 32 82 / 62; with a pool 29 / 36, 33 / 36, 39 / 35, 45 / 51,
 // 61 / 49; 8 images of 304^2, one stack, with a pool, 3 -> 8 18 / 17; 5x5 3 -> 4 59 / 72, -> 8 78 / 73; 3x3 of stride 2, 32 images of 608^2, 3 -> 8 117 / 136, -> 16 207 / 153).
+// So do 16-bit maps without a pool of which half the rows or tiles begin between dwords: their neighbours are stored one by one here (16 images of
+// 262^2 in 3 x 6 stacks, 3 -> 16 36 / 45, -> 64 1.19 times; 35 of 199^2 in 1 x 5, 3 -> 32 74 / 91; 24 of 549 x 247 in one stack 0.93 to 1.0 times).
 bool stem_fwd_pays(const ConvArgs& c)
 {
     const int rest = c.Cout % 32, blocks = c.Cout / 32 * 2 + (rest == 0 ? 0 : rest <= 16 ? 1 : 2);
     const double real = (double)c.Cout / blocks * (c.Cin <= 3 ? 3 : 4) / 3.0, pixels = (double)c.batch * c.Hc * c.Wc;
+    if (c.K == 3 && c.S == 1 && c.bf16 && !c.pooled && pixels >= 3e5) {
+        int odd = 0;
+        for (int t = 0; t < c.M; ++t) odd += (int)((((uintptr_t)c.out.p >> 1) + (unsigned)(c.rect.x0[t] - c.out.x0[t])) & 1);
+        if ((c.out.pitch & 1) || 2 * odd >= c.M) return false;
+    }
     if (c.K == 3 && c.S == 1) return pixels < 1.5e5 || real >= (pixels < (c.pooled ? 1e6 : 3e5) ? 9 : 13);
     if (c.K >= 5 && c.S == 1) return pixels < 8e4 || real >= 6;
     if (c.K == 3) return pixels < 5e5 || real >= 9;

@@ -1343,7 +1343,10 @@ ThinStream stream_geom(const ConvArgs& c)
 
 }  // namespace
 
-constexpr long long kBackThinMost = 4096;            // workgroups (about two of them a CU at a time: four rounds and more hide each other's ends)
+// Workgroups of a joint launch (about two of them a CU at a time: four rounds and more hide each other's ends), and of its delta where they are
+// long: alone, six of them share a CU (us a step, joint / apart: 3 -> 64, 41 images of 38^2 in 4 x 8 stacks, 1312 of them, 101 / 76; 3 -> 32 55 / 52, -> 16
+// 39 / 42; 64 images of 20^2 in 2 x 3 stacks, 384, 3 -> 64 56 / 63; pooled 1 -> 64, 32 of 52^2 in 5 x 5 stacks, 800, 101 / 77).
+constexpr long long kBackThinMost = 4096, kBackThinLong = 640;
 
 // c.rect must hold the owned rectangles.
 bool thin_wgrad_eligible(const ConvArgs& c)
@@ -1385,8 +1388,7 @@ bool back_thin(const ConvArgs& w, float* scratch, const ConvArgs& c, hipStream_t
     a.w = thin_args(w, scratch);
     a.w.PK = ts.cb_max; a.w.zs = ts.zs; a.w.stage_words = ts.stage_words;
     a.wgroups = (int)shares_order(a.w, ts.max_chunks);
-    // (launches that fill the chip several times over keep their own kernels: more workgroups of the delta share a CU there)
-    if ((a.wgroups & 7) || (long long)a.wgroups + dgroups > kBackThinMost) return false;
+    if ((a.wgroups & 7) || (long long)a.wgroups + dgroups > kBackThinMost || (w.Cout > 16 && dgroups > kBackThinLong)) return false;
     g_kernel_label = "k_back_thin";
     const dim3 grid((unsigned)a.wgroups + dgroups);
 #define FTP_BT(T, NB, PL, CI) hipLaunchKernelGGL((k_back_thin<T, NB, PL, CI>), grid, dim3(320), std::max<size_t>(ts.lds, 4 * (size_t)thin4_words(CI)), s, a)

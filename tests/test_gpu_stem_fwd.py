@@ -131,3 +131,17 @@ def test_maps_beyond_the_matrix_kernel_offsets():
         ref = torch.where(ref > 0, ref, ref * 0.1)
         # (27 products and their sums, each rounded to 24 bits)
         assert float((got.cpu().double() - ref).abs().max() / ref.abs().max()) < 28 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("batch,h,w,grid,thin", [(20, 127, 128, (1, 1), False), (20, 127, 129, (1, 1), True), (20, 126, 130, (1, 2), True), (20, 126, 130, (1, 5), False), (2, 127, 129, (1, 1), False)])
+def test_16_bit_rows_between_dwords(batch, h, w, grid, thin):
+    """Tile columns of 65 pixels (half begin between dwords), of 26 (none do), odd rows; the same bits from either kernel."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(8)
+    x, weights = torch.randn((1, 3, h, w), device="cuda", generator=g), (torch.randn((32, 3, 3, 3), device="cuda", generator=g) / 5).to(torch.bfloat16)
+    many, names = _one_layer(3, 1, 3, 32, batch, h, w, grid, "bf16", False, x, weights)
+    assert names == {"k_conv_fwd_thin" if thin else "k_conv_fwd_stem"}
+    alone, names = _one_layer(3, 1, 3, 32, 1, h, w, grid, "bf16", False, x, weights)
+    assert names == {"k_conv_fwd_stem"}
+    for a, b in zip(alone, many):
+        assert torch.equal(a, b)
