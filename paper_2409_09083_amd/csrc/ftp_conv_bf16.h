@@ -135,7 +135,9 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
     // NARROW: bytes from `src` to the caller's buffer and to its end
     if (IN == BF_NARROW) xoff += skew;
     const int first = IN == BF_NARROW ? (int)((const char*)sv.p - (const char*)src < 0 ? 0 : (const char*)sv.p - (const char*)src) : 0;
-    const long long room = IN == BF_NARROW ? (const char*)((const bf16_t*)sv.p + (long long)a.batch * sv.ns) - (const char*)src : 0;
+    // (offsets stay below 2^31, so 32 bits are enough; the wide workgroups have no register left: with 64 bits they spilled 70 times, not 46, and
+    // 64 -> 128, 8 images of 151^2 in 4 x 4 stacks, took 92 us for 77)
+    const unsigned room = IN == BF_NARROW ? (unsigned)min(0x7FFFFFFFll, (long long)((const char*)((const bf16_t*)sv.p + (long long)a.batch * sv.ns) - (const char*)src)) : 0u;
     bool rounded = true;                               // NARROW (uniform): this stage's units were loaded from rounded addresses
 
     typedef uint32_t v4u __attribute__((ext_vector_type(4)));
@@ -147,7 +149,7 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
         if constexpr (IN == BF_NARROW) {
             // (units of channels beyond the last are not loaded)
             const int last = a.C - 1 - c0 - 8 * u_oct < 7 ? a.C - 1 - c0 - 8 * u_oct : 7;
-            const bool inside = xin == 0u || last < 0 || ((int)(xoff & ~3u) >= first && (long long)(xoff + 2u * (unsigned)((c0 + last) * (int)sv.cs)) + 20 <= room);
+            const bool inside = xin == 0u || last < 0 || ((int)(xoff & ~3u) >= first && xoff + 2u * (unsigned)((c0 + last) * (int)sv.cs) + 20u <= room);
             rounded = __builtin_amdgcn_ballot_w64(!inside) == 0ull;
         }
         if (IN == BF_NARROW && !rounded) {

@@ -42,3 +42,22 @@ def test_caller_buffers_that_start_anywhere(k, cin, h, w, batch, offset):
     # (the filter gradient of a buffer that is not on a dword takes another kernel, in another order of sums)
     assert float((s.wgrad - ref[2]).norm() / ref[2].norm()) < 1e-5
     s.close()
+
+
+def test_caller_buffers_beyond_2_gib():
+    """Maps that begin between dwords in a buffer of more than 2 GiB: an image has the bits that it has alone, the first ones and the last."""
+    from paper_2409_09083_amd.harness import Session
+    g = torch.Generator(device="cuda").manual_seed(12)
+    x = torch.empty((1, 16, 513, 511), device="cuda").normal_(generator=g).bfloat16()
+    w = (torch.empty((64, 16, 3, 3), device="cuda").normal_(generator=g) / 12).bfloat16()
+    out = []
+    for batch in (1, 260):
+        s = Session((conv(16, 64),), batch, 16, 513, 511, (1, 2), (1,), dtype="bf16")
+        s.x.copy_(x.expand(s.in_shape))
+        s.weights = [w]
+        s.forward()
+        torch.cuda.synchronize()
+        out.append(s.y)
+        s.close()
+    assert 2 * 260 * x.numel() > 2 ** 31
+    assert all(torch.equal(out[1][n], out[0][0]) for n in range(260))
