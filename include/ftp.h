@@ -227,6 +227,9 @@ const char* ftp_strerror(int code);
 /* hipError_t value of the last failed HIP call on this thread (0 if none). */
 int ftp_last_hip_error(void);
 
+/* Units whose filter gradient and delta ftp_backward took in one launch, since this thread began (tests ask which way a unit went). */
+long long ftp_joint_launches(void);
+
 #ifdef __cplusplus
 }
 #endif

@@ -83,6 +83,7 @@ def _load():
     lib.ftp_strerror.argtypes = [ctypes.c_int]
     lib.ftp_strerror.restype = ctypes.c_char_p
     lib.ftp_last_hip_error.restype = ctypes.c_int
+    lib.ftp_joint_launches.restype = ctypes.c_longlong
     for f in ("ftp_profile", "ftp_profile_read", "ftp_set_overlap", "ftp_plan_buffer", "ftp_plan_rect", "ftp_plan_map_shape", "ftp_plan_sizes", "ftp_plan_work", "ftp_forward",
               "ftp_forward_static", "ftp_backward", "ftp_reduce_wgrad", "ftp_sgd_step"):
         getattr(lib, f).restype = ctypes.c_int
@@ -92,7 +93,8 @@ def _load():
 _lib = _load()
 
 EXPORTS = ("ftp_profile", "ftp_profile_read", "ftp_set_overlap", "ftp_plan", "ftp_plan_destroy", "ftp_plan_buffer", "ftp_plan_rect", "ftp_plan_map_shape", "ftp_plan_sizes", "ftp_plan_work",
-           "ftp_forward", "ftp_forward_static", "ftp_backward", "ftp_reduce_wgrad", "ftp_sgd_step", "ftp_strerror", "ftp_last_hip_error")
+           "ftp_forward", "ftp_forward_static", "ftp_backward", "ftp_reduce_wgrad", "ftp_sgd_step", "ftp_strerror", "ftp_last_hip_error",
+           "ftp_joint_launches")
 
 
 def _check(rc, where):
@@ -217,3 +219,7 @@ def ftp_strerror(code):
 
 def ftp_last_hip_error():
     return _lib.ftp_last_hip_error()
+
+
+def ftp_joint_launches():
+    return _lib.ftp_joint_launches()

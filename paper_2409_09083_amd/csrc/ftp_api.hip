@@ -21,6 +21,7 @@ void* g_static_ws[kMaxDevices] = {};
 std::mutex g_static_ws_lock;
 
 thread_local int g_last_hip = 0;
+thread_local long long g_joint_launches = 0;
 
 struct UserBufs {
     const void* x = nullptr; void* y = nullptr; const void* dy = nullptr; void* dx = nullptr; void* ws = nullptr;
@@ -498,6 +499,7 @@ int ftp_backward(const ftp_plan_t* plan, const void* dy, const void* x, const vo
             if (overlap && apart && (rc = order(aux, s)) != FTP_OK) return rc;
             a.rect = make_rect(p, u.group, FTP_RECT_BWD, u.bi);
             if (delta_done) {
+                ++g_joint_launches;
             } else if (use_mfma() && mfma_conv_eligible(a, true)) {
                 float* wt = (float*)((char*)workspace + u.wt_bwd_offset);
                 const RectTab ext = view_extent(p, u.in_delta, u.group, u.bo);
@@ -663,6 +665,8 @@ const char* ftp_strerror(int code)
 }
 
 int ftp_last_hip_error(void) { return g_last_hip; }
+
+long long ftp_joint_launches(void) { return g_joint_launches; }
 
 }  // extern "C"
 

@@ -1,5 +1,5 @@
 """Filter gradient and delta back-propagation in one launch against launches of their own (timing records on): the same bits, over the
-workgroup shapes both have, with and without a pool, from the caller's map and from the workspace."""
+workgroup shapes both have, with and without a pool, from the caller's map and from the workspace; how many units took one launch."""
 import pytest
 import torch
 
@@ -10,15 +10,15 @@ from paper_2409_09083_amd.harness import Session
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("layers,batch,h,w,grid", [
-    ((conv(8, 24), conv(24, 32), pool(32)), 2, 30, 44, (2, 2)),            # at most 32 channels on both sides
-    ((conv(16, 72), conv(72, 72, slope=1.0)), 1, 37, 29, (1, 3)),           # 32 rows of the delta, 64 of the gradient; odd maps
-    ((conv(40, 64), pool(64), conv(64, 36)), 3, 52, 40, (3, 2)),            # 64 rows, through a pool and not
-    ((conv(128, 64), pool(64), conv(64, 32)), 1, 26, 26, (1, 1)),           # a launch too small for wide blocks of channels
-    ((conv(136, 48), conv(48, 128), pool(128)), 16, 76, 60, (2, 2)),        # 128 rows and several rounds
-    ((conv(64, 64), conv(64, 200)), 9, 65, 90, (3, 3)),
+@pytest.mark.parametrize("layers,batch,h,w,grid,joint", [
+    ((conv(8, 24), conv(24, 32), pool(32)), 2, 30, 44, (2, 2), 1),         # at most 32 channels on both sides
+    ((conv(16, 72), conv(72, 72, slope=1.0)), 1, 37, 29, (1, 3), 2),        # 32 rows of the delta, 64 of the gradient; odd maps
+    ((conv(40, 64), pool(64), conv(64, 36)), 3, 52, 40, (3, 2), 2),         # 64 rows, through a pool and not
+    ((conv(128, 64), pool(64), conv(64, 32)), 1, 26, 26, (1, 1), 2),        # a launch too small for wide blocks of channels
+    ((conv(136, 48), conv(48, 128), pool(128)), 16, 76, 60, (2, 2), 2),     # 128 rows and several rounds
+    ((conv(64, 64), conv(64, 200)), 9, 65, 90, (3, 3), 2),
 ])
-def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, dtype="f32"):
+def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, joint, dtype="f32"):
     g = torch.Generator().manual_seed(11)
     out = []
     for apart in (False, True):
@@ -29,55 +29,67 @@ def test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, dtype="f3
         s.load(x=x.numpy(), weights=ws, dy=dy.numpy())
         if apart:
             B.ftp_profile(s.plan, 1)
+        before = B.ftp_joint_launches()
         s.step()
         torch.cuda.synchronize()
+        assert B.ftp_joint_launches() - before == (0 if apart else joint)
         out.append((s.dx.clone(), s.wgrad.clone()))
         s.close()
     assert bool(torch.isfinite(out[0][1]).all())
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
-@pytest.mark.parametrize("layers,batch,h,w,grid", [
-    ((conv(3, 8), conv(8, 16)), 1, 31, 33, (2, 2)),                         # first layer without a pool, odd maps
-    ((conv(3, 40), pool(40), conv(40, 20, 1)), 2, 36, 52, (1, 2)),          # ... with one, two blocks of output channels
-    ((conv(4, 16, slope=1.0),), 3, 20, 70, (3, 1)),                         # 36 columns of the product, the image wider than a tile
-    ((conv(1, 24), pool(24)), 1, 64, 130, (2, 1)),
+@pytest.mark.parametrize("layers,batch,h,w,grid,joint", [
+    ((conv(3, 8), conv(8, 16)), 1, 31, 33, (2, 2), 1),                      # first layer without a pool, odd maps
+    ((conv(3, 40), pool(40), conv(40, 20, 1)), 2, 36, 52, (1, 2), 1),       # ... with one, two blocks of output channels
+    ((conv(4, 16, slope=1.0),), 3, 20, 70, (3, 1), 1),                      # 36 columns of the product, the image wider than a tile
+    ((conv(1, 24), pool(24)), 1, 64, 130, (2, 1), 1),
 ])
-def test_first_layers(layers, batch, h, w, grid):
-    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid)
+def test_first_layers(layers, batch, h, w, grid, joint):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, joint)
 
 
-@pytest.mark.parametrize("layers,batch,h,w,grid", [
-    ((conv(24, 64, 1), conv(64, 160, 1)), 1, 27, 31, (1, 2)),               # 32 and 64 input channels, odd maps
-    ((conv(136, 72, 1), pool(72), conv(72, 32, 1)), 2, 26, 30, (1, 1)),     # 128 rows of the delta, through a pool
-    ((conv(48, 256, 1), pool(256), conv(256, 44, 1)), 1, 52, 40, (2, 2)),
+@pytest.mark.parametrize("layers,batch,h,w,grid,joint", [
+    ((conv(24, 64, 1), conv(64, 160, 1)), 1, 27, 31, (1, 2), 1),            # 32 and 64 input channels, odd maps
+    ((conv(136, 72, 1), pool(72), conv(72, 32, 1)), 2, 26, 30, (1, 1), 2),  # 128 rows of the delta, through a pool
+    ((conv(48, 256, 1), pool(256), conv(256, 44, 1)), 1, 52, 40, (2, 2), 2),
 ])
-def test_one_by_one_layers(layers, batch, h, w, grid):
-    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid)
+def test_one_by_one_layers(layers, batch, h, w, grid, joint):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, joint)
 
 
-@pytest.mark.parametrize("layers,batch,h,w,grid", [
-    ((conv(24, 32), pool(32), conv(32, 72)), 2, 36, 44, (2, 2)),            # 32 input channels, through a pool and not
-    ((conv(64, 64), conv(64, 40, slope=1.0)), 1, 37, 29, (1, 2)),           # small workgroups of the delta, odd deltas
-    ((conv(128, 96), pool(96), conv(96, 128)), 6, 52, 60, (3, 2)),
-    ((conv(256, 64), conv(64, 256)), 16, 76, 77, (2, 2)),                   # wide ones, several rounds
+@pytest.mark.parametrize("layers,batch,h,w,grid,joint", [
+    ((conv(24, 32), pool(32), conv(32, 72)), 2, 36, 44, (2, 2), 2),         # 32 input channels, through a pool and not
+    ((conv(64, 64), conv(64, 40, slope=1.0)), 1, 37, 29, (1, 2), 1),        # small workgroups of the delta, odd deltas
+    ((conv(128, 96), pool(96), conv(96, 128)), 6, 52, 60, (3, 2), 2),
+    ((conv(256, 64), conv(64, 256)), 16, 76, 77, (2, 2), 1),                # wide ones, several rounds
 ])
-def test_16_bit_layers(layers, batch, h, w, grid):
-    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, "bf16")
+def test_16_bit_layers(layers, batch, h, w, grid, joint):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, joint, "bf16")
 
 
-@pytest.mark.parametrize("layers,batch,h,w,grid", [
-    ((conv(24, 64, 1), conv(64, 160, 1)), 1, 27, 31, (1, 2)),               # odd deltas
-    ((conv(136, 72, 1), pool(72), conv(72, 32, 1)), 2, 26, 30, (1, 1)),     # through a pool
-    ((conv(256, 44, 1), conv(44, 200, 1)), 1, 52, 40, (2, 2)),
+@pytest.mark.parametrize("layers,batch,h,w,grid,joint", [
+    ((conv(24, 64, 1), conv(64, 160, 1)), 1, 27, 31, (1, 2), 1),            # odd deltas
+    ((conv(136, 72, 1), pool(72), conv(72, 32, 1)), 2, 26, 30, (1, 1), 2),  # through a pool
+    ((conv(256, 44, 1), conv(44, 200, 1)), 1, 52, 40, (2, 2), 2),
 ])
-def test_16_bit_one_by_one_layers(layers, batch, h, w, grid):
-    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, "bf16")
+def test_16_bit_one_by_one_layers(layers, batch, h, w, grid, joint):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, joint, "bf16")
 
 
 @pytest.mark.parametrize("cin,cout,batch,h,w,grid", [(24, 40, 1, 27, 31, (1, 2)), (64, 32, 2, 30, 20, (2, 1)), (128, 96, 1, 26, 26, (1, 1))])
 def test_5x5_layers(cin, cout, batch, h, w, grid):
-    test_same_bits_as_launches_of_their_own((conv(cin, cout, 5), conv(cout, 36, 5)), batch, h, w, grid)
+    test_same_bits_as_launches_of_their_own((conv(cin, cout, 5), conv(cout, 36, 5)), batch, h, w, grid, 2)
+
+
+@pytest.mark.parametrize("layers,batch,h,w,grid,dtype", [
+    ((conv(64, 64, 1),), 32, 104, 104, (1, 1), "f32"),                      # launches that fill the chip several times: 1x1,
+    ((conv(64, 64, 1),), 64, 104, 104, (1, 1), "bf16"),
+    ((conv(32, 64), pool(64)), 16, 152, 152, (1, 1), "bf16"),               # small workgroups of the 16-bit 3x3 delta,
+    ((conv(3, 64),), 41, 38, 38, (4, 8), "f32"),                            # a first layer with long workgroups of the delta
+])
+def test_launches_that_stay_apart(layers, batch, h, w, grid, dtype):
+    test_same_bits_as_launches_of_their_own(layers, batch, h, w, grid, 0, dtype)
 
 
 @pytest.mark.parametrize("overlap", [False, True])
