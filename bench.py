@@ -2,9 +2,9 @@
 """Benchmark of the fused-tile forward + backward + gradient-sum pass on one MI355X.
 
 One step = ftp_forward, ftp_backward, ftp_reduce_wgrad over one batch of synthetic input that is
-already resident in HBM.  Prints ONE JSON line: whole-job images/s, the roofline of the dominant
-kernel (timed live with HIP events inside the timed region), the kernels below the ridge against the HBM
-roof, the bf16 workload with its layer-grouping sweep, and the CPU oracle timed on the host.
+already resident in HBM.  Prints ONE JSON line: whole-job images/s over K steps as a user's program runs
+them, the roofline of the dominant kernel (HIP events around every launch of K further steps, which keep a layer's
+filter gradient and delta apart), the kernels below the ridge against the HBM roof, the bf16 workload with its layer-grouping sweep, and the CPU oracle timed on the host.
 """
 import argparse
 import json
@@ -77,7 +77,7 @@ def matrix_peak(name, dtype):
     """Peak of the matrix cores for a kernel's arithmetic (None: it does not use them)."""
     if "_split<" in name:
         return PEAK_SPLIT_TFLOPS
-    if "bwd_data_thin_s2" in name:
+    if "bwd_data_thin_s2" in name or "conv_fwd_stem" in name:       # (the fp32 instruction for either storage type)
         return PEAK_MFMA_TFLOPS["f32"]
     if "mfma" in name or "conv_bf16" in name or "thin16" in name:
         return PEAK_MFMA_TFLOPS[dtype]
@@ -111,7 +111,7 @@ def roofline_of(name, k, dtype, workload, step_ms_total):
 
 
 def run_workload(cfg, steps, warmup, with_update=False, overlap=False, per_kernel=False, extras=True):
-    """Times `steps` steps of one workload (inputs resident in HBM) with the per-kernel HIP events on.
+    """Times `steps` steps of one workload (inputs resident in HBM), then as many again with the per-kernel HIP events on.
     Returns the fields of the JSON line that describe this workload."""
     import torch
     from ftp_synth import configs as C
@@ -130,7 +130,6 @@ def run_workload(cfg, steps, warmup, with_update=False, overlap=False, per_kerne
     for _ in range(warmup):
         one_step()
     torch.cuda.synchronize()
-    F.ftp_profile(s.plan, True)
     # (every step is also bracketed by two events on the stream the kernels run on: median and minimum over steps)
     marks = [torch.cuda.Event(enable_timing=True) for _ in range(steps + 1)]
     t0 = time.perf_counter()
@@ -140,9 +139,16 @@ def run_workload(cfg, steps, warmup, with_update=False, overlap=False, per_kerne
         marks[i + 1].record()
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    per_step = [marks[i].elapsed_time(marks[i + 1]) for i in range(steps)]
+    # the same K steps with the records on: each launch by itself, a layer's filter gradient and delta apart
+    F.ftp_profile(s.plan, True)
+    t0 = time.perf_counter()
+    for _ in range(steps):
+        one_step()
+    torch.cuda.synchronize()
+    dt_rec = time.perf_counter() - t0
     F.ftp_profile(s.plan, False)
     recs = F.ftp_profile_read(s.plan)
-    per_step = [marks[i].elapsed_time(marks[i + 1]) for i in range(steps)]
 
     if per_kernel:
         for r in sorted(recs, key=lambda r: (r["layer"], r["pass"])):
@@ -153,12 +159,12 @@ def run_workload(cfg, steps, warmup, with_update=False, overlap=False, per_kerne
     ms_per_step = dt * 1e3 / steps
     by_kernel = pooled_by_kernel(recs)
     name, dom = max(by_kernel.items(), key=lambda kv: kv[1]["ms"])
-    roof = roofline_of(name, dom, cfg.dtype, cfg.name, dt * 1e3)
+    roof = roofline_of(name, dom, cfg.dtype, cfg.name, dt_rec * 1e3)
     # the kernels below the ridge of their arithmetic unit (first layer, 1x1 bottlenecks, lone pools, dy scaling, gradient
     # sum): achieved algorithmic GB/s against the HBM roof, each kernel symbol pooled over its layers
     below = []
     for kn, k in sorted(by_kernel.items(), key=lambda kv: -kv[1]["ms"]):
-        r = roofline_of(kn, k, cfg.dtype, cfg.name, dt * 1e3)
+        r = roofline_of(kn, k, cfg.dtype, cfg.name, dt_rec * 1e3)
         if r["bound"] == "hbm":
             below.append({"kernel": kn, "layers": r["layers"], "achieved": r["achieved"], "unit": "GB/s", "frac": r["frac"],
                           "tflops": k["flops"] / (k["ms"] * 1e-3) / 1e12, "avg_launch_ms": r["avg_launch_ms"],
@@ -177,12 +183,11 @@ def run_workload(cfg, steps, warmup, with_update=False, overlap=False, per_kerne
         "useful_tflops": 2.0 * work["useful_macs"] / (ms_per_step * 1e-3) / 1e12,
         "executed_over_useful_macs": work["executed_macs"] / work["useful_macs"],
         "halo_bytes_per_step": [work["halo_bytes_fwd"], work["halo_bytes_bwd"]],
-        "phases_ms_per_step": phases,
+        "phases_ms_per_step": phases, "ms_per_step_with_records": dt_rec * 1e3 / steps,
     }
     if extras:
         if not overlap:
-            # the same K steps once more with the two-stream backward pass (ftp_set_overlap) and without per-kernel events:
-            # reported beside `value`, which stays the single-stream figure the roofline above belongs to
+            # the same K steps once more with the two-stream backward pass (ftp_set_overlap), reported beside `value`, the single-stream figure
             s.set_overlap(True)
             for _ in range(min(warmup, 2)):
                 one_step()
@@ -238,8 +243,8 @@ def main():
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-sweep", action="store_true", help="leave out the config-5 grouping sweep (cfg5_sweep)")
     ap.add_argument("--no-extras", action="store_true",
-                    help="leave out the legs that follow the timed region (two-stream backward, forward only): profiler "
-                         "runs then see the timed region's launches only")
+                    help="leave out the two-stream backward and forward-only legs: profiler runs then see the timed steps and those "
+                         "with the per-kernel records only")
     ap.add_argument("--with-update", action="store_true",
                     help="close every step with the fused gradient sum + filter update (lr 0) instead of the plain gradient sum")
     ap.add_argument("--overlap", action="store_true",

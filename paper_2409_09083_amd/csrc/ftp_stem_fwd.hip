@@ -359,24 +359,20 @@ k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
 
 namespace {
 
-template <typename T, int K, int S, bool POOL, int CI>
-void launch_stem(const StemArgs& s, const PrepArgs<kPrepFew>& p, dim3 grid, size_t lds, hipStream_t st)
-{
-    hipLaunchKernelGGL((k_conv_fwd_stem<T, K, S, POOL, CI>), grid, dim3(256), lds, st, s, p);
-}
-template <typename T, int K, int S, bool POOL>
-void launch_stem(const StemArgs& s, const PrepArgs<kPrepFew>& p, dim3 grid, size_t lds, hipStream_t st)
-{
-    if (s.Cin <= 3) launch_stem<T, K, S, POOL, 3>(s, p, grid, lds, st); else launch_stem<T, K, S, POOL, 4>(s, p, grid, lds, st);
-}
 template <typename T>
 void launch_stem(const ConvArgs& c, const StemArgs& s, const PrepArgs<kPrepFew>& p, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (c.K == 3 && c.S == 1) { if (c.pooled) launch_stem<T, 3, 1, true>(s, p, grid, lds, st); else launch_stem<T, 3, 1, false>(s, p, grid, lds, st); }
-    else if (c.K == 3) launch_stem<T, 3, 2, false>(s, p, grid, lds, st);
-    else if (c.K == 5) { if (c.S == 2) launch_stem<T, 5, 2, false>(s, p, grid, lds, st); else launch_stem<T, 5, 1, false>(s, p, grid, lds, st); }
-    else if (c.K == 7) { if (c.S == 2) launch_stem<T, 7, 2, false>(s, p, grid, lds, st); else launch_stem<T, 7, 1, false>(s, p, grid, lds, st); }
-    else launch_stem<T, 1, 2, false>(s, p, grid, lds, st);
+#define FTP_ST(K, S, POOL, CI) do { \
+        g_kernel_label = c.bf16 ? "k_conv_fwd_stem<unsigned short, " #K ", " #S ", " #POOL ", " #CI ">" : "k_conv_fwd_stem<float, " #K ", " #S ", " #POOL ", " #CI ">"; \
+        hipLaunchKernelGGL((k_conv_fwd_stem<T, K, S, POOL, CI>), grid, dim3(256), lds, st, s, p); } while (0)
+#define FTP_STC(K, S, POOL) do { if (s.Cin <= 3) FTP_ST(K, S, POOL, 3); else FTP_ST(K, S, POOL, 4); } while (0)
+    if (c.K == 3 && c.S == 1) { if (c.pooled) FTP_STC(3, 1, true); else FTP_STC(3, 1, false); }
+    else if (c.K == 3) FTP_STC(3, 2, false);
+    else if (c.K == 5) { if (c.S == 2) FTP_STC(5, 2, false); else FTP_STC(5, 1, false); }
+    else if (c.K == 7) { if (c.S == 2) FTP_STC(7, 2, false); else FTP_STC(7, 1, false); }
+    else FTP_STC(1, 2, false);
+#undef FTP_STC
+#undef FTP_ST
 }
 
 }  // namespace
@@ -430,7 +426,6 @@ void stem_fwd(const ConvArgs& c, const PrepJob* jobs, int n, hipStream_t st)
     s.blocks = s.xcd ? (int)xcd_grid(s.lines, row) : s.lines * row;
     PrepArgs<kPrepFew> p;
     const dim3 grid((unsigned)(s.blocks + fill_prep(p, jobs, n)));
-    g_kernel_label = "k_conv_fwd_stem";
     if (c.bf16) launch_stem<bf16_t>(c, s, p, grid, t.lds, st); else launch_stem<float>(c, s, p, grid, t.lds, st);
 }
 
