@@ -192,7 +192,8 @@ int ftp_sgd_step(const ftp_plan_t* plan, const float* wgrad_partials, void* cons
  * overwrites a map another one still reads; before ftp_backward returns, the caller's stream has been made to wait for
  * the second one, so the caller sees one stream as before.  Results are bit-identical either way.  Off by default
  * (on if the environment variable FTP_OVERLAP is 1 when the plan is created).  Kernels that run side by side share the
- * GPU, so the per-kernel records of ftp_profile then show longer launches while the whole pass gets shorter. */
+ * GPU, so the per-kernel records of ftp_profile then show longer launches.  One stream takes a unit's gradient and delta in one launch where
+ * that pays, and is the faster pass in most networks. */
 int ftp_set_overlap(ftp_plan_t* plan, int32_t enable);
 
 /* Per-kernel timing for benchmarks.  While enabled, every kernel launch of the three passes is
