@@ -18,6 +18,7 @@ __global__ void __launch_bounds__(256, 2)
 k_back16(Back16Args a)
 {
     const int index = (int)blockIdx.x;
+    if (index < 256) touch_args<0, sizeof(Back16Args)>();
     if (index < a.wgroups) wgrad16_group<WAVES_CI, IN == BF_POOL ? 1 : 0, WS>(a.w, index);
     else conv_bf16_group<3, WM, MT, NT, false, true, IN, Back16Lds>(a.d, index - a.wgroups);
 }

@@ -16,6 +16,7 @@ __global__ void __launch_bounds__(256, 2)
 k_back16_1x1(Back16OneArgs a)
 {
     const int index = (int)blockIdx.x;
+    if (index < 256) touch_args<0, sizeof(Back16OneArgs)>();
     if (index < a.wgroups) wgrad_mfma_group<bf16_t, 1, 2, WAVES_CI, IN == BF_POOL ? 1 : 0, 1>(a.w, index);
     else conv_bf16_group<1, WM, MT, NT, false, true, IN, Back16OneLds>(a.d, index - a.wgroups);
 }

@@ -18,6 +18,7 @@ __global__ void __launch_bounds__(256, 2)
 k_back_split(BackSplitArgs a)
 {
     const int index = (int)blockIdx.x;
+    if (index < 256) touch_args<0, sizeof(BackSplitArgs)>();
     if (index < a.wgroups) wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS>(a.w, index);
     else delta_split_group<3, WAVES_M, BN, POOL ? IN_POOL : IN_WIDE>(a.d, index - a.wgroups);
 }

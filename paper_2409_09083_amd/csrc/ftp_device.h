@@ -22,6 +22,21 @@ struct RectTab {
     int x0[kTabGrid], x1[kTabGrid], y0[kTabGrid], y1[kTabGrid];
 };
 
+// Reads one dword of every 64-byte line of the kernel's argument block from byte FROM on, so that all of them are on their way at once: the block
+// lies in host memory and is new with every launch, and its tables were met one after the other, a wait of 1.5 us each (stamps in a forward
+// kernel: 7.4 k cycles before the first load of the map, 3.5 k of them such waits, 2 k more in front of the first store; step of two small layers 48.5 -> 43.5 us, three
+// layers of one image 150.5 -> 142.6, forward 38.8 -> 36.9).  The launch's first workgroups do it (512; 256 where two kernels' arguments travel together): what
+// they fetched serves the others (all of 1024: 16-bit 1x1 / 3x3 pair, 8 images of 76^2, 314 -> 317 us).
+template <int FROM, int BYTES>
+__device__ __forceinline__ void touch_args()
+{
+    const uint32_t __attribute__((address_space(4)))* const p = (const uint32_t __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t x = 0;
+#pragma unroll
+    for (int i = FROM; i < FROM + BYTES; i += 64) x |= p[i / 4];
+    asm volatile("" :: "s"(x));
+}
+
 typedef uint16_t bf16_t;          // raw bfloat16 bits
 
 __device__ __forceinline__ float ld(const float* p) { return *p; }

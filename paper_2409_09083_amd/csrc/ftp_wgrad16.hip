@@ -8,6 +8,7 @@ template <int WAVES_CI, int HALF, bool WS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_mfma16(Wgrad16Args a)
 {
+    if (blockIdx.x < 512) touch_args<0, sizeof(Wgrad16Args)>();
     wgrad16_group<WAVES_CI, HALF, WS>(a, (int)blockIdx.x);
 }
 

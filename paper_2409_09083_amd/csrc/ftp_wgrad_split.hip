@@ -8,6 +8,7 @@ template <int WAVES_CO, int WAVES_CI, bool POOL, bool WS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_split(WsplitArgs a)
 {
+    if (blockIdx.x < 512) touch_args<0, sizeof(WsplitArgs)>();
     wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS>(a, (int)blockIdx.x);
 }
 
