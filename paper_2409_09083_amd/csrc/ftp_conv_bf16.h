@@ -72,11 +72,11 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
     const int hi = lane >> 5, l32 = lane & 31;
     int vgroup, vtile;
     if (!tile_order(a, index, vgroup, vtile)) return;
-    const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
+    const int stack = quot(vgroup, a.mblocks), ti = quot(stack, a.M), tj = stack - ti * a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<S, P, 8>(a, x0, x1, y0, y1, vtile);
     if (g.empty) return;
-    const int m0 = (vgroup % a.mblocks) * BM;
+    const int m0 = (vgroup - stack * a.mblocks) * BM;
     const int PW = g.PW, npos = g.npos;
     const View& sv = DELTA_IN ? a.din : a.in;
     // patch rows start on the dword grid of the map (POOL: at an even column), up to one position early
@@ -103,11 +103,11 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
     unsigned xoff = 0, moff = 0, xin = 0;              // byte offsets of the first element (POOL: window) and its code, channel 8 * u_oct; elements inside the map
     uint32_t row2 = 0;                                 // POOL: 2 for odd rows
     if (u_pos < npos) {
-        const int pr = u_pos / PW, c = u_pos - pr * PW;
+        const int pr = quot_small(u_pos, PW), c = u_pos - pr * PW;
         int k = 0, lr = pr, ybase = g.y_a * S;
         if (pr >= g.first_cnt) {
             const int t = pr - g.first_cnt;
-            k = 1 + t / g.per_cnt; lr = t - (k - 1) * g.per_cnt; ybase = 0;
+            k = 1 + quot_small(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
         }
         const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P - sh + c;
         const int sy = IN == BF_POOL ? gy >> 1 : gy, sx = IN == BF_POOL ? gx >> 1 : gx;

@@ -26,7 +26,7 @@ __device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int index, int
     const int ntiles = a.tiles_x * a.tiles_r, order = a.order;
     if (order > 0) return row_order(index, a.stacks / a.M, a.M, a.mblocks, ntiles, order, vgroup, vtile);
     if (order < 0) return xcd_order(index, a.mblocks * a.stacks, ntiles, vgroup, vtile);
-    vgroup = index / ntiles; vtile = index - vgroup * ntiles;
+    vgroup = quot(index, ntiles); vtile = index - vgroup * ntiles;
     return true;
 }
 

@@ -83,11 +83,11 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
     // block then run on one XCD, which meets one channel block's slice of the filter only
     int vgroup, vtile;
     if (!tile_order(a, index, vgroup, vtile)) return;
-    const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
+    const int stack = quot(vgroup, a.mblocks), ti = quot(stack, a.M), tj = stack - ti * a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<1, P, IN == IN_POOL ? 2 : 4>(a, x0, x1, y0, y1, vtile);
     if (g.empty) return;
-    const int m0 = (vgroup % a.mblocks) * BM;
+    const int m0 = (vgroup - stack * a.mblocks) * BM;
     const int PW = g.PW, npos = g.npos;
     const int sh = IN == IN_POOL ? ((g.ox0 - P) & 1) : 0;      // patch rows start at an even column
 
@@ -117,11 +117,11 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
         const int s = 4 * (unit % UPO);
         xoff[u] = kOobS; moff[u] = kOobS; xin[u] = 0;
         if (s < npos && unit < UNITS) {
-            const int pr = s / PW, c = s - pr * PW;
+            const int pr = quot_small(s, PW), c = s - pr * PW;
             int k = 0, lr = pr, ybase = g.y_a;
             if (pr >= g.first_cnt) {
                 const int t = pr - g.first_cnt;
-                k = 1 + t / g.per_cnt; lr = t - (k - 1) * g.per_cnt; ybase = 0;
+                k = 1 + quot_small(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
             }
             const int gy = y0 + ybase + lr - P, gx = g.ox0 - P - sh + c;
             const int sy = IN >= IN_POOL ? gy >> 1 : gy, sx = IN >= IN_POOL ? gx >> 1 : gx;

@@ -42,12 +42,12 @@ k_conv_fwd_direct(View in, View out, View mask, View osign, RectTab rt, RectTab 
                   const T* __restrict__ bias, int Cin, int Cout, int Hi, int Wi, float slope, int M, int batch)
 {
     static_assert(COB == 8, "a workgroup's channels fill one byte of the sign word");
-    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
-    const int ti = stack / M, tj = stack % M;
+    const int stack = quot((int)blockIdx.z, batch), n = (int)blockIdx.z - stack * batch;
+    const int ti = quot(stack, M), tj = stack - ti * M;
     const int rw = rt.x1[tj] - rt.x0[tj] + 1, rh = rt.y1[ti] - rt.y0[ti] + 1;
     const int pid = blockIdx.x * blockDim.x + threadIdx.x;
     if (pid >= rw * rh) return;
-    const int oy = rt.y0[ti] + pid / rw, ox = rt.x0[tj] + pid % rw;
+    const int py = quot_lane(pid, rw), oy = rt.y0[ti] + py, ox = rt.x0[tj] + pid - py * rw;
     const int co0 = blockIdx.y * COB;
     constexpr int NP = POOL ? 2 : 1, P = K / 2, R = (NP - 1) * S + K;
     float acc[COB][NP * NP];
@@ -117,8 +117,8 @@ __global__ void __launch_bounds__(64)
 k_conv_bwd_data_direct(View din, View mask, View dout, View isign, int scale_out, float in_slope, RectTab rt,
                        const T* __restrict__ w, int Cin, int Cout, int Hc, int Wc, int M, int batch, int blocks_per_class)
 {
-    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
-    const int ti = stack / M, tj = stack % M;
+    const int stack = quot((int)blockIdx.z, batch), n = (int)blockIdx.z - stack * batch;
+    const int ti = quot(stack, M), tj = stack - ti * M;
     const int rw = rt.x1[tj] - rt.x0[tj] + 1, rh = rt.y1[ti] - rt.y0[ti] + 1;
     int ry, rx, cls = 0;
     if (S == 2) {
@@ -132,7 +132,7 @@ k_conv_bwd_data_direct(View din, View mask, View dout, View isign, int scale_out
     } else {
         const int pid = blockIdx.x * blockDim.x + threadIdx.x;
         if (pid >= rw * rh) return;
-        ry = pid / rw; rx = pid - ry * rw;
+        ry = quot_lane(pid, rw); rx = pid - ry * rw;
     }
     const int iy = rt.y0[ti] + ry, ix = rt.x0[tj] + rx;
     const int ci0 = blockIdx.y * CIB;
@@ -214,7 +214,7 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
 {
     touch_args<0, 3 * sizeof(View) + sizeof(RectTab)>();
     const int ci = blockIdx.x, co = blockIdx.y, stack = blockIdx.z;
-    const int ti = stack / M, tj = stack % M;
+    const int ti = quot(stack, M), tj = stack - ti * M;
     const int rw = own.x1[tj] - own.x0[tj] + 1, rh = own.y1[ti] - own.y0[ti] + 1;
     const int px = rw * rh, items = px * batch;
     constexpr int P = K / 2, KK = K * K;
@@ -222,8 +222,8 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
 #pragma unroll
     for (int t = 0; t <= KK; ++t) acc[t] = 0.0f;
     for (int it = threadIdx.x; it < items; it += 256) {
-        const int n = it / px, r = it - n * px;
-        const int qy = own.y0[ti] + r / rw, qx = own.x0[tj] + r % rw;
+        const int n = quot_lane(it, px), r = it - n * px, ry = quot_lane(r, rw);
+        const int qy = own.y0[ti] + ry, qx = own.x0[tj] + r - ry * rw;
         const float dz = delta_z<T, POOL>(din, mask, stack, ti, tj, n, co, qy, qx, Hc >> 1, Wc >> 1);
         acc[KK] += dz;
 #pragma unroll
@@ -265,7 +265,7 @@ template <typename T, int kBiasThreads, int U>
 __device__ __forceinline__ void bias_block(const BiasArgs& a, int co, int stack)
 {
     const View& din = a.din;
-    const int ti = stack / a.M, tj = stack % a.M, batch = a.batch;
+    const int ti = quot(stack, a.M), tj = stack - ti * a.M, batch = a.batch;
     int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     if (a.pooled) {
         // (windows whose first pixel is owned; a pool fused with its convolution has whole windows in every rectangle)
@@ -286,7 +286,7 @@ __device__ __forceinline__ void bias_block(const BiasArgs& a, int co, int stack)
 #pragma unroll
             for (int u = 0; u < U; ++u) {              // (beyond the last one: the last one again, not added)
                 const int it = it0 + u * kBiasThreads < items ? it0 + u * kBiasThreads : items - 1;
-                const int n = it / px, r = it - n * px, y = r / rw;
+                const int n = quot_lane(it, px), r = it - n * px, y = quot_lane(r, rw);
                 d[u] = ld(base + (long long)(n0 + n) * din.ns + (long long)y * din.pitch + (r - y * rw));
             }
 #pragma unroll
@@ -355,12 +355,12 @@ template <typename T>
 __global__ void __launch_bounds__(64)
 k_pool_fwd(View in, View out, View mask, RectTab rt, RectTab own, int C, int M, int batch)
 {
-    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
-    const int ti = stack / M, tj = stack % M;
+    const int stack = quot((int)blockIdx.z, batch), n = (int)blockIdx.z - stack * batch;
+    const int ti = quot(stack, M), tj = stack - ti * M;
     const int rw = rt.x1[tj] - rt.x0[tj] + 1, rh = rt.y1[ti] - rt.y0[ti] + 1;
     const int pid = blockIdx.x * blockDim.x + threadIdx.x;
     if (pid >= rw * rh) return;
-    const int oy = rt.y0[ti] + pid / rw, ox = rt.x0[tj] + pid % rw;
+    const int py = quot_lane(pid, rw), oy = rt.y0[ti] + py, ox = rt.x0[tj] + pid - py * rw;
     const int c = blockIdx.y;
     float best = ld(at<T>(in, stack, ti, tj, n, c, 2 * oy, 2 * ox));
     int bi = 0;
@@ -383,13 +383,13 @@ template <typename T, int CH>
 __global__ void __launch_bounds__(256)
 k_pool_bwd(View din, View mask, View dout, View isign, int scale_out, float in_slope, RectTab rt, int C, int Ho, int Wo, int M, int batch)
 {
-    const int stack = blockIdx.z / batch, n = blockIdx.z % batch;
-    const int ti = stack / M, tj = stack % M;
+    const int stack = quot((int)blockIdx.z, batch), n = (int)blockIdx.z - stack * batch;
+    const int ti = quot(stack, M), tj = stack - ti * M;
     const int x0 = rt.x0[tj], x1 = rt.x1[tj], y0 = rt.y0[ti], y1 = rt.y1[ti];
     const int wx0 = x0 >> 1, wy0 = y0 >> 1, ww = (x1 >> 1) - wx0 + 1, wh = (y1 >> 1) - wy0 + 1;
     const int pid = blockIdx.x * blockDim.x + threadIdx.x;
     if (pid >= ww * wh) return;
-    const int wy = wy0 + pid / ww, wx = wx0 + pid % ww;
+    const int py = quot_lane(pid, ww), wy = wy0 + py, wx = wx0 + pid - py * ww;
     const int c0 = blockIdx.y * CH;
     const bool has = wy < Ho && wx < Wo;
     // the loads are unconditional: a window of the dropped row / column reads the rectangle's first window instead,
@@ -652,7 +652,7 @@ k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
 {
     if (CAP <= kPrepFew && blockIdx.x < 512) touch_args<0, sizeof(ScaleArgs) + sizeof(PrepArgs<CAP>)>();
     if ((int)blockIdx.x >= a.blocks) { prep_block(prep, (int)blockIdx.x - a.blocks); return; }
-    const int image = (int)blockIdx.x / a.per;
+    const int image = quot((int)blockIdx.x, a.per);
     const unsigned i = ((unsigned)blockIdx.x - (unsigned)(image * a.per)) * 256u + threadIdx.x, units = (unsigned)(a.HW / V);
     const unsigned g = i / units;
     if (g >= (unsigned)a.groups) return;

@@ -96,11 +96,11 @@ k_conv_mfma_dl(MfmaConvArgs a)
     // 256 -> 512 layers do not stay in a 4 MB L2).
     int vgroup, vtile;
     if (!tile_order(a, (int)blockIdx.x, vgroup, vtile)) return;
-    const int stack = vgroup / a.mblocks, ti = stack / a.M, tj = stack % a.M;
+    const int stack = quot(vgroup, a.mblocks), ti = quot(stack, a.M), tj = stack - ti * a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
     const TileGeom g = tile_geom<S, P, WIDE ? 4 : 0>(a, x0, x1, y0, y1, vtile);
     if (g.empty) return;
-    const int m0 = (vgroup % a.mblocks) * BM;
+    const int m0 = (vgroup - stack * a.mblocks) * BM;
     const int PW = g.PW, CS = a.cs;                    // CS: whole 64-position blocks cover every patch
 
     int baseB[NT];
@@ -129,11 +129,11 @@ k_conv_mfma_dl(MfmaConvArgs a)
             const int s = 4 * (blk * 64 + lane);
             xoff[ub] = kOobOffset; xfix[ub] = 0;
             if (s < npos) {
-                const int pr = s / PW, c = s - pr * PW;
+                const int pr = quot_small(s, PW), c = s - pr * PW;
                 int k = 0, lr = pr, ybase = g.y_a * S;
                 if (pr >= g.first_cnt) {
                     const int t = pr - g.first_cnt;
-                    k = 1 + t / g.per_cnt; lr = t - (k - 1) * g.per_cnt; ybase = 0;
+                    k = 1 + quot_small(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
                 }
                 const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P + c;
                 // rows no valid output pixel of this stack reads may lie outside the view; columns beside the needed ones
@@ -152,11 +152,11 @@ k_conv_mfma_dl(MfmaConvArgs a)
         const int s = tid + j * 256;
         xoff[j] = kOobOffset;
         if (s < npos) {
-            const int pr = s / PW, c = s - pr * PW;
+            const int pr = quot_small(s, PW), c = s - pr * PW;
             int k = 0, lr = pr, ybase = g.y_a * S;
             if (pr >= g.first_cnt) {
                 const int t = pr - g.first_cnt;
-                k = 1 + t / g.per_cnt; lr = t - (k - 1) * g.per_cnt; ybase = 0;
+                k = 1 + quot_small(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
             }
             const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P + c;
             if (g.n_a + k < a.batch && gy >= 0 && gy < a.Hc && gx >= 0 && gx < a.Wc) {

@@ -13,7 +13,7 @@ namespace ftp {
 FTP_HD inline bool xcd_order(int index, int groups, int gx, int& group, int& block)
 {
     const int xcd = index & 7, slot = index >> 3;
-    const int round = slot / gx;
+    const int round = quot(slot, gx);
     block = slot - round * gx;
     group = xcd + 8 * round;
     return group < groups;
@@ -30,12 +30,12 @@ FTP_HD inline bool xcd_shares(int index, bool eighths, int shares, int stacks, i
     if (!eighths) {
         int g;
         const bool ok = xcd_order(index, shares * stacks, gx, g, block);
-        stack = g / shares; share = g - stack * shares;
+        stack = quot(g, shares); share = g - stack * shares;
         return ok;
     }
     const int total = shares * stacks * gx, per = (total + 7) >> 3, slot = index >> 3;
-    const int i = (index & 7) * per + slot, r = i / gx;
-    block = i - r * gx; share = r / stacks; stack = r - share * stacks;
+    const int i = (index & 7) * per + slot, r = quot(i, gx);
+    block = i - r * gx; share = quot(r, stacks); stack = r - share * stacks;
     return slot < per && i < total;
 }
 FTP_HD inline unsigned xcd_shares_grid(bool eighths, int shares, int stacks, int gx)

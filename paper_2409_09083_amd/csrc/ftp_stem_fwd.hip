@@ -102,12 +102,12 @@ k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
     if (a.xcd) {
         if (!xcd_order((int)blockIdx.x, a.lines, row, line, w)) return;
     } else {
-        line = (int)blockIdx.x / row; w = (int)blockIdx.x - line * row;
+        line = quot((int)blockIdx.x, row); w = (int)blockIdx.x - line * row;
     }
     int strip, gr;
     stem_line(line, a.rows, strip, gr);
-    const int n = gr / a.N, ti = gr - n * a.N;
-    const int tj = w / a.tiles_x, bx = w - tj * a.tiles_x, stack = ti * a.M + tj;
+    const int n = quot(gr, a.N), ti = gr - n * a.N;
+    const int tj = quot(w, a.tiles_x), bx = w - tj * a.tiles_x, stack = ti * a.M + tj;
     const int x1 = a.rt.x1[tj], y1 = a.rt.y1[ti];
     const int ox0 = a.rt.x0[tj] + bx * a.tw;
     int oy0 = a.rt.y0[ti] + strip * a.run * a.th;

@@ -65,6 +65,6 @@ inline StemTiles stem_tiles(int K, int S, bool pool, bool bf16, int Cin, int Cou
 
 // Runs (strip of the stack, image, grid row) in the order they are numbered: the strips of an image's grid row lie `rows` runs apart, so
 // that short last ones do not all fall to the same XCDs (runs go to them round-robin).  rows: grid rows of all images.
-FTP_HD inline void stem_line(int line, int rows, int& strip, int& row) { strip = line / rows; row = line - strip * rows; }
+FTP_HD inline void stem_line(int line, int rows, int& strip, int& row) { strip = quot(line, rows); row = line - strip * rows; }
 
 }  // namespace ftp

@@ -31,3 +31,7 @@ def test_first_layer_tiles_fit_their_lds_limits():
 
 def test_orders_of_workgroups_name_each_once_and_load_the_xcds_evenly():
     _build_and_run("order_check")
+
+
+def test_quotients_by_reciprocals_are_exact():
+    _build_and_run("quot_check")
