@@ -317,7 +317,8 @@ k_bias_grad(BiasArgs a)
 }
 
 // Sum of the batch shares of one layer's partial gradient, in share order.  V = 4: four consecutive parameters per thread,
-// the shares' 16-byte loads four at a time in flight (layers whose parameter count is a multiple of 4); V = 1 otherwise.
+// the shares' 16-byte loads eight at a time in flight (layers whose parameter count is a multiple of 4; narrow layers have few threads and many
+// shares: 3 -> 16 channels of one image of 416^2 10.7 -> 7.2 us, four at a time before; 16 at a time 6.2, but wide ones 0.4 more); V = 1 otherwise.
 // The sum of a small layer's bias gradient (bias_block, BIAS: further blocks) travels along: a launch less a layer.
 template <typename T, int V, bool BIAS>
 __global__ void __launch_bounds__(256)
@@ -337,6 +338,13 @@ k_wgrad_splitk_reduce(const float* __restrict__ scratch, float* __restrict__ par
         auto add = [](float4& v, const float4& b) { v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w; };
         float4 v = ld4(0);
         int sh = 1;
+        for (; sh + 7 < splits; sh += 8) {
+            float4 b[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) b[e] = ld4(sh + e);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) add(v, b[e]);
+        }
         for (; sh + 3 < splits; sh += 4) {
             const float4 b0 = ld4(sh), b1 = ld4(sh + 1), b2 = ld4(sh + 2), b3 = ld4(sh + 3);
             add(v, b0); add(v, b1); add(v, b2); add(v, b3);
