@@ -19,9 +19,11 @@ bool back16_1x1(const ConvArgs& w, float* scratch, const ConvArgs& c, const Rect
     mfma_conv_bwd_args(a.d, c, inrect, wt);
     const unsigned dgroups = bf_delta_plan(a.d, c, sh, in);
     if (!dgroups) return false;
-    a.wgroups = (int)wgrad_mfma_plan(a.w, w, scratch, lds, half, waves_co, waves_ci);
+    int nj = 0;
+    if (wgrad16_1x1_takes(w)) { a.wgroups = (int)wgrad16_1x1_plan(a.w, w, scratch, nj); lds = kOneLds; waves_co = 2; waves_ci = 0; }
+    else a.wgroups = (int)wgrad_mfma_plan(a.w, w, scratch, lds, half, waves_co, waves_ci);
     const long long all = (long long)a.wgroups + dgroups;
-    if ((a.wgroups & 7) || all > kBack16OneMost || waves_co != 2 || lds > 64 * 1024) return false;
+    if (nj == 4 || (a.wgroups & 7) || all > kBack16OneMost || waves_co != 2 || lds > 64 * 1024) return false;
     g_kernel_label = "k_back16_1x1";
     if (in == BF_POOL) launch_back16_1x1<BF_POOL>(a, waves_ci, sh, (unsigned)all, lds, s);
     else if (in == BF_WS) launch_back16_1x1<BF_WS>(a, waves_ci, sh, (unsigned)all, lds, s);

@@ -155,6 +155,7 @@ struct MfmaWgradArgs {
     int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
     bool eighths;                                   // order of the workgroups
     int PK;                                         // pixels staged per step
+    int caller = 0;                                 // ftp_wgrad16_1x1.h: X is a buffer of the caller's
     int zs = 0, stage_words = 0;                    // streamed thin-layer kernel: dwords between the dZ rows of two channels; dwords of a stage
     float slope;
     int M, batch;
@@ -203,6 +204,7 @@ void wgrad_split(const ConvArgs& c, float* scratch, hipStream_t s);
 // ... together with the unit's delta back-propagation (ftp_back_split.h); false: nothing was launched
 bool back_split(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s);
+bool wgrad16_1x1(const ConvArgs& c, float* scratch, hipStream_t s);       // (ftp_wgrad16_1x1.hip) false: does not apply
 // ... of small layers together with the delta; false: nothing was launched
 bool back_small(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);        // fp32 1x1, 5x5
 bool back16_1x1(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab& inrect, float* wt, hipStream_t s);

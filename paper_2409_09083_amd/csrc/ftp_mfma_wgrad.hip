@@ -60,6 +60,7 @@ unsigned wgrad_mfma_plan(MfmaWgradArgs& a, const ConvArgs& c, float* scratch, si
 
 void mfma_wgrad(const ConvArgs& c, float* scratch, hipStream_t s)
 {
+    if (wgrad16_1x1(c, scratch, s)) return;
     MfmaWgradArgs a;
     size_t lds;
     int half, waves_co, waves_ci;
