@@ -3,7 +3,7 @@
 
 namespace ftp {
 
-template bool launch_back16<BF_WS, false>(const Back16Args&, int, BfShape, unsigned, size_t, hipStream_t);
+template bool launch_back16<BF_WS, false, false>(const Back16Args&, int, BfShape, unsigned, size_t, hipStream_t);
 
 // The small workgroups of the delta (one block of 32 channels a wavefront) run three a CU by themselves: launches that fill the chip
 // more than about twice keep them apart.
@@ -25,9 +25,11 @@ bool back16(const ConvArgs& w, float* scratch, const ConvArgs& c, const RectTab&
     if ((a.wgroups & 7) || all > 0x7FFFFFFFll || (sh.MT == 1 && all > kBack16Small)) return false;
     g_kernel_label = "k_back16";
     const unsigned grid = (unsigned)all;
-#define FTP_BI(I) (w.in_ws ? launch_back16<I, true>(a, waves_ci, sh, grid, lds, s) : launch_back16<I, false>(a, waves_ci, sh, grid, lds, s))
+#define FTP_BR(I, WSP) (a.w.run ? launch_back16<I, WSP, true>(a, waves_ci, sh, grid, lds, s) : launch_back16<I, WSP, false>(a, waves_ci, sh, grid, lds, s))
+#define FTP_BI(I) (w.in_ws ? FTP_BR(I, true) : FTP_BR(I, false))
     return in == BF_POOL ? FTP_BI(BF_POOL) : in == BF_WS ? FTP_BI(BF_WS) : FTP_BI(BF_ODD);
 #undef FTP_BI
+#undef FTP_BR
 }
 
 }  // namespace ftp

@@ -3,6 +3,6 @@
 
 namespace ftp {
 
-template bool launch_back16<BF_POOL, false>(const Back16Args&, int, BfShape, unsigned, size_t, hipStream_t);
+template bool launch_back16<BF_POOL, false, false>(const Back16Args&, int, BfShape, unsigned, size_t, hipStream_t);
 
 }  // namespace ftp

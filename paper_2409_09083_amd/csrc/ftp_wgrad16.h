@@ -40,6 +40,7 @@ struct Wgrad16Args {
     int splits, M, batch;
     int gx, stacks;                                 // blocks per (stack, share); stacks (the grid is 1-D, see xcd_shares)
     bool eighths;                                   // order of the workgroups
+    int run;                                        // > 0: ftp_wgrad16_rows.h, rows a wavefront walks down at once; 0: wgrad16_group
 };
 
 #define FTP_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))

@@ -1,15 +1,15 @@
 // 16-bit 3x3 filter gradient: launches of its own (ftp_wgrad16.h).
-#include "ftp_wgrad16.h"
+#include "ftp_wgrad16_rows.h"
 #include <algorithm>
 
 namespace ftp {
 
-template <int WAVES_CI, int HALF, bool WS>
+template <int WAVES_CI, int HALF, bool WS, bool ROWS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_mfma16(Wgrad16Args a)
 {
     if (blockIdx.x < 512) touch_args<0, sizeof(Wgrad16Args)>();
-    wgrad16_group<WAVES_CI, HALF, WS>(a, (int)blockIdx.x);
+    wgrad16_form<WAVES_CI, HALF, WS, ROWS>(a, (int)blockIdx.x);
 }
 
 
@@ -49,10 +49,14 @@ unsigned wgrad16_plan(Wgrad16Args& a, const ConvArgs& c, float* scratch, size_t&
     a.splits = c.wgrad_shares16;
     waves_ci = w16_waves_ci(c.Cin);
     const int BCI = 32 * waves_ci;
-    lds = (size_t)2 * BCI * w16_row_bytes(waves_ci) + (size_t)kW16Groups * 64 * 20 + (size_t)kW16Groups * 4;
     const int tiles = ((c.Cout + 63) / 64) * ((c.Cin + BCI - 1) / BCI);
     a.gx = tiles; a.stacks = c.N * c.M;
-    return shares_order(a, wgrad16_chunks(largest_width(c), largest_height(c), c.batch, w16_patch_elems(waves_ci), 1).total);
+    const int rw = largest_width(c), rh = largest_height(c), waves_k = waves_ci == 2 ? 1 : 2;
+    const int chunks = wgrad16_chunks(rw, rh, c.batch, w16_patch_elems(waves_ci), 1).total;
+    a.run = rows16_run(rw, rh, c.batch, a.splits, waves_k, c.pooled != 0);
+    if (!rows16_pays(rw, rows16_items(rw, rh, c.batch, a.splits, waves_k, a.run) * waves_k, (chunks + a.splits - 1) / a.splits, (long long)a.gx * a.stacks * a.splits)) a.run = 0;
+    lds = a.run ? (size_t)kRows16Lds : (size_t)2 * BCI * w16_row_bytes(waves_ci) + (size_t)kW16Groups * 64 * 20 + (size_t)kW16Groups * 4;
+    return shares_order(a, chunks);
 }
 
 void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s)
@@ -61,16 +65,18 @@ void wgrad16(const ConvArgs& c, float* scratch, hipStream_t s)
     size_t lds;
     int waves_ci;
     const dim3 grid(wgrad16_plan(a, c, scratch, lds, waves_ci)), block(256);
-#define FTP_W16(WCI, HF, WSP) do { \
-        static thread_local bool granted = false; \
-        if (!granted) { (void)hipFuncSetAttribute((const void*)k_wgrad_mfma16<WCI, HF, WSP>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); granted = true; } \
-        g_kernel_label = "k_wgrad_mfma16<" #WCI ", " #HF ", " #WSP ">"; \
-        hipLaunchKernelGGL((k_wgrad_mfma16<WCI, HF, WSP>), grid, block, lds, s, a); } while (0)
+#define FTP_W16R(WCI, HF, WSP, RW) do { \
+        static thread_local size_t granted = 64 * 1024; \
+        if (lds > granted) { (void)hipFuncSetAttribute((const void*)k_wgrad_mfma16<WCI, HF, WSP, RW>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); granted = lds; } \
+        g_kernel_label = "k_wgrad_mfma16<" #WCI ", " #HF ", " #WSP ", " #RW ">"; \
+        hipLaunchKernelGGL((k_wgrad_mfma16<WCI, HF, WSP, RW>), grid, block, lds, s, a); } while (0)
+#define FTP_W16(WCI, HF, WSP) do { if (a.run) FTP_W16R(WCI, HF, WSP, true); else FTP_W16R(WCI, HF, WSP, false); } while (0)
 #define FTP_W16P(WCI, WSP) do { if (c.pooled) FTP_W16(WCI, 1, WSP); else FTP_W16(WCI, 0, WSP); } while (0)
     if (waves_ci == 2) { if (c.in_ws) FTP_W16P(2, true); else FTP_W16P(2, false); }
     else               { if (c.in_ws) FTP_W16P(1, true); else FTP_W16P(1, false); }
 #undef FTP_W16P
 #undef FTP_W16
+#undef FTP_W16R
 }
 
 }  // namespace ftp
