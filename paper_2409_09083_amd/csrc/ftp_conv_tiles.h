@@ -27,6 +27,9 @@ FTP_HD constexpr int split_max_positions(int K, int BN) { return K >= 5 ? (BN ==
 FTP_HD constexpr int conv_bf_positions(int K, int BN) { return K == 3 ? (BN == 512 ? 1024 : 512) : BN == 512 ? 512 : 256; }
 FTP_HD constexpr int conv_bf_octets(int K, int BN) { return 2048 / conv_bf_positions(K, BN); }
 
+// The fp32 forward kernel of small launches (ftp_conv_small.hip): patch positions of a channel in LDS.
+FTP_HD constexpr int small_positions(int K) { return K == 3 ? 256 : 128; }
+
 // Geometry of one tile.  A rectangle is cut into column blocks of TC columns and runs of whole rows (c0 = 0), or, where
 // the launch says so (a rectangle of one column block whose rows fill a tile badly), into runs of `cap` consecutive pixels
 // of its row-major pixel list, counted through the batch: a tile then starts at column c0 of flattened row R0 and need not
@@ -107,7 +110,7 @@ inline TileChoice choose_tile(const int* rws, const int* rhs, int N, int M, int 
 {
     int mw = 0;
     for (int t = 0; t < M; ++t) mw = mw > rws[t] ? mw : rws[t];
-    const int max_tc = 64 / S;                         // widest column block of a tile
+    const int max_tc = cap0 < 64 / S ? cap0 : 64 / S;  // widest column block of a tile
     // One way of cutting: `tx` column blocks and runs of whole rows, or (flat) runs of pixels.  The tile capacity is cut
     // down until the largest patch fits LDS; `tiles` = workgroups of one channel block, each of which costs the same
     // matrix-core work however many of its slots are filled.

@@ -138,6 +138,8 @@ int mfma_conv_bwd_data(const ConvArgs& c, const RectTab& inrect, float* wt, hipS
 // ... of 16-bit maps, the layers mfma_conv_packs_bf16 names (ftp_conv_bf16.hip)
 int conv_bf16_fwd(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s);
 int conv_bf16_bwd_data(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s);
+// ... of fp32 1x1 / 3x3 layers in launches that do not fill the chip (ftp_conv_small.hip); false: does not apply
+bool conv_small_fwd(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s);
 // ... of fp32 maps, on the bfloat matrix cores (ftp_delta_split.hip)
 int split_conv_bwd_data(MfmaConvArgs& a, const ConvArgs& c, hipStream_t s);
 // delta through a 3x3 stride-2 convolution by parity classes (ftp_delta_s2.hip); non-zero: does not fit

@@ -524,6 +524,7 @@ int mfma_conv_fwd(const ConvArgs& c, const RectTab& inrect, float* wt, hipStream
     a.Hc = c.Hi; a.Wc = c.Wi;                           // the patch is cut from the input map
     if (mfma_conv_packs_bf16(c)) return conv_bf16_fwd(a, c, s);
     if (c.S == 2) return c.K == 3 ? launch_m<3, false, false, 2>(a, c, s) : launch_m<1, false, false, 2>(a, c, s);
+    if (conv_small_fwd(a, c, s)) return 0;
     if (c.K == 7) return launch_m<7, false, false>(a, c, s);
     if (c.K == 5) return launch_m<5, false, false>(a, c, s);
     if (c.K == 3) return c.pooled ? launch_m<3, true, false>(a, c, s) : launch_m<3, false, false>(a, c, s);

@@ -88,10 +88,11 @@ int main()
         {1, 256, 1, 4, false}, {1, 128, 1, 4, false}, {1, 256, 1, 0, false},
         {5, 256, 1, 4, false}, {7, 128, 1, 4, false},
         {3, 128, 2, 4, true},                                                                           // strided forward
+        {3, 64, 1, 4, false}, {3, 64, 1, 0, false}, {3, 64, 2, 4, false}, {3, 64, 2, 0, false}, {1, 64, 1, 4, false}, {1, 64, 2, 0, false},   // small launches
     };
     for (const Mode& m : modes) {
         const int P = m.K / 2;
-        const int max_pos = conv_dl_max_positions(m.K, m.BN, m.strided, m.npl == 4);
+        const int max_pos = m.BN == 64 ? small_positions(m.K) : conv_dl_max_positions(m.K, m.BN, m.strided, m.npl == 4);
         const int cap0 = (m.S == 2 && !m.strided) ? m.BN / 4 : m.BN;
         for (int rw = 1; rw <= 70; rw += (rw < 34 ? 1 : 3))
             for (int rh = 1; rh <= 40; rh += (rh < 12 ? 1 : 5))
