@@ -1357,6 +1357,10 @@ constexpr long long kBackThinMost = 4096, kBackThinLong = 640;
 bool thin_wgrad_eligible(const ConvArgs& c)
 {
     if (!(c.Cin * c.K * c.K <= 32 || (c.Cin <= 4 && c.Cin * c.K * c.K <= 160))) return false;
+    // (1x1 layers of 5 to 32 input channels with something to multiply: the kernels of the wider ones, whose pixels are not staged element by element (back-propagation,
+    // here / there, us: 16 bits 32 -> 64, 4 images of 52 x 78, 40 / 17, 16 -> 256, 8 of 108^2, 128 / 72; fp32 32 -> 64, 4 of 190^2, 105 / 58, 16 -> 64, 8 of 194^2 147 / 106, 32 -> 32, 32 of
+    // 108^2, 80 / 83; 59 shapes 0.78 times in the mean, of less than 4e6 products alike either way)
+    if (c.K == 1 && c.Cin > 4 && (double)c.batch * c.Hc * c.Wc * c.Cin * c.Cout >= 4.0e6 && mfma_wgrad_eligible(c)) return false;
     if (c.pooled && (c.S != 1 || c.K > 3)) return false;
     if (c.pooled) {
         // owned rectangles of a pooled convolution consist of whole windows; anything else goes to the generic kernel

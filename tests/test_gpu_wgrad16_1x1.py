@@ -23,16 +23,18 @@ def _step(layers, batch, h, w, grid, groups, x, ws, dy):
 
 
 @pytest.mark.parametrize("cin,cout,batch,h,w,grid", [
-    (16, 32, 1, 6, 5, (1, 1)),            # rows of one unit, fewer steps than wavefronts
-    (32, 40, 3, 8, 38, (1, 8)),           # 4 and 5 columns, odd beginnings
+    (40, 32, 1, 6, 5, (1, 1)),            # rows of one unit, fewer steps than wavefronts
+    (36, 40, 3, 8, 38, (1, 8)),           # 4 and 5 columns, odd beginnings
     (64, 64, 2, 7, 24, (1, 1)),           # whole units only
     (96, 72, 2, 13, 26, (2, 3)),          # ragged blocks, rows of 8 and 9
     (130, 68, 5, 20, 76, (4, 8)),         # the wide block's remainder
     (256, 128, 4, 76, 76, (8, 8)),        # the wide block: many stacks
     (128, 512, 8, 64, 64, (8, 8)),        # ... several of them a stack
     (48, 36, 1, 4, 126, (1, 1)),          # the widest rows
-    (24, 36, 2, 6, 130, (1, 1)),          # wider ones: the other kernel
-    (32, 32, 2, 5, 7, (1, 1)),            # odd channel stride: the other kernel
+    (40, 36, 2, 6, 130, (1, 1)),          # wider ones: the other kernel
+    (40, 32, 2, 5, 7, (1, 1)),            # odd channel stride: the other kernel
+    (16, 64, 4, 66, 70, (2, 2)),          # few input channels: half a block
+    (8, 32, 8, 64, 64, (3, 1)),
 ])
 def test_gradient_of_one_layer(cin, cout, batch, h, w, grid):
     g = torch.Generator().manual_seed(5 + cin)
@@ -49,7 +51,7 @@ def test_gradient_of_one_layer(cin, cout, batch, h, w, grid):
 @pytest.mark.parametrize("h,w,grid", [(10, 38, (2, 4)), (9, 22, (1, 3)), (16, 50, (3, 3))])
 def test_deltas_and_maps_of_other_parity(h, w, grid):
     """The delta of a layer inside a group lies in a stack's slot, X in the whole map: their rows begin between dwords independently."""
-    cin, mid, cout, batch = 32, 32, 32, 3
+    cin, mid, cout, batch = 40, 40, 40, 3
     g = torch.Generator().manual_seed(h)
     x = torch.randn(batch, cin, h, w, generator=g).bfloat16()
     dy = torch.randn(batch, cout, h, w, generator=g).bfloat16()
@@ -67,7 +69,7 @@ def test_deltas_and_maps_of_other_parity(h, w, grid):
 @pytest.mark.parametrize("value", [float("inf"), float("nan")])
 def test_what_lies_beside_a_stack_stays_out_of_its_gradient(value):
     """One column of the map is not finite: only the gradients of the stacks that own it are not."""
-    cin = cout = 32
+    cin = cout = 40
     batch, h, w = 2, 8, 38
     g = torch.Generator().manual_seed(1)
     x = torch.randn(batch, cin, h, w, generator=g).bfloat16()
