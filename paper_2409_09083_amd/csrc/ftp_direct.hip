@@ -361,7 +361,8 @@ k_wgrad_splitk_reduce(const float* __restrict__ scratch, float* __restrict__ par
 // ---- lone 2x2 max-pool ---------------------------------------------------------------------------------
 // One window a thread, CH channels of it: their loads are in flight together, two neighbours at once where elements are dwords (a channel a thread and 64 threads a
 // workgroup: 64 channels of 304^2, 32 images, fp32, 282 -> 266 us, at 3.7 TB/s; 128 of 76^2 128 -> 77, 256 of 38^2 35 -> 12; 16 bits, 128 of 76^2 in 8 x 8 stacks, 16 images, 43 us less).
-template <typename T, int CH>
+// PAST: the map is read past the caches, which could not hold it (the first 266 -> 222 us; the second, which they do hold, 77 -> 94).
+template <typename T, int CH, bool PAST>
 __global__ void __launch_bounds__(256)
 k_pool_fwd(View in, View out, View mask, RectTab rt, RectTab own, int C, int M, int batch)
 {
@@ -379,7 +380,15 @@ k_pool_fwd(View in, View out, View mask, RectTab rt, RectTab own, int C, int M, 
     for (int k = 0; k < CH; ++k) {
         if (c0 + k >= C) break;
 #pragma unroll
-        for (int r = 0; r < 2; ++r) v[k][r] = *(const Pair*)(src + k * in.cs + r * in.pitch);
+        for (int r = 0; r < 2; ++r) {
+            const T* const p = src + k * in.cs + r * in.pitch;
+            if constexpr (PAST) {
+                typedef uint32_t words __attribute__((ext_vector_type(2), aligned(4)));
+                v[k][r] = __builtin_bit_cast(Pair, __builtin_nontemporal_load((const words*)p));
+            } else {
+                v[k][r] = *(const Pair*)p;
+            }
+        }
     }
     T* const dst = at<T>(out, stack, ti, tj, n, c0, oy, ox);
     uint8_t* const code = in_rect(own, ti, tj, oy, ox) ? at<uint8_t>(mask, stack, ti, tj, n, c0, oy, ox) : nullptr;
@@ -646,9 +655,10 @@ void pool_fwd(const PoolArgs& a, hipStream_t s)
     // (8 channels a thread where that leaves several workgroups a CU)
     const bool wide = a.C >= 8 && (long long)bx * ((a.C + 7) / 8) * images * bs >= 256ll * 2048;
     const dim3 grid(bx, wide ? (a.C + 7) / 8 : a.C, images), block(bs);
-#define FTP_PF(T, CH) hipLaunchKernelGGL((k_pool_fwd<T, CH>), grid, block, 0, s, a.in, a.out, a.mask, a.rect, a.own, a.C, a.M, a.batch)
-    if (a.bf16) { if (wide) FTP_PF(bf16_t, 8); else FTP_PF(bf16_t, 1); }
-    else        { if (wide) FTP_PF(float, 8); else FTP_PF(float, 1); }
+    const bool past = wide && !a.bf16 && 16.0 * a.batch * a.C * a.Ho * a.Wo >= 4.0e8;           // (bytes; the last-level cache has 256 MB)
+#define FTP_PF(T, CH, PAST) hipLaunchKernelGGL((k_pool_fwd<T, CH, PAST>), grid, block, 0, s, a.in, a.out, a.mask, a.rect, a.own, a.C, a.M, a.batch)
+    if (a.bf16) { if (wide) FTP_PF(bf16_t, 8, false); else FTP_PF(bf16_t, 1, false); }
+    else        { if (past) FTP_PF(float, 8, true); else if (wide) FTP_PF(float, 8, false); else FTP_PF(float, 1, false); }
 #undef FTP_PF
 }
 
