@@ -358,6 +358,49 @@ k_wgrad_splitk_reduce(const float* __restrict__ scratch, float* __restrict__ par
     }
 }
 
+// The same of few parameters and many shares, same bits: 8 threads read 64 shares of 4 parameters at once into LDS, where a thread a parameter adds them up in
+// share order.  Bound by the chain launch, loads, LDS, sums, store: 432 parameters in 9 stacks 7.2 -> 4.5 us; back-propagation of 3 -> 16, one image of
+// 416^2, 72.3 -> 66.3, of 16 -> 32 of 208^2 41.2 -> 36.8, of 64 -> 64 in 1x1, 4 images of 52^2, 27.1 -> 21.2.
+constexpr int kShareChunk = 64;
+template <typename T, bool BIAS>
+__global__ void __launch_bounds__(256)
+k_wgrad_shares_few(const float* __restrict__ scratch, float* __restrict__ partial, long long layer_params, long long n_params,
+                   long long w_off, int splits, int blocks, BiasArgs bias)
+{
+    if constexpr (BIAS) {
+        if ((int)blockIdx.x >= blocks) { bias_block<T, 256, 1>(bias, (int)blockIdx.x - blocks, blockIdx.y); return; }
+    }
+    __shared__ float4 part[kShareChunk][32];
+    const int t = threadIdx.x, q = t & 31, m = t >> 5, stack = blockIdx.y;
+    const long long first = 128ll * blockIdx.x, n4 = layer_params / 4, i4 = first / 4 + q;
+    const float4* const src = (const float4*)(scratch + (long long)stack * splits * layer_params) + (i4 < n4 ? i4 : n4 - 1);
+    float v = 0.0f;
+    for (int s0 = 0; s0 < splits; s0 += kShareChunk) {
+        float4 b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { const int sh = s0 + 8 * u + m; b[u] = src[(sh < splits ? sh : splits - 1) * n4]; }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) part[8 * u + m][q] = b[u];
+        __syncthreads();
+        if (t < 128) {
+            const float* const mine = (const float*)part + t;
+            const int n = splits - s0 < kShareChunk ? splits - s0 : kShareChunk;
+            int e = 0;
+            if (s0 == 0) { v = mine[0]; e = 1; }
+            for (; e + 7 < n; e += 8) {
+                float w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) w[u] = mine[128 * (e + u)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v += w[u];
+            }
+            for (; e < n; ++e) v += mine[128 * e];
+        }
+        __syncthreads();
+    }
+    if (t < 128 && first + t < layer_params) partial[(long long)stack * n_params + w_off + first + t] = v;
+}
+
 // ---- lone 2x2 max-pool ---------------------------------------------------------------------------------
 // One window a thread, CH channels of it: their loads are in flight together, two neighbours at once where elements are dwords (a channel a thread and 64 threads a
 // workgroup: 64 channels of 304^2, 32 images, fp32, 282 -> 266 us, at 3.7 TB/s; 128 of 76^2 128 -> 77, 256 of 38^2 35 -> 12; 16 bits, 128 of 76^2 in 8 x 8 stacks, 16 images, 43 us less).
@@ -679,6 +722,19 @@ void wgrad_share_sum(const ConvArgs& c, const float* scratch, int shares, bool b
     g_kernel_label = "k_wgrad_splitk_reduce";
     // (the share scratch is 256-byte aligned, so with a parameter count that is a multiple of 4 every share's slice is too)
     const int V = lp % 4 == 0 && ((uintptr_t)scratch & 15) == 0 ? 4 : 1, blocks = (int)((lp / V + 255) / 256);
+    // (where the other kernel fills a quarter of the CUs its waits are hidden, and up to 16 shares take it two: 64 -> 128, 4 images of 104^2, 99.2 and 98.2 us, 128 ->
+    // 128 180.3 and 180.7, 256 -> 64 in 1x1, 8 images of 52^2, 16 bits, 26.0 and 26.3)
+    if (V == 4 && shares > 16 && blocks * c.N * c.M <= 64) {
+        g_kernel_label = "k_wgrad_shares_few";
+        const int few = (int)((lp + 127) / 128);
+        const dim3 grid((unsigned)(few + (bias ? c.Cout : 0)), c.N * c.M);
+#define FTP_SF(T, B) hipLaunchKernelGGL((k_wgrad_shares_few<T, B>), grid, dim3(256), 0, s, scratch, c.partial, lp, c.n_params, c.w_off, shares, few, bias_args(c))
+        if (!bias)       FTP_SF(float, false);
+        else if (c.bf16) FTP_SF(bf16_t, true);
+        else             FTP_SF(float, true);
+#undef FTP_SF
+        return;
+    }
     const dim3 grid((unsigned)(blocks + (bias ? c.Cout : 0)), c.N * c.M);
 #define FTP_SR(T, VV, B) hipLaunchKernelGGL((k_wgrad_splitk_reduce<T, VV, B>), grid, dim3(256), 0, s, scratch, c.partial, lp, c.n_params, c.w_off, shares, blocks, bias_args(c))
     if (!bias)       { if (V == 4) FTP_SR(float, 4, false); else FTP_SR(float, 1, false); }

@@ -1,10 +1,11 @@
-"""Sum of the stacks' gradients: its fixed tree of pairs, bit for bit, around the groups of 8 and 64 stacks and the number of parameters at which another
-kernel takes over."""
+"""Sums of a layer's shares and of the stacks' gradients: the latter's fixed tree of pairs, bit for bit, around the groups of 8 and 64
+stacks and the number of parameters at which another kernel takes over."""
 import numpy as np
 import pytest
 import torch
 
-from ftp_synth.configs import conv
+from ftp_synth.configs import Config, conv
+from tests import parity as P
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +29,36 @@ def test_tree_of_pairs(grid, cin, cout):
     got = s.wgrad.cpu().numpy()
     s.close()
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("k,cin,cout,h,w,grid", [
+    (3, 3, 4, 416, 416, (1, 1)),                  # 108 parameters: fewer than a workgroup's, 100 shares and more
+    (3, 3, 16, 203, 187, (1, 1)),                 # 432: the last workgroup not full
+    (3, 3, 5, 200, 200, (1, 1)),                  # 135: no multiple of 4, the other kernel
+    (3, 4, 33, 200, 200, (3, 3)),
+    (3, 16, 32, 208, 208, (1, 1)),
+    (1, 64, 64, 104, 104, (1, 1)),
+])
+@pytest.mark.parametrize("has_bias", [False, True])
+def test_shares_of_a_layer(k, cin, cout, h, w, grid, has_bias):
+    """The layer's gradient against sums in 64 bits (no kinks: slope 1)."""
+    s = P.make_session(Config("shares", 1, cin, h, w, (conv(cin, cout, k, slope=1.0),), grid, (1,), "f32"), 1, has_bias)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    s.x.copy_(torch.randn(s.x.shape, generator=g, device="cuda"))
+    s.dy.copy_(torch.randn(s.dy.shape, generator=g, device="cuda"))
+    s.weights = [torch.randn((cout, cin, k, k), generator=g, device="cuda")]
+    if has_bias:
+        s.biases = [torch.zeros(cout, device="cuda")]
+    s.forward(); s.backward(); s.reduce()
+    torch.cuda.synchronize()
+    got = s.wgrad.cpu().double().numpy()
+    x, dy = s.x.cpu().double(), s.dy.cpu().double()
+    s.close()
+    xp = torch.nn.functional.pad(x, [k // 2] * 4)
+    rows = [(dy[0] * xp[0, c, a:a + h, b:b + w]).sum((1, 2)) for c in range(cin) for a in range(k) for b in range(k)]
+    want = torch.stack(rows, 1).reshape(-1).numpy()
+    n = len(want)
+    assert np.max(np.abs(got[:n] - want)) <= P.TOL_GRAD_F32 * np.max(np.abs(want))
+    if has_bias:
+        db = dy.sum((0, 2, 3)).numpy()
+        assert np.max(np.abs(got[n:n + cout] - db)) <= P.TOL_GRAD_F32 * np.max(np.abs(db))
