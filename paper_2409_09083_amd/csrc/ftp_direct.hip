@@ -777,12 +777,15 @@ void pool_bwd(const PoolArgs& a, hipStream_t s)
 // A thread handles V consecutive pixels (16 bytes; 8, where planes of 16-bit maps are a multiple of 4 pixels but not of 8; else one) of
 // kScaleCh channels: their loads are in flight together and share the pixels' sign words, which cost as much traffic as the deltas with
 // a channel a thread (16 bits, 64 channels of 152^2, 32 images: 39 -> 35 us; 512 of 38^2 22, with one pixel a thread 30).
-// Units start on dwords, no more (dy may).  dy is read once: past the caches (32 channels of 304^2, 32 images, 16 bits, 70.0 -> 66.8 us, 64 of 152^2 39.4 -> 36.4).
+// Units start on dwords, no more (dy may).
+// PAST: dy, which is read once, is read past the caches, where it and its copy fill the last of them (256 MB): us of a step, through / past them, fp32: 189 MB
+// 96 / 77, 379 181 / 175 and 184 / 173; 16 bits: 379 MB 132 / 130, 189 75 / 69 and 65.2 / 66.4.  Smaller ones lie in the caches that whoever made them wrote them
+// to: fp32 47 MB 16.4 / 19.1, 24 9.8 / 11.8; 16 bits 95 MB 35.5 / 35.8, 47 17.6 / 20.5, 24 9.8 / 11.6.
 // The blocks behind the last one relay filters.
 constexpr int kScaleCh = 4;
 struct ScaleArgs { const void* dy; const uint32_t* sign; void* dst; int C, groups, per, blocks; long long HW; float slope; };
 
-template <typename T, int V, int CAP>
+template <typename T, int V, bool PAST, int CAP>
 __global__ void __launch_bounds__(256)
 k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
 {
@@ -805,7 +808,7 @@ k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
 #pragma unroll
     for (int k = 0; k < kScaleCh; ++k) {
         if (c0 + k >= a.C) break;
-        if constexpr (V > 1) {
+        if constexpr (PAST) {
             typedef uint32_t words __attribute__((ext_vector_type(sizeof(Unit) / 4), aligned(4)));
             d[k] = __builtin_bit_cast(Unit, __builtin_nontemporal_load((const words*)(src + k * a.HW)));
         } else {
@@ -826,6 +829,7 @@ void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C,
     // (every plane starts where the map does, as far as a unit goes)
     const bool dwords = (((uintptr_t)dy | (uintptr_t)dst) & 3) == 0;
     const int V = !dwords ? 1 : bf16 && HW % 8 == 0 ? 8 : HW % 4 == 0 ? 4 : 1;
+    const bool past = V > 1 && (double)batch * C * HW * (bf16 ? 2.0 : 4.0) >= 1.28e8;
     ScaleArgs a{dy, sign, dst, C, (C + kScaleCh - 1) / kScaleCh, 0, 0, HW, slope};
     a.per = (int)(((long long)a.groups * (HW / V) + 255) / 256);
     a.blocks = a.per * batch;
@@ -833,9 +837,11 @@ void scale_dy(const void* dy, const uint32_t* sign, void* dst, int batch, int C,
         constexpr int CAP = decltype(cap)::value;
         PrepArgs<CAP> p;
         const dim3 grid((unsigned)(a.blocks + fill_prep(p, jobs, n)));
-#define FTP_SD(T, VV) do { g_kernel_label = "k_scale_dy<" #T ", " #VV ">"; hipLaunchKernelGGL((k_scale_dy<T, VV, CAP>), grid, dim3(256), 0, s, a, p); } while (0)
-        if (bf16) { if (V == 8) FTP_SD(bf16_t, 8); else if (V == 4) FTP_SD(bf16_t, 4); else FTP_SD(bf16_t, 1); }
-        else      { if (V == 4) FTP_SD(float, 4); else FTP_SD(float, 1); }
+#define FTP_SD(T, VV, P) do { g_kernel_label = P ? "k_scale_dy<" #T ", " #VV ", past>" : "k_scale_dy<" #T ", " #VV ">"; hipLaunchKernelGGL((k_scale_dy<T, VV, P, CAP>), grid, dim3(256), 0, s, a, p); } while (0)
+#define FTP_SP(T, VV) do { if (past) FTP_SD(T, VV, true); else FTP_SD(T, VV, false); } while (0)
+        if (bf16) { if (V == 8) FTP_SP(bf16_t, 8); else if (V == 4) FTP_SP(bf16_t, 4); else FTP_SD(bf16_t, 1, false); }
+        else      { if (V == 4) FTP_SP(float, 4); else FTP_SD(float, 1, false); }
+#undef FTP_SP
 #undef FTP_SD
     };
     if (n <= kPrepFew) launch(std::integral_constant<int, kPrepFew>()); else launch(std::integral_constant<int, kPrepJobs>());
