@@ -20,7 +20,7 @@ k_back16_1x1(Back16OneArgs a)
     if (index < 256) touch_args<0, sizeof(Back16OneArgs)>();
     if (index < a.wgroups) {
         if constexpr (WAVES_CI == 0) wgrad16_1x1_group<2>(a.w, index);
-        else wgrad_mfma_group<bf16_t, 1, 2, WAVES_CI, IN == BF_POOL ? 1 : 0, 1>(a.w, index);
+        else wgrad_mfma_group<bf16_t, 1, 2, WAVES_CI, IN == BF_POOL ? 1 : 0, 1, true>(a.w, index);
     } else conv_bf16_group<1, WM, MT, NT, false, true, IN, Back16OneLds>(a.d, index - a.wgroups);
 }
 

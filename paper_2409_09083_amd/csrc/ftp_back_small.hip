@@ -15,7 +15,7 @@ k_back_small(BackSmallArgs a)
 {
     const int index = (int)blockIdx.x;
     if (index < 256) touch_args<0, sizeof(BackSmallArgs)>();
-    if (index < a.wgroups) wgrad_mfma_group<float, K, 2, WAVES_CI, POOL ? 1 : 0, K == 5 ? 2 : 1>(a.w, index);
+    if (index < a.wgroups) wgrad_mfma_group<float, K, 2, WAVES_CI, POOL ? 1 : 0, K == 5 ? 2 : 1, true>(a.w, index);
     else delta_split_group<K, WAVES_M, BN, POOL ? IN_POOL : IN_WIDE>(a.d, index - a.wgroups);
 }
 

@@ -11,22 +11,23 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // (tile geometry: ftp_conv_tiles.h)
-template <int S, int P, int Q>
+template <int S, int P, int Q, bool RCP = true>
 __device__ __forceinline__ TileGeom tile_geom(const MfmaConvArgs& a, int x0, int x1, int y0, int y1, int bx)
 {
-    return conv_tile_geom(a.tiles_x, a.TC, a.cap, a.flat, a.batch, x0, x1, y0, y1, bx, S, P, Q);
+    return conv_tile_geom<RCP>(a.tiles_x, a.TC, a.cap, a.flat, a.batch, x0, x1, y0, y1, bx, S, P, Q);
 }
-template <int S, int P>
-__device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) { return conv_tile_pix(g, wq, x1, S, P); }
+template <int S, int P, bool RCP = true>
+__device__ __forceinline__ TilePix tile_pix(const TileGeom& g, int wq, int x1) { return conv_tile_pix<RCP>(g, wq, x1, S, P); }
 
 // The workgroup's stack and channel block (vgroup = stack * mblocks + channel block) and tile, in the order the launch chose (one word of
 // the arguments says it: a wait more for them in front of every workgroup was 0.1 to 0.3 us of launches of 10 to 20).
+template <bool RCP = true>
 __device__ __forceinline__ bool tile_order(const MfmaConvArgs& a, int index, int& vgroup, int& vtile)
 {
     const int ntiles = a.tiles_x * a.tiles_r, order = a.order;
-    if (order > 0) return row_order(index, a.stacks / a.M, a.M, a.mblocks, ntiles, order, vgroup, vtile);
-    if (order < 0) return xcd_order(index, a.mblocks * a.stacks, ntiles, vgroup, vtile);
-    vgroup = quot(index, ntiles); vtile = index - vgroup * ntiles;
+    if (order > 0) return row_order<RCP>(index, a.stacks / a.M, a.M, a.mblocks, ntiles, order, vgroup, vtile);
+    if (order < 0) return xcd_order<RCP>(index, a.mblocks * a.stacks, ntiles, vgroup, vtile);
+    vgroup = quot<RCP>(index, ntiles); vtile = index - vgroup * ntiles;
     return true;
 }
 
@@ -64,7 +65,7 @@ __device__ __forceinline__ void quad_trade(float& a, float& b, bool upper)
     b = upper ? b : t;
 }
 
-template <typename T, int K, int S, int WAVES_M, int MT, bool POOL_OUT, bool DELTA_IN, int NT>
+template <typename T, int K, int S, int WAVES_M, int MT, bool POOL_OUT, bool DELTA_IN, bool RCP = true, int NT>
 __device__ __forceinline__ void conv_epilogue(const MfmaConvArgs& a, const TileGeom& g, v16f (&acc)[MT][NT], float* bias_lds,
                                               int m0, int x0, int x1, int y0, int stack, int ti, int tj)
 {
@@ -98,7 +99,7 @@ __device__ __forceinline__ void conv_epilogue(const MfmaConvArgs& a, const TileG
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int q = (wave_n * NT + t) * 32 + l32;
-            const TilePix tp = tile_pix<S, P>(g, q, x1);
+            const TilePix tp = tile_pix<S, P, RCP>(g, q, x1);
             const int pn = tp.valid ? tp.n : 0, py = tp.valid ? y0 + tp.y : y0, pxx = tp.valid ? g.ox0 + tp.xl : x0;
             vo[t] = tp.valid ? ES * (unsigned)((pn - g.n_a) * (int)ov.ns + (py - ov.y0[ti]) * ov.pitch + (pxx - ov.x0[tj])) + 4u * hi * ocs : 0x80000000u;
 #pragma unroll
@@ -171,7 +172,7 @@ __device__ __forceinline__ void conv_epilogue(const MfmaConvArgs& a, const TileG
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
             const int q = (wave_n * NT + t) * 32 + l32;
-            const TilePix tp = tile_pix<S, P>(g, q >> 2, x1);
+            const TilePix tp = tile_pix<S, P, RCP>(g, q >> 2, x1);
             const int pn = tp.n, py = y0 + tp.y, pxx = g.ox0 + tp.xl;
             const bool pvalid = tp.valid;
             const bool powned = pvalid && py >= a.own.y0[ti] && py <= a.own.y1[ti] && pxx >= a.own.x0[tj] && pxx <= a.own.x1[tj];
@@ -217,7 +218,7 @@ __device__ __forceinline__ void conv_epilogue(const MfmaConvArgs& a, const TileG
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int q = (wave_n * NT + t) * 32 + l32;
-        const TilePix tp = tile_pix<S, P>(g, q, x1);
+        const TilePix tp = tile_pix<S, P, RCP>(g, q, x1);
         const int pn = tp.n, py = y0 + tp.y, pxx = g.ox0 + tp.xl;
         const bool pvalid = tp.valid;
         const bool powned = pvalid && py >= a.own.y0[ti] && py <= a.own.y1[ti] && pxx >= a.own.x0[tj] && pxx <= a.own.x1[tj];

@@ -49,29 +49,30 @@ struct TileGeom {
 // Q: positions of a patch row a lane loads at once (0: one; 4: fp32 quads; 2: fp32 quads through pool winners, whose rows
 // start up to one position early, at a window's left pixel; 8: packed bfloats, whose rows start up to one position early, on
 // the dword grid of the map): patch rows are padded to whole units.
+template <bool RCP = true>
 FTP_HD inline TileGeom conv_tile_geom(int tiles_x, int TC, int cap, int flat, int batch, int x0, int x1, int y0, int y1, int bx, int S, int P, int Q)
 {
     TileGeom g;
     g.rw = x1 - x0 + 1; g.rh = y1 - y0 + 1;
-    const int tb = quot(bx, tiles_x), tx = bx - tb * tiles_x;
+    const int tb = quot<RCP>(bx, tiles_x), tx = bx - tb * tiles_x;
     g.TC = tiles_x == 1 ? g.rw : TC;
     g.ox0 = x0 + tx * g.TC;
     const int rtot = batch * g.rh;
     if (flat) {
         const int p0 = tb * cap, total = rtot * g.rw;
         g.empty = p0 >= total;
-        g.R0 = quot(p0, g.rw); g.c0 = p0 - g.R0 * g.rw;
+        g.R0 = quot<RCP>(p0, g.rw); g.c0 = p0 - g.R0 * g.rw;
         g.npx = total - p0 < cap ? total - p0 : cap;
-        g.nrows = blocks_of(g.c0 + g.npx, g.rw);
+        g.nrows = blocks_of<RCP>(g.c0 + g.npx, g.rw);
     } else {
-        int trf = quot(cap, g.TC); if (trf < 1) trf = 1;
+        int trf = quot<RCP>(cap, g.TC); if (trf < 1) trf = 1;
         g.R0 = tb * trf; g.c0 = 0;
         g.empty = g.ox0 > x1 || g.R0 >= rtot;
         g.nrows = rtot - g.R0 < trf ? rtot - g.R0 : trf;
         g.npx = g.nrows * g.TC;
     }
-    g.n_a = quot(g.R0, g.rh); g.y_a = g.R0 - g.n_a * g.rh;
-    const int n_l = quot(g.R0 + g.nrows - 1, g.rh);
+    g.n_a = quot<RCP>(g.R0, g.rh); g.y_a = g.R0 - g.n_a * g.rh;
+    const int n_l = quot<RCP>(g.R0 + g.nrows - 1, g.rh);
     g.PW = g.TC * S + 2 * P;
     if (Q == 4) g.PW = (g.PW + 3) & ~3;
     if (Q == 2) g.PW = (g.PW + 1 + 3) & ~3;
@@ -85,14 +86,15 @@ FTP_HD inline TileGeom conv_tile_geom(int tiles_x, int TC, int cap, int flat, in
 
 // Pixel (or pool window) wq of a tile -> image, row (relative to the rectangle), column, and its patch row.
 struct TilePix { int n, y, xl, prow; bool valid; };
+template <bool RCP = true>
 FTP_HD inline TilePix conv_tile_pix(const TileGeom& g, int wq, int x1, int S, int P)
 {
     TilePix t;
     const int lin = g.c0 + wq;
-    const int fr = quot_small(lin, g.TC);
+    const int fr = quot_small<RCP>(lin, g.TC);
     t.xl = lin - fr * g.TC;
     const int R = g.R0 + fr;
-    const int past = quot_lane(g.y_a + fr, g.rh);           // images behind the tile's first
+    const int past = quot_lane<RCP>(g.y_a + fr, g.rh);           // images behind the tile's first
     t.n = g.n_a + past;
     t.y = R - t.n * g.rh;
     t.prow = S * fr + 2 * P * past;
@@ -212,10 +214,11 @@ FTP_HD inline unsigned row_order_grid(int N, int M, int mblocks, int ntiles, int
     return 8u * (unsigned)((row_order_units(N, ntiles, run) + 7) / 8) * (unsigned)(run * M * mblocks);
 }
 // Workgroup `block` -> channel block and stack (vgroup = stack * mblocks + channel block), tile.  False: padding.
+template <bool RCP = true>
 FTP_HD inline bool row_order(int block, int N, int M, int mblocks, int ntiles, int run, int& vgroup, int& vtile)
 {
-    const int row = M * mblocks, size = run * row, slot = block >> 3, round = quot(slot, size), w = slot - round * size;
-    const int unit = (block & 7) + 8 * round, per = blocks_of(ntiles, run), ti = quot(unit, per), v = quot(w, row);
+    const int row = M * mblocks, size = run * row, slot = block >> 3, round = quot<RCP>(slot, size), w = slot - round * size;
+    const int unit = (block & 7) + 8 * round, per = blocks_of<RCP>(ntiles, run), ti = quot<RCP>(unit, per), v = quot<RCP>(w, row);
     vtile = (unit - ti * per) * run + v;
     vgroup = ti * row + (w - v * row);
     return ti < N && vtile < ntiles;

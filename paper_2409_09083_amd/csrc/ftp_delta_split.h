@@ -67,6 +67,7 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
     constexpr int BM = 32 * WAVES_M;
     constexpr int CK = split_stage_channels(K), OCT = CK / 8;
     constexpr int KK = K * K, P = K / 2;
+    constexpr bool RCP = K < 7;
     constexpr int XMAX = split_max_positions(K, BN);
     constexpr int UPO = XMAX / 4;                      // units (4 positions x 8 channels) per group of 8 channels
     constexpr int UNITS = OCT * UPO, NU = (UNITS + 255) / 256;
@@ -82,10 +83,10 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
     // (tile, channel block, stack), tile fastest; in XCD order where the launch says so: the tiles of one stack and channel
     // block then run on one XCD, which meets one channel block's slice of the filter only
     int vgroup, vtile;
-    if (!tile_order(a, index, vgroup, vtile)) return;
-    const int stack = quot(vgroup, a.mblocks), ti = quot(stack, a.M), tj = stack - ti * a.M;
+    if (!tile_order<RCP>(a, index, vgroup, vtile)) return;
+    const int stack = quot<RCP>(vgroup, a.mblocks), ti = quot<RCP>(stack, a.M), tj = stack - ti * a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
-    const TileGeom g = tile_geom<1, P, IN == IN_POOL ? 2 : 4>(a, x0, x1, y0, y1, vtile);
+    const TileGeom g = tile_geom<1, P, IN == IN_POOL ? 2 : 4, RCP>(a, x0, x1, y0, y1, vtile);
     if (g.empty) return;
     const int m0 = (vgroup - stack * a.mblocks) * BM;
     const int PW = g.PW, npos = g.npos;
@@ -95,7 +96,7 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int q = (wave_n * NT + t) * 32 + l32;
-        const TilePix tp = tile_pix<1, P>(g, q, x1);
+        const TilePix tp = tile_pix<1, P, RCP>(g, q, x1);
         baseB[t] = (tp.valid ? tp.prow * PW + tp.xl + sh : 0) + hi * XMAX;
     }
 
@@ -117,11 +118,11 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
         const int s = 4 * (unit % UPO);
         xoff[u] = kOobS; moff[u] = kOobS; xin[u] = 0;
         if (s < npos && unit < UNITS) {
-            const int pr = quot_small(s, PW), c = s - pr * PW;
+            const int pr = quot_small<RCP>(s, PW), c = s - pr * PW;
             int k = 0, lr = pr, ybase = g.y_a;
             if (pr >= g.first_cnt) {
                 const int t = pr - g.first_cnt;
-                k = 1 + quot_small(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
+                k = 1 + quot_small<RCP>(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
             }
             const int gy = y0 + ybase + lr - P, gx = g.ox0 - P - sh + c;
             const int sy = IN >= IN_POOL ? gy >> 1 : gy, sx = IN >= IN_POOL ? gx >> 1 : gx;
@@ -340,7 +341,7 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
             float z = 0.0f;
 #pragma unroll
             for (int i = 0; i < 16; ++i) z = __builtin_fmaf(acc[0][t][i], 0.0f, z);
-            bad = bad || (tile_pix<1, P>(g, (wave_n * NT + t) * 32 + l32, x1).valid && !(z == 0.0f));
+            bad = bad || (tile_pix<1, P, RCP>(g, (wave_n * NT + t) * 32 + l32, x1).valid && !(z == 0.0f));
         }
         if (bad) redo = 1;
         __syncthreads();
@@ -358,7 +359,7 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
         int at[NT];                                    // the pixel's first patch position, this lane half's 8 channels
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            const TilePix tp = tile_pix<1, P>(g, (__builtin_amdgcn_readfirstlane(tr >> 6) / WAVES_M * NT + t) * 32 + (tr & 31), x1);
+            const TilePix tp = tile_pix<1, P, RCP>(g, (__builtin_amdgcn_readfirstlane(tr >> 6) / WAVES_M * NT + t) * 32 + (tr & 31), x1);
             at[t] = (tp.valid ? tp.prow * PW + tp.xl + sh : 0) + 8 * hr * XMAX;
         }
 #pragma unroll
@@ -391,7 +392,7 @@ __device__ __forceinline__ void delta_split_group(const MfmaConvArgs& a, int ind
             }
         }
     }
-    conv_epilogue<float, K, 1, WAVES_M, 1, false, true>(a, g, acc, (float*)Xl, m0, x0, x1, y0, stack, ti, tj);
+    conv_epilogue<float, K, 1, WAVES_M, 1, false, true, RCP>(a, g, acc, (float*)Xl, m0, x0, x1, y0, stack, ti, tj);
 }
 
 struct SplitShape { int BM, BN; };                   // channels, pixels of a workgroup

@@ -36,7 +36,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 constexpr int kWgradZPos = 64;                         // the limits wgrad_chunks() cuts to: this and wgrad_xpos(P)
 
 // Workgroup `index` of the launch.
-template <typename T, int K, int WAVES_CO, int WAVES_CI, int HALF, int TROWS>
+template <typename T, int K, int WAVES_CO, int WAVES_CI, int HALF, int TROWS, bool RCP>
 __device__ __forceinline__ void wgrad_mfma_group(const MfmaWgradArgs& a, int index)
 {
     constexpr bool POOL = HALF == 1;
@@ -60,7 +60,7 @@ __device__ __forceinline__ void wgrad_mfma_group(const MfmaWgradArgs& a, int ind
     const int wave_co = wave % WAVES_CO, wave_ci = (wave / WAVES_CO) % WAVES_CI, wave_k = wave / (WAVES_CO * WAVES_CI);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    if (!xcd_shares(index, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    if (!xcd_shares<RCP>(index, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;

@@ -9,7 +9,7 @@ __global__ void __launch_bounds__(256, 2)
 k_wgrad_mfma(MfmaWgradArgs a)
 {
     if (blockIdx.x < 512) touch_args<0, sizeof(MfmaWgradArgs)>();
-    wgrad_mfma_group<T, K, WAVES_CO, WAVES_CI, HALF, TROWS>(a, (int)blockIdx.x);
+    wgrad_mfma_group<T, K, WAVES_CO, WAVES_CI, HALF, TROWS, false>(a, (int)blockIdx.x);
 }
 
 // Geometry: stride 1 with K = 1, 3 (with or without the fused pool), K = 5, 7 without; stride 2 with K = 1, 3.

@@ -10,10 +10,11 @@ namespace ftp {
 // 8 * gx * ceil(groups / 8) workgroups and number them so that a group's workgroups run on one XCD, one after the
 // other, while consecutive groups go to different XCDs (so uneven groups still spread over the chip):
 // XCD x = index % 8 (index: the workgroup's) works through the groups x, x + 8, x + 16, ...  Returns false for the padding (group >= groups).
+template <bool RCP = true>
 FTP_HD inline bool xcd_order(int index, int groups, int gx, int& group, int& block)
 {
     const int xcd = index & 7, slot = index >> 3;
-    const int round = quot(slot, gx);
+    const int round = quot<RCP>(slot, gx);
     block = slot - round * gx;
     group = xcd + 8 * round;
     return group < groups;
@@ -25,17 +26,18 @@ FTP_HD inline unsigned xcd_grid(int groups, int gx) { return (unsigned)(8 * gx *
 // block fastest, and XCD x takes its x-th eighth: neighbours run side by side on one XCD, and each takes about a share of all stacks (fp32
 // 32 -> 64 with a pool, 64 images of 304^2, 6 x 6 stacks, 14 shares: 1.60 -> 1.39 ms).  With fewer shares an eighth would be a few stacks, whose sizes
 // differ (1x1 shares, 512 -> 256 at 38^2 in stacks of 6 or 7 rows: 1.52 -> 1.69 ms): stacks and shares go round-robin then.  (Either is the better one by up to 13 % where no rule is known to tell: the eighths in two cases of three.)
+template <bool RCP = true>
 FTP_HD inline bool xcd_shares(int index, bool eighths, int shares, int stacks, int gx, int& share, int& stack, int& block)
 {
     if (!eighths) {
         int g;
-        const bool ok = xcd_order(index, shares * stacks, gx, g, block);
-        stack = quot(g, shares); share = g - stack * shares;
+        const bool ok = xcd_order<RCP>(index, shares * stacks, gx, g, block);
+        stack = quot<RCP>(g, shares); share = g - stack * shares;
         return ok;
     }
     const int total = shares * stacks * gx, per = (total + 7) >> 3, slot = index >> 3;
-    const int i = (index & 7) * per + slot, r = quot(i, gx);
-    block = i - r * gx; share = quot(r, stacks); stack = r - share * stacks;
+    const int i = (index & 7) * per + slot, r = quot<RCP>(i, gx);
+    block = i - r * gx; share = quot<RCP>(r, stacks); stack = r - share * stacks;
     return slot < per && i < total;
 }
 FTP_HD inline unsigned xcd_shares_grid(bool eighths, int shares, int stacks, int gx)
