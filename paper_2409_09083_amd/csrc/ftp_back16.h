@@ -11,14 +11,14 @@ namespace ftp {
 // (the area that the gradient's workgroups have)
 struct Back16Lds { static __device__ __forceinline__ uint4* at() { extern __shared__ __attribute__((aligned(16))) unsigned char lds16[]; return (uint4*)lds16; } };
 
-struct Back16Args { Wgrad16Args w; MfmaConvArgs d; int wgroups; };
+struct Back16Args { int wgroups; Wgrad16Args w; MfmaConvArgs d; };
 
 template <int WAVES_CI, int WM, int MT, int NT, int IN, bool WS, bool ROWS>
 __global__ void __launch_bounds__(256, 2)
 k_back16(Back16Args a)
 {
     const int index = (int)blockIdx.x;
-    if (index < 256) touch_args<0, sizeof(Back16Args)>();
+    touch_joint_args<Back16Args>(index, a.wgroups);
     if (index < a.wgroups) wgrad16_form<WAVES_CI, IN == BF_POOL ? 1 : 0, WS, ROWS>(a.w, index);
     else conv_bf16_group<3, WM, MT, NT, false, true, IN, Back16Lds>(a.d, index - a.wgroups);
 }

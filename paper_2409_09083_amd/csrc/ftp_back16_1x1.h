@@ -10,14 +10,14 @@ namespace ftp {
 
 struct Back16OneLds { static __device__ __forceinline__ uint4* at() { extern __shared__ __attribute__((aligned(16))) uint4 one_lds[]; return one_lds; } };
 
-struct Back16OneArgs { MfmaWgradArgs w; MfmaConvArgs d; int wgroups; };
+struct Back16OneArgs { int wgroups; MfmaWgradArgs w; MfmaConvArgs d; };
 
 template <int WAVES_CI, int WM, int MT, int NT, int IN>
 __global__ void __launch_bounds__(256, 2)
 k_back16_1x1(Back16OneArgs a)
 {
     const int index = (int)blockIdx.x;
-    if (index < 256) touch_args<0, sizeof(Back16OneArgs)>();
+    touch_joint_args<Back16OneArgs>(index, a.wgroups);
     if (index < a.wgroups) {
         if constexpr (WAVES_CI == 0) wgrad16_1x1_group<2>(a.w, index);
         else wgrad_mfma_group<bf16_t, 1, 2, WAVES_CI, IN == BF_POOL ? 1 : 0, 1, true>(a.w, index);

@@ -7,14 +7,14 @@
 
 namespace ftp {
 
-struct BackSmallArgs { MfmaWgradArgs w; MfmaConvArgs d; int wgroups; };
+struct BackSmallArgs { int wgroups; MfmaWgradArgs w; MfmaConvArgs d; };
 
 template <int K, int WAVES_CI, int WAVES_M, int BN, bool POOL>
 __global__ void __launch_bounds__(256, 2)
 k_back_small(BackSmallArgs a)
 {
     const int index = (int)blockIdx.x;
-    if (index < 256) touch_args<0, sizeof(BackSmallArgs)>();
+    touch_joint_args<BackSmallArgs>(index, a.wgroups);
     if (index < a.wgroups) wgrad_mfma_group<float, K, 2, WAVES_CI, POOL ? 1 : 0, K == 5 ? 2 : 1, true>(a.w, index);
     else delta_split_group<K, WAVES_M, BN, POOL ? IN_POOL : IN_WIDE>(a.d, index - a.wgroups);
 }

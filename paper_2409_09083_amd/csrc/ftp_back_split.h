@@ -11,14 +11,14 @@
 
 namespace ftp {
 
-struct BackSplitArgs { WsplitArgs w; MfmaConvArgs d; int wgroups; };
+struct BackSplitArgs { int wgroups; WsplitArgs w; MfmaConvArgs d; };
 
 template <int WAVES_CO, int WAVES_CI, int WAVES_M, int BN, bool POOL, bool WS>
 __global__ void __launch_bounds__(256, 2)
 k_back_split(BackSplitArgs a)
 {
     const int index = (int)blockIdx.x;
-    if (index < 256) touch_args<0, sizeof(BackSplitArgs)>();
+    touch_joint_args<BackSplitArgs>(index, a.wgroups);
     if (index < a.wgroups) wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS>(a.w, index);
     else delta_split_group<3, WAVES_M, BN, POOL ? IN_POOL : IN_WIDE>(a.d, index - a.wgroups);
 }

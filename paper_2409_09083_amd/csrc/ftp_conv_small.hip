@@ -42,7 +42,7 @@ template <int K, bool POOL, bool WIDE>
 __global__ void __launch_bounds__(256, 2)
 k_conv_small(MfmaConvArgs a)
 {
-    touch_args<0, sizeof(MfmaConvArgs)>();
+    touch_args<0, sizeof(MfmaConvArgs)>((int)blockIdx.x);
     typedef SmallStage<K> ST;
     constexpr int P = K / 2, S = POOL ? 2 : 1, CK = ST::CK, XP = ST::XP, PER = ST::kPerLoad, PAIR = ST::kPair, WF = ST::WF;
     constexpr int D = 4;                               // stages of LDS: three workgroups share a CU

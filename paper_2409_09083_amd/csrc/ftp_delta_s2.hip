@@ -36,7 +36,7 @@ template <typename T, int K, int MT, int NC>
 __global__ void __launch_bounds__(320)
 k_delta_s2_mfma(DeltaS2Args a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(DeltaS2Args)>();
+    touch_args<0, sizeof(DeltaS2Args)>((int)blockIdx.x);
     static_assert(K == 1 || K == 3, "1x1 and 3x3 filters");
     constexpr int BM = 32 * MT, ES = sizeof(T), NR = 32 / NC, KK = K * K, P = K / 2;
     constexpr int PW = NC + P, NPOS = (NR + P) * PW, XPASS = (NPOS + 63) / 64;     // (a 1x1 filter reads no neighbour: only the pixels (2j, 2i) receive a delta)

@@ -9,7 +9,7 @@ template <int K, int WAVES_M, int BN, int IN>
 __global__ void __launch_bounds__(256, split_waves(K, WAVES_M, BN))
 k_delta_split(MfmaConvArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(MfmaConvArgs)>();
+    touch_args<0, sizeof(MfmaConvArgs)>((int)blockIdx.x);
     delta_split_group<K, WAVES_M, BN, IN>(a, (int)blockIdx.x);
 }
 

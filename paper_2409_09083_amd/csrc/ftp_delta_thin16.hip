@@ -30,7 +30,7 @@ __global__ void __launch_bounds__(256, 2)
 k_delta_thin16(View din, View mask, View dout, View isign, int scale_out, float in_slope, RectTab rt, const bf16_t* __restrict__ w,
                int Cin, int Cout, int Hc, int Wc, int N, int M, int tiles_x, int tiles, int TX, int total)
 {
-    touch_args<0, 4 * sizeof(View) + sizeof(RectTab)>();
+    touch_args<0, 4 * sizeof(View) + sizeof(RectTab)>((int)blockIdx.x);
     typedef float v4f __attribute__((ext_vector_type(4)));
     typedef uint32_t v3u __attribute__((ext_vector_type(3), aligned(4)));
     typedef uint32_t v2u __attribute__((ext_vector_type(2), aligned(4)));

@@ -1,6 +1,7 @@
 // Device-side addressing shared by the kernels of libftp (gfx950).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <cstddef>
 #include <cstdint>
 #include "ftp_order.h"
 
@@ -25,16 +26,28 @@ struct RectTab {
 // Reads one dword of every 64-byte line of the kernel's argument block from byte FROM on, so that all of them are on their way at once: the block
 // lies in host memory and is new with every launch, and its tables were met one after the other, a wait of 1.5 us each (stamps in a forward
 // kernel: 7.4 k cycles before the first load of the map, 3.5 k of them such waits, 2 k more in front of the first store; step of two small layers 48.5 -> 43.5 us, three
-// layers of one image 150.5 -> 142.6, forward 38.8 -> 36.9).  The launch's first workgroups do it (512; 256 where two kernels' arguments travel together): what
-// they fetched serves the others (all of 1024: 16-bit 1x1 / 3x3 pair, 8 images of 76^2, 314 -> 317 us).
+// layers of one image 150.5 -> 142.6, forward 38.8 -> 36.9).  The launch's first workgroups do it, four an XCD: what they fetched serves the others, and
+// lines that many fetch at once come slower than one after the other (5x5 1 -> 256, 27 images of 32^2 in 4 x 4 stacks, 49.8 us without, 50.6 by 32, 54.9 by 512;
+// 130 shapes of all layers against none: forward 0.92 times the time by 32, 0.93 by 512, back-propagation 0.978 and 0.983; 8, 16 and 64 as 32).
+constexpr int kTouching = 32;
 template <int FROM, int BYTES>
-__device__ __forceinline__ void touch_args()
+__device__ __forceinline__ void touch_args(int index)
 {
+    if (index >= kTouching) return;
     const uint32_t __attribute__((address_space(4)))* const p = (const uint32_t __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
     uint32_t x = 0;
 #pragma unroll
     for (int i = FROM; i < FROM + BYTES; i += 64) x |= p[i / 4];
     asm volatile("" :: "s"(x));
+}
+// ... of two kernels whose arguments `w` and `d` travel together, the first `wgroups` workgroups being of `w`: each workgroup its own part (16-bit 3x3 32 -> 56, one
+// image of 38^2, 20.9 -> 20.4 us; 12 small fp32 3x3 layers 0.988 times the time of untouched arguments -> 0.977, 1.003 with both parts).
+template <class Args>
+__device__ __forceinline__ void touch_joint_args(int index, int wgroups)
+{
+    constexpr int D = (int)offsetof(Args, d) & ~63;
+    if (index < wgroups) touch_args<0, (int)offsetof(Args, d)>(index);
+    else touch_args<D, (int)sizeof(Args) - D>(index - wgroups);
 }
 
 typedef uint16_t bf16_t;          // raw bfloat16 bits

@@ -212,7 +212,7 @@ __global__ void __launch_bounds__(256)
 k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ partial, long long n_params,
                long long w_off, long long b_off, int has_bias, int Cin, int Cout, int Hi, int Wi, int Hc, int Wc, int M, int batch)
 {
-    touch_args<0, 3 * sizeof(View) + sizeof(RectTab)>();
+    if (blockIdx.z == 0 && blockIdx.y == 0) touch_args<0, 3 * sizeof(View) + sizeof(RectTab)>((int)blockIdx.x);
     const int ci = blockIdx.x, co = blockIdx.y, stack = blockIdx.z;
     const int ti = quot(stack, M), tj = stack - ti * M;
     const int rw = own.x1[tj] - own.x0[tj] + 1, rh = own.y1[ti] - own.y0[ti] + 1;
@@ -789,7 +789,7 @@ template <typename T, int V, bool PAST, int CAP>
 __global__ void __launch_bounds__(256)
 k_scale_dy(ScaleArgs a, PrepArgs<CAP> prep)
 {
-    if (CAP <= kPrepFew && blockIdx.x < 512) touch_args<0, sizeof(ScaleArgs) + sizeof(PrepArgs<CAP>)>();
+    if (CAP <= kPrepFew) touch_args<0, sizeof(ScaleArgs) + sizeof(PrepArgs<CAP>)>((int)blockIdx.x);
     if ((int)blockIdx.x >= a.blocks) { prep_block(prep, (int)blockIdx.x - a.blocks); return; }
     const int image = quot((int)blockIdx.x, a.per);
     const unsigned i = ((unsigned)blockIdx.x - (unsigned)(image * a.per)) * 256u + threadIdx.x, units = (unsigned)(a.HW / V);

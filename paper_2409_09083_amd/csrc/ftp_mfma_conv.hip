@@ -57,7 +57,7 @@ template <typename T, int K, int WAVES_M, int MT, int BN, bool POOL_OUT, bool DE
 __global__ void __launch_bounds__(256, conv_dl_waves(sizeof(T), K, STRIDE, MT, BN, WAVES_M))
 k_conv_mfma_dl(MfmaConvArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(MfmaConvArgs)>();
+    touch_args<0, sizeof(MfmaConvArgs)>((int)blockIdx.x);
     // WIDE: the patch travels 16 bytes a lane, a quad of positions
     static_assert(!WIDE || conv_dl_quads(sizeof(T), false, STRIDE == 2 && DELTA_IN), "wide patch loads: fp32 patches that are not gathered element by element");
     static_assert(sizeof(T) == 4 || K >= 5 || STRIDE == 2, "16-bit 1x1 / 3x3 layers of stride 1 take ftp_conv_bf16.hip");

@@ -8,7 +8,7 @@ template <typename T, int K, int WAVES_CO, int WAVES_CI, int HALF, int TROWS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_mfma(MfmaWgradArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(MfmaWgradArgs)>();
+    touch_args<0, sizeof(MfmaWgradArgs)>((int)blockIdx.x);
     wgrad_mfma_group<T, K, WAVES_CO, WAVES_CI, HALF, TROWS, false>(a, (int)blockIdx.x);
 }
 

@@ -89,7 +89,7 @@ template <typename T, int K, int S, bool POOL, int CI>
 __global__ void __launch_bounds__(256, 3)
 k_conv_fwd_stem(StemArgs a, PrepArgs<kPrepFew> prep)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(StemArgs)>();
+    touch_args<0, sizeof(StemArgs)>((int)blockIdx.x);
     if ((int)blockIdx.x >= a.blocks) { prep_block(prep, (int)blockIdx.x - a.blocks); return; }       // filters of the layers behind
     constexpr int KK = K * K, P = K / 2, STEPS = stem_steps(K, CI), NP = POOL ? 2 : 1;
     constexpr unsigned ES = sizeof(T);

@@ -497,7 +497,7 @@ template <typename T, bool POOL, int CI>
 __global__ void __launch_bounds__(256, 6)              // (six wavefronts a SIMD: the kernel waits for LDS and memory, not for registers)
 k_conv_bwd_data_thin4(Thin4Args a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(Thin4Args)>();
+    touch_args<0, sizeof(Thin4Args)>((int)blockIdx.x);
     __shared__ __attribute__((aligned(16))) float lds[thin4_words(CI)];
     bwd_thin4_group<T, POOL, CI>(a, (int)blockIdx.x, lds);
 }
@@ -530,7 +530,7 @@ __global__ void __launch_bounds__(256, 4)
 k_conv_bwd_data_thin_s2(View din, View dout, View isign, int scale_out, float in_slope, RectTab rt, RectTab ext,
                         const T* __restrict__ w, int Cin, int Cout, int M, int batch, int tiles_x, int tiles)
 {
-    if (blockIdx.x < 512) touch_args<0, 3 * sizeof(View) + 2 * sizeof(RectTab)>();
+    touch_args<0, 3 * sizeof(View) + 2 * sizeof(RectTab)>((int)blockIdx.x);
     typedef StridedTaps<K> G;
     constexpr int P = G::P, QLO = G::QLO, NQ = G::NQ, KK = K * K;
     constexpr bool SQ = K == 3;                        // the neighbourhood (2 x 2) is one step
@@ -781,7 +781,7 @@ template <typename T, int K, int S, int NB, bool POOL>
 __global__ void __launch_bounds__(256)
 k_wgrad_mfma_thin(MfmaWgradArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(MfmaWgradArgs)>();
+    touch_args<0, sizeof(MfmaWgradArgs)>((int)blockIdx.x);
     constexpr int KK = K * K, P = K / 2, ZP = 33;
     extern __shared__ float lds[];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1282,7 +1282,7 @@ template <typename T, int K, int S, int NB, bool POOL>
 __global__ void __launch_bounds__(320)
 k_wgrad_thin_dl(MfmaWgradArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(MfmaWgradArgs)>();
+    touch_args<0, sizeof(MfmaWgradArgs)>((int)blockIdx.x);
     extern __shared__ __attribute__((aligned(16))) float thin_lds[];
     wgrad_thin_dl_group<T, K, S, NB, POOL>(a, (int)blockIdx.x, thin_lds);
 }
@@ -1290,13 +1290,13 @@ k_wgrad_thin_dl(MfmaWgradArgs a)
 // Small 3x3 first layers: filter gradient and delta at the image in one launch, as in ftp_back_split.h: the first `wgroups` workgroups
 // are those of k_wgrad_thin_dl, the others (their first four wavefronts) those of k_conv_bwd_data_thin4.
 // 3 -> 8, one image of 32^2: step of its net 57 -> 49 us; 3 -> 16 with a pool, one image of 416^2: 157 -> 151.
-struct BackThinArgs { MfmaWgradArgs w; Thin4Args d; int wgroups; };
+struct BackThinArgs { int wgroups; MfmaWgradArgs w; Thin4Args d; };
 
 template <typename T, int NB, bool POOL, int CI>
 __global__ void __launch_bounds__(320)
 k_back_thin(BackThinArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(BackThinArgs)>();
+    touch_joint_args<BackThinArgs>((int)blockIdx.x, a.wgroups);
     extern __shared__ __attribute__((aligned(16))) float thin_lds[];
     const int index = (int)blockIdx.x;
     if (index < a.wgroups) { wgrad_thin_dl_group<T, 3, 1, NB, POOL>(a.w, index, thin_lds); return; }

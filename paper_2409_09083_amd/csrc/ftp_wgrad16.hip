@@ -8,7 +8,7 @@ template <int WAVES_CI, int HALF, bool WS, bool ROWS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_mfma16(Wgrad16Args a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(Wgrad16Args)>();
+    touch_args<0, sizeof(Wgrad16Args)>((int)blockIdx.x);
     wgrad16_form<WAVES_CI, HALF, WS, ROWS>(a, (int)blockIdx.x);
 }
 

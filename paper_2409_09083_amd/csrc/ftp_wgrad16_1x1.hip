@@ -7,7 +7,7 @@ template <int NJ>
 __global__ void __launch_bounds__(256, NJ == 2 ? 3 : 2)
 k_wgrad16_1x1(MfmaWgradArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(MfmaWgradArgs)>();
+    touch_args<0, sizeof(MfmaWgradArgs)>((int)blockIdx.x);
     wgrad16_1x1_group<NJ>(a, (int)blockIdx.x);
 }
 

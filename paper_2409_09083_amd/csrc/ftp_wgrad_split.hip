@@ -8,7 +8,7 @@ template <int WAVES_CO, int WAVES_CI, bool POOL, bool WS>
 __global__ void __launch_bounds__(256, 2)
 k_wgrad_split(WsplitArgs a)
 {
-    if (blockIdx.x < 512) touch_args<0, sizeof(WsplitArgs)>();
+    touch_args<0, sizeof(WsplitArgs)>((int)blockIdx.x);
     wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS>(a, (int)blockIdx.x);
 }
 

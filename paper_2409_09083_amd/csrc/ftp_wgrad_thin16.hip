@@ -25,7 +25,7 @@ constexpr int kT16Pitch = 104;                        // LDS row, elements: 13 u
 __global__ void __launch_bounds__(256, 3)
 k_wgrad_thin16(MfmaWgradArgs a)
 {
-    touch_args<0, sizeof(MfmaWgradArgs)>();
+    touch_args<0, sizeof(MfmaWgradArgs)>((int)blockIdx.x);
     typedef uint32_t v4u __attribute__((ext_vector_type(4), aligned(4)));
     typedef uint32_t v3u __attribute__((ext_vector_type(3), aligned(4)));
     constexpr int W = 4;                               // wavefronts
