@@ -194,6 +194,15 @@ inline TileChoice choose_tile(const int* rws, const int* rhs, int N, int M, int 
     return best;
 }
 
+// Workgroups a launch has at the least, whatever choose_tile makes of it: no tile holds more than cap0 pixels of the largest stack.
+inline long long least_workgroups(const int* rws, const int* rhs, int N, int M, int batch, int cap0, int mblocks)
+{
+    int rw = 0, rh = 0;
+    for (int j = 0; j < M; ++j) rw = rw > rws[j] ? rw : rws[j];
+    for (int i = 0; i < N; ++i) rh = rh > rhs[i] ? rh : rhs[i];
+    return (long long)mblocks * N * M * (((long long)batch * rw * rh + cap0 - 1) / cap0);
+}
+
 // Tiles one stack's rectangle is cut into (what tile_geom() enumerates).
 inline long long tile_slots(const TileChoice& tc, int rw, int rh, int batch)
 {

@@ -35,3 +35,7 @@ def test_orders_of_workgroups_name_each_once_and_load_the_xcds_evenly():
 
 def test_quotients_by_reciprocals_are_exact():
     _build_and_run("quot_check")
+
+
+def test_large_launches_are_told_from_small_ones_before_they_are_cut():
+    _build_and_run("small_launch_check")
