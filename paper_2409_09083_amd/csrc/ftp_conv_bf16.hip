@@ -25,10 +25,14 @@ bool even_view(const View& v) { return ((uintptr_t)v.p & 3) == 0 && !((v.pitch |
 template <int K, bool POOL_OUT, bool DELTA_IN, int IN>
 void launch_bf(const MfmaConvArgs& a, BfShape sh, dim3 grid, hipStream_t s)
 {
-    static char label[6][104];                   // (every write of an entry stores the same text: entries depend on the template and the shape only)
-    const int v = sh.MT == 1 ? 3 + sh.NT : (sh.WM == 2 ? 0 : 2) + (sh.NT == 4 ? 0 : 1);
-    std::snprintf(label[v], sizeof(label[v]), "k_conv_bf16<%d, %d, %d, %d, %s, %s, %d>", K, sh.WM, sh.MT, sh.NT, POOL_OUT ? "true" : "false", DELTA_IN ? "true" : "false", IN);
-    g_kernel_label = label[v];
+    static const Labels<6> labels = [] {
+        Labels<6> l;
+        const int shapes[6][3] = {{2, 2, 4}, {2, 2, 2}, {1, 2, 4}, {1, 2, 2}, {1, 1, 1}, {1, 1, 2}};
+        for (int v = 0; v < 6; ++v)
+            std::snprintf(l.text[v], sizeof(l.text[v]), "k_conv_bf16<%d, %d, %d, %d, %s, %s, %d>", K, shapes[v][0], shapes[v][1], shapes[v][2], POOL_OUT ? "true" : "false", DELTA_IN ? "true" : "false", IN);
+        return l;
+    }();
+    g_kernel_label = labels.text[sh.MT == 1 ? 3 + sh.NT : (sh.WM == 2 ? 0 : 2) + (sh.NT == 4 ? 0 : 1)];
 #define FTP_BF(WM, MT, NT) hipLaunchKernelGGL((k_conv_bf16<K, WM, MT, NT, POOL_OUT, DELTA_IN, IN>), grid, dim3(256), 0, s, a)
     if (sh.MT == 1) { if (sh.NT == 2) FTP_BF(1, 1, 2); else FTP_BF(1, 1, 1); }
     else if (sh.WM == 2) { if (sh.NT == 4) FTP_BF(2, 2, 4); else FTP_BF(2, 2, 2); }

@@ -19,10 +19,12 @@ namespace {
 template <int K, int IN>
 void launch_split(const MfmaConvArgs& a, SplitShape sh, dim3 grid, hipStream_t s)
 {
-    static char label[6][104];                   // (every write of an entry stores the same text: entries depend on the template and the shape only)
-    const int v = (sh.BM == 128 ? 0 : sh.BM == 64 ? 1 : 2) * 2 + (sh.BN == 256 ? 0 : 1);
-    std::snprintf(label[v], sizeof(label[v]), "k_delta_split<%d, %d, %d, %d>", K, sh.BM / 32, sh.BN, IN);
-    g_kernel_label = label[v];
+    static const Labels<6> labels = [] {
+        Labels<6> l;
+        for (int v = 0; v < 6; ++v) std::snprintf(l.text[v], sizeof(l.text[v]), "k_delta_split<%d, %d, %d, %d>", K, 4 >> (v >> 1), v & 1 ? 128 : 256, IN);
+        return l;
+    }();
+    g_kernel_label = labels.text[(sh.BM == 128 ? 0 : sh.BM == 64 ? 1 : 2) * 2 + (sh.BN == 256 ? 0 : 1)];
 #define FTP_SP(WM, BN) do { \
         constexpr int lds = split_lds(K, BN); \
         if (lds > 64 * 1024) { \

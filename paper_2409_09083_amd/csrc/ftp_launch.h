@@ -9,6 +9,8 @@ namespace ftp {
 
 // Name of the main kernel of the most recent launch on this thread (for the timing records).
 extern thread_local const char* g_kernel_label;
+// Names of a launcher's kernels, written by the first call only: other threads may be reading them.
+template <int N> struct Labels { char text[N][104]; };
 
 // One convolution unit (convolution + leaky ReLU, optionally with the 2x2 pool behind it).
 // Which fields a pass reads:

@@ -360,12 +360,14 @@ constexpr int conv_dl_max_bm(int K) { return K >= 7 ? 64 : 128; }
 template <typename T, int K, bool POOL_OUT, bool DELTA_IN, int STRIDE>
 void launch_dl(const MfmaConvArgs& a, DlShape sh, bool wide, dim3 grid, hipStream_t s)
 {
-    static char label[12][104];                  // (every write of an entry stores the same text: entries depend on the template and the shape only)
-    const int v = ((sh.BM == 128 ? 0 : sh.BM == 64 ? 1 : 2) * 2 + (sh.BN == 256 ? 0 : 1)) * 2 + (wide ? 1 : 0);
-    std::snprintf(label[v], sizeof(label[v]), "k_conv_mfma_dl<%s, %d, %d, %d, %d, %s, %s, %d, %s>", sizeof(T) == 4 ? "float" : "unsigned short",
-                  K, sh.BM == 128 ? 2 : 1, sh.BM == 32 ? 1 : 2, sh.BN, POOL_OUT ? "true" : "false", DELTA_IN ? "true" : "false",
-                  STRIDE, wide ? "true" : "false");
-    g_kernel_label = label[v];
+    static const Labels<12> labels = [] {
+        Labels<12> l;
+        for (int v = 0; v < 12; ++v)               // (128, 64, 32 channels) x (256, 128 pixels) x (element by element, quads)
+            std::snprintf(l.text[v], sizeof(l.text[v]), "k_conv_mfma_dl<%s, %d, %d, %d, %d, %s, %s, %d, %s>", sizeof(T) == 4 ? "float" : "unsigned short",
+                          K, v < 4 ? 2 : 1, v < 8 ? 2 : 1, v & 2 ? 128 : 256, POOL_OUT ? "true" : "false", DELTA_IN ? "true" : "false", STRIDE, v & 1 ? "true" : "false");
+        return l;
+    }();
+    g_kernel_label = labels.text[((sh.BM == 128 ? 0 : sh.BM == 64 ? 1 : 2) * 2 + (sh.BN == 256 ? 0 : 1)) * 2 + (wide ? 1 : 0)];
     constexpr bool STRIDED_FWD = STRIDE == 2 && !DELTA_IN;
     constexpr bool QUADABLE = conv_dl_quads(sizeof(T), false, STRIDE == 2 && DELTA_IN);
 #define FTP_DL(WM, MT, BN) do { \
