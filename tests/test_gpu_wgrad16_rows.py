@@ -82,6 +82,7 @@ def test_gradient_of_one_layer(cin, cout, batch, h, w, grid, rows, inner):
 
 @pytest.mark.parametrize("cin,cout,batch,h,w,grid", [
     (64, 64, 1, 60, 64, (1, 1)), (32, 64, 2, 24, 76, (2, 8)), (96, 32, 3, 20, 36, (5, 3)), (64, 64, 2, 8, 12, (2, 3)), (128, 64, 4, 40, 40, (8, 8)),
+    (64, 33, 6, 30, 30, (1, 1)), (32, 45, 4, 30, 42, (3, 2)),           # pooled planes and images of odd size: deltas and codes begin on any byte
 ])
 @pytest.mark.parametrize("inner", [False, True])
 def test_gradient_through_a_pool(cin, cout, batch, h, w, grid, inner):
