@@ -15,6 +15,7 @@
 #pragma once
 #include "ftp_device.h"
 #include "ftp_launch.h"
+#include "ftp_wgrad16_walk.h"
 
 namespace ftp {
 
@@ -67,15 +68,12 @@ __device__ __forceinline__ void wgrad16_1x1_group(const MfmaWgradArgs& a, int in
     }
     __syncthreads();
 
-    const int units = a.batch * rh * G, steps = (units + 1) >> 1, per = quot(steps, a.splits), more = steps - per * a.splits;
-    const int s0 = split * per + (split < more ? split : more), s1 = s0 + per + (split < more ? 1 : 0);
-    const int last = 2 * s1 < units ? 2 * s1 : units;                                      // units of the share end here
+    const int units = a.batch * rh * G;
+    const ShareRange sr = share_range((units + 1) >> 1, a.splits, split);                  // steps
+    const int last = 2 * sr.end < units ? 2 * sr.end : units;                              // units of the share end here
     // this lane half's unit: image n, row y, unit g; a step of this wavefront is 8 units on
-    const int ob = 2 * (s0 + wave), rb = quot(ob, G), nb = quot(rb, rh);
-    int o = ob + hi, g = ob - rb * G + hi, y = rb - nb * rh, n = nb;
-    if (g >= G) { g -= G; ++y; }
-    if (y >= rh) { y -= rh; ++n; }
-    const int dr = quot(8, G), dg = 8 - dr * G, dn = quot(dr, rh), dy = dr - dn * rh;
+    OneWalk at = one_start(G, rh, sr.first + wave, hi);
+    const OneStride stride = one_stride(G, rh);
 
     const unsigned xch = 2u * (unsigned)a.in.cs, zch = 2u * (unsigned)a.din.cs;            // bytes between channels (multiples of 4)
     const unsigned xl = ci0 + l32 < a.Cin ? (unsigned)(ci0 + l32) * xch : kOob, zl = co0 + l32 < a.Cout ? (unsigned)(co0 + l32) * zch : kOob;
@@ -86,8 +84,8 @@ __device__ __forceinline__ void wgrad16_1x1_group(const MfmaWgradArgs& a, int in
     struct Step { v4u x[NJ], z[2]; uint32_t z5[2]; int mask; };
     Step ring[RING];
     auto issue = [&](Step& st) {
-        const bool there = o < last;
-        const int xo = xfirst + n * xns + y * xp, e = xo & 1, zo = zfirst + n * zns + y * zp + 8 * g - e;
+        const bool there = at.o < last;
+        const int g = at.g, xo = xfirst + at.n * xns + at.y * xp, e = xo & 1, zo = zfirst + at.n * zns + at.y * zp + 8 * g - e;
         const unsigned xv = 2u * (unsigned)(xo - e + 8 * g), zv = 2u * (unsigned)zo & ~3u;
         st.mask = (e * kOneUnits + g) | (zo & 1) << 8;
         const unsigned za = there && zl != kOob ? zv + zl : kOob;
@@ -108,8 +106,8 @@ __device__ __forceinline__ void wgrad16_1x1_group(const MfmaWgradArgs& a, int in
                     uint32_t w = 0;
 #pragma unroll
                     for (int k = 0; k < 2; ++k) {
-                        const unsigned at = xb[b] + 4u * i + 2u * k;
-                        w |= (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xr, xb[b] != kOob && at + 32u * b * xch < end ? at : kOob, 32u * b * xch, 0) << (16 * k);
+                        const unsigned p = xb[b] + 4u * i + 2u * k;
+                        w |= (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(xr, xb[b] != kOob && p + 32u * b * xch < end ? p : kOob, 32u * b * xch, 0) << (16 * k);
                     }
                     st.x[b][i] = w;
                 }
@@ -123,9 +121,7 @@ __device__ __forceinline__ void wgrad16_1x1_group(const MfmaWgradArgs& a, int in
             st.z5[0] = __builtin_amdgcn_raw_buffer_load_b32(zr, za != kOob ? za + 16u : kOob, 0, 0);
             st.z5[1] = __builtin_amdgcn_raw_buffer_load_b32(zr, zb != kOob ? zb + 16u : kOob, 32u * zch, 0);
         }
-        o += 8; g += dg; y += dy; n += dn;
-        if (g >= G) { g -= G; ++y; }
-        if (y >= rh) { y -= rh; ++n; }
+        one_next(at, stride, G, rh);
     };
     v16 acc[2][NJ];
 #pragma unroll
@@ -158,7 +154,7 @@ __device__ __forceinline__ void wgrad16_1x1_group(const MfmaWgradArgs& a, int in
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b, st.z[i]), __builtin_bit_cast(v8b, st.x[j]), acc[i][j], 0, 0, 0);
     };
     // (steps beyond the share load and add zeros)
-    const int turns = s1 - s0 - wave > 0 ? (s1 - s0 - wave + 3) >> 2 : 0;
+    const int turns = one_turns(sr.end - sr.first, wave);
 #pragma unroll
     for (int r = 0; r < RING; ++r) issue(ring[r]);
     for (int t = 0; t < turns; t += RING) {

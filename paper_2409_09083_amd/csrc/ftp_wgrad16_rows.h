@@ -18,6 +18,7 @@
 // 32 of 76^2, 247 / 199; 140 shapes 0.91 times in the mean.
 #pragma once
 #include "ftp_wgrad16.h"
+#include "ftp_wgrad16_walk.h"
 
 namespace ftp {
 
@@ -51,12 +52,9 @@ __device__ __forceinline__ void wgrad16_rows_group(const Wgrad16Args& a, int ind
     const int xpitch = a.in.pitch, zpitch = a.din.pitch, mpitch = a.mask.pitch;
     const int s = (x0 - 1 - in_x0) & 1;                // (strides of the input view are even: the same for all rows and channels)
     const int col0 = x0 - 1 - s;                       // map column of position 0
-    const int G = (rw + 2 + s + 7) >> 3, strips = a.batch * G, pairs = (strips + 1) >> 1;
-    const int RS = a.run < rh ? a.run : rh, SEG = blocks_of(rh, RS);       // rows of a run, runs of a strip
-    const int units = pairs * SEG;                     // (strip pair, run)
-    const int per = quot(units, a.splits), more = units - per * a.splits;
-    const int u0 = split * per + (split < more ? split : more), u1 = u0 + per + (split < more ? 1 : 0);
-    const int mine = u1 - u0 - wave_k > 0 ? (u1 - u0 - wave_k + WAVES_K - 1) / WAVES_K : 0;         // units of this wavefront
+    const Rows16 r16 = rows16(rw, rh, a.batch, s, a.run);
+    const ShareRange sr = share_range(r16.units, a.splits, split);
+    const int u0 = sr.first, u1 = sr.end, mine = rows16_mine(u1 - u0, wave_k, WAVES_K);
 
     constexpr int FRONT = WS ? 8 : 0;                  // the buffers start 8 elements early (workspace): offsets stay non-negative
     const int ybase = y0 - 1 > 0 ? y0 - 1 : 0;         // first row of X there is
@@ -78,11 +76,10 @@ __device__ __forceinline__ void wgrad16_rows_group(const Wgrad16Args& a, int ind
     __amdgpu_buffer_rsrc_t xr, zr, mr;
     unsigned xend = 0;                                 // a caller's buffer: its end from the unit's first image on (bytes)
     auto enter = [&]() {
-        const int sp = quot(iu, SEG), nb = quot(2 * sp, G);
-        iq0 = (iu - sp * SEG) * RS; irows = (rh - iq0 < RS ? rh - iq0 : RS) + 2;
-        int g = 2 * sp - nb * G + hi, dn = 0;
-        if (g >= G) { g -= G; dn = 1; }
-        const bool on = i_left > 0 && 2 * sp + hi < strips;
+        const Rows16Unit u = rows16_unit(r16, rh, iu, hi);
+        const int nb = u.image, g = u.g, dn = u.dn;
+        iq0 = u.row; irows = u.items;
+        const bool on = i_left > 0 && 2 * u.pair + hi < r16.strips;
         x_on = on && x_there; z_on = on && z_there;
         ig = g;
         xo = xlane + dn * (int)a.in.ns + 8 * g;
@@ -145,10 +142,9 @@ __device__ __forceinline__ void wgrad16_rows_group(const Wgrad16Args& a, int ind
     uint32_t xm[4], zm[5];                             // elements of X, of the 10 deltas, that count
     v4u x0r, x1r;                                      // the two rows of X above
     auto arrive = [&]() {                              // ... in a new unit
-        const int sp = quot(cu, SEG), nb = quot(2 * sp, G);
-        cq0 = (cu - sp * SEG) * RS; crows = (rh - cq0 < RS ? rh - cq0 : RS) + 2;
-        int g = 2 * sp - nb * G + hi, dn = 0;
-        if (g >= G) { g -= G; dn = 1; }
+        const Rows16Unit u = rows16_unit(r16, rh, cu, hi);
+        const int g = u.g, dn = u.dn;
+        cq0 = u.row; crows = u.items;
         cz = zlane + dn * (int)a.din.ns + (POOL ? 4 : 8) * g; cm = mlane + dn * (int)a.mask.ns + 4 * g;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -220,7 +216,7 @@ __device__ __forceinline__ void wgrad16_rows_group(const Wgrad16Args& a, int ind
         for (int r = 0; r < RING; ++r) issue(ring[r]);
         // (the same number of items for all wavefronts: those behind one's last load and add zeros.  The barrier keeps them at the same
         // rows, whose lines they share)
-        const int turns = blocks_of(blocks_of(u1 - u0, WAVES_K) * (RS + 2), RING);
+        const int turns = blocks_of(rows16_items_most(u1 - u0, WAVES_K, r16.RS), RING);
         for (int t = 0; t < turns; ++t) {
 #pragma unroll
             for (int r = 0; r < RING; ++r) { __builtin_amdgcn_s_barrier(); consume(ring[r]); issue(ring[r]); }
@@ -258,37 +254,6 @@ __device__ __forceinline__ void wgrad16_rows_group(const Wgrad16Args& a, int ind
             }
         }
     }
-}
-
-// Items (a row of a pair of strips, 9 matrix instructions) of a share of a stack's strips cut into runs of `run` rows, of the wavefront with the most.
-inline long long rows16_items(int rw, int rh, int batch, int shares, int waves_k, int run)
-{
-    const int pairs = (batch * ((rw + 2 + 1 + 7) / 8) + 1) / 2, units = pairs * ((rh + run - 1) / run);
-    return (long long)(((units + shares - 1) / shares + waves_k - 1) / waves_k) * (run + 2);
-}
-// The run that takes the fewest: long runs read few rows of X twice, short ones spread few strips evenly over the shares.
-inline int rows16_run(int rw, int rh, int batch, int shares, int waves_k, bool pooled)
-{
-    int best = 0; long long least = 0;
-    for (int runs = 1; runs <= (rh + 3) / 4; ++runs) {
-        int run = (rh + runs - 1) / runs;
-        if (pooled) run = (run + 1) & ~1;              // (whole windows)
-        const long long n = rows16_items(rw, rh, batch, shares, waves_k, run);
-        if (!best || n < least) { best = run; least = n; }
-    }
-    return best;
-}
-
-// Whether that beats the chunks of wgrad16_group, 8 items' worth of matrix instructions each: items, chunks of a share, workgroups of the launch.
-// An odd number of strips a row puts the halves of every other wavefront in two images, whose lines they do not share: with the chip full, that costs what
-// the chunks' LDS does (back-propagation, chunks / here, us: 32 images in 8 x 8 stacks, 64 -> 128 at 152^2, rows of 19, 456 / 518, 256 -> 512 at 38^2, rows of 5, 568 / 643; 128 -> 96, 48
-// images in stacks of 14 x 14, 651 / 703, 128 -> 128, 24 images of 63 x 88 in 6 x 6, 0.8 times the items, 205 / 215; even numbers 0.83 to 1.02 times).  Launches that leave CUs idle lose only where the strips
-// cannot be dealt out evenly (64 -> 128, one image of 152^2 in 8 x 8 stacks, 42.0 / 44.7; others 0.54 to 1.02 times).
-inline bool rows16_pays(int rw, long long items, int chunks, long long workgroups)
-{
-    const int strips = (rw + 2 + 1 + 7) / 8;
-    const double limit = workgroups < 250 ? 1.3 : strips <= 5 && (strips & 1) ? 0.8 : 1.15;
-    return (double)items < limit * 8.0 * chunks || (workgroups < 250 && !(strips & 1));
 }
 
 // The workgroup's form of the gradient.

@@ -39,3 +39,7 @@ def test_quotients_by_reciprocals_are_exact():
 
 def test_large_launches_are_told_from_small_ones_before_they_are_cut():
     _build_and_run("small_launch_check")
+
+
+def test_direct_16_bit_gradients_multiply_every_pixel_once():
+    _build_and_run("wgrad16_walk_check")
