@@ -54,7 +54,8 @@ unsigned wgrad16_plan(Wgrad16Args& a, const ConvArgs& c, float* scratch, size_t&
     const int rw = largest_width(c), rh = largest_height(c), waves_k = waves_ci == 2 ? 1 : 2;
     const int chunks = wgrad16_chunks(rw, rh, c.batch, w16_patch_elems(waves_ci), 1).total;
     a.run = rows16_run(rw, rh, c.batch, a.splits, waves_k, c.pooled != 0);
-    if (!rows16_pays(rw, rows16_items(rw, rh, c.batch, a.splits, waves_k, a.run) * waves_k, (chunks + a.splits - 1) / a.splits, (long long)a.gx * a.stacks * a.splits)) a.run = 0;
+    if (!rows16_pays({rw, c.Cin, c.Cout, a.splits, (chunks + a.splits - 1) / a.splits, c.pooled != 0, rows16_items(rw, rh, c.batch, a.splits, waves_k, a.run) * waves_k,
+                      (long long)a.gx * a.stacks * a.splits, 2.0 * c.batch * c.Hc * c.Wc * (c.Cin + c.Cout)})) a.run = 0;
     lds = a.run ? (size_t)kRows16Lds : (size_t)2 * BCI * w16_row_bytes(waves_ci) + (size_t)kW16Groups * 64 * 20 + (size_t)kW16Groups * 4;
     return shares_order(a, chunks);
 }

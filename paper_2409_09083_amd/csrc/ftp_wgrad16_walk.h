@@ -61,16 +61,34 @@ inline int rows16_run(int rw, int rh, int batch, int shares, int waves_k, bool p
     return best;
 }
 
-// Whether that beats the chunks of wgrad16_group, 8 items' worth of matrix instructions each: items, chunks of a share, workgroups of the launch.
-// An odd number of strips a row puts the halves of every other wavefront in two images, whose lines they do not share: with the chip full, that costs what
-// the chunks' LDS does (back-propagation, chunks / here, us: 32 images in 8 x 8 stacks, 64 -> 128 at 152^2, rows of 19, 456 / 518, 256 -> 512 at 38^2, rows of 5, 568 / 643; 128 -> 96, 48
-// images in stacks of 14 x 14, 651 / 703, 128 -> 128, 24 images of 63 x 88 in 6 x 6, 0.8 times the items, 205 / 215; even numbers 0.83 to 1.02 times).  Launches that leave CUs idle lose only where the strips
-// cannot be dealt out evenly (64 -> 128, one image of 152^2 in 8 x 8 stacks, 42.0 / 44.7; others 0.54 to 1.02 times).
-inline bool rows16_pays(int rw, long long items, int chunks, long long workgroups)
+// Whether that beats the chunks of wgrad16_group, 8 items' worth of matrix instructions each: items, chunks of a share, workgroups of the launch, shares, bytes of
+// both maps.  What the items' count leaves out (back-propagation, chunks / here, us, of 348 layers timed in both forms; 0.917 times the chunks' time in
+// the mean by this rule, 0.910 by the better form of each):
+// - An odd number of strips a row puts the halves of every other wavefront in two images, whose lines they do not share: with the chip full, that costs what
+//   the chunks' LDS does (32 images in 8 x 8 stacks, 64 -> 128 at 152^2, rows of 19, 456 / 518, 256 -> 512 at 38^2, rows of 5, 568 / 643; 48 images in 3 x 2
+//   stacks of 94 x 8, 64 -> 64, 97 / 109).
+// - A pair of strips is a quarter of a line, and the next pair's turn comes a run of rows later: maps that the caches do not hold come from memory several
+//   times, which the chunks' whole rows do not, and the fewer products there are to a byte the sooner that is the bound (48 images of 64 x 212 in 4 x 4 stacks,
+//   64 -> 64, seven strips, 202 / 243; 64 x 112 in 4 x 3, 64 -> 128, 210 / 237; 128 -> 128, 32 x 64 in 2 x 1, a third of the items, 0.77 times).  Two strips
+//   or one lie in two lines at most; through a pool the lines are shorter (0.71 to 1.03 times).
+// - Launches that leave CUs idle lose only where the strips cannot be dealt out (64 -> 128, one image of 152^2 in 8 x 8 stacks, 42.0 / 44.7; one share
+//   of 4 rows a stack, 256 -> 256, 28 images of 12 x 24 in 3 x 3, 96 / 113, rows of 5 96 -> 128 1.17 times; others 0.46 to 1.04).
+struct Rows16Case { int rw, cin, cout, shares, chunks; bool pooled; long long items, workgroups; double bytes; };
+inline bool rows16_pays(const Rows16Case& c)
 {
-    const int strips = (rw + 2 + 1 + 7) / 8;
-    const double limit = workgroups < 250 ? 1.3 : strips <= 5 && (strips & 1) ? 0.8 : 1.15;
-    return (double)items < limit * 8.0 * chunks || (workgroups < 250 && !(strips & 1));
+    const int strips = (c.rw + 2 + 1 + 7) / 8;
+    const bool odd = (strips & 1) != 0, few = c.workgroups < 250;
+    const double q = (double)c.items / (8.0 * c.chunks);
+    if (few) {
+        if (c.pooled) return q < 1.3 || !odd;
+        if (strips == 1 && c.chunks >= 5) return q < 1.1;
+        return c.shares == 1 ? q < (odd ? 1.3 : 1.4) : q < 1.3 || !odd;
+    }
+    const double most = strips <= 5 && odd ? 0.8 : 1.15;
+    if (q >= most) return false;
+    if (c.pooled || strips <= 2) return true;
+    if (c.bytes < 7.0e7) return !odd || q < 0.92;
+    return q < (c.cin <= 32 ? 0.9 : 1.03 - 16.0 / c.cin - 16.0 / c.cout);
 }
 
 // ---- 1x1: a unit is 8 pixels of a row (G of them a row), a step two of them, one for each half; a wavefront takes every fourth step ----
