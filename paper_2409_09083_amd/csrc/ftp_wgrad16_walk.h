@@ -62,8 +62,8 @@ inline int rows16_run(int rw, int rh, int batch, int shares, int waves_k, bool p
 }
 
 // Whether that beats the chunks of wgrad16_group, 8 items' worth of matrix instructions each: items, chunks of a share, workgroups of the launch, shares, bytes of
-// both maps.  What the items' count leaves out (back-propagation, chunks / here, us, of 348 layers timed in both forms; 0.917 times the chunks' time in
-// the mean by this rule, 0.910 by the better form of each):
+// both maps.  What the items' count leaves out (back-propagation, chunks / here, us, of 568 layers timed in both forms; 0.912 times the chunks' time in
+// the mean by this rule, 1.06 at most; 0.905 by the better form of each):
 // - An odd number of strips a row puts the halves of every other wavefront in two images, whose lines they do not share: with the chip full, that costs what
 //   the chunks' LDS does (32 images in 8 x 8 stacks, 64 -> 128 at 152^2, rows of 19, 456 / 518, 256 -> 512 at 38^2, rows of 5, 568 / 643; 48 images in 3 x 2
 //   stacks of 94 x 8, 64 -> 64, 97 / 109).
@@ -88,7 +88,9 @@ inline bool rows16_pays(const Rows16Case& c)
     if (q >= most) return false;
     if (c.pooled || strips <= 2) return true;
     if (c.bytes < 7.0e7) return !odd || q < 0.92;
-    return q < (c.cin <= 32 ? 0.9 : 1.03 - 16.0 / c.cin - 16.0 / c.cout);
+    // (channels read to a block's products, which are 64 x 64 whatever is there)
+    const double blocks = (double)((c.cin + 63) / 64) * ((c.cout + 63) / 64) * 4096.0;
+    return q < (c.cin <= 32 ? 0.9 : 1.0 - 16.0 * (c.cin + c.cout) / blocks);
 }
 
 // ---- 1x1: a unit is 8 pixels of a row (G of them a row), a step two of them, one for each half; a wavefront takes every fourth step ----
