@@ -1353,14 +1353,25 @@ ThinStream stream_geom(const ConvArgs& c)
 // 39 / 42; 64 images of 20^2 in 2 x 3 stacks, 384, 3 -> 64 56 / 63; pooled 1 -> 64, 32 of 52^2 in 5 x 5 stacks, 800, 101 / 77).
 constexpr long long kBackThinMost = 4096, kBackThinLong = 640;
 
+// fp32 1x1 layers of 5 to 8 input and few output channels: half a block of the wider kernel is empty, and rows of 65 to 104 pixels (33 to 44) leave a third of
+// its chunks of 64 so, too, where a chunk here takes a row (several) whole.  Large maps only: of others the launches and sums are most.  Back-propagation, here /
+// there, us: 5 -> 16, 11 images of 201 x 301 in 4 x 4 stacks, 89 / 107, 6 -> 24, 25 of 297 x 269 in 4 x 3, 275 / 306, 8 -> 12, rows of 88, 0.85 times; 0.945 times in the mean of
+// 70 such layers, 1.15 at most; wider rows 1.0 to 1.3 times, 36 output channels 1.06 to 1.35, 8 input and 20 to 32 output channels 1.05.
+static bool narrow_1x1_stays(const ConvArgs& c)
+{
+    if (c.bf16 || c.S != 1 || c.pooled || c.Cin > 8 || c.Cout > (c.Cin < 8 ? 32 : 16) || (double)c.batch * c.Hc * c.Wc < 4.5e5) return false;
+    const int w = largest_width(c);
+    return (w > 64 && w <= 104) || (c.Cin < 7 && w > 32 && w <= 44);
+}
+
 // c.rect must hold the owned rectangles.
 bool thin_wgrad_eligible(const ConvArgs& c)
 {
     if (!(c.Cin * c.K * c.K <= 32 || (c.Cin <= 4 && c.Cin * c.K * c.K <= 160))) return false;
     // (1x1 layers of 5 to 32 input channels with something to multiply: the kernels of the wider ones, whose pixels are not staged element by element (back-propagation,
-    // here / there, us: 16 bits 32 -> 64, 4 images of 52 x 78, 40 / 17, 16 -> 256, 8 of 108^2, 128 / 72; fp32 32 -> 64, 4 of 190^2, 105 / 58, 16 -> 64, 8 of 194^2 147 / 106, 32 -> 32, 32 of
-    // 108^2, 80 / 83; 59 shapes 0.78 times in the mean, of less than 4e6 products alike either way)
-    if (c.K == 1 && c.Cin > 4 && (double)c.batch * c.Hc * c.Wc * c.Cin * c.Cout >= 4.0e6 && mfma_wgrad_eligible(c)) return false;
+    // here / there, us: 16 bits 32 -> 64, 4 images of 52 x 78, 40 / 17, 16 -> 256, 8 of 108^2, 128 / 72; fp32 32 -> 64, 4 of 190^2, 111 / 58, 16 -> 64, 8 of 194^2 149 / 99, 32 -> 32, 32 of
+    // 108^2, 154 / 91; of less than 4e6 products alike either way)
+    if (c.K == 1 && c.Cin > 4 && (double)c.batch * c.Hc * c.Wc * c.Cin * c.Cout >= 4.0e6 && mfma_wgrad_eligible(c) && !narrow_1x1_stays(c)) return false;
     if (c.pooled && (c.S != 1 || c.K > 3)) return false;
     if (c.pooled) {
         // owned rectangles of a pooled convolution consist of whole windows; anything else goes to the generic kernel

@@ -94,3 +94,30 @@ def test_bias_gradients_against_64_bits(layers, batch, h, w, grid, dtype):
     # (fp32 sums: a rounding of 2^-24 of the magnitudes per addition of a thread, 64 at most here, of the tree and the last sum)
     assert bool(((got - ref).abs() <= 100 * 2.0 ** -24 * mag).all())
     s.close()
+
+
+@pytest.mark.parametrize("cin,cout,batch,h,w,grid,kernel", [
+    (6, 24, 24, 140, 138, (2, 2), "k_wgrad_mfma_thin"), (6, 24, 23, 140, 138, (2, 2), "k_wgrad_mfma"),          # as many pixels and fewer
+    (6, 24, 22, 100, 208, (1, 2), "k_wgrad_mfma_thin"), (6, 24, 22, 100, 210, (1, 2), "k_wgrad_mfma"),          # the widest rows
+    (7, 32, 8, 200, 288, (3, 3), "k_wgrad_mfma_thin"), (7, 33, 8, 200, 288, (3, 3), "k_wgrad_mfma"),
+    (8, 16, 24, 140, 138, (2, 2), "k_wgrad_mfma_thin"), (8, 17, 24, 140, 138, (2, 2), "k_wgrad_mfma"),
+    (5, 16, 16, 170, 170, (4, 4), "k_wgrad_mfma_thin"), (7, 16, 16, 170, 170, (4, 4), "k_wgrad_mfma"),          # rows of 42 and 43
+])
+def test_narrow_1x1_layers(cin, cout, batch, h, w, grid, kernel):
+    """The kernel that each side of the rule's lines takes; whole numbers, so that the sums are exact in any order."""
+    import torch
+    from paper_2409_09083_amd import binding as B
+    from paper_2409_09083_amd.harness import Session
+    g = torch.Generator(device="cuda").manual_seed(cin)
+    s = Session((conv(cin, cout, 1, slope=1.0),), batch, cin, h, w, grid, (1,), "f32")
+    s.x.copy_(torch.randint(-4, 5, s.x.shape, generator=g, device="cuda"))
+    s.dy.copy_(torch.randint(-2, 3, s.dy.shape, generator=g, device="cuda"))
+    s.weights = [torch.randn((cout, cin, 1, 1), generator=g, device="cuda")]
+    B.ftp_profile(s.plan, 1)
+    s.step()
+    torch.cuda.synchronize()
+    assert [r["kernel"].split("<")[0] for r in B.ftp_profile_read(s.plan) if r["pass"] == "wgrad"] == [kernel]
+    got = s.wgrad.double().reshape(cout, cin)
+    x, dy = s.x.double().transpose(0, 1).reshape(cin, -1), s.dy.double().transpose(0, 1).reshape(cout, -1)
+    s.close()
+    assert 8 * batch * h * w < 2 ** 24 and torch.equal(got, dy @ x.T)
