@@ -47,7 +47,7 @@ k_conv_fwd_direct(View in, View out, View mask, View osign, RectTab rt, RectTab 
     const int rw = rt.x1[tj] - rt.x0[tj] + 1, rh = rt.y1[ti] - rt.y0[ti] + 1;
     const int pid = blockIdx.x * blockDim.x + threadIdx.x;
     if (pid >= rw * rh) return;
-    const int py = quot_lane(pid, rw), oy = rt.y0[ti] + py, ox = rt.x0[tj] + pid - py * rw;
+    const int py = quot_rows(pid, rw), oy = rt.y0[ti] + py, ox = rt.x0[tj] + pid - py * rw;
     const int co0 = blockIdx.y * COB;
     constexpr int NP = POOL ? 2 : 1, P = K / 2, R = (NP - 1) * S + K;
     float acc[COB][NP * NP];
@@ -132,7 +132,7 @@ k_conv_bwd_data_direct(View din, View mask, View dout, View isign, int scale_out
     } else {
         const int pid = blockIdx.x * blockDim.x + threadIdx.x;
         if (pid >= rw * rh) return;
-        ry = quot_lane(pid, rw); rx = pid - ry * rw;
+        ry = quot_rows(pid, rw); rx = pid - ry * rw;
     }
     const int iy = rt.y0[ti] + ry, ix = rt.x0[tj] + rx;
     const int ci0 = blockIdx.y * CIB;
@@ -222,7 +222,7 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
 #pragma unroll
     for (int t = 0; t <= KK; ++t) acc[t] = 0.0f;
     for (int it = threadIdx.x; it < items; it += 256) {
-        const int n = quot_lane(it, px), r = it - n * px, ry = quot_lane(r, rw);
+        const int n = quot_lane(it, px), r = it - n * px, ry = quot_rows(r, rw);
         const int qy = own.y0[ti] + ry, qx = own.x0[tj] + r - ry * rw;
         const float dz = delta_z<T, POOL>(din, mask, stack, ti, tj, n, co, qy, qx, Hc >> 1, Wc >> 1);
         acc[KK] += dz;
@@ -286,7 +286,7 @@ __device__ __forceinline__ void bias_block(const BiasArgs& a, int co, int stack)
 #pragma unroll
             for (int u = 0; u < U; ++u) {              // (beyond the last one: the last one again, not added)
                 const int it = it0 + u * kBiasThreads < items ? it0 + u * kBiasThreads : items - 1;
-                const int n = quot_lane(it, px), r = it - n * px, y = quot_lane(r, rw);
+                const int n = quot_lane(it, px), r = it - n * px, y = quot_rows(r, rw);
                 d[u] = ld(base + (long long)(n0 + n) * din.ns + (long long)y * din.pitch + (r - y * rw));
             }
 #pragma unroll
@@ -414,7 +414,7 @@ k_pool_fwd(View in, View out, View mask, RectTab rt, RectTab own, int C, int M, 
     const int rw = rt.x1[tj] - rt.x0[tj] + 1, rh = rt.y1[ti] - rt.y0[ti] + 1;
     const int pid = blockIdx.x * blockDim.x + threadIdx.x;
     if (pid >= rw * rh) return;
-    const int py = quot_lane(pid, rw), oy = rt.y0[ti] + py, ox = rt.x0[tj] + pid - py * rw;
+    const int py = quot_rows(pid, rw), oy = rt.y0[ti] + py, ox = rt.x0[tj] + pid - py * rw;
     const int c0 = blockIdx.y * CH;
     struct __attribute__((packed, aligned(sizeof(T)))) Pair { T e[2]; };
     const T* const src = at<T>(in, stack, ti, tj, n, c0, 2 * oy, 2 * ox);
@@ -466,7 +466,7 @@ k_pool_bwd(View din, View mask, View dout, View isign, int scale_out, float in_s
     const int wx0 = x0 >> 1, wy0 = y0 >> 1, ww = (x1 >> 1) - wx0 + 1, wh = (y1 >> 1) - wy0 + 1;
     const int pid = blockIdx.x * blockDim.x + threadIdx.x;
     if (pid >= ww * wh) return;
-    const int py = quot_lane(pid, ww), wy = wy0 + py, wx = wx0 + pid - py * ww;
+    const int py = quot_rows(pid, ww), wy = wy0 + py, wx = wx0 + pid - py * ww;
     const int c0 = blockIdx.y * CH;
     const bool has = wy < Ho && wx < Wo;
     // the loads are unconditional: a window of the dropped row / column reads the rectangle's first window instead,

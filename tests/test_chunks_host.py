@@ -43,3 +43,7 @@ def test_large_launches_are_told_from_small_ones_before_they_are_cut():
 
 def test_direct_16_bit_gradients_multiply_every_pixel_once():
     _build_and_run("wgrad16_walk_check")
+
+
+def test_rows_of_narrow_maps_of_any_height_are_exact():
+    _build_and_run("quot_rows_check")
