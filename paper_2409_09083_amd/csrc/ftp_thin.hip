@@ -1353,14 +1353,20 @@ ThinStream stream_geom(const ConvArgs& c)
 // 39 / 42; 64 images of 20^2 in 2 x 3 stacks, 384, 3 -> 64 56 / 63; pooled 1 -> 64, 32 of 52^2 in 5 x 5 stacks, 800, 101 / 77).
 constexpr long long kBackThinMost = 4096, kBackThinLong = 640;
 
-// fp32 1x1 layers of 5 to 8 input and few output channels: half a block of the wider kernel is empty, and rows of 65 to 104 pixels (33 to 44) leave a third of
-// its chunks of 64 so, too, where a chunk here takes a row (several) whole.  Large maps only: of others the launches and sums are most.  Back-propagation, here /
-// there, us: 5 -> 16, 11 images of 201 x 301 in 4 x 4 stacks, 89 / 107, 6 -> 24, 25 of 297 x 269 in 4 x 3, 275 / 306, 8 -> 12, rows of 88, 0.85 times; 0.945 times in the mean of
-// 70 such layers, 1.15 at most; wider rows 1.0 to 1.3 times, 36 output channels 1.06 to 1.35, 8 input and 20 to 32 output channels 1.05.
+// 1x1 layers of 5 to 12 input and few output channels: half a block of the wider kernel is empty.  Large maps only: of others the launches and sums are most.
+// Through a pool the deltas are routed a pixel at a time there, a window at a time here, where rows are not too short (back-propagation, here / there: fp32 8 -> 16, 974
+// thousand pixels in rows of 70, 0.69 times, 6 -> 12, rows of 34, 0.71, 5 -> 32, rows of 54, 0.84, 10 -> 24, rows of 29, 1.12; 0.87 in the mean of 30 such layers, rows of 10 to 24 1.2 to
+// 2.4; 16 bits 5 -> 16, rows of 36, 0.73, 12 -> 16, rows of 66, 0.86, 12 -> 8, rows of 60, 1.13; 0.91 in the mean of 21, shorter rows 1.2, fewer pixels 1.05; 14 to 16 channels 1.1 to 1.3).
+// Without one, fp32 of 5 to 8 channels: rows of 65 to 104 pixels (33 to 44) leave a third of the wider kernel's chunks of 64 empty, where a chunk here takes a row (several) whole (us:
+// 5 -> 16, 11 images of 201 x 301 in 4 x 4 stacks, 89 / 107, 6 -> 24, 25 of 297 x 269 in 4 x 3, 275 / 306, 8 -> 12, rows of 88, 0.85 times; 0.945 times in the mean of
+// 70 such layers, 1.15 at most; wider rows 1.0 to 1.3 times, 36 output channels 1.06 to 1.35, 8 input and 20 to 32 output channels 1.05).
 static bool narrow_1x1_stays(const ConvArgs& c)
 {
-    if (c.bf16 || c.S != 1 || c.pooled || c.Cin > 8 || c.Cout > (c.Cin < 8 ? 32 : 16) || (double)c.batch * c.Hc * c.Wc < 4.5e5) return false;
+    if (c.S != 1 || c.Cin > 12 || c.Cout > 32) return false;
+    const double pixels = (double)c.batch * c.Hc * c.Wc;
     const int w = largest_width(c);
+    if (c.pooled) return !c.bf16 ? w >= 25 && pixels >= 2.4e5 : c.Cin <= 8 ? w >= 33 && pixels >= 3.0e5 : w >= 40 && pixels >= 4.7e5;
+    if (c.bf16 || c.Cin > 8 || (c.Cin == 8 && c.Cout > 16) || pixels < 4.5e5) return false;
     return (w > 64 && w <= 104) || (c.Cin < 7 && w > 32 && w <= 44);
 }
 

@@ -105,19 +105,50 @@ def test_bias_gradients_against_64_bits(layers, batch, h, w, grid, dtype):
 ])
 def test_narrow_1x1_layers(cin, cout, batch, h, w, grid, kernel):
     """The kernel that each side of the rule's lines takes; whole numbers, so that the sums are exact in any order."""
+    _narrow((conv(cin, cout, 1, slope=1.0),), batch, h, w, grid, "f32", kernel)
+
+
+@pytest.mark.parametrize("dtype,cin,cout,batch,h,w,grid,kernel", [
+    ("f32", 5, 32, 4, 300, 208, (3, 8), "k_wgrad_mfma_thin"), ("f32", 5, 33, 4, 300, 208, (3, 8), "k_wgrad_mfma"),             # rows of 26
+    ("f32", 12, 20, 4, 250, 240, (3, 10), "k_wgrad_mfma"), ("f32", 12, 20, 4, 250, 244, (3, 9), "k_wgrad_mfma_thin"),            # rows of 24, and 26 and 28
+    ("f32", 13, 20, 4, 250, 244, (3, 9), "k_wgrad_mfma"), ("f32", 12, 20, 3, 250, 244, (3, 9), "k_wgrad_mfma"),
+    ("bf16", 6, 28, 6, 248, 204, (2, 6), "k_wgrad_mfma_thin"), ("bf16", 6, 28, 6, 248, 204, (2, 7), "k_wgrad_mfma"),           # rows of 34, and 28 and 30
+    ("bf16", 8, 20, 6, 248, 204, (2, 4), "k_wgrad_mfma_thin"), ("bf16", 8, 20, 5, 248, 204, (2, 4), "k_wgrad_mfma"),
+    ("bf16", 9, 20, 8, 248, 240, (2, 6), "k_wgrad_mfma_thin"), ("bf16", 9, 20, 8, 248, 240, (2, 7), "k_wgrad_mfma"),           # rows of 40, and 34 and 36
+    ("bf16", 12, 32, 8, 300, 200, (1, 2), "k_wgrad_mfma_thin"), ("bf16", 12, 32, 7, 300, 200, (1, 2), "k_wgrad_mfma"),
+])
+def test_narrow_1x1_layers_with_a_pool(dtype, cin, cout, batch, h, w, grid, kernel):
+    """The filter hands channels of x on, and the four pixels of a window differ: the winners are those of x."""
+    _narrow((conv(cin, cout, 1, slope=1.0), pool(cout)), batch, h, w, grid, dtype, kernel)
+
+
+def _narrow(layers, batch, h, w, grid, dtype, kernel):
     import torch
     from paper_2409_09083_amd import binding as B
     from paper_2409_09083_amd.harness import Session
+    cin, cout, pooled = layers[0].cin, layers[0].cout, len(layers) > 1
     g = torch.Generator(device="cuda").manual_seed(cin)
-    s = Session((conv(cin, cout, 1, slope=1.0),), batch, cin, h, w, grid, (1,), "f32")
-    s.x.copy_(torch.randint(-4, 5, s.x.shape, generator=g, device="cuda"))
+    s = Session(layers, batch, cin, h, w, grid, (len(layers),), dtype)
+    one = [[c % cin] for c in range(cout)]
+    if pooled:
+        place = torch.rand((batch, cin, h // 2, w // 2, 4), generator=g, device="cuda").argsort(-1)
+        place = place.reshape(batch, cin, h // 2, w // 2, 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(s.x.shape)
+        s.x.copy_(4 * torch.randint(-2, 2, s.x.shape, generator=g, device="cuda") + place)          # (-8 .. 7)
+    else:
+        s.x.copy_(torch.randint(-4, 5, s.x.shape, generator=g, device="cuda"))
     s.dy.copy_(torch.randint(-2, 3, s.dy.shape, generator=g, device="cuda"))
-    s.weights = [torch.randn((cout, cin, 1, 1), generator=g, device="cuda")]
+    wt = torch.zeros(cout, cin, device="cuda").scatter_(1, torch.tensor(one, device="cuda"), 1.0).view(cout, cin, 1, 1).to(s.tdtype)
+    s.weights = [wt] + [None] * pooled
     B.ftp_profile(s.plan, 1)
     s.step()
     torch.cuda.synchronize()
     assert [r["kernel"].split("<")[0] for r in B.ftp_profile_read(s.plan) if r["pass"] == "wgrad"] == [kernel]
-    got = s.wgrad.double().reshape(cout, cin)
-    x, dy = s.x.double().transpose(0, 1).reshape(cin, -1), s.dy.double().transpose(0, 1).reshape(cout, -1)
+    got, x, dz = s.wgrad.double().reshape(cout, cin), s.x.double(), s.dy.double()
     s.close()
-    assert 8 * batch * h * w < 2 ** 24 and torch.equal(got, dy @ x.T)
+    if pooled:
+        z = x[:, [c[0] for c in one]].reshape(batch, cout, h // 2, 2, w // 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(batch, cout, h // 2, w // 2, 4)
+        dz = torch.zeros_like(z).scatter_(-1, z.argmax(-1, keepdim=True), dz[..., None])
+        dz = dz.reshape(batch, cout, h // 2, w // 2, 2, 2).permute(0, 1, 2, 4, 3, 5).reshape(batch, cout, h, w)
+    assert 8 * batch * h * w < 2 ** 24
+    x, dz = x.transpose(0, 1).reshape(cin, -1), dz.transpose(0, 1).reshape(cout, -1)
+    assert torch.equal(got, dz @ x.T)
