@@ -96,7 +96,7 @@ struct Plan {
 // with these against the compiler's: one image, 16 -> 32 channels at 208^2 with a pool, 15.5 -> 13.8 us, 24 -> 40 of 77 x 53 13.6 -> 11.3; 16-bit 1x1, 32 images,
 // 512 -> 256 at 38^2, 74 -> 72 (the filter gradients' lists of chunks keep the compiler's: k_wgrad_mfma took 12 registers more and 5 % longer).
 // quot: of values that are the same in all lanes; what the first product lacked comes from its rest.  quot_rows: the same of any values (rows of a rectangle, which
-// may be any number).  quot_lane: for quotients below 2^21, a below 2^30.  quot_small: a < 2^21, as positions in LDS are (a + 0.5 is at least 0.5 / b away from where its quotient's whole part changes).
+// may be any number).  quot_lane: for quotients below 2^21 (kLaneRows).  quot_small: a < 2^21, as positions in LDS are (a + 0.5 is at least 0.5 / b away from where its quotient's whole part changes).
 FTP_HD inline int all_lanes(int v)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -124,6 +124,7 @@ FTP_HD inline int quot_lane_rcp(int a, int b, float rcp)
     const int q = (int)((float)a * rcp), r = a - q * b;
     return q + (r >= b ? 1 : r < 0 ? -1 : 0);
 }
+constexpr int kLaneRows = 1 << 21;
 FTP_HD inline int quot_small_rcp(int a, float rcp) { return (int)(((float)a + 0.5f) * rcp); }
 #if defined(__HIP_DEVICE_COMPILE__)
 FTP_HD inline int quot(int a, int b) { return quot_rcp(a, b, __builtin_amdgcn_rcpf((float)b)); }
