@@ -48,6 +48,10 @@ constexpr int bf_waves(int K, int blocks) { return blocks == 2 || (blocks == 4 &
 
 constexpr int kBfLds = 2048;                          // units of 16 bytes of LDS
 
+// Short divisions in a workgroup's first lines (ftp_plan.h), and arguments fetched early.  Not for the widest 3x3 workgroups without a pool that read a caller's odd rows: they
+// spill in their main loop, whichever the registers happen to be, and behind the short ones stored in it twice as often.
+constexpr bool bf_reciprocals(int K, int WAVES_M, int NT, bool pool_out, int in) { return !(in == BF_NARROW && K == 3 && WAVES_M == 1 && NT == 4 && !pool_out); }
+
 // Workgroup `index` of the launch; LDS::at(): kBfLds units of LDS, [8 channels][position (swizzled)].  (A type and no pointer: captured by the
 // lambdas below, a pointer is not seen to be the start of LDS in time, and 3x3 layers lose 2 to 5 %: 256 -> 256, 4 images of 52^2, 36.8 -> 38.1 us.)
 template <int K, int WAVES_M, int MT, int NT, bool POOL_OUT, bool DELTA_IN, int IN, class LDS>
@@ -55,6 +59,7 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
 {
     constexpr int WAVES_N = 4 / WAVES_M, BN = 32 * NT * WAVES_N, BM = 32 * MT * WAVES_M;
     constexpr int KK = K * K, P = K / 2, S = POOL_OUT ? 2 : 1;
+    constexpr bool RCP = bf_reciprocals(K, WAVES_M, NT, POOL_OUT, IN);
     constexpr int XMAX = conv_bf_positions(K, BN), OCT = conv_bf_octets(K, BN);
     constexpr int UPO = XMAX / 8;                      // units (8 positions x 8 channels) per group of 8 channels
     static_assert(OCT * UPO == 256, "one unit a thread");
@@ -71,10 +76,10 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
     const int wave_m = wave % WAVES_M, wave_n = wave / WAVES_M;
     const int hi = lane >> 5, l32 = lane & 31;
     int vgroup, vtile;
-    if (!tile_order(a, index, vgroup, vtile)) return;
-    const int stack = quot(vgroup, a.mblocks), ti = quot(stack, a.M), tj = stack - ti * a.M;
+    if (!tile_order<RCP>(a, index, vgroup, vtile)) return;
+    const int stack = quot<RCP>(vgroup, a.mblocks), ti = quot<RCP>(stack, a.M), tj = stack - ti * a.M;
     const int x0 = a.rect.x0[tj], x1 = a.rect.x1[tj], y0 = a.rect.y0[ti], y1 = a.rect.y1[ti];
-    const TileGeom g = tile_geom<S, P, 8>(a, x0, x1, y0, y1, vtile);
+    const TileGeom g = tile_geom<S, P, 8, RCP>(a, x0, x1, y0, y1, vtile);
     if (g.empty) return;
     const int m0 = (vgroup - stack * a.mblocks) * BM;
     const int PW = g.PW, npos = g.npos;
@@ -86,7 +91,7 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int q = (wave_n * NT + t) * 32 + l32;
-        const TilePix tp = tile_pix<S, P>(g, POOL_OUT ? (q >> 2) : q, x1);
+        const TilePix tp = tile_pix<S, P, RCP>(g, POOL_OUT ? (q >> 2) : q, x1);
         const int pos = POOL_OUT ? (q & 3) : 0;
         baseB[t] = tp.valid ? (tp.prow + (pos >> 1)) * PW + tp.xl * S + (pos & 1) + sh : 0;
     }
@@ -103,11 +108,11 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
     unsigned xoff = 0, moff = 0, xin = 0;              // byte offsets of the first element (POOL: window) and its code, channel 8 * u_oct; elements inside the map
     uint32_t row2 = 0;                                 // POOL: 2 for odd rows
     if (u_pos < npos) {
-        const int pr = quot_small(u_pos, PW), c = u_pos - pr * PW;
+        const int pr = quot_small<RCP>(u_pos, PW), c = u_pos - pr * PW;
         int k = 0, lr = pr, ybase = g.y_a * S;
         if (pr >= g.first_cnt) {
             const int t = pr - g.first_cnt;
-            k = 1 + quot_small(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
+            k = 1 + quot_small<RCP>(t, g.per_cnt); lr = t - (k - 1) * g.per_cnt; ybase = 0;
         }
         const int gy = y0 * S + ybase + lr - P, gx = g.ox0 * S - P - sh + c;
         const int sy = IN == BF_POOL ? gy >> 1 : gy, sx = IN == BF_POOL ? gx >> 1 : gx;
@@ -349,7 +354,7 @@ __device__ __forceinline__ void conv_bf16_group(const MfmaConvArgs& a, int index
             else if (gr + r < ng) group(gr + r, r, gr + r + 1 == ng);
         }
     }
-    conv_epilogue<bf16_t, K, S, WAVES_M, MT, POOL_OUT, DELTA_IN>(a, g, acc, (float*)LDS::at(), m0, x0, x1, y0, stack, ti, tj);
+    conv_epilogue<bf16_t, K, S, WAVES_M, MT, POOL_OUT, DELTA_IN, RCP>(a, g, acc, (float*)LDS::at(), m0, x0, x1, y0, stack, ti, tj);
 }
 
 struct BfShape { int WM, MT, NT; };                     // wavefronts along the channels, blocks of 32 channels / pixels of a wavefront

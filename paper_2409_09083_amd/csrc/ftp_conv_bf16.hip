@@ -11,7 +11,7 @@ template <int K, int WAVES_M, int MT, int NT, bool POOL_OUT, bool DELTA_IN, int 
 __global__ void __launch_bounds__(256, bf_waves(K, NT * MT))
 k_conv_bf16(MfmaConvArgs a)
 {
-    touch_args<0, sizeof(MfmaConvArgs)>((int)blockIdx.x);
+    if (bf_reciprocals(K, WAVES_M, NT, POOL_OUT, IN)) touch_args<0, sizeof(MfmaConvArgs)>((int)blockIdx.x);
     conv_bf16_group<K, WAVES_M, MT, NT, POOL_OUT, DELTA_IN, IN, ConvLds>(a, (int)blockIdx.x);
 }
 

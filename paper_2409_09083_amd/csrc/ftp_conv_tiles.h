@@ -94,7 +94,7 @@ FTP_HD inline TilePix conv_tile_pix(const TileGeom& g, int wq, int x1, int S, in
     const int fr = quot_small<RCP>(lin, g.TC);
     t.xl = lin - fr * g.TC;
     const int R = g.R0 + fr;
-    const int past = quot_lane<RCP>(g.y_a + fr, g.rh);           // images behind the tile's first
+    const int past = RCP ? quot_lane(g.y_a + fr, g.rh) : R / g.rh - g.n_a;           // images behind the tile's first
     t.n = g.n_a + past;
     t.y = R - t.n * g.rh;
     t.prow = S * fr + 2 * P * past;
