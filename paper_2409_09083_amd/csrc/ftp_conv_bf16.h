@@ -49,7 +49,8 @@ constexpr int bf_waves(int K, int blocks) { return blocks == 2 || (blocks == 4 &
 constexpr int kBfLds = 2048;                          // units of 16 bytes of LDS
 
 // Short divisions in a workgroup's first lines (ftp_plan.h), and arguments fetched early.  Not for the widest 3x3 workgroups without a pool that read a caller's odd rows: they
-// spill in their main loop, whichever the registers happen to be, and behind the short ones stored in it twice as often.
+// spill in their main loop, whichever the registers happen to be, and behind the short ones stored in it twice as often (256 -> 64, 64 images of 285 x 33, 338 -> 312 us,
+// 64 -> 64, 32 of 113 x 91 in 4 x 4 stacks, 97 -> 92).
 constexpr bool bf_reciprocals(int K, int WAVES_M, int NT, bool pool_out, int in) { return !(in == BF_NARROW && K == 3 && WAVES_M == 1 && NT == 4 && !pool_out); }
 
 // Workgroup `index` of the launch; LDS::at(): kBfLds units of LDS, [8 channels][position (swizzled)].  (A type and no pointer: captured by the

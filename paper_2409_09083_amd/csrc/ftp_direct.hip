@@ -222,20 +222,24 @@ k_wgrad_direct(View xin, View din, View mask, RectTab own, float* __restrict__ p
     float acc[KK + 1];
 #pragma unroll
     for (int t = 0; t <= KK; ++t) acc[t] = 0.0f;
-    for (int it = threadIdx.x; it < items; it += 256) {
-        const int n = quot_lane(it, px), r = it - n * px, ry = rh < kLaneRows ? quot_lane(r, rw) : quot_rows(r, rw);
-        const int qy = own.y0[ti] + ry, qx = own.x0[tj] + r - ry * rw;
-        const float dz = delta_z<T, POOL>(din, mask, stack, ti, tj, n, co, qy, qx, Hc >> 1, Wc >> 1);
-        acc[KK] += dz;
+    // (two loops: the choice inside one costs a tenth - 40 -> 8 in 1x1 at stride 2, 39 images of 48 x 212, 63 -> 77 us)
+    auto walk = [&](auto tall) {
+        for (int it = threadIdx.x; it < items; it += 256) {
+            const int n = quot_lane(it, px), r = it - n * px, ry = tall.value ? quot_rows(r, rw) : quot_lane(r, rw);
+            const int qy = own.y0[ti] + ry, qx = own.x0[tj] + r - ry * rw;
+            const float dz = delta_z<T, POOL>(din, mask, stack, ti, tj, n, co, qy, qx, Hc >> 1, Wc >> 1);
+            acc[KK] += dz;
 #pragma unroll
-        for (int ky = 0; ky < K; ++ky)
+            for (int ky = 0; ky < K; ++ky)
 #pragma unroll
-            for (int kx = 0; kx < K; ++kx) {
-                const int y = qy * S - P + ky, x = qx * S - P + kx;
-                if (y >= 0 && y < Hi && x >= 0 && x < Wi)
-                    acc[ky * K + kx] = fmaf(dz, ld(at<T>(xin, stack, ti, tj, n, ci, y, x)), acc[ky * K + kx]);
-            }
-    }
+                for (int kx = 0; kx < K; ++kx) {
+                    const int y = qy * S - P + ky, x = qx * S - P + kx;
+                    if (y >= 0 && y < Hi && x >= 0 && x < Wi)
+                        acc[ky * K + kx] = fmaf(dz, ld(at<T>(xin, stack, ti, tj, n, ci, y, x)), acc[ky * K + kx]);
+                }
+        }
+    };
+    if (rh < kLaneRows) walk(std::false_type()); else walk(std::true_type());
     __shared__ float red[4][KK + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
