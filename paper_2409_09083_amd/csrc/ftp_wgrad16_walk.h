@@ -62,15 +62,16 @@ inline int rows16_run(int rw, int rh, int batch, int shares, int waves_k, bool p
 }
 
 // Whether that beats the chunks of wgrad16_group, 8 items' worth of matrix instructions each: items, chunks of a share, workgroups of the launch, shares, bytes of
-// both maps.  What the items' count leaves out (back-propagation, chunks / here, us, of 568 layers timed in both forms; 0.912 times the chunks' time in
-// the mean by this rule, 1.06 at most; 0.905 by the better form of each):
+// both maps.  What the items' count leaves out (back-propagation, chunks / here, us; of 1540 layers whose gradients were timed in both forms, half of them not looked
+// at before, 0.861 times the chunks' time in the mean by this rule, 16 more than 1.1 times, one 1.45; 0.837 by the better form of each):
 // - An odd number of strips a row puts the halves of every other wavefront in two images, whose lines they do not share: with the chip full, that costs what
 //   the chunks' LDS does (32 images in 8 x 8 stacks, 64 -> 128 at 152^2, rows of 19, 456 / 518, 256 -> 512 at 38^2, rows of 5, 568 / 643; 48 images in 3 x 2
 //   stacks of 94 x 8, 64 -> 64, 97 / 109).
 // - A pair of strips is a quarter of a line, and the next pair's turn comes a run of rows later: maps that the caches do not hold come from memory several
 //   times, which the chunks' whole rows do not, and the fewer products there are to a byte the sooner that is the bound (48 images of 64 x 212 in 4 x 4 stacks,
-//   64 -> 64, seven strips, 202 / 243; 64 x 112 in 4 x 3, 64 -> 128, 210 / 237; 128 -> 128, 32 x 64 in 2 x 1, a third of the items, 0.77 times).  Two strips
-//   or one lie in two lines at most; through a pool the lines are shorter (0.71 to 1.03 times).
+//   64 -> 64, seven strips, 202 / 243; 64 x 112 in 4 x 3, 64 -> 128, 210 / 237; 128 -> 128, 32 x 64 in 2 x 1, a third of the items, 0.77 times; gradients alone: 32 -> 64,
+//   26 images of 304^2 in 4 x 7 stacks, 461 MB, 238 / 361, 96 -> 64, 16 in 4 x 6, 379 / 673; 16 -> 32, 14 of 294 x 304 in 3 x 6, 120 MB, 113 / 79, 128 -> 16, 14 of 304 x 86 in
+//   6 x 2, 114 / 84).  Two strips or one lie in two lines at most; through a pool the lines are shorter (0.7 to 1.03 times; wide blocks in odd strips 0.98 to 1.42).
 // - Launches that leave CUs idle lose only where the strips cannot be dealt out (64 -> 128, one image of 152^2 in 8 x 8 stacks, 42.0 / 44.7; one share
 //   of 4 rows a stack, 256 -> 256, 28 images of 12 x 24 in 3 x 3, 96 / 113, rows of 5 96 -> 128 1.17 times; others 0.46 to 1.04).
 struct Rows16Case { int rw, cin, cout, shares, chunks; bool pooled; long long items, workgroups; double bytes; };
@@ -86,11 +87,16 @@ inline bool rows16_pays(const Rows16Case& c)
     }
     const double most = strips <= 5 && odd ? 0.8 : 1.15;
     if (q >= most) return false;
-    if (c.pooled || strips <= 2) return true;
+    if (strips <= 2) return true;
+    if (c.pooled) return !(odd && strips > 5 && q >= 0.95 && c.bytes >= 9.0e7 && c.cin > 32 && c.cout > 32);
     if (c.bytes < 7.0e7) return !odd || q < 0.92;
+    // (few output channels: both forms read what there is once, and the chunks' products are half empty)
+    if (c.cout <= 32) return c.cin <= 32 || q < 0.87;
+    // (few input channels: as little for the chunks to read, and the last-level cache has 256 MB)
+    if (c.cin <= 32) return q < (c.bytes > (c.cout >= 128 ? 1.5e8 : 2.5e8) ? 0.65 : c.cout <= 64 && c.bytes < 1.6e8 ? 1.0 : 0.9);
     // (channels read to a block's products, which are 64 x 64 whatever is there)
     const double blocks = (double)((c.cin + 63) / 64) * ((c.cout + 63) / 64) * 4096.0;
-    return q < (c.cin <= 32 ? 0.9 : 1.0 - 16.0 * (c.cin + c.cout) / blocks);
+    return q < 1.0 - 16.0 * (c.cin + c.cout) / blocks;
 }
 
 // ---- 1x1: a unit is 8 pixels of a row (G of them a row), a step two of them, one for each half; a wavefront takes every fourth step ----
