@@ -19,7 +19,7 @@ k_back_split(BackSplitArgs a)
 {
     const int index = (int)blockIdx.x;
     touch_joint_args<BackSplitArgs>(index, a.wgroups);
-    if (index < a.wgroups) wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS>(a.w, index);
+    if (index < a.wgroups) wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS, true>(a.w, index);
     else delta_split_group<3, WAVES_M, BN, POOL ? IN_POOL : IN_WIDE>(a.d, index - a.wgroups);
 }
 

@@ -866,7 +866,8 @@ void reduce_wgrad(const float* partial, float* wgrad, long long n_params, int st
     g_kernel_label = "k_reduce_wgrad";
     const long long threads = n_params % 4 == 0 ? n_params / 4 : n_params;
     // (parameters for more workgroups than CUs hide the waits of few stacks by themselves: 295 thousand of 9 stacks 167.3 us a step so and 168.7 shared, 590
-    // thousand of 64 221.7 and 219.7, of 144 619.6 and 600.7; 8 stacks are one group)
+    // thousand of 64 221.7 and 219.7, of 144 619.6 and 600.7; 8 stacks are one group.  Up to 16 stacks either is launch and one load deep - between events, 864 to 258
+    // thousand parameters, 5.9 to 7.0 us apart and 6.0 to 7.0 shared -, 25 of 74 and 147 thousand 6.8 and 7.5 / 6.1 and 6.3, 36 7.8 and 8.5 / 6.1 and 7.1, 64 9.8 and 10.7 / 6.8 and 9.5)
     if (n_params % 4 == 0 && stacks > (threads <= 65536 ? 8 : 63) && (((uintptr_t)partial | (uintptr_t)wgrad) & 15) == 0) {
         g_kernel_label = "k_reduce_wgrad_shared";
         hipLaunchKernelGGL(k_reduce_wgrad_shared, dim3((unsigned)((threads + kShareQuads - 1) / kShareQuads)), dim3(8 * kShareQuads), 0, s, (const float4*)partial, (float4*)wgrad, threads, stacks);

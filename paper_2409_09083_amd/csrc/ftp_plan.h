@@ -139,7 +139,7 @@ FTP_HD inline int quot_small(int a, int b) { return a / b; }
 #endif
 // RCP false: the compiler's division, for kernels whose main loops the compiler schedules worse behind the others, although these touch the first
 // lines only (us, compiler's / reciprocals: filter gradients of k_wgrad_mfma, 16 bits, 5x5 128 -> 96, 4 images of 217^2, 1001 / 1072, 3x3 240 -> 96, 11 of 117^2, 479 / 509; fp32
-// 7x7 deltas, 32 -> 196, 48^2 in 8 x 8 stacks, 141 / 151, 32 -> 256, 15 images of 35^2, 181 / 195; and those of k_wgrad_split).  Elsewhere they gain up to 5 % of short launches
+// 7x7 deltas, 32 -> 196, 48^2 in 8 x 8 stacks, 141 / 151, 32 -> 256, 15 images of 35^2, 181 / 195; and those of k_wgrad_split by themselves).  Elsewhere they gain up to 5 % of short launches
 // and lose nothing, also where a kernel takes a register or two more for them or spills one or two (40 layers of all kinds: forward 0.99 times the time, back-propagation 0.998).
 template <bool RCP> FTP_HD inline int quot(int a, int b) { return RCP ? quot(a, b) : a / b; }
 template <bool RCP> FTP_HD inline int quot_lane(int a, int b) { return RCP ? quot_lane(a, b) : a / b; }

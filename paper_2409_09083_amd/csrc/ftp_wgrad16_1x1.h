@@ -7,7 +7,8 @@
 // Units begin on the dword at or below a row's first element of X, one pixel early where that is odd, and dZ is shifted to it where its parity differs (one
 // dword more is loaded then).  What a unit brings along beside the row is cleared in both operands (masks from LDS): maps may hold
 // infinities there, workspace rows anything.
-// What bounds it: HBM and L2 lines (a stack's rows are pieces of them), latency.
+// What bounds it: lines on their way from L2 and beyond (a stack's rows are pieces of them): 0.45 L1 look-ups a cycle and CU, some waiting in 0.59 of the cycles, two of five
+// go on to L2, which has four of five of those.
 // k_wgrad_mfma (both maps widened to dwords and transposed through LDS, the half-rate instruction) -> this, back-propagation of the layer in us:
 // 32 images, 256 -> 128 at 76^2 in 8 x 8 stacks 279 / 218, in 3 x 3 212 / 166, 128 -> 64 at 152^2 in 8 x 8 292 / 251, 512 -> 256 at 38^2 (rows of 5 pixels) 313 / 307; 16 images,
 // 512 -> 256 at 38^2, one stack, 113 / 64; one image 41 / 36 in 8 x 8 stacks.  128 input channels a workgroup instead of 64, where that

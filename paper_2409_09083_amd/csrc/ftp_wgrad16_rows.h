@@ -10,8 +10,9 @@
 // the pooled ones and the winner codes.  The loads of the next item are in flight.
 // Wavefronts of a workgroup: 32 x 32 (co, ci) blocks of 64 x 64, or of 64 x 32 with the strips dealt out to two; they share lines in L1.
 // What a strip brings along beside the needed columns is cleared in both operands: maps may hold infinities there.
-// What bounds it: the lines that the L1s look up (an instruction of 64 lanes meets 32 channels' rows, two more loads a row for the deltas), then the
-// unit's first loads.  The barrier an item keeps the wavefronts of a workgroup on the same lines (64 -> 128, 32 images of 152^2, 534 -> 518 us); four items
+// What bounds it: the lines that the L1s look up (an instruction of 64 lanes meets 32 channels' rows, two more loads a row for the deltas): 128 -> 256, 32 images of 76^2 in
+// 8 x 8 stacks, 0.92 look-ups a cycle and CU, tag conflicts in 0.25 of the cycles; 32 -> 64 with a pool at 304^2 0.50, a read of three goes on to L2 and the data unit
+// waits for the L1 in 0.72 of the cycles.  Then the unit's first loads.  The barrier an item keeps the wavefronts of a workgroup on the same lines (64 -> 128, 32 images of 152^2, 534 -> 518 us); four items
 // in flight instead of two meet fewer of them (561 -> 596, third case below).
 // wgrad16_group (ftp_wgrad16.h: patch and deltas in LDS, a chunk at a time, MFMA busy 17 to 25 %) -> this, back-propagation of the layer in us: 128 -> 256, 32 images of
 // 76^2 in 8 x 8 stacks 531 / 459, with a pool 550 / 453; 32 -> 64 with a pool at 304^2 653 / 557; 64 -> 64, 32 of 104^2, one stack, 473 / 254, one image 41 / 30; 64 -> 256,

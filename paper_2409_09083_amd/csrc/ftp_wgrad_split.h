@@ -56,7 +56,7 @@ constexpr unsigned kRecordsW = 0x7FFFFFFFu;
 // if it is the window's winner.  WS: the input map lies inside the workspace (which has margins: a quad may begin beside the
 // map); otherwise quads that straddle a row's end are loaded element by element.
 // Workgroup `index` of the launch.
-template <int WAVES_CO, int WAVES_CI, bool POOL, bool WS>
+template <int WAVES_CO, int WAVES_CI, bool POOL, bool WS, bool RCP>
 __device__ __forceinline__ void wgrad_split_group(const WsplitArgs& a, int index)
 {
     constexpr int WAVES_K = 4 / (WAVES_CO * WAVES_CI);
@@ -74,9 +74,9 @@ __device__ __forceinline__ void wgrad_split_group(const WsplitArgs& a, int index
     const int wave_co = wave % WAVES_CO, wave_ci = (wave / WAVES_CO) % WAVES_CI, wave_k = wave / (WAVES_CO * WAVES_CI);
     const int hi = lane >> 5, l32 = lane & 31;
     int split, stack, bx;
-    // (the compiler's division: with reciprocals the pooled forms spilled two registers, and all were 1.2 % slower by themselves - 64 -> 128 with a pool, 8 images of
-    // 152^2 in 6 x 6 stacks, 177 -> 173 us, 256 -> 256, one of 52^2, 49.7 -> 47.0)
-    if (!xcd_shares<false>(index, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
+    // (launches of its own: the compiler's division - with reciprocals the pooled forms spilled two registers, and all were 1.2 % slower: 64 -> 128 with a pool, 8 images of
+    // 152^2 in 6 x 6 stacks, 177 -> 173 us, 256 -> 256, one of 52^2, 49.7 -> 47.0.  Joined with the delta: reciprocals, back-propagation of the small network 1046 -> 1043 us)
+    if (!xcd_shares<RCP>(index, a.eighths, a.splits, a.stacks, a.gx, split, stack, bx)) return;
     const int ti = stack / a.M, tj = stack % a.M;
     const int x0 = a.own.x0[tj], x1 = a.own.x1[tj], y0 = a.own.y0[ti], y1 = a.own.y1[ti];
     const int rw = x1 - x0 + 1, rh = y1 - y0 + 1;

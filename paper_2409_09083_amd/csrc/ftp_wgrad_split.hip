@@ -9,7 +9,7 @@ __global__ void __launch_bounds__(256, 2)
 k_wgrad_split(WsplitArgs a)
 {
     touch_args<0, sizeof(WsplitArgs)>((int)blockIdx.x);
-    wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS>(a, (int)blockIdx.x);
+    wgrad_split_group<WAVES_CO, WAVES_CI, POOL, WS, false>(a, (int)blockIdx.x);
 }
 
 // fp32 maps, 3x3, stride 1, with or without the fused pool; offsets of a chunk's images within 31 bits.
